@@ -74,91 +74,10 @@ __device__ __forceinline__ void gather_range(const Src& src, const int* __restri
   }
 }
 
-// Phase 1 of the wide kernels: row r of the tile becomes
-//   sa_i * ( src(i) + sum_{j in N(i)} src(j) ),  i = row0 + r,
-// handed to `sink` (put_vec: VEC consecutive columns of a row; put_one: a single
-// element); rows nrows..kTileRows are handed zeros.  Short rows are summed by
-// one lane group, rows longer than kLightMax by the whole workgroup in a second
-// pass, and pre-reduced rows take their chunk partials.
-// LDS: red [kBlock * VEC] floats, hlist [kTileRows + 1] ints.  Ends with a barrier.
-template <typename T, int D, class Src, class Sink>
-__device__ void aggregate_tile(const GraphView& g, const Src& src, const Sink& sink, int row0,
-                               int nrows, float* red, int* hlist,
-                               const float* __restrict__ heavy_partial) {
-  constexpr int VEC = Store<T>::VEC;
-  constexpr int LPR = D / VEC;        // lanes per feature row
-  constexpr int G = kBlock / LPR;     // lane groups per workgroup
-  const int tid = threadIdx.x;
-  const int grp = tid / LPR;
-  const int c0 = (tid % LPR) * VEC;
-  if (tid == 0) hlist[0] = 0;
-  __syncthreads();
-  for (int r = grp; r < kTileRows; r += G) {
-    float acc[VEC];
-    if (r >= nrows) {
-#pragma unroll
-      for (int x = 0; x < VEC; ++x) acc[x] = 0.f;
-      sink.template put_vec<VEC>(r, c0, acc);
-      continue;
-    }
-    const int i = row0 + r;
-    const int e0 = g.rowptr[i], e1 = g.rowptr[i + 1];
-    const int h = g.num_heavy > 0 ? g.heavy_of_row[i] : -1;
-    if (h < 0 && e1 - e0 > kLightMax) {
-      if (tid % LPR == 0) {
-        const int q = atomicAdd(&hlist[0], 1);
-        hlist[1 + q] = r;
-      }
-      continue;
-    }
-    src.load(i, c0, acc);  // the self loop of A + I
-    if (h >= 0) {
-      for (int ch = g.heavy_chunk_ptr[h]; ch < g.heavy_chunk_ptr[h + 1]; ++ch) {
-        const float4* pp = reinterpret_cast<const float4*>(heavy_partial + static_cast<size_t>(ch) * D + c0);
-#pragma unroll
-        for (int x = 0; x < VEC; x += 4) {
-          const float4 q4 = pp[x / 4];
-          acc[x] += q4.x; acc[x + 1] += q4.y; acc[x + 2] += q4.z; acc[x + 3] += q4.w;
-        }
-      }
-    } else {
-      gather_range(src, g.col, e0, e1, 1, c0, acc);
-    }
-    const float sa = g.sa[i];
-#pragma unroll
-    for (int x = 0; x < VEC; ++x) acc[x] *= sa;
-    sink.template put_vec<VEC>(r, c0, acc);
-  }
-  __syncthreads();
-  const int nh = hlist[0];
-  for (int q = 0; q < nh; ++q) {
-    const int r = hlist[1 + q];
-    const int i = row0 + r;
-    const int e0 = g.rowptr[i], e1 = g.rowptr[i + 1];
-    float acc[VEC];
-    if (grp == 0) {
-      src.load(i, c0, acc);
-    } else {
-#pragma unroll
-      for (int x = 0; x < VEC; ++x) acc[x] = 0.f;
-    }
-    gather_range(src, g.col, e0 + grp, e1, G, c0, acc);
-#pragma unroll
-    for (int x = 0; x < VEC; ++x) red[grp * D + c0 + x] = acc[x];
-    __syncthreads();
-    if (tid < D) {
-      float s = 0.f;
-      for (int gq = 0; gq < G; ++gq) s += red[gq * D + tid];
-      sink.put_one(r, tid, g.sa[i] * s);
-    }
-    __syncthreads();
-  }
-}
-
 // Chunked pre-reduction of very long rows: partial[c, :] = sum_{e in chunk c} src(col[e]).
-template <typename T, int D, class Src>
+template <int D, class Src>
 __global__ __launch_bounds__(kBlock) void heavy_wide_kernel(GraphView g, Src src, float* partial) {
-  constexpr int VEC = Store<T>::VEC;
+  constexpr int VEC = Src::VEC;
   constexpr int LPR = D / VEC;
   constexpr int G = kBlock / LPR;
   __shared__ float red[kBlock * VEC];

@@ -433,12 +433,12 @@ void build_block_map(int P, const std::vector<int>& part_rows, const std::vector
 }
 
 // Wave-per-tile kernels: workgroups are dealt to the subgraphs as above; the tiles of a
-// subgraph (kWaveRows rows each) are then cut into one contiguous run per wavefront such
+// subgraph (tile_rows rows each) are then cut into one contiguous run per wavefront such
 // that every run costs about the same: a tile costs its light-stream entries (one per row
 // plus the neighbours of rows that are not pre-reduced) plus row_cost per row, which
 // stands for the per-row work of the kernel's dense part and epilogue.
 void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<int32_t>& lrowptr,
-                    int target_blocks, double row_cost, bool group_by_xcd, std::vector<int>& wblk_k,
+                    int tile_rows, int target_blocks, double row_cost, bool group_by_xcd, std::vector<int>& wblk_k,
                     std::vector<WaveRun>& wave_runs) {
   constexpr int kWaves = kBlock / 64;
   std::vector<int> blk_s, blk_S;
@@ -450,7 +450,7 @@ void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<
       const int deg = lrowptr[r + 1] - lrowptr[r];
       light[k] += 1 + (deg >= kHeavyMin ? 0 : deg);
     }
-  build_block_map(P, part_rows, lrowptr, kWaveRows * kWaves, target_blocks, 0, wblk_k, blk_s, blk_S,
+  build_block_map(P, part_rows, lrowptr, tile_rows * kWaves, target_blocks, 0, wblk_k, blk_s, blk_S,
                   group_by_xcd, row_cost, &light);
   wave_runs.assign(wblk_k.size() * kWaves, WaveRun{});
   // light-stream offset of every row (one entry per row plus the neighbours of rows that
@@ -462,18 +462,18 @@ void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<
     wrow[r + 1] = wrow[r] + 1 + (deg >= kHeavyMin ? 0 : deg);
   }
   for (int k = 0; k < P; ++k)
-    tbase[k + 1] = tbase[k] + (part_rows[k + 1] - part_rows[k] + kWaveRows - 1) / kWaveRows;
+    tbase[k + 1] = tbase[k] + (part_rows[k + 1] - part_rows[k] + tile_rows - 1) / tile_rows;
   std::vector<std::vector<int>> cuts(P);  // cuts[k][v] = first tile of wavefront v of subgraph k
   for (size_t b = 0; b < wblk_k.size(); ++b) {
     const int k = wblk_k[b];
     if (k < 0) continue;
     if (cuts[k].empty()) {
       const int rows = part_rows[k + 1] - part_rows[k];
-      const int tiles = (rows + kWaveRows - 1) / kWaveRows;
+      const int tiles = (rows + tile_rows - 1) / tile_rows;
       std::vector<double> pre(static_cast<size_t>(tiles) + 1, 0);  // cost before tile t
       for (int t = 0; t < tiles; ++t) {
-        double c = row_cost * kWaveRows;
-        for (int r = part_rows[k] + t * kWaveRows; r < std::min(part_rows[k + 1], part_rows[k] + (t + 1) * kWaveRows); ++r) {
+        double c = row_cost * tile_rows;
+        for (int r = part_rows[k] + t * tile_rows; r < std::min(part_rows[k + 1], part_rows[k] + (t + 1) * tile_rows); ++r) {
           const int deg = lrowptr[r + 1] - lrowptr[r];
           c += 1 + (deg >= kHeavyMin ? 0 : deg);
         }
@@ -496,8 +496,8 @@ void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<
       run.tile1 = cuts[k][v + 1];
       run.rbeg = part_rows[k];
       run.rend = part_rows[k + 1];
-      run.e0 = wrow[std::min(run.rend, run.rbeg + run.tile0 * kWaveRows)];
-      run.e1 = wrow[std::min(run.rend, run.rbeg + run.tile1 * kWaveRows)];
+      run.e0 = wrow[std::min(run.rend, run.rbeg + run.tile0 * tile_rows)];
+      run.e1 = wrow[std::min(run.rend, run.rbeg + run.tile1 * tile_rows)];
       run.tglob = tbase[k];
     }
   }
@@ -885,7 +885,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     GALLOC(ctx->d_wrowid, static_cast<size_t>(nnz_light) + kEntPad);
     launch_fill_u32(st, ctx->d_wrowid + nnz_light, kEntPad, 0xffffffffu);
     launch_light_fill(st, n, ctx->d_lrowptr, ctx->d_ent, ctx->d_diag, d_wptr64, ctx->d_wrowptr, ctx->d_went,
-                      ctx->d_wval, ctx->d_wrowid);
+                      ctx->d_wval, ctx->d_wrowid, ctx->wave_path());
     if (ctx->d_ent_t == ctx->d_ent) {
       ctx->d_went_t = ctx->d_went;
       ctx->d_wval_t = ctx->d_wval;
@@ -895,7 +895,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
       GALLOC(ctx->d_went_t, static_cast<size_t>(nnz_light) + kEntPad);
       launch_fill_u32(st, ctx->d_went_t + nnz_light, 2 * kEntPad, 0u);
       launch_light_fill(st, n, ctx->d_lrowptr, ctx->d_ent_t, ctx->d_diag, d_wptr64, ctx->d_wrowptr,
-                        ctx->d_went_t, ctx->d_wval_t, nullptr);
+                        ctx->d_went_t, ctx->d_wval_t, nullptr, ctx->wave_path());
     }
   }
 
@@ -909,9 +909,11 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   // one decomposition per kernel kind (different cost per row)
   for (int v = 0; v < kWaveMaps; ++v) {
     std::vector<WaveRun> wave_runs;
-    build_wave_map(P, part_rows, lrowptr, (ctx->cfg.dim == 128 ? kWaveBlocksFor128 : kWaveBlocksFor)[v],
-                   kWaveRowCost[v], group_by_xcd, ctx->hm.wblk_k[v],
-                   wave_runs);
+    const bool f32 = ctx->cfg.storage == GCO_STORAGE_FP32;
+    const int target = f32 ? wave_blocks_f32(ctx->cfg.dim, v)
+                           : (ctx->cfg.dim == 128 ? kWaveBlocksFor128 : kWaveBlocksFor)[v];
+    build_wave_map(P, part_rows, lrowptr, f32 && v != WM_NARROW ? kTileRowsF32 : kWaveRows, target,
+                   (f32 ? kWaveRowCostF32 : kWaveRowCost)[v], group_by_xcd, ctx->hm.wblk_k[v], wave_runs);
     ctx->num_wblocks[v] = static_cast<int>(ctx->hm.wblk_k[v].size());
     GALLOC(ctx->d_wave_runs[v], wave_runs.size());
     HIPCHK(h2d(ctx, ctx->d_wave_runs[v], wave_runs.data(), wave_runs.size()));
@@ -1227,7 +1229,8 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     GALLOC(q, nd * eb);
     ctx->GT = q;
   }
-  GALLOC(ctx->gwout_partial, static_cast<size_t>(std::max(g.num_blocks, g.num_nblocks)) * D);
+  GALLOC(ctx->gwout_partial, static_cast<size_t>(std::max({g.num_blocks, g.num_nblocks, g.num_wblocks[WM_BWD],
+                                                          g.num_wblocks[WM_EMBED]})) * D);
   GALLOC(ctx->d_bc, static_cast<size_t>(kLossSets) * (P + ctx->Pw));
   GALLOC(ctx->t, static_cast<size_t>(n));
   GALLOC(ctx->z, static_cast<size_t>(n));
@@ -1524,16 +1527,17 @@ static void run_backward(gco_ctx* ctx, const GraphView& gv, const gco_ctx::Activ
     wt[l - 1].partial = l < L ? ctx->gW_partial[l - 1] : ctx->gwout_partial;
     wt[l - 1].grad_out = (!update && gW) ? gW[l - 1] : nullptr;
     wt[l - 1].elems = w_elems(ctx, l);
-    // who wrote the partials: the wide kernels' workgroups, or, on the wave-per-tile path,
-    // its own workgroups (hidden layers) and the narrow ones (scalar layer)
-    const bool wave = ctx->wave_path() && L >= 2;
-    const int wm = ctx->grad_map(l);  // the decomposition whose workgroups wrote gW_l
-    wt[l - 1].blk_ptr = !wave ? maps.pbl_ptr : (l < L ? maps.wpbl_ptr[wm] : maps.nwbl_ptr);
-    wt[l - 1].blk_list = !wave ? maps.pbl_list : (l < L ? maps.wpbl_list[wm] : maps.nwbl_list);
+    // who wrote the partials: the workgroups of the layer's backward kernel; the scalar
+    // layer's gradient comes from the launch that forms G_Z of the last hidden layer (bf16:
+    // narrow workgroups; fp32: that layer's backward kernel), from bwd_single without layers
+    const bool narrow = l == L && ctx->wave_path();
+    const int wm = ctx->grad_map(l < L ? l : L - 1);  // the decomposition whose workgroups wrote gW_l
+    wt[l - 1].blk_ptr = L == 1 ? maps.pbl_ptr : (narrow ? maps.nwbl_ptr : maps.wpbl_ptr[wm]);
+    wt[l - 1].blk_list = L == 1 ? maps.pbl_list : (narrow ? maps.nwbl_list : maps.wpbl_list[wm]);
   }
-  const int writers = (ctx->wave_path() && L >= 2)
-                          ? std::max({gv.num_wblocks[WM_BWD], gv.num_wblocks[WM_EMBED], gv.num_nblocks})
-                          : gv.num_blocks;
+  const int writers = L == 1 ? gv.num_blocks
+                             : std::max({gv.num_wblocks[WM_BWD], gv.num_wblocks[WM_EMBED],
+                                         ctx->wave_path() ? gv.num_nblocks : 0});
   const bool many_partials = writers / ctx->Pw >= 512;
   // the last launch of an epoch also pre-reduces the long rows of the new embeddings
   ChunkTail tail;

@@ -15,7 +15,6 @@ namespace gco {
 constexpr int kBlock = 256;      // threads per workgroup in every kernel here (4 wavefronts)
 constexpr int kTileRows = 64;    // rows of one feature tile in the wide kernels
 constexpr int kNarrowRows = 256; // rows of one tile in the width-1 kernels
-constexpr int kLightMax = 64;    // rows with more local neighbours are reduced by the whole block
 constexpr int kHeavyMin = 256;   // rows with at least this many neighbours are pre-reduced in chunks
 constexpr int kChunk = 256;      // neighbours per chunk of a pre-reduced row
 constexpr int kNarrowPartChunks = 8;  // width-1 passes: chunks of a pre-reduced row summed by one workgroup
@@ -31,6 +30,17 @@ constexpr int kWaveBlocksFor[kWaveMaps] = {768, 512, 3072, 2048, 256};
 // width 128 (two workgroups of the layer kernels per compute unit): forward two rounds of 512,
 // embedding backward twelve
 constexpr int kWaveBlocksFor128[kWaveMaps] = {1024, 1024, 6144, 2048, 256};
+// fp32 storage: rows of a tile; workgroups aimed at, in rounds of those resident at once.  Up to
+// width 32 two rounds (700 k rows of width 16, forward / embedding backward: 45 / 91 us against
+// 47 / 99 with one), from width 64 on, where W and the first tile cost more per workgroup, one
+// (150 k rows of width 64: 78 / 125 us against 80 / 131 with two); and the cost of a row.
+constexpr int kTileRowsF32 = 16;
+inline int wave_blocks_f32(int dim, int map) {
+  if (map == WM_FWD) return dim <= 16 ? 2 * 1536 : (dim == 32 ? 2 * 1024 : (dim == 64 ? 768 : 512));
+  if (map == WM_BWD || map == WM_EMBED) return dim <= 16 ? 2 * 1024 : (dim == 32 ? 2 * 768 : 512);
+  return kWaveBlocksFor[map];
+}
+constexpr double kWaveRowCostF32[kWaveMaps] = {4.0, 6.0, 8.0, 1.0, 100.0};
 constexpr int kEntPad = 512;             // zero entries appended to the packed entry arrays
 // gco_round_repair_static works inside a block of device memory that is part of the
 // library's code object: up to this many nodes, 7 bytes per node plus counters.
@@ -62,7 +72,7 @@ enum KernelKind : int {
 // its first loads of the stream sits in this one 32-byte record, so that it starts them
 // after a single lookup.
 struct __attribute__((aligned(16))) WaveRun {
-  int tile0, tile1;  // tiles [tile0, tile1) of its subgraph (kWaveRows rows each, from the subgraph's first row)
+  int tile0, tile1;  // tiles [tile0, tile1) of its subgraph (kWaveRows or kTileRowsF32 rows each, from its first row)
   int rbeg, rend;    // rows of the subgraph
   int e0, e1;        // light-stream range of the run's rows
   int tglob;         // global number of the subgraph's first tile
@@ -315,6 +325,14 @@ struct BwdArgs {
 };
 void launch_bwd_hidden(const Launch& ln, int storage, int D, bool last, bool to_embed,
                        const GraphView& g, const BwdArgs& a);
+
+// fp32-storage versions (tile_kernels_f32.hip); weight-gradient partials per workgroup of
+// decomposition WM_EMBED (first layer) or WM_BWD, those of w_out by the last hidden layer's
+void launch_fwd_hidden_f32(const Launch& ln, int D, const GraphView& g, const void* X, const float* W,
+                           int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
+                           float* heavy_partial);
+void launch_bwd_hidden_f32(const Launch& ln, int D, bool last, bool to_embed, const GraphView& gt,
+                           const BwdArgs& a);
 
 // bf16-storage, matrix-core versions (layer_launch_bf16.hip, widths 64 and 128); `gt`
 // already has the scale vectors of A_hat^T.

@@ -241,7 +241,7 @@ __device__ __forceinline__ int split_bf16(float w) {
 }
 
 // One wavefront per row: {i, diag[i]}, then a light row's entries, to the light stream,
-// the values split into bf16 pairs.  wrowid (may be null) receives the row of every entry of
+// the values split into bf16 pairs (split) or in fp32.  wrowid (may be null) receives the row of every entry of
 // the stream, -2 for the lone entry of a pre-reduced row.
 __global__ __launch_bounds__(kBlock) void light_fill_kernel(int n, const int32_t* __restrict__ rowptr,
                                                             const int2* __restrict__ ent,
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kBlock) void light_fill_kernel(int n, const int32_t
                                                             int32_t* __restrict__ wrowptr,
                                                             int2* __restrict__ went,
                                                             float* __restrict__ wval,
-                                                            int32_t* __restrict__ wrowid) {
+                                                            int32_t* __restrict__ wrowid, int split) {
   const int i = blockIdx.x * (kBlock / 64) + threadIdx.x / 64;
   if (i > n) return;
   const int lane = threadIdx.x % 64;
@@ -259,14 +259,14 @@ __global__ __launch_bounds__(kBlock) void light_fill_kernel(int n, const int32_t
   const int64_t out = wptr64[i];
   const int deg = rowptr[i + 1] - rowptr[i];
   if (lane == 0) {
-    went[out] = make_int2(i, split_bf16(diag[i]));
+    went[out] = make_int2(i, split ? split_bf16(diag[i]) : __float_as_int(diag[i]));
     wval[out] = diag[i];
     if (wrowid != nullptr) wrowid[out] = deg >= kHeavyMin ? -2 : i;
   }
   if (deg >= kHeavyMin) return;
   for (int q = lane; q < deg; q += 64) {
     const int2 en = ent[rowptr[i] + q];
-    went[out + 1 + q] = make_int2(en.x, split_bf16(__int_as_float(en.y)));
+    went[out + 1 + q] = make_int2(en.x, split ? split_bf16(__int_as_float(en.y)) : en.y);
     wval[out + 1 + q] = __int_as_float(en.y);
     if (wrowid != nullptr) wrowid[out + 1 + q] = i;
   }
@@ -511,9 +511,9 @@ void launch_light_count(hipStream_t st, int n, const int32_t* rowptr, int64_t* c
 }
 
 void launch_light_fill(hipStream_t st, int n, const int32_t* rowptr, const int2* ent, const float* diag,
-                       const int64_t* wptr64, int32_t* wrowptr, int2* went, float* wval, int32_t* wrowid) {
+                       const int64_t* wptr64, int32_t* wrowptr, int2* went, float* wval, int32_t* wrowid, bool split) {
   light_fill_kernel<<<blocks_for(static_cast<int64_t>(n) + 1, kBlock / 64), kBlock, 0, st>>>(
-      n, rowptr, ent, diag, wptr64, wrowptr, went, wval, wrowid);
+      n, rowptr, ent, diag, wptr64, wrowptr, went, wval, wrowid, split ? 1 : 0);
 }
 
 void launch_linear_coeff(hipStream_t st, int n, const float* c_base, const float* extra_orig,

@@ -21,122 +21,6 @@ namespace {
 
 constexpr int R = kTileRows;
 
-template <int D>
-struct Geo {
-  static constexpr int LD = D + 4;  // LDS row pitch in floats (keeps 16-byte alignment)
-};
-
-// Where the fp32 kernels leave the gathered rows: an fp32 LDS tile [R][LD].
-template <int D>
-struct TileSink {
-  float* tile;
-  template <int VEC>
-  __device__ __forceinline__ void put_vec(int r, int c0, const float (&v)[VEC]) const {
-#pragma unroll
-    for (int x = 0; x < VEC; ++x) tile[r * Geo<D>::LD + c0 + x] = v[x];
-  }
-  __device__ __forceinline__ void put_one(int r, int c, float v) const { tile[r * Geo<D>::LD + c] = v; }
-};
-
-// ---------------------------------------------------------------------------
-// Dense transform of an LDS tile (fp32 FMA form)
-// ---------------------------------------------------------------------------
-
-// out[i] = sum_k tile[r_i, k] * Wl[k, c] for this thread's column c = tid % D and
-// rows r_i = tid / D + i * (kBlock / D).
-template <int D>
-__device__ __forceinline__ void tile_times_matrix(const float* tile, const float* Wl,
-                                                  float (&out)[R * D / kBlock]) {
-  constexpr int RG = kBlock / D;
-  constexpr int NR = R / RG;
-  constexpr int LD = Geo<D>::LD;
-  const int c = threadIdx.x % D;
-  const int rg = threadIdx.x / D;
-#pragma unroll
-  for (int i = 0; i < NR; ++i) out[i] = 0.f;
-  for (int k = 0; k < D; k += 4) {
-    const float w0 = Wl[(k + 0) * D + c], w1 = Wl[(k + 1) * D + c];
-    const float w2 = Wl[(k + 2) * D + c], w3 = Wl[(k + 3) * D + c];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const float4 a = *reinterpret_cast<const float4*>(tile + (rg + i * RG) * LD + k);
-      out[i] = fmaf(a.x, w0, out[i]);
-      out[i] = fmaf(a.y, w1, out[i]);
-      out[i] = fmaf(a.z, w2, out[i]);
-      out[i] = fmaf(a.w, w3, out[i]);
-    }
-  }
-}
-
-template <int D>
-constexpr size_t fwd_lds_bytes(int vec) {
-  return (static_cast<size_t>(R) * Geo<D>::LD + D * D + kBlock * vec + D) * sizeof(float) +
-         (R + 4) * sizeof(int);
-}
-template <int D>
-constexpr size_t bwd_lds_bytes(int vec) {
-  return (2 * static_cast<size_t>(R) * Geo<D>::LD + D * D + kBlock * vec + D) * sizeof(float) +
-         (R + 4) * sizeof(int);
-}
-
-// ---------------------------------------------------------------------------
-// Forward, hidden layer: Y = relu((A_hat X) W^k)  [+ t = Y w_out^k]
-// ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(kBlock) void fwd_hidden_kernel(GraphView g, const T* __restrict__ X,
-                                                            const float* __restrict__ W,
-                                                            int w_stride, T* __restrict__ Y,
-                                                            const float* __restrict__ w_out,
-                                                            int wout_stride, float* __restrict__ t,
-                                                            const float* __restrict__ heavy_partial) {
-  constexpr int VEC = Store<T>::VEC;
-  constexpr int LD = Geo<D>::LD;
-  constexpr int RG = kBlock / D;
-  constexpr int NR = R / RG;
-  extern __shared__ __align__(16) unsigned char smem[];
-  float* tile = reinterpret_cast<float*>(smem);
-  float* Wl = tile + R * LD;
-  float* red = Wl + D * D;
-  float* wo = red + kBlock * VEC;
-  int* hlist = reinterpret_cast<int*>(wo + D);
-
-  const int k = g.blk_k[blockIdx.x];
-  if (k < 0) return;
-  const int s = g.blk_s[blockIdx.x];
-  const int tid = threadIdx.x;
-  const float* Wk = W + static_cast<size_t>(k) * w_stride;
-  for (int idx = tid; idx < D * D; idx += kBlock) Wl[idx] = Wk[idx];
-  if (w_out != nullptr && tid < D) wo[tid] = w_out[static_cast<size_t>(k) * wout_stride + tid];
-  PlainSrc<T, D> src{X, g.sb};
-  const int rbeg = g.part_rows[k], rend = g.part_rows[k + 1];
-  const int c = tid % D, rg = tid / D;
-  for (int row0 = rbeg + s * R; row0 < rend; row0 += g.blk_S[blockIdx.x] * R) {
-    const int nrows = min(R, rend - row0);
-    aggregate_tile<T, D>(g, src, TileSink<D>{tile}, row0, nrows, red, hlist, heavy_partial);
-    __syncthreads();
-    float out[NR];
-    tile_times_matrix<D>(tile, Wl, out);
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-      const int r = rg + i * RG;
-      out[i] = Store<T>::as_stored(fmaxf(out[i], 0.f));
-      if (r < nrows) Store<T>::put(Y + static_cast<size_t>(row0 + r) * D + c, out[i]);
-    }
-    if (w_out != nullptr) {
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < NR; ++i) tile[(rg + i * RG) * LD + c] = out[i];
-      __syncthreads();
-      if (tid < nrows) {
-        float acc = 0.f;
-        for (int cc = 0; cc < D; ++cc) acc = fmaf(tile[tid * LD + cc], wo[cc], acc);
-        t[row0 + tid] = acc;
-      }
-    }
-    __syncthreads();
-  }
-}
-
 // t = X w^k for L = 1 (no hidden layer).
 template <typename T, int D>
 __global__ __launch_bounds__(kBlock) void fwd_gemv_kernel(GraphView g, const T* __restrict__ X,
@@ -156,118 +40,6 @@ __global__ __launch_bounds__(kBlock) void fwd_gemv_kernel(GraphView g, const T* 
       t[i] = acc;
     }
   }
-}
-
-// ---------------------------------------------------------------------------
-// Backward of a hidden layer (see BwdArgs)
-// ---------------------------------------------------------------------------
-template <typename T, int D, bool LAST, bool TO_EMBED>
-__global__ __launch_bounds__(kBlock) void bwd_hidden_kernel(GraphView g, BwdArgs a) {
-  constexpr int VEC = Store<T>::VEC;
-  constexpr int LPR = D / VEC;
-  constexpr int LD = Geo<D>::LD;
-  constexpr int RG = kBlock / D;
-  constexpr int NR = R / RG;
-  constexpr int AG = kBlock / D;                       // row groups of the D x D gradient
-  constexpr int NA = (D * D >= kBlock) ? (D * D / kBlock) : 1;
-  extern __shared__ __align__(16) unsigned char smem[];
-  float* tile = reinterpret_cast<float*>(smem);        // G_T tile
-  float* hp = tile + R * LD;                           // Hprev tile
-  float* Wt = hp + R * LD;                             // Wt[b, a] = W[a, b]
-  float* red = Wt + D * D;
-  float* gtl = red + kBlock * VEC;                     // g_t of the tile rows (LAST)
-  int* hlist = reinterpret_cast<int*>(gtl + D);
-
-  const int k = g.blk_k[blockIdx.x];
-  if (k < 0) return;
-  const AdamStep ad = a.adam.for_part(k);
-  const int s = g.blk_s[blockIdx.x];
-  const int tid = threadIdx.x;
-  const T* Hprev = static_cast<const T*>(a.Hprev);
-  const float* Wk = a.W + static_cast<size_t>(k) * a.w_stride;
-  for (int idx = tid; idx < D * D; idx += kBlock) Wt[(idx % D) * D + idx / D] = Wk[idx];
-
-  PlainSrc<T, D> psrc{static_cast<const T*>(a.GZ_in), g.sb};
-  LastSrc<T, D> lsrc{static_cast<const T*>(a.Hcur), g.sb, a.g_t, a.w_out, a.wout_stride, {}};
-  if (LAST) lsrc.set_part(k, (tid % LPR) * VEC);
-
-  const int rbeg = g.part_rows[k], rend = g.part_rows[k + 1];
-  const int c = tid % D, rg = tid / D;
-  const bool gw_active = (D * D >= kBlock) || (rg < D);
-  float gw[NA];
-#pragma unroll
-  for (int i = 0; i < NA; ++i) gw[i] = 0.f;
-  float gwo = 0.f;  // gradient of w_out[c] (LAST, threads tid < D)
-
-  for (int row0 = rbeg + s * R; row0 < rend; row0 += g.blk_S[blockIdx.x] * R) {
-    const int nrows = min(R, rend - row0);
-    if (LAST)
-      aggregate_tile<T, D>(g, lsrc, TileSink<D>{tile}, row0, nrows, red, hlist, a.heavy_partial);
-    else
-      aggregate_tile<T, D>(g, psrc, TileSink<D>{tile}, row0, nrows, red, hlist, a.heavy_partial);
-    // Hprev tile -> LDS (fp32), zero beyond the tile's rows
-    for (int idx = tid; idx < R * LPR; idx += kBlock) {
-      const int r = idx / LPR, cc = (idx % LPR) * VEC;
-      float v[VEC];
-      if (r < nrows) {
-        Store<T>::load(Hprev + static_cast<size_t>(row0 + r) * D + cc, v);
-      } else {
-#pragma unroll
-        for (int x = 0; x < VEC; ++x) v[x] = 0.f;
-      }
-#pragma unroll
-      for (int x = 0; x < VEC; ++x) hp[r * LD + cc + x] = v[x];
-    }
-    if (LAST && tid < D) {
-      const T* Hcur = static_cast<const T*>(a.Hcur);
-      for (int r = 0; r < nrows; ++r)
-        gwo = fmaf(Store<T>::get(Hcur + static_cast<size_t>(row0 + r) * D + tid), a.g_t[row0 + r], gwo);
-    }
-    __syncthreads();
-    // gW[a_, c] += sum_r Hprev[r, a_] * G_T[r, c]
-    if (gw_active) {
-      for (int r = 0; r < R; ++r) {
-        const float gt = tile[r * LD + c];
-#pragma unroll
-        for (int i = 0; i < NA; ++i) gw[i] = fmaf(hp[r * LD + rg + i * AG], gt, gw[i]);
-      }
-    }
-    // G_Hprev[r, c] = sum_b G_T[r, b] * W[c, b]
-    if (!(TO_EMBED && a.mode == EMBED_SKIP)) {
-      float gh[NR];
-      tile_times_matrix<D>(tile, Wt, gh);
-#pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const int r = rg + i * RG;
-        if (r >= nrows) continue;
-        const size_t idx = static_cast<size_t>(row0 + r) * D + c;
-        if (TO_EMBED) {
-          if (a.mode == EMBED_WRITE_GRAD) {
-            a.gE[idx] = gh[i];
-          } else {
-            const float gq = gh[i];
-            const float m = ad.b1 * a.mE[idx] + (1.f - ad.b1) * gq;
-            const float v = ad.b2 * a.vE[idx] + (1.f - ad.b2) * gq * gq;
-            const float upd = (m * ad.inv_bc1) / (sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps);
-            const float e = a.E[idx] - ad.lr * upd;
-            a.mE[idx] = m;
-            a.vE[idx] = v;
-            a.E[idx] = e;
-            if (sizeof(T) == 2) Store<T>::put(static_cast<T*>(a.Eb) + idx, e);
-          }
-        } else {
-          Store<T>::put(static_cast<T*>(a.GZ_out) + idx, hp[r * LD + c] > 0.f ? gh[i] : 0.f);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (gw_active) {
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-      a.gW_partial[static_cast<size_t>(blockIdx.x) * D * D + (rg + i * AG) * D + c] = gw[i];
-  }
-  if (LAST && tid < D) a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + tid] = gwo;
 }
 
 // L = 1: p = sigmoid(A_hat (E w)).  gw partial = sum_i X[i,:] g_t[i]; gE[i,:] = g_t[i] w.
@@ -629,31 +401,13 @@ void allow_lds(K kernel, size_t bytes) {
     default: break;                                                 \
   }
 
-template <typename T, int D>
-static void fwd_hidden_t(const Launch& ln, const GraphView& g, const void* X, const float* W,
-                         int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
-                         float* heavy_partial) {
-  if (g.num_chunks > 0) {
-    ln.begin(KK_HEAVY);
-    PlainSrc<T, D> src{static_cast<const T*>(X), g.sb};
-    heavy_wide_kernel<T, D, PlainSrc<T, D>><<<g.num_chunks, kBlock, 0, ln.st>>>(g, src, heavy_partial);
-    ln.end(KK_HEAVY);
-  }
-  const size_t lds = fwd_lds_bytes<D>(Store<T>::VEC);
-  allow_lds(fwd_hidden_kernel<T, D>, lds);
-  ln.begin(KK_FWD_HIDDEN);
-  fwd_hidden_kernel<T, D><<<g.num_blocks, kBlock, lds, ln.st>>>(
-      g, static_cast<const T*>(X), W, w_stride, static_cast<T*>(Y), w_out, wout_stride, t, heavy_partial);
-  ln.end(KK_FWD_HIDDEN);
-}
-
 void launch_fwd_hidden(const Launch& ln, int storage, int D, const GraphView& g, const void* X,
                        const float* W, int w_stride, void* Y, const float* w_out, int wout_stride,
                        float* t, float* heavy_partial, bool partial_ready) {
   if (storage == GCO_STORAGE_BF16) {
     launch_fwd_hidden_bf16(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, heavy_partial, partial_ready);
   } else {
-    GCO_DISPATCH_D(float, D, (fwd_hidden_t<float, DD>(ln, g, X, W, w_stride, Y, w_out, wout_stride, t, heavy_partial)))
+    launch_fwd_hidden_f32(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, heavy_partial);
   }
 }
 
@@ -705,43 +459,12 @@ void launch_loss_reduce(const Launch& ln, const GraphView& g, const double* loss
   ln.end(KK_LOSS_REDUCE);
 }
 
-template <typename T, int D>
-static void bwd_hidden_t(const Launch& ln, bool last, bool to_embed, const GraphView& g,
-                         const BwdArgs& a) {
-  const GraphView gt = transposed(g);
-  if (g.num_chunks > 0) {
-    ln.begin(KK_HEAVY);
-    if (last) {
-      LastSrc<T, D> src{static_cast<const T*>(a.Hcur), gt.sb, a.g_t, a.w_out, a.wout_stride, {}};
-      heavy_wide_kernel<T, D, LastSrc<T, D>><<<g.num_chunks, kBlock, 0, ln.st>>>(gt, src, a.heavy_partial);
-    } else {
-      PlainSrc<T, D> src{static_cast<const T*>(a.GZ_in), gt.sb};
-      heavy_wide_kernel<T, D, PlainSrc<T, D>><<<g.num_chunks, kBlock, 0, ln.st>>>(gt, src, a.heavy_partial);
-    }
-    ln.end(KK_HEAVY);
-  }
-  const size_t lds = bwd_lds_bytes<D>(Store<T>::VEC);
-  const int kind = to_embed ? KK_BWD_EMBED : KK_BWD_HIDDEN;
-  ln.begin(kind);
-#define GCO_BWD(L_, E_)                                                        \
-  {                                                                            \
-    allow_lds(bwd_hidden_kernel<T, D, L_, E_>, lds);                           \
-    bwd_hidden_kernel<T, D, L_, E_><<<g.num_blocks, kBlock, lds, ln.st>>>(gt, a); \
-  }
-  if (last && to_embed) GCO_BWD(true, true)
-  else if (last) GCO_BWD(true, false)
-  else if (to_embed) GCO_BWD(false, true)
-  else GCO_BWD(false, false)
-#undef GCO_BWD
-  ln.end(kind);
-}
-
 void launch_bwd_hidden(const Launch& ln, int storage, int D, bool last, bool to_embed,
                        const GraphView& g, const BwdArgs& a) {
   if (storage == GCO_STORAGE_BF16) {
     launch_bwd_hidden_bf16(ln, D, last, to_embed, transposed(g), a);
   } else {
-    GCO_DISPATCH_D(float, D, (bwd_hidden_t<float, DD>(ln, last, to_embed, g, a)))
+    launch_bwd_hidden_f32(ln, D, last, to_embed, transposed(g), a);
   }
 }
 

@@ -1,0 +1,62 @@
+"""GPU parity of the fp32 hidden-layer kernels where their 16-row tiles, the shares of a tile's
+entries and the classes of row lengths begin and end.  Tolerance as in test_gpu_parity: fp32
+sums of at most a few hundred terms against fp64, norm-wise 1e-5."""
+import numpy as np
+import pytest
+
+from oracle import gcn
+from paper_2511_09261_amd import inputs
+from tests.parity import rel
+
+pytestmark = pytest.mark.gpu
+
+
+def ragged_subgraphs(seed):
+    """Subgraphs of 1, 15, 16, 17, 32, 33, 64, 65 and 129 rows with random edges, and three with a
+    hub of 255, 256 and 257 neighbours (the last class that is summed in place, the first two
+    that come pre-reduced), all node ids shuffled."""
+    rs = np.random.RandomState(seed)
+    us, vs, part, base = [], [], [], 0
+    for k, rows in enumerate([1, 15, 16, 17, 32, 33, 64, 65, 129, 256, 300, 700]):
+        m = 3 * rows if rows > 1 else 0
+        us.append(base + rs.randint(0, rows, m))
+        vs.append(base + rs.randint(0, rows, m))
+        spokes = {256: 255, 300: 256, 700: 257}.get(rows, 0)
+        if spokes:  # the hub is a node the random edges leave alone
+            us[-1][us[-1] == base + rows // 2] = base
+            vs[-1][vs[-1] == base + rows // 2] = base
+            others = np.setdiff1d(np.arange(rows), [rows // 2])[:spokes]
+            us.append(np.full(spokes, base + rows // 2))
+            vs.append(base + others)
+        part.append(np.full(rows, k))
+        base += rows
+    name = rs.permutation(base)
+    ids = np.empty(base, dtype=np.int32)
+    ids[name] = np.concatenate(part)
+    return inputs.from_edges(base, name[np.concatenate(us)], name[np.concatenate(vs)]), ids, 12
+
+
+@pytest.mark.parametrize("D", [8, 16, 32, 64, 128])
+@pytest.mark.parametrize("L,norm,share", [(2, "sym", False), (3, "mean", False), (3, "sym", True)])
+def test_tile_and_row_length_edges(gco, D, L, norm, share):
+    g, part, P = ragged_subgraphs(D + L)
+    E, Ws = inputs.init_params(g.n, part, 1 if share else P, L, D, 3)
+    E, Ws = (E * 5).astype(np.float32), [W * 1.5 for W in Ws]
+    ctx = gco.Context(num_layers=L, dim=D, norm=norm, weight_sharing=share)
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    spec = gcn.Spec(num_layers=L, norm=norm, weight_sharing=share)
+    lg = gcn.local_graph(g.n, g.rowptr, g.col, part, P, norm)
+    cache = gcn.forward(lg, E, Ws, spec)
+    gE, gWs = gcn.backward(lg, cache, Ws, spec)
+    dE, dWs = ctx.get_grads()
+    assert rel(ctx.get_probs(), cache["p"]) <= 1e-5
+    for l in range(1, L):
+        assert rel(ctx.get_hidden(l), cache["H"][l]) <= 1e-5
+    assert rel(dE, gE) <= 1e-5
+    for l in range(L):
+        assert rel(dWs[l], gWs[l]) <= 1e-5, f"layer {l + 1}"
+    first = ctx.train(3)
+    ctx.set_params(E, Ws)
+    assert np.array_equal(first, ctx.train(3))  # one fixed order of additions
+    ctx.destroy()
