@@ -25,7 +25,7 @@ namespace {
 const char* const kKindNames[KK_COUNT] = {
     "fwd_hidden", "fwd_gemv", "fwd_readout", "loss", "bwd_readout",
     "bwd_hidden", "bwd_embed_adam", "adam_w", "loss_reduce", "heavy_rows", "form_gz",
-    "best_snapshot", "grad_w", "scalar_layer"};
+    "best_snapshot", "grad_w", "scalar_layer", "small_train"};
 
 struct EventPair {
   hipEvent_t a, b;
@@ -151,6 +151,8 @@ struct gco_ctx {
   int staged_wgs = 0, staged_cap = 0;
   int32_t *d_staged_k = nullptr, *d_staged_ptr = nullptr, *d_staged_launch = nullptr;
   int scalar_form_wanted = GCO_SCALAR_AUTO;
+  // whole epochs in one launch, a workgroup per subgraph (small_train.hip); its LDS, 0 = not used
+  size_t small_train_lds = 0;
   int2* d_fused_cuts = nullptr;
   int32_t* d_heavy_ptr = nullptr;
   WaveRun* d_wave_runs[kWaveMaps] = {};
@@ -501,6 +503,25 @@ void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<
       run.tglob = tbase[k];
     }
   }
+}
+
+// Whether training runs faster with a workgroup per subgraph for whole epochs (small_train.hip)
+// than with four to eight launches per epoch over the whole chip; microseconds per epoch, from a
+// sweep over 1 .. 512 subgraphs of 60 .. 2500 rows with 3 .. 8 neighbours.  One compute unit is
+// bound by its instructions: a round of tiles (one per wavefront) takes a fixed time and one per
+// entry.  Measured, one / launches (us): 200 rows of width 16: 9.4 / 26 (1 subgraph), 22 / 55 (512);
+// 1250 rows: 37 / 44 and 94 / 184; width 32, 200 rows: 19 / 30, 1250 rows: 83 / 48 (1), 102 / 164
+// (256); width 64, 200 rows: 41 / 36 (1), 48 / 82 (256); bf16, 200 rows: 50 / 37, 59 / 71.
+bool small_train_pays(const gco_config& c, int P, int n, int64_t entries, int max_rows, int64_t max_entries) {
+  const bool bf16 = c.storage == GCO_STORAGE_BF16;
+  const double e = static_cast<double>(entries) / n;  // entries per row, the diagonal included
+  const double round = c.dim <= 16 ? 2.1 + 1.07 * e : c.dim == 32 ? 8.2 + 1.7 * e : (bf16 ? 17.0 : 11.0) + 1.4 * e;
+  const int tiles = (max_rows + kTileRowsF32 - 1) / kTileRowsF32, waves = c.dim <= 32 ? 16 : 8;
+  const double one = ((P + 255) / 256) * (8.0 + (c.num_layers - 1) * ((tiles + waves - 1) / waves) * round);
+  const double row_ns = c.dim <= 16 ? 0.1 + 0.04 * e : (bf16 ? 0.0095 : 0.0125) * c.dim;
+  const double launches = (c.num_layers == 2 ? 26.0 : 38.0) + 1.5e-3 * static_cast<double>(max_entries) +
+                          (c.num_layers - 1) * row_ns * 1e-3 * n;
+  return one < 0.9 * launches;
 }
 
 // Workgroup ids grouped by the subgraph they work on (ascending within a group);
@@ -989,7 +1010,8 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     const int cap = std::max(4, (max_rows + 3) / 4 * 4);
     constexpr size_t kLdsPerComputeUnit = 160 * 1024;
     constexpr int64_t kFusedMaxEntries = 40960;  // 40 steps per wavefront and pass
-    const int fused_nw = max_rows > 2048 ? 16 : 4;
+    // 16 wavefronts, 4 where the subgraphs are many (several workgroups per compute unit) or tiny
+    const int fused_nw = max_rows > 2048 || (P <= 256 && max_light > 512) ? 16 : 4;
     const bool fused_fits = scalar_fused_lds_bytes(fused_nw, cap) <= kLdsPerComputeUnit;
     const int staged_cap = (max_rows + 3 + 3) / 4 * 4;
     const bool staged_fits =
@@ -1004,6 +1026,17 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     ctx->fused_scalar =
         form == GCO_SCALAR_ONE_LAUNCH || (form == GCO_SCALAR_AUTO && fused_fits && max_light <= kFusedMaxEntries);
     ctx->staged_scalar = form == GCO_SCALAR_STAGED || (form == GCO_SCALAR_AUTO && !ctx->fused_scalar && staged_fits);
+    // Whole epochs in one launch: where the scalar layer is one launch anyway, every subgraph has
+    // weights of its own and fits the LDS with its stream, and that is the faster way
+    ctx->small_train_lds = 0;
+    if (ctx->fused_scalar && ctx->Pw == P && L >= 2 && D <= 64 && num_heavy == 0 &&
+        small_train_pays(ctx->cfg, P, n, total_light, max_rows, max_light)) {
+      size_t lds = 0;
+      for (int kk = 0; kk < P; ++kk)
+        lds = std::max(lds, small_train_lds_bytes(D, L, part_rows[kk + 1] - part_rows[kk],
+                                                  static_cast<int>(light_of[kk]), ctx->cfg.norm != GCO_NORM_SYM));
+      if (lds <= kLdsPerComputeUnit) ctx->small_train_lds = lds;
+    }
     ctx->fused_waves = fused_nw;
     ctx->fused_cap = cap;
     ctx->staged_cap = staged_cap;
@@ -1459,11 +1492,6 @@ static void run_scalar_layer(gco_ctx* ctx, const GraphView& gv, int passes, int 
   ctx->probs_valid = true;
 }
 
-static void run_forward(gco_ctx* ctx) {
-  run_hidden_forward(ctx, ctx->gv);
-  run_scalar_layer(ctx, ctx->gv, 1, 0);
-}
-
 // Adam constants for one more step when every subgraph and weight set has seen `step` steps.
 static AdamStep adam_constants(const gco_config& c, int64_t step) {
   AdamStep ad{};
@@ -1475,6 +1503,48 @@ static AdamStep adam_constants(const gco_config& c, int64_t step) {
   ad.inv_bc1 = static_cast<float>(1.0 / (1.0 - std::pow(static_cast<double>(c.adam_b1), tt)));
   ad.inv_sqrt_bc2 = static_cast<float>(1.0 / std::sqrt(1.0 - std::pow(static_cast<double>(c.adam_b2), tt)));
   return ad;
+}
+
+// Small subgraphs (small_train_lds != 0).  passes = 1: forward; 2: forward and loss, to set `slot`
+// of the loss partials; 3: `epochs` (at most kLossSets) epochs in one launch, their losses to the
+// sets from `slot` on.  uniform: the step counts of all models are `steps` before it; else bc
+// holds the bias corrections.  Forward, loss and training take every sum in the same order.
+static void run_small(gco_ctx* ctx, const GraphView& gv, int passes, int epochs, int slot, bool uniform,
+                      int64_t steps, const float2* bc) {
+  const gco_config& c = ctx->cfg;
+  SmallTrain a;
+  for (int l = 0; l < c.num_layers; ++l) {
+    a.H[l] = ctx->H[l];
+    a.W[l] = ctx->W[l];
+    a.mW[l] = ctx->mW[l];
+    a.vW[l] = ctx->vW[l];
+  }
+  a.GZ = c.num_layers == 3 ? ctx->GZ[1] : nullptr;
+  a.E = ctx->E;
+  a.mE = ctx->mE;
+  a.vE = ctx->vE;
+  a.Eb = ctx->Eb;
+  a.p = ctx->p;
+  a.c = ctx->d_c;
+  a.q = c.problem == GCO_PROBLEM_MAXCUT ? 2.f : c.alpha;
+  a.loss_partial = ctx->loss_partial + static_cast<size_t>(slot) * gv.num_loss_slots;
+  a.adam = adam_constants(c, 1);
+  if (!uniform) a.adam.per_part = bc;
+  for (int e = 0; uniform && e < epochs; ++e) {
+    const AdamStep ad = adam_constants(c, steps + e + 1);
+    a.bc[e] = make_float2(ad.inv_bc1, ad.inv_sqrt_bc2);
+  }
+  a.epochs = epochs;
+  a.passes = passes;
+  a.train_embed = c.train_embed;
+  launch_small_train(ctx->launch(), c.storage, c.dim, c.num_layers, gv, a, ctx->small_train_lds);
+  ctx->probs_valid = true;
+}
+
+static void run_forward(gco_ctx* ctx) {
+  if (ctx->small_train_lds != 0) return run_small(ctx, ctx->gv, 1, 1, 0, true, 0, nullptr);
+  run_hidden_forward(ctx, ctx->gv);
+  run_scalar_layer(ctx, ctx->gv, 1, 0);
 }
 
 // Backward pass from g_t on (run_scalar_layer with passes = 3 has run).
@@ -1599,6 +1669,13 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
   for (int64_t t : ctx->stepE) uniform = uniform && t == ctx->stepE[0];
   for (int64_t t : ctx->stepW) uniform = uniform && t == ctx->stepE[0];
   const gco_config& c = ctx->cfg;
+  // the losses of set e against the lowest so far, while the parameters still are the ones they
+  // belong to
+  auto offer_snapshot = [&](int e) {
+    launch_best_update(ctx->launch(), gv, ctx->loss_partial + static_cast<size_t>(e) * gv.num_loss_slots, Pw,
+                       ctx->d_best_loss, ctx->d_improved, ctx->d_has_best);
+    copy_params(ctx, gv, ctx->d_improved, /*to_best=*/true);
+  };
   std::vector<float2> bc;
   // the loss partials of up to kLossSets epochs are reduced by one launch; so are the
   // per-subgraph bias corrections of those epochs uploaded at once
@@ -1616,6 +1693,17 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
         }
       HIPCHK(h2d(ctx, ctx->d_bc, bc.data(), bc.size()));
     }
+    if (ctx->small_train_lds != 0) {
+      const int64_t steps = ctx->stepE.empty() ? 0 : ctx->stepE[0] + e0;
+      if (!ctx->best_on) run_small(ctx, gv, 3, ne, 0, uniform, steps, ctx->d_bc);
+      for (int e = 0; ctx->best_on && e < ne; ++e) {
+        run_small(ctx, gv, 2, 1, e, true, 0, nullptr);
+        offer_snapshot(e);
+        run_small(ctx, gv, 3, 1, e, uniform, steps + e, ctx->d_bc + static_cast<size_t>(e) * (P + Pw));
+      }
+      launch_loss_reduce(ctx->launch(), gv, ctx->loss_partial, ne, gv.num_loss_slots, nullptr, ctx->loss_hist + e0);
+      continue;
+    }
     for (int e = 0; e < ne; ++e) {
       AdamStep adE = adam_constants(c, ctx->stepE.empty() ? 1 : ctx->stepE[0] + e0 + e + 1), adW = adE;
       if (!uniform) {
@@ -1624,12 +1712,7 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
       }
       run_hidden_forward(ctx, gv);
       run_scalar_layer(ctx, gv, 3, e);
-      if (ctx->best_on) {
-        // the parameters still are the ones this loss belongs to
-        launch_best_update(ctx->launch(), gv, ctx->loss_partial + static_cast<size_t>(e) * gv.num_loss_slots,
-                           Pw, ctx->d_best_loss, ctx->d_improved, ctx->d_has_best);
-        copy_params(ctx, gv, ctx->d_improved, /*to_best=*/true);
-      }
+      if (ctx->best_on) offer_snapshot(e);
       run_backward(ctx, gv, maps, true, adE, adW, nullptr, nullptr);
     }
     launch_loss_reduce(ctx->launch(), gv, ctx->loss_partial, ne, gv.num_loss_slots, nullptr, ctx->loss_hist + e0);
@@ -1764,8 +1847,12 @@ int gco_get_probs(gco_ctx* ctx, float* p) {
 int gco_loss(gco_ctx* ctx, double* total, double* per_part) {
   if (!ctx) return GCO_EINVAL;
   NEED(ctx->has_params, GCO_ESTATE, "set_params must precede loss");
-  run_hidden_forward(ctx, ctx->gv);
-  run_scalar_layer(ctx, ctx->gv, 2, 0);
+  if (ctx->small_train_lds != 0) {
+    run_small(ctx, ctx->gv, 2, 1, 0, true, 0, nullptr);
+  } else {
+    run_hidden_forward(ctx, ctx->gv);
+    run_scalar_layer(ctx, ctx->gv, 2, 0);
+  }
   launch_loss_reduce(ctx->launch(), ctx->gv, ctx->loss_partial, 1, 0, ctx->loss_part, ctx->loss_one);
   HIPCHK(hipGetLastError());
   if (total) HIPCHK(d2h(ctx, total, ctx->loss_one, 1));

@@ -65,6 +65,7 @@ enum KernelKind : int {
   KK_BEST,             // best-by-loss snapshot: decision per model + copy of the improved ones
   KK_GRAD_W,           // weight gradient of a hidden layer from stored rows (bf16, width 128)
   KK_SCALAR_FUSED,     // read-out, loss and the scalar layer's backward aggregation in one launch
+  KK_SMALL_TRAIN,      // whole epochs of small subgraphs (up to kLossSets of them per launch)
   KK_COUNT
 };
 
@@ -383,6 +384,30 @@ struct ChunkTail {
 };
 void launch_adam_w(const Launch& ln, int Pw, const WeightTensor* tensors, int count, const AdamStep& adam,
                    bool update, bool many_partials, const ChunkTail* tail = nullptr);  // adam.per_part, if set, is indexed by weight set; sets without partials are left alone
+
+// ---- whole epochs of small subgraphs in one launch (small_train.hip) ----
+// For two or three layers of width <= 64, weights per subgraph and no pre-reduced rows; a
+// subgraph's stream has to fit the LDS (small_train_lds_bytes <= a compute unit's).  Loss
+// partials as by launch_scalar_fused: one per subgraph and epoch.
+struct SmallTrain {
+  void* H[3] = {};        // H[0]: the embeddings in storage type, H[l]: hidden layer l
+  void* GZ = nullptr;     // gradient rows between two hidden layers (three layers)
+  float *E = nullptr, *mE = nullptr, *vE = nullptr;
+  void* Eb = nullptr;     // bf16 working copy of E (bf16 storage)
+  float *W[3] = {}, *mW[3] = {}, *vW[3] = {};
+  float* p = nullptr;
+  const float* c = nullptr;
+  float q = 0.f;
+  double* loss_partial = nullptr;  // set e at loss_partial + e * num_loss_slots
+  AdamStep adam{};                 // per_part, if set: [epochs][2 P] (embeddings, then weights)
+  float2 bc[kLossSets];            // else the two bias corrections of every epoch
+  int epochs = 0;
+  int passes = 3;  // 1: forward only (p of one epoch); 2: and the loss; 3: whole epochs
+  int train_embed = 1;
+};
+size_t small_train_lds_bytes(int D, int L, int rows, int entries, bool mean);
+void launch_small_train(const Launch& ln, int storage, int D, int L, const GraphView& g, const SmallTrain& a,
+                        size_t lds);
 
 // fp32 -> bf16 copy (round to nearest even).
 // X[i, :] <- softmax((X[i, :] - log(-log(U[i, :]))) / tau), rows of width D (Sec. 3.2).

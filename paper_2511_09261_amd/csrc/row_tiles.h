@@ -1,0 +1,309 @@
+// Device code of the kernels that work on 16-row tiles of one wavefront each (see
+// tile_kernels_f32.hip for the layout): rows of fp32 or bf16 features, the aggregation of a
+// tile, and the fp32 matrix-core step of its dense products.
+#pragma once
+
+#include "device_utils.h"
+#include "gco_internal.h"
+
+namespace gco {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kTile = kTileRowsF32;  // rows of a tile
+static_assert(kTile == 16, "one 16-row matrix-core tile");
+
+template <int D>
+struct TF {
+  static constexpr int DP = D < 16 ? 16 : D;  // width of the tiles (width 8: upper half zero)
+  static constexpr int NQ = DP / 16;
+  static constexpr int U = D <= 16 ? 4 : (D <= 64 ? 3 : 1);  // entries of a lane group in flight at once
+  // pitch of 16-row tiles in LDS: the four rows of a B operand fall into different banks
+  static constexpr int PT = DP == 16 ? 16 : DP + 4;
+  static constexpr int kWaveLds = 2 * kTile * PT;  // floats: row sums, carries
+};
+
+__device__ __forceinline__ f32x4 mfma(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// This lane's four features of group q of row j.
+template <int D>
+__device__ __forceinline__ f32x4 load4(const float* X, int j, int q, int h) {
+  if (D == 8 && h >= 2) return f32x4{0.f, 0.f, 0.f, 0.f};
+  return *reinterpret_cast<const f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h);
+}
+template <int D>
+__device__ __forceinline__ f32x4 load4(const bf16_t* X, int j, int q, int h) {
+  const uint2 u = *reinterpret_cast<const uint2*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h);
+  return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+               __uint_as_float(u.y & 0xffff0000u)};
+}
+template <int D>
+__device__ __forceinline__ void store4(float* X, int j, int q, int h, const f32x4& v) {
+  if (D == 8 && h >= 2) return;
+  *reinterpret_cast<f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h) = v;
+}
+template <int D>
+__device__ __forceinline__ void store4(bf16_t* X, int j, int q, int h, const f32x4& v) {
+  *reinterpret_cast<uint2*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h) =
+      make_uint2(f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]));
+}
+
+// ---- sources of gathered rows: request() starts the loads of a row, add() uses them ----
+template <int D, typename T = float>
+struct PlainRows {
+  struct Row {
+    f32x4 x[TF<D>::NQ];
+  };
+  const T* X;
+  __device__ __forceinline__ void request(Row& r, int j, int h) const {
+#pragma unroll
+    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = load4<D>(X, j, q, h);
+  }
+  __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
+#pragma unroll
+    for (int q = 0; q < TF<D>::NQ; ++q)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[q][x] = fmaf(val, r.x[q][x], acc[q][x]);
+  }
+};
+
+// Rows of dL/dZ of the last hidden layer, formed from H and the scalar layer's gradient:
+// g_t[j] w[c] where H[j, c] > 0, rounded as stored.
+template <int D, typename T = float>
+struct LastRows {
+  struct Row {
+    f32x4 x[TF<D>::NQ];
+    float gt;
+  };
+  const T* H;
+  const float* g_t;
+  f32x4 w[D <= 64 ? TF<D>::NQ : 1];
+  const float* w_lds;  // width 128: w is read from LDS when used (32 registers less)
+  __device__ __forceinline__ void request(Row& r, int j, int h) const {
+    r.gt = g_t[j];
+#pragma unroll
+    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = load4<D>(H, j, q, h);
+  }
+  __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
+    int off = 4 * (threadIdx.x % 64 / 16);
+    if (D > 64) asm volatile("" : "+v"(off));  // not read ahead of the loop over the entries
+#pragma unroll
+    for (int q = 0; q < TF<D>::NQ; ++q) {
+      const f32x4 wq = D <= 64 ? w[D <= 64 ? q : 0] : *reinterpret_cast<const f32x4*>(w_lds + 16 * q + off);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) acc[q][x] = fmaf(val, r.x[q][x] > 0.f ? Store<T>::as_stored(r.gt * wq[x]) : 0.f, acc[q][x]);
+    }
+  }
+};
+
+// The lane number for reading the operands of W.  From width 32 on its value is hidden from
+// the compiler, which otherwise reads all operands before the tile loop and keeps them in
+// registers that the gather needs (width 64: 64 of them; measured as spills).
+template <int D>
+__device__ __forceinline__ int operand_lane(int lane) {
+  if (D >= 32) asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// Sum over the 16 lanes of a data-parallel-primitive row (all n of one h); every lane ends
+// with the total, in a fixed order.
+__device__ __forceinline__ float row16_sum(float v) {
+#define GCO_ROR(N) \
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+  GCO_ROR(8) GCO_ROR(4) GCO_ROR(2) GCO_ROR(1)
+#undef GCO_ROR
+  return v;
+}
+
+// What the aggregation of a tile starts from, requested a tile ahead: the tile's range of the
+// stream, the range of this lane's row in it, and the lane group's first entries.
+struct Entry {
+  int col, row;
+  float val;
+};
+// The light stream in memory (fp32 values); rows of the pre-reduced kind read -2.
+struct StreamInMemory {
+  const int2* went;
+  const int* wrowid;
+  const int* wrowptr;
+  static constexpr bool kPreReduced = true;
+  static constexpr int kByRow = 3;  // halves, see TileFacts::deal
+  __device__ __forceinline__ int begin_of(int row) const { return wrowptr[row]; }
+  __device__ __forceinline__ Entry at(int e) const {
+    const int2 c = went[e];
+    return Entry{c.x, wrowid[e], __int_as_float(c.y)};
+  }
+};
+template <int D>
+struct TileFacts {
+  int a, b;  // row n's range; rows past the end have the empty range at the end of the tile's
+  Entry first[TF<D>::U];
+  // Nothing here waits: the tile's own range is read from the lanes when it is needed.
+  template <class Stream>
+  __device__ __forceinline__ void request(const Stream& s, int r0, int r1) {
+    const int row = r0 + static_cast<int>(threadIdx.x % 16);
+    a = s.begin_of(min(row, r1));
+    b = s.begin_of(min(row + 1, r1));
+  }
+  int share;    // entries per lane group (uniform)
+  bool by_row;  // every lane group sums the row of its own number (uniform)
+  // How the tile's entries are dealt to the lane groups.  Row by row the tile takes its longest
+  // row, but an entry costs a third of the instructions (no row to watch for, no sums through
+  // LDS).  From memory every batch of entries is a round trip: taken up to 1.5 times the mean and
+  // two (150 k rows of width 64 with hubs: 9.6 ms per 20 epochs, with 3 times and four 10.5); with the
+  // stream in LDS and one compute unit's instructions the limit, up to 3 times and four (1250
+  // rows of width 16: 40.3 -> 37.0 us per epoch against equal shares throughout).
+  template <class Stream>
+  __device__ __forceinline__ void deal(const Stream&) {
+    const int len = b - a;
+    int longest = len;
+#define GCO_ROR(N) longest = max(longest, __builtin_amdgcn_update_dpp(0, longest, 0x120 + N, 0xf, 0xf, false));
+    GCO_ROR(8) GCO_ROR(4) GCO_ROR(2) GCO_ROR(1)
+#undef GCO_ROR
+    longest = __builtin_amdgcn_readfirstlane(longest);
+    share = (E1() - E0() + 15) / 16;
+    by_row = 2 * longest <= Stream::kByRow * (share + 1) + 1;
+    if (by_row) share = longest;
+  }
+  __device__ __forceinline__ int E0() const { return __builtin_amdgcn_readlane(a, 0); }
+  __device__ __forceinline__ int E1() const { return __builtin_amdgcn_readlane(b, 15); }
+  // first entry of this lane's group, and the end of its share
+  __device__ __forceinline__ int begin() const {
+    return by_row ? a : E0() + static_cast<int>(threadIdx.x % 16) * share;
+  }
+  __device__ __forceinline__ int end() const { return by_row ? b : min(begin() + share, E1()); }
+  // No branches around the loads, here and for the rows: a group whose share has ended reads on
+  // into the next one's (the stream is padded), and fetches its own row again.
+  template <class Stream>
+  static __device__ __forceinline__ void request_entries_at(const Stream& s, int e, Entry (&en)[TF<D>::U]) {
+#pragma unroll
+    for (int u = 0; u < TF<D>::U; ++u) en[u] = s.at(e + u);
+  }
+  template <class Stream>
+  __device__ __forceinline__ void request_entries(const Stream& s) {
+    deal(s);
+    request_entries_at(s, begin(), first);
+  }
+};
+
+// acc = (A_hat x)(row n of the tile at r0, this lane's features); zero for rows past r1.
+// `sums` is kWaveLds floats of this wavefront's LDS.  on_own(x) is called by one lane group
+// for every row of the tile with the gathered row itself.
+template <int D, class Stream, class Rows, class OnOwn>
+__device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stream, const Rows& rows,
+                                          const TileFacts<D>& f, int r0, int r1,
+                                          const float* __restrict__ heavy_partial, float* sums,
+                                          f32x4 (&acc)[TF<D>::NQ], OnOwn&& on_own) {
+  constexpr int NQ = TF<D>::NQ, U = TF<D>::U, PT = TF<D>::PT;
+  const int lane = threadIdx.x % 64, n = lane % 16, h = lane / 16;
+  float* carries = sums + kTile * PT;
+  const int E0 = f.E0(), share = f.share, e1 = f.end();
+  if (share == 0) {  // no rows (a wavefront that keeps step with its workgroup)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    return;
+  }
+  int e = f.begin();
+  Entry en[U];
+  typename Rows::Row x[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    en[u] = f.first[u];
+    rows.request(x[u], e + u < e1 ? en[u].col : r0, h);
+  }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bool pre_reduced = false;  // such a row is among this group's
+  const bool valid = r0 + n < r1;
+  // The row in hand (by_row: the group's own throughout) and the place of its sum.
+  int cur = f.by_row ? r0 + n : -1;
+  float* place = carries;
+  auto leave = [&]() {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(place + 16 * q + 4 * h) = acc[q];
+  };
+  if (f.by_row && valid) {  // a row begins with its diagonal entry
+    on_own(x[0]);
+    if (Stream::kPreReduced) pre_reduced = en[0].row < 0;
+  }
+  for (int b = 0; b < share; b += U, e += U) {
+    Entry nx[U];
+    TileFacts<D>::request_entries_at(stream, e + U, nx);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (e + u < e1) {
+        // the lone entry of a pre-reduced row has no row number; it is the diagonal one
+        const int row = Stream::kPreReduced && en[u].row < 0 ? en[u].col : en[u].row;
+        if (row != cur) {
+          if (cur >= 0) leave();
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+          cur = row;
+          if (Stream::kPreReduced) pre_reduced |= en[u].row < 0;
+          place = carries + n * PT;
+          if (en[u].col == row) {  // the row's diagonal entry
+            place = sums + (row - r0) * PT;
+            on_own(x[u]);
+          }
+        }
+        rows.add(x[u], en[u].val, acc);
+      }
+    }
+    if (b + U < share) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        en[u] = nx[u];
+        rows.request(x[u], e + U + u < e1 ? en[u].col : r0, h);
+      }
+    }
+  }
+  if (!f.by_row) {
+    if (cur >= 0) leave();
+    wave_lds_handoff();
+    // the row's sum: its place, then the carries of the groups it ran through.  Shares are far
+    // below 2^20 entries, so the float quotients of half-integers are on the right side.
+    const float inv = 1.f / static_cast<float>(share);
+    int grp = static_cast<int>((static_cast<float>(f.a - E0) + 0.5f) * inv);
+    const int last = static_cast<int>((static_cast<float>(f.b - E0) - 0.5f) * inv);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(sums + n * PT + 16 * q + 4 * h);
+#pragma unroll
+      for (int y = 0; y < 4; ++y) acc[q][y] = valid ? v[y] : 0.f;
+    }
+    for (++grp; __any(valid && grp <= last); ++grp) {
+      if (valid && grp <= last) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q] += *reinterpret_cast<const f32x4*>(carries + grp * PT + 16 * q + 4 * h);
+      }
+    }
+    wave_lds_handoff();
+  }
+  if (Stream::kPreReduced && __any(pre_reduced)) {  // pre-reduced rows: lane group n adds chunks n, n + 16, ...
+    const int hh = valid ? g.heavy_of_row[r0 + n] : -1;
+    unsigned todo = static_cast<unsigned>(__ballot(hh >= 0)) & 0xffffu;
+    while (todo != 0) {
+      const int r = __builtin_ctz(todo);
+      todo &= todo - 1;
+      const int hr = __builtin_amdgcn_readlane(hh, r);
+      const float scale = g.sa[r0 + r];  // the partials are sums without the row's scale
+      f32x4 part[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) part[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int ch = g.heavy_chunk_ptr[hr] + n; ch < g.heavy_chunk_ptr[hr + 1]; ch += 16)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) part[q] += load4<D>(heavy_partial, ch, q, h);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          const float s = row16_sum(part[q][y]);
+          if (n == r) acc[q][y] = fmaf(scale, s, acc[q][y]);
+        }
+    }
+  }
+}
+
+}  // namespace gco

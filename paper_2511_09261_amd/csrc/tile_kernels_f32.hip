@@ -26,262 +26,23 @@
 #include "device_utils.h"
 #include "gather.h"
 #include "gco_internal.h"
+#include "row_tiles.h"
 
 #include <type_traits>
 
 namespace gco {
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kTile = kTileRowsF32;  // rows of a tile
-static_assert(kTile == 16, "one 16-row matrix-core tile");
 constexpr int kWavesPerBlock = kBlock / 64;
 
 template <int D>
-struct TF {
-  static constexpr int DP = D < 16 ? 16 : D;  // width of the tiles (width 8: upper half zero)
-  static constexpr int NQ = DP / 16;
-  static constexpr int U = D <= 32 ? 4 : (D == 64 ? 3 : 1);  // entries of a lane group in flight at once
-  // pitch of 16-row tiles in LDS: the four rows of a B operand fall into different banks
-  static constexpr int PT = DP == 16 ? 16 : DP + 4;
+struct TK : TF<D> {
   // width 128: the weight-gradient accumulators (256 registers) are shared out over the four
   // wavefronts of the workgroup, which then advance in step
-  static constexpr int kWaveLds = 2 * kTile * PT;  // floats: row sums, carries
   static constexpr bool SHARED_GW = D == 128;
-  static constexpr int TB = SHARED_GW ? NQ / kWavesPerBlock : NQ;  // column tiles of gW per wavefront
+  static constexpr int TB = SHARED_GW ? TF<D>::NQ / kWavesPerBlock : TF<D>::NQ;  // column tiles of gW per wavefront
   static constexpr bool W_IN_LDS = D <= 64;  // width 128 reads the operands of W through the caches
 };
-
-__device__ __forceinline__ f32x4 mfma(float a, float b, const f32x4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// This lane's four features of group q of row j.
-template <int D>
-__device__ __forceinline__ f32x4 load4(const float* __restrict__ X, int j, int q, int h) {
-  if (D == 8 && h >= 2) return f32x4{0.f, 0.f, 0.f, 0.f};
-  return *reinterpret_cast<const f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h);
-}
-template <int D>
-__device__ __forceinline__ void store4(float* __restrict__ X, int j, int q, int h, const f32x4& v) {
-  if (D == 8 && h >= 2) return;
-  *reinterpret_cast<f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h) = v;
-}
-
-// ---- sources of gathered rows: request() starts the loads of a row, add() uses them ----
-template <int D>
-struct PlainRows {
-  struct Row {
-    f32x4 x[TF<D>::NQ];
-  };
-  const float* __restrict__ X;
-  __device__ __forceinline__ void request(Row& r, int j, int h) const {
-#pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = load4<D>(X, j, q, h);
-  }
-  __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
-#pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q)
-#pragma unroll
-      for (int x = 0; x < 4; ++x) acc[q][x] = fmaf(val, r.x[q][x], acc[q][x]);
-  }
-};
-
-// Rows of dL/dZ of the last hidden layer, formed from H and the scalar layer's gradient:
-// g_t[j] w[c] where H[j, c] > 0.
-template <int D>
-struct LastRows {
-  struct Row {
-    f32x4 x[TF<D>::NQ];
-    float gt;
-  };
-  const float* __restrict__ H;
-  const float* __restrict__ g_t;
-  f32x4 w[D <= 64 ? TF<D>::NQ : 1];
-  const float* w_lds;  // width 128: w is read from LDS when used (32 registers less)
-  __device__ __forceinline__ void request(Row& r, int j, int h) const {
-    r.gt = g_t[j];
-#pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = load4<D>(H, j, q, h);
-  }
-  __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
-    int off = 4 * (threadIdx.x % 64 / 16);
-    if (D > 64) asm volatile("" : "+v"(off));  // not read ahead of the loop over the entries
-#pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) {
-      const f32x4 wq = D <= 64 ? w[D <= 64 ? q : 0] : *reinterpret_cast<const f32x4*>(w_lds + 16 * q + off);
-#pragma unroll
-      for (int x = 0; x < 4; ++x) acc[q][x] = fmaf(val, r.x[q][x] > 0.f ? r.gt * wq[x] : 0.f, acc[q][x]);
-    }
-  }
-};
-
-// The lane number for reading the operands of W.  From width 32 on its value is hidden from
-// the compiler, which otherwise reads all operands before the tile loop and keeps them in
-// registers that the gather needs (width 64: 64 of them; measured as spills).
-template <int D>
-__device__ __forceinline__ int operand_lane(int lane) {
-  if (D >= 32) asm volatile("" : "+v"(lane));
-  return lane;
-}
-
-// Sum over the 16 lanes of a data-parallel-primitive row (all n of one h); every lane ends
-// with the total, in a fixed order.
-__device__ __forceinline__ float row16_sum(float v) {
-#define GCO_ROR(N) \
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
-  GCO_ROR(8) GCO_ROR(4) GCO_ROR(2) GCO_ROR(1)
-#undef GCO_ROR
-  return v;
-}
-
-// What the aggregation of a tile starts from, requested a tile ahead: the tile's range of the
-// stream, the range of this lane's row in it, and the lane group's first entries.
-struct Entry {
-  int col, row;
-  float val;
-};
-template <int D>
-struct TileFacts {
-  int a, b;  // row n's range; rows past the end have the empty range at the end of the tile's
-  Entry first[TF<D>::U];
-  // Nothing here waits: the tile's own range is read from the lanes when it is needed.
-  __device__ __forceinline__ void request(const GraphView& g, int r0, int r1) {
-    const int row = r0 + static_cast<int>(threadIdx.x % 16);
-    a = g.wrowptr[min(row, r1)];
-    b = g.wrowptr[min(row + 1, r1)];
-  }
-  __device__ __forceinline__ int E0() const { return __builtin_amdgcn_readlane(a, 0); }
-  __device__ __forceinline__ int E1() const { return __builtin_amdgcn_readlane(b, 15); }
-  __device__ __forceinline__ int share() const { return (E1() - E0() + 15) / 16; }  // entries per lane group
-  // first entry of this lane's group, and the end of its share
-  __device__ __forceinline__ int begin() const { return E0() + static_cast<int>(threadIdx.x % 16) * share(); }
-  __device__ __forceinline__ int end() const { return min(begin() + share(), E1()); }
-  __device__ __forceinline__ void request_entries(const GraphView& g) { request_entries_at(g, begin(), first); }
-  // No branches around the loads, here and for the rows: a group whose share has ended reads on
-  // into the next one's (the stream is padded), and fetches its own row again.
-  static __device__ __forceinline__ void request_entries_at(const GraphView& g, int e, Entry (&en)[TF<D>::U]) {
-#pragma unroll
-    for (int u = 0; u < TF<D>::U; ++u) {
-      const int2 c = g.went[e + u];
-      en[u].col = c.x;
-      en[u].val = __int_as_float(c.y);
-      en[u].row = g.wrowid[e + u];
-    }
-  }
-};
-
-// acc = (A_hat x)(row n of the tile at r0, this lane's features); zero for rows past r1.
-// `sums` is kWaveLds floats of this wavefront's LDS.  on_own(x) is called by one lane group
-// for every row of the tile with the gathered row itself.
-template <int D, class Rows, class OnOwn>
-__device__ __forceinline__ void aggregate(const GraphView& g, const Rows& rows, const TileFacts<D>& f, int r0,
-                                          int r1, const float* __restrict__ heavy_partial, float* sums,
-                                          f32x4 (&acc)[TF<D>::NQ], OnOwn&& on_own) {
-  constexpr int NQ = TF<D>::NQ, U = TF<D>::U, PT = TF<D>::PT;
-  const int lane = threadIdx.x % 64, n = lane % 16, h = lane / 16;
-  float* carries = sums + kTile * PT;
-  const int E0 = f.E0(), share = f.share(), e1 = f.end();
-  if (share == 0) {  // no rows (a wavefront that keeps step with its workgroup)
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    return;
-  }
-  int e = f.begin();
-  Entry en[U];
-  typename Rows::Row x[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    en[u] = f.first[u];
-    rows.request(x[u], e + u < e1 ? en[u].col : r0, h);
-  }
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bool pre_reduced = false;  // such a row is among this group's
-  int cur = -1;              // the row in hand
-  float* place = carries;    // where its sum goes
-  auto leave = [&]() {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(place + 16 * q + 4 * h) = acc[q];
-  };
-  for (int b = 0; b < share; b += U, e += U) {
-    Entry nx[U];
-    TileFacts<D>::request_entries_at(g, e + U, nx);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (e + u < e1) {
-        // the lone entry of a pre-reduced row has no row number; it is the diagonal one
-        const int row = en[u].row < 0 ? en[u].col : en[u].row;
-        if (row != cur) {
-          if (cur >= 0) leave();
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-          cur = row;
-          pre_reduced |= en[u].row < 0;
-          // a row begins with its diagonal entry
-          place = carries + n * PT;
-          if (en[u].col == row) {
-            place = sums + (row - r0) * PT;
-            on_own(x[u]);
-          }
-        }
-        rows.add(x[u], en[u].val, acc);
-      }
-    }
-    if (b + U < share) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        en[u] = nx[u];
-        rows.request(x[u], e + U + u < e1 ? en[u].col : r0, h);
-      }
-    }
-  }
-  if (cur >= 0) leave();
-  wave_lds_handoff();
-  // the row's sum: its place, then the carries of the groups it ran through.  Shares are far
-  // below 2^20 entries, so the float quotients of half-integers are on the right side.
-  const float inv = 1.f / static_cast<float>(max(share, 1));
-  int grp = static_cast<int>((static_cast<float>(f.a - E0) + 0.5f) * inv);
-  const int last = static_cast<int>((static_cast<float>(f.b - E0) - 0.5f) * inv);
-  const bool valid = r0 + n < r1;
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(sums + n * PT + 16 * q + 4 * h);
-#pragma unroll
-    for (int y = 0; y < 4; ++y) acc[q][y] = valid ? v[y] : 0.f;
-  }
-  for (++grp; __any(valid && grp <= last); ++grp) {
-    if (valid && grp <= last) {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) acc[q] += *reinterpret_cast<const f32x4*>(carries + grp * PT + 16 * q + 4 * h);
-    }
-  }
-  wave_lds_handoff();
-  if (__any(pre_reduced)) {  // pre-reduced rows of the tile: lane group n adds chunks n, n + 16, ...
-    const int hh = valid ? g.heavy_of_row[r0 + n] : -1;
-    unsigned todo = static_cast<unsigned>(__ballot(hh >= 0)) & 0xffffu;
-    while (todo != 0) {
-      const int r = __builtin_ctz(todo);
-      todo &= todo - 1;
-      const int hr = __builtin_amdgcn_readlane(hh, r);
-      const float scale = g.sa[r0 + r];  // the partials are sums without the row's scale
-      f32x4 part[NQ];
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) part[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int ch = g.heavy_chunk_ptr[hr] + n; ch < g.heavy_chunk_ptr[hr + 1]; ch += 16)
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) part[q] += load4<D>(heavy_partial, ch, q, h);
-#pragma unroll
-      for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int y = 0; y < 4; ++y) {
-          const float s = row16_sum(part[q][y]);
-          if (n == r) acc[q][y] = fmaf(scale, s, acc[q][y]);
-        }
-    }
-  }
-}
 
 // Rows [r0, r1) of this wavefront's run.
 __device__ __forceinline__ void run_rows(const WaveRun& run, int& r0, int& r1) {
@@ -292,8 +53,8 @@ __device__ __forceinline__ void run_rows(const WaveRun& run, int& r0, int& r1) {
 // operand(ta, q, lane) of all tiles to LDS, wl[(ta NQ + q) 64 + lane]: all loads first, one wait.
 template <int D, class Operand>
 __device__ __forceinline__ void fill_operands(f32x4* wl, const Operand& operand) {
-  constexpr int NQ = TF<D>::NQ;
-  if constexpr (TF<D>::W_IN_LDS) {
+  constexpr int NQ = TK<D>::NQ;
+  if constexpr (TK<D>::W_IN_LDS) {
     constexpr int kPer = (NQ * NQ * 64 + kBlock - 1) / kBlock;
     f32x4 v[kPer];
 #pragma unroll
@@ -312,8 +73,8 @@ __device__ __forceinline__ void fill_operands(f32x4* wl, const Operand& operand)
 // ---------------------------------------------------------------------------
 template <int D>
 constexpr size_t fwd_tile_lds() {
-  return (static_cast<size_t>(TF<D>::W_IN_LDS ? TF<D>::DP * TF<D>::DP : 0) + kWavesPerBlock * TF<D>::kWaveLds +
-          TF<D>::DP) *
+  return (static_cast<size_t>(TK<D>::W_IN_LDS ? TK<D>::DP * TK<D>::DP : 0) + kWavesPerBlock * TK<D>::kWaveLds +
+          TK<D>::DP) *
          sizeof(float);
 }
 
@@ -322,7 +83,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
     GraphView g, const float* __restrict__ X, const float* __restrict__ W, int w_stride, float* __restrict__ Y,
     const float* __restrict__ w_out, int wout_stride, float* __restrict__ t,
     const float* __restrict__ heavy_partial) {
-  constexpr int NQ = TF<D>::NQ;
+  constexpr int NQ = TK<D>::NQ;
   constexpr int kTaUnroll = D <= 64 ? NQ : 1;
   extern __shared__ __align__(16) unsigned char smem[];
   f32x4* wl = reinterpret_cast<f32x4*>(smem);
@@ -346,22 +107,23 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
   int r0, r1;
   run_rows(run, r0, r1);
   TileFacts<D> f, nf;
-  f.request(g, r0, r1);
+  const StreamInMemory stream{g.went, g.wrowid, g.wrowptr};
+  f.request(stream, r0, r1);
   fill_operands<D>(wl, w_operand);
-  float* wo = reinterpret_cast<float*>(smem + fwd_tile_lds<D>()) - TF<D>::DP;  // w_out^k
+  float* wo = reinterpret_cast<float*>(smem + fwd_tile_lds<D>()) - TK<D>::DP;  // w_out^k
   const bool last = w_out != nullptr;
-  if (last && tid < TF<D>::DP) wo[tid] = tid < D ? w_out[static_cast<size_t>(k) * wout_stride + tid] : 0.f;
+  if (last && tid < TK<D>::DP) wo[tid] = tid < D ? w_out[static_cast<size_t>(k) * wout_stride + tid] : 0.f;
   __syncthreads();
-  float* sums = reinterpret_cast<float*>(smem) + (TF<D>::W_IN_LDS ? TF<D>::DP * TF<D>::DP : 0) + wave * TF<D>::kWaveLds;
+  float* sums = reinterpret_cast<float*>(smem) + (TK<D>::W_IN_LDS ? TK<D>::DP * TK<D>::DP : 0) + wave * TK<D>::kWaveLds;
   if (r0 >= r1) return;
   const PlainRows<D> rows{X};
-  f.request_entries(g);
+  f.request_entries(stream);
   for (; r0 < r1; r0 += kTile) {
     const int row = r0 + n;
-    nf.request(g, r0 + kTile, r1);
+    nf.request(stream, r0 + kTile, r1);
     f32x4 acc[NQ];
-    aggregate<D>(g, rows, f, r0, r1, heavy_partial, sums, acc, [](const typename PlainRows<D>::Row&) {});
-    nf.request_entries(g);
+    aggregate<D>(g, stream, rows, f, r0, r1, heavy_partial, sums, acc, [](const typename PlainRows<D>::Row&) {});
+    nf.request_entries(stream);
     float part = 0.f;
     const int wlane = operand_lane<D>(lane);
 #pragma unroll kTaUnroll
@@ -369,7 +131,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
       f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int q = 0; q < NQ; ++q) {
-        const f32x4 w = TF<D>::W_IN_LDS ? wl[(ta * NQ + q) * 64 + wlane] : w_operand(ta, q, wlane);
+        const f32x4 w = TK<D>::W_IN_LDS ? wl[(ta * NQ + q) * 64 + wlane] : w_operand(ta, q, wlane);
 #pragma unroll
         for (int j = 0; j < 4; ++j) z = mfma(w[j], acc[q][j], z);
       }
@@ -396,15 +158,15 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
 // ---------------------------------------------------------------------------
 template <int D>
 constexpr size_t bwd_tile_lds() {
-  constexpr size_t w = TF<D>::W_IN_LDS ? static_cast<size_t>(TF<D>::DP) * TF<D>::DP : 0;
-  constexpr size_t gt = static_cast<size_t>(kWavesPerBlock) * TF<D>::kWaveLds;
-  constexpr size_t reduce = TF<D>::SHARED_GW ? 0 : 2 * static_cast<size_t>(TF<D>::DP) * TF<D>::DP;
-  return (w + (gt > reduce ? gt : reduce) + kWavesPerBlock * TF<D>::DP) * sizeof(float);
+  constexpr size_t w = TK<D>::W_IN_LDS ? static_cast<size_t>(TK<D>::DP) * TK<D>::DP : 0;
+  constexpr size_t gt = static_cast<size_t>(kWavesPerBlock) * TK<D>::kWaveLds;
+  constexpr size_t reduce = TK<D>::SHARED_GW ? 0 : 2 * static_cast<size_t>(TK<D>::DP) * TK<D>::DP;
+  return (w + (gt > reduce ? gt : reduce) + kWavesPerBlock * TK<D>::DP) * sizeof(float);
 }
 
 template <int D, bool LAST, bool TO_EMBED>
 __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_tile_kernel(GraphView g, BwdArgs a) {
-  using T = TF<D>;
+  using T = TK<D>;
   constexpr int NQ = T::NQ, DP = T::DP, PT = T::PT, TB = T::TB;
   constexpr int WM = TO_EMBED ? WM_EMBED : WM_BWD;
   using Rows = std::conditional_t<LAST, LastRows<D>, PlainRows<D>>;
@@ -443,7 +205,8 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   }
   const int first = T::SHARED_GW ? r0 - wave * kTile : r0;  // of the workgroup, or of the wavefront
   TileFacts<D> f, nf;
-  f.request(g, r0, r1);
+  const StreamInMemory stream{g.went, g.wrowid, g.wrowptr};
+  f.request(stream, r0, r1);
   // A operands of G_H^T = W G_T^T: [(ta NQ + q) 64 + lane][j] = W[16 ta + n][16 q + 4 h + j]
   fill_operands<D>(wl, [&](int ta, int q, int l) {
     const int o = 16 * ta + l % 16;
@@ -475,7 +238,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
 #pragma unroll
   for (int q = 0; q < (LAST ? NQ : 1); ++q) gwo[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  f.request_entries(g);
+  f.request_entries(stream);
   // what the epilogue needs of the row: Adam's E, m, v, or the row of Hprev for its mask
   const bool adam = TO_EMBED && a.mode == EMBED_ADAM;
   f32x4 s_e[NS], s_m[TO_EMBED ? NS : 1], s_v[TO_EMBED ? NS : 1];
@@ -495,7 +258,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   for (int base = first; base < r1; base += kStep, r0 += kStep) {
     const int row = r0 + n;
     const bool valid = row < r1;
-    nf.request(g, r0 + kStep, r1);
+    nf.request(stream, r0 + kStep, r1);
     // rows of Hprev as the A operand of the weight gradient (contraction index h of step s:
     // row 4 s + h), requested ahead of the gather
     float av[T::SHARED_GW ? 1 : 4][NQ];
@@ -511,7 +274,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
     }
     if (kState == BEFORE_GATHER) request_state(row, 0);
     f32x4 acc[NQ];
-    aggregate<D>(g, rows, f, r0, r1, a.heavy_partial, gt, acc, [&](const typename Rows::Row& own) {
+    aggregate<D>(g, stream, rows, f, r0, r1, a.heavy_partial, gt, acc, [&](const typename Rows::Row& own) {
       if constexpr (LAST) {  // gradient of w_out
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
@@ -519,7 +282,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
           for (int y = 0; y < 4; ++y) gwo[q][y] = fmaf(own.x[q][y], own.gt, gwo[q][y]);
       }
     });
-    nf.request_entries(g);
+    nf.request_entries(stream);
     if (kState != BEFORE_GATHER) request_state(row, 0);
     // gW[a, c] += sum over the tile's rows of Hprev[row, a] G_T[row, c]
 #pragma unroll
@@ -581,10 +344,11 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
               f32x4 e;
 #pragma unroll
               for (int x = 0; x < 4; ++x) {
-                m[x] = ad.b1 * m[x] + (1.f - ad.b1) * z[x];
-                v[x] = ad.b2 * v[x] + (1.f - ad.b2) * z[x] * z[x];
-                const float upd = (m[x] * ad.inv_bc1) / (sqrtf(v[x]) * ad.inv_sqrt_bc2 + ad.eps);
-                e[x] = hold_e[x] - ad.lr * upd;
+                float ex = hold_e[x], mx = m[x], vx = v[x];
+                adam_value(ad, z[x], ex, mx, vx);
+                e[x] = ex;
+                m[x] = mx;
+                v[x] = vx;
               }
               store4<D>(a.mE, row, ta, h, m);
               store4<D>(a.vE, row, ta, h, v);

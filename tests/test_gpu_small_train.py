@@ -1,0 +1,102 @@
+"""GPU parity of the kernel that trains small subgraphs for whole epochs in one launch: loss
+trajectories and parameters against the fp64 checker where its tiles, wavefront rounds and
+launches begin and end; forward, loss and training agree bit for bit.
+
+Tolerances: fp32 1e-4 over ten epochs and bf16 2e-2, as in test_gpu_parity."""
+import numpy as np
+import pytest
+
+from oracle import gcn
+from paper_2511_09261_amd import inputs
+from tests.parity import rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def ragged(sizes, seed, per_node=2):
+    """Subgraphs of the given sizes (0: no node) with about `per_node` edges per node, ids shuffled."""
+    rs = np.random.RandomState(seed)
+    us, vs, part, base = [], [], [], 0
+    for k, rows in enumerate(sizes):
+        m = per_node * rows if rows > 1 else 0
+        us.append(base + rs.randint(0, max(rows, 1), m))
+        vs.append(base + rs.randint(0, max(rows, 1), m))
+        part.append(np.full(rows, k))
+        base += rows
+    name = rs.permutation(base)
+    ids = np.empty(base, dtype=np.int32)
+    ids[name] = np.concatenate(part)
+    return inputs.from_edges(base, name[np.concatenate(us)], name[np.concatenate(vs)]), ids, len(sizes)
+
+
+def used(ctx):
+    return ctx.get_timing()["small_train"]["launches"]
+
+
+@pytest.mark.parametrize("D,L,norm,storage", [(8, 2, "sym", "fp32"), (16, 3, "mean", "fp32"), (32, 2, "mean", "fp32"),
+                                              (32, 3, "sym", "fp32"), (64, 2, "sym", "fp32"), (64, 3, "mean", "fp32"),
+                                              (64, 2, "mean", "bf16"), (64, 3, "sym", "bf16")])
+def test_whole_epochs_of_small_subgraphs(gco, D, L, norm, storage):
+    # one row, tile edges, and one to two rounds of tiles; enough subgraphs that this is the chosen way
+    sizes = [1, 0, 15, 16, 17, 33, 63, 64] + [64] * 240 if D >= 32 else [1, 0, 15, 16, 17, 33, 255, 256, 257] + [60] * 60
+    g, part, P = ragged(sizes, D + L, 1 if D == 64 else 2)
+    E, Ws = inputs.init_params(g.n, part, P, L, D, 5)
+    E = (E * 3).astype(np.float32)
+    ctx = gco.Context(num_layers=L, dim=D, norm=norm, storage=storage, lr=1e-2)
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    spec = gcn.Spec(num_layers=L, norm=norm, lr=1e-2, storage="bf16" if storage == "bf16" else "exact")
+    lg = gcn.local_graph(g.n, g.rowptr, g.col, part, P, norm)
+    tol = 1e-4 if storage == "fp32" else 2e-2
+    extra = (np.arange(g.n) % 7 == 0).astype(np.float32) * 0.5
+    ctx.set_linear_penalty(extra)
+    ctx.set_profiling(1)
+    total, per = ctx.loss()
+    got = ctx.train(10)
+    assert used(ctx) == 2
+    assert got[0] == total == pytest.approx(per.sum(), rel=1e-12)
+    st = gcn.init_state(E, Ws)
+    want, _ = gcn.train(lg, st, spec, 10, extra_linear=extra)
+    assert np.abs(got - want).max() <= tol * np.abs(want).max()
+    dE, dW = ctx.get_params()
+    # Parameters in the 2-norm: a single value whose gradient is zero to within rounding may end up to
+    # 2 * 10 epochs * lr = 0.2 apart, since Adam's step is about lr * sign(gradient) however small
+    # the gradient is; with at most 1 value in 10^4 (fp32; 1 in 30 with bf16 roundings of 2^-9) of
+    # that kind, moved by lr per epoch on values of about 0.15, the 2-norms are within
+    # sqrt(1e-4) * 0.1 / 0.15 < 1e-2 (fp32) and sqrt(1/30) * 0.1 / 0.15 < 0.13 (bf16).
+    bound = 1e-2 if storage == "fp32" else 0.13
+    assert rel_l2(dE, st.E) <= bound
+    for l in range(L):
+        assert rel_l2(dW[l], st.Ws[l]) <= bound
+    # a subset with step counts of its own, the others bit for bit as they were
+    listed = np.arange(0, P, 3, dtype=np.int32)
+    out = ~np.isin(part, listed)
+    p = ctx.get_probs()
+    ctx.train_subset(3, listed)
+    E2, _ = ctx.get_params()
+    assert np.array_equal(E2[out], dE[out]) and np.array_equal(ctx.get_probs()[out], p[out])
+    assert ctx.get_steps()[0].tolist() == [13 if k % 3 == 0 else 10 for k in range(P)]
+    # more epochs than one launch takes: the same as two calls
+    ctx.set_params(E, Ws)
+    long = ctx.train(70)
+    ctx.set_params(E, Ws)
+    assert np.array_equal(long, np.concatenate([ctx.train(64), ctx.train(6)]))
+    ctx.destroy()
+
+
+def test_snapshots_of_small_subgraphs_cost_no_bit(gco):
+    g, part, P = ragged([40] * 50 + [0, 1], 9)
+    E, Ws = inputs.init_params(g.n, part, P, 2, 16, 5)
+    ctx = gco.Context(num_layers=2, dim=16, lr=5e-2)
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    plain = ctx.train(12)
+    ctx.set_params(E, Ws)
+    ctx.keep_best(True)
+    assert np.array_equal(plain, ctx.train(12))
+    best = ctx.get_best_loss()
+    ctx.restore_best()
+    _, per = ctx.loss()
+    has = np.isfinite(best)
+    assert np.array_equal(per[has], best[has])
+    ctx.destroy()
