@@ -987,12 +987,10 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   }
   {  // Form of the scalar layer's three passes.
      // ONE launch (a workgroup per subgraph, vectors in LDS): if two vectors of the largest
-     // subgraph fit a compute unit's LDS and no subgraph is so large that its one workgroup
-     // would take longer than three launches spread over the whole chip (measured at c4: one
-     // subgraph with 147 k entries of the light stream, 3.8 times the mean, 0.40 ms against
-     // 0.09 ms).  Else three launches that STAGE the gathered vector of a subgraph in LDS
-     // (several workgroups per subgraph), if that vector fits twice per compute unit.  Else
-     // three launches that gather from memory.
+     // subgraph fit a compute unit's LDS and its one workgroup takes no longer than three
+     // launches spread over the whole chip.  Else three launches that STAGE the gathered vector
+     // of a subgraph in LDS (several workgroups per subgraph), if that vector fits twice per
+     // compute unit.  Else three launches that gather from memory.
     int max_rows = 0;
     int64_t max_light = 0, total_light = 0;
     std::vector<int64_t> light_of(P, 0);
@@ -1009,7 +1007,6 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     }
     const int cap = std::max(4, (max_rows + 3) / 4 * 4);
     constexpr size_t kLdsPerComputeUnit = 160 * 1024;
-    constexpr int64_t kFusedMaxEntries = 40960;  // 40 steps per wavefront and pass
     // 16 wavefronts, 4 where the subgraphs are many (several workgroups per compute unit) or tiny
     const int fused_nw = max_rows > 2048 || (P <= 256 && max_light > 512) ? 16 : 4;
     const bool fused_fits = scalar_fused_lds_bytes(fused_nw, cap) <= kLdsPerComputeUnit;
@@ -1023,8 +1020,14 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     NEED(form != GCO_SCALAR_STAGED || staged_fits, GCO_ERANGE,
          "the staged scalar layer needs the largest subgraph's vector (%d rows) twice in %zu bytes of LDS and at "
          "most %d rows", max_rows, kLdsPerComputeUnit, scalar_staged_max_cap() - 3);
-    ctx->fused_scalar =
-        form == GCO_SCALAR_ONE_LAUNCH || (form == GCO_SCALAR_AUTO && fused_fits && max_light <= kFusedMaxEntries);
+    // ONE launch takes 6 us and 2.3 per 1024 entries of the largest subgraph (a step of its
+    // wavefronts) for every 256 subgraphs, three staged ones 27 and 13 per million entries of all;
+    // measured, one / staged: 64 subgraphs of 41 k entries 121 / 57, of 31 k entries 64 / 45, 6 of
+    // 64 subgraphs of 24 k entries 58 / 36, 16 subgraphs of 2 k entries 9 / 25, 256 of 25 k 71 / 110.
+    const double steps = static_cast<double>((max_light + 1023) / 1024);
+    const bool fused_pays = 6.0 + 2.3 * steps * ((P + 255) / 256) <= 27.0 + 13e-6 * static_cast<double>(total_light);
+    ctx->fused_scalar = form == GCO_SCALAR_ONE_LAUNCH ||
+                        (form == GCO_SCALAR_AUTO && fused_fits && (fused_pays || !staged_fits));
     ctx->staged_scalar = form == GCO_SCALAR_STAGED || (form == GCO_SCALAR_AUTO && !ctx->fused_scalar && staged_fits);
     // Whole epochs in one launch: where the scalar layer is one launch anyway, every subgraph has
     // weights of its own and fits the LDS with its stream, and that is the faster way
