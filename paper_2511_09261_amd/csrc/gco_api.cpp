@@ -27,6 +27,9 @@ const char* const kKindNames[KK_COUNT] = {
     "bwd_hidden", "bwd_embed_adam", "adam_w", "loss_reduce", "heavy_rows", "form_gz",
     "best_snapshot", "grad_w", "scalar_layer", "small_train"};
 
+// Whether the workgroups of a subgraph are placed on one XCD (see build_block_map).
+enum class Grouping { kNone, kIfEven, kAlways };
+
 struct EventPair {
   hipEvent_t a, b;
 };
@@ -125,22 +128,28 @@ struct gco_ctx {
   // at upload) and on the device twice: for all subgraphs (`full`) and for the subset of
   // the current gco_train_subset call (`sub`, units of the other subgraphs marked -1).
   struct HostMaps {
-    std::vector<int> blk_k, nblk_k, wblk_k[kWaveMaps], chunk_part, heavy_rows, heavy_part, staged_k;
+    std::vector<int> blk_k, nblk_k, chunk_part, heavy_rows, heavy_part, staged_k;
+    // what the runs of the wave kernels are cut from: first row of every subgraph, offset of
+    // every row in the light stream
+    std::vector<int> part_rows, wrow;
+    Grouping grouping = Grouping::kNone;
   } hm;
   struct ActiveMaps {
-    int32_t *blk_k = nullptr, *nblk_k = nullptr, *wblk_k[kWaveMaps] = {}, *chunk_part = nullptr,
-            *heavy_rows = nullptr;
+    int32_t* block = nullptr;  // one allocation and one copy hold all of the following
+    size_t capacity = 0;       // in ints
+    const WaveRun* wave_runs[kWaveMaps] = {};
+    int num_wblocks[kWaveMaps] = {};
+    const int32_t *blk_k = nullptr, *nblk_k = nullptr, *wblk_k[kWaveMaps] = {}, *chunk_part = nullptr,
+                  *heavy_rows = nullptr;
     // workgroups that hold partials, per weight set: wide kernels, wave kernels, narrow tiles
-    int32_t *pbl_ptr = nullptr, *pbl_list = nullptr;
-    int32_t *wpbl_ptr[kWaveMaps] = {}, *wpbl_list[kWaveMaps] = {};
-    int32_t *nwbl_ptr = nullptr, *nwbl_list = nullptr;
+    const int32_t *pbl_ptr = nullptr, *pbl_list = nullptr;
+    const int32_t *wpbl_ptr[kWaveMaps] = {}, *wpbl_list[kWaveMaps] = {};
+    const int32_t *nwbl_ptr = nullptr, *nwbl_list = nullptr;
     // loss partial slots per subgraph
-    int32_t *loss_ptr = nullptr, *loss_list = nullptr;
-    bool allocated = false;
+    const int32_t *loss_ptr = nullptr, *loss_list = nullptr;
   } full, sub;
   GraphView gv_sub;
   std::vector<uint8_t> sub_active;  // the subset `sub` was built for
-  int num_wblocks[kWaveMaps] = {};
   int num_loss_slots = 0;
   // the three width-1 passes as one launch with a workgroup per subgraph: possible when
   // two float vectors of the largest subgraph fit the LDS of a compute unit
@@ -155,7 +164,6 @@ struct gco_ctx {
   size_t small_train_lds = 0;
   int2* d_fused_cuts = nullptr;
   int32_t* d_heavy_ptr = nullptr;
-  WaveRun* d_wave_runs[kWaveMaps] = {};
   int2 *d_went = nullptr, *d_went_t = nullptr;
   float *d_wval = nullptr, *d_wval_t = nullptr;
   int32_t* d_wrowid = nullptr;
@@ -313,14 +321,17 @@ int w_elems(const gco_ctx* ctx, int l /*1..L*/) {
 
 // Workgroup -> (subgraph k, first tile s, stride S_k) tables: workgroup b walks
 // tiles s, s + S_k, s + 2 S_k, ... of subgraph k.  S_k is proportional to the
-// subgraph's share of the work (rows and CSR entries), at least
-// ceil(tiles_k / max_tiles_per_block), at most tiles_k.  With group_by_xcd, all
+// subgraph's share of the work (rows and entries), at least
+// ceil(tiles_k / max_tiles_per_block), at most tiles_k.  With grouping, all
 // workgroups of a subgraph get ids that are equal modulo 8, so that they land on
 // one XCD and share its L2 (workgroups are dealt to the 8 XCDs round-robin by id);
-// subgraphs are spread over the XCDs longest-first.  The caller asks for that when
-// the feature matrix does not fit the Infinity Cache: while it fits, grouping gains
-// nothing measurable (c4: 0.977 against 0.973 ms per epoch) and costs the balance of
-// runs in which only some subgraphs train.
+// subgraphs are spread over the XCDs longest-first.
+// kAlways: one feature matrix exceeds the 256 MB Infinity Cache.  kIfEven: fp32 rows that
+// exceed the L2s together, which without grouping each fetch all of it (700 k rows of width 16 in
+// 48 subgraphs: forward 45 -> 39 us, embedding backward 91 -> 76) -- but only if no XCD gets 5 %
+// more workgroups than the mean (150 k rows of width 64 in 24 uneven subgraphs: 78 -> 91 us).  bf16
+// rows within the Infinity Cache gain nothing measurable (c4: 0.977 against 0.973 ms per epoch).
+// Runs over some of the subgraphs only are never grouped (active != nullptr).
 // Shares of `target` units in proportion to work[k], share k within [lo[k], hi[k]].  The
 // shares add up to exactly `target` whenever the bounds allow it: a launch sized to a whole
 // number of rounds of resident workgroups must not spill a handful of workgroups into one
@@ -366,19 +377,16 @@ std::vector<int> apportion(const std::vector<double>& work, int64_t target, cons
   return share;
 }
 
-void build_block_map(int P, const std::vector<int>& part_rows, const std::vector<int32_t>& lrowptr,
-                     int tile_rows, int target_blocks, int max_tiles_per_block,
-                     std::vector<int>& blk_k, std::vector<int>& blk_s, std::vector<int>& blk_S,
-                     bool group_by_xcd, double row_cost = 2.0, const std::vector<double>* entries_of = nullptr) {
-  // entries_of: the entries a subgraph's workgroups walk, where that is not every local
-  // neighbour (the wave kernels leave the rows with very many neighbours to other workgroups)
+void build_block_map(int P, const std::vector<int>& part_rows, const std::vector<double>& entries, int tile_rows,
+                     int target_blocks, int max_tiles_per_block, std::vector<int>& blk_k, std::vector<int>& blk_s,
+                     std::vector<int>& blk_S, Grouping grouping, double row_cost = 2.0,
+                     const uint8_t* active = nullptr) {
   std::vector<int> tiles(P), Sk(P);
   std::vector<double> work(P);
   for (int k = 0; k < P; ++k) {
-    const int rows = part_rows[k + 1] - part_rows[k];
+    const int rows = active == nullptr || active[k] ? part_rows[k + 1] - part_rows[k] : 0;
     tiles[k] = (rows + tile_rows - 1) / tile_rows;
-    work[k] = row_cost * rows +
-              (entries_of ? (*entries_of)[k] : static_cast<double>(lrowptr[part_rows[k + 1]] - lrowptr[part_rows[k]]));
+    work[k] = rows == 0 ? 0.0 : row_cost * rows + entries[k];
   }
   {
     std::vector<int> lo(P), hi(P);
@@ -392,11 +400,11 @@ void build_block_map(int P, const std::vector<int>& part_rows, const std::vector
   blk_k.clear();
   blk_s.clear();
   blk_S.clear();
-  if (group_by_xcd && P >= 8) {
+  if (grouping != Grouping::kNone && active == nullptr && P >= 8) {
     std::vector<int> order(P);
     for (int k = 0; k < P; ++k) order[k] = k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return Sk[x] > Sk[y]; });
-    std::vector<std::vector<int>> per_xcd(8);   // unit = k * 2^? not needed: store (k, s) pairs flat
+    std::vector<std::vector<int>> per_xcd(8);
     std::vector<std::vector<int>> per_xcd_s(8);
     for (int k : order) {
       int best = 0;
@@ -409,17 +417,22 @@ void build_block_map(int P, const std::vector<int>& part_rows, const std::vector
     }
     size_t depth = 0;
     for (int x = 0; x < 8; ++x) depth = std::max(depth, per_xcd[x].size());
-    blk_k.assign(depth * 8, -1);
-    blk_s.assign(depth * 8, 0);
-    blk_S.assign(depth * 8, 1);
-    for (int x = 0; x < 8; ++x)
-      for (size_t q = 0; q < per_xcd[x].size(); ++q) {
-        const size_t b = q * 8 + x;
-        blk_k[b] = per_xcd[x][q];
-        blk_s[b] = per_xcd_s[x][q];
-        blk_S[b] = Sk[per_xcd[x][q]];
-      }
-  } else {
+    int64_t total = 0;
+    for (int k = 0; k < P; ++k) total += Sk[k];
+    if (grouping == Grouping::kAlways || depth * 8 * 100 <= static_cast<size_t>(total) * 105) {
+      blk_k.assign(depth * 8, -1);
+      blk_s.assign(depth * 8, 0);
+      blk_S.assign(depth * 8, 1);
+      for (int x = 0; x < 8; ++x)
+        for (size_t q = 0; q < per_xcd[x].size(); ++q) {
+          const size_t b = q * 8 + x;
+          blk_k[b] = per_xcd[x][q];
+          blk_s[b] = per_xcd_s[x][q];
+          blk_S[b] = Sk[per_xcd[x][q]];
+        }
+    }
+  }
+  if (blk_k.empty()) {
     for (int k = 0; k < P; ++k)
       for (int sidx = 0; sidx < Sk[k]; ++sidx) {
         blk_k.push_back(k);
@@ -439,55 +452,38 @@ void build_block_map(int P, const std::vector<int>& part_rows, const std::vector
 // that every run costs about the same: a tile costs its light-stream entries (one per row
 // plus the neighbours of rows that are not pre-reduced) plus row_cost per row, which
 // stands for the per-row work of the kernel's dense part and epilogue.
-void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<int32_t>& lrowptr,
-                    int tile_rows, int target_blocks, double row_cost, bool group_by_xcd, std::vector<int>& wblk_k,
-                    std::vector<WaveRun>& wave_runs) {
+void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<int>& wrow, int tile_rows,
+                    int target_blocks, double row_cost, Grouping grouping, std::vector<int>& wblk_k,
+                    std::vector<WaveRun>& wave_runs, const uint8_t* active) {
   constexpr int kWaves = kBlock / 64;
   std::vector<int> blk_s, blk_S;
   // the subgraphs' shares follow the same cost as the cuts below: the light stream's entries
   // (the neighbours of pre-reduced rows are summed elsewhere) plus row_cost per row
-  std::vector<double> light(static_cast<size_t>(P), 0.0);
-  for (int k = 0; k < P; ++k)
-    for (int r = part_rows[k]; r < part_rows[k + 1]; ++r) {
-      const int deg = lrowptr[r + 1] - lrowptr[r];
-      light[k] += 1 + (deg >= kHeavyMin ? 0 : deg);
-    }
-  build_block_map(P, part_rows, lrowptr, tile_rows * kWaves, target_blocks, 0, wblk_k, blk_s, blk_S,
-                  group_by_xcd, row_cost, &light);
+  std::vector<double> light(static_cast<size_t>(P));
+  for (int k = 0; k < P; ++k) light[k] = wrow[part_rows[k + 1]] - wrow[part_rows[k]];
+  build_block_map(P, part_rows, light, tile_rows * kWaves, target_blocks, 0, wblk_k, blk_s, blk_S, grouping, row_cost,
+                  active);
   wave_runs.assign(wblk_k.size() * kWaves, WaveRun{});
-  // light-stream offset of every row (one entry per row plus the neighbours of rows that
-  // are not pre-reduced) and global number of every subgraph's first tile
-  const int n = part_rows[P];
-  std::vector<int> wrow(static_cast<size_t>(n) + 1, 0), tbase(static_cast<size_t>(P) + 1, 0);
-  for (int r = 0; r < n; ++r) {
-    const int deg = lrowptr[r + 1] - lrowptr[r];
-    wrow[r + 1] = wrow[r] + 1 + (deg >= kHeavyMin ? 0 : deg);
-  }
-  for (int k = 0; k < P; ++k)
-    tbase[k + 1] = tbase[k] + (part_rows[k + 1] - part_rows[k] + tile_rows - 1) / tile_rows;
+  std::vector<int> tbase(static_cast<size_t>(P) + 1, 0);  // global number of every subgraph's first tile
+  for (int k = 0; k < P; ++k) tbase[k + 1] = tbase[k] + (part_rows[k + 1] - part_rows[k] + tile_rows - 1) / tile_rows;
   std::vector<std::vector<int>> cuts(P);  // cuts[k][v] = first tile of wavefront v of subgraph k
   for (size_t b = 0; b < wblk_k.size(); ++b) {
     const int k = wblk_k[b];
     if (k < 0) continue;
+    const int rbeg = part_rows[k], rend = part_rows[k + 1];
     if (cuts[k].empty()) {
-      const int rows = part_rows[k + 1] - part_rows[k];
-      const int tiles = (rows + tile_rows - 1) / tile_rows;
-      std::vector<double> pre(static_cast<size_t>(tiles) + 1, 0);  // cost before tile t
-      for (int t = 0; t < tiles; ++t) {
-        double c = row_cost * tile_rows;
-        for (int r = part_rows[k] + t * tile_rows; r < std::min(part_rows[k + 1], part_rows[k] + (t + 1) * tile_rows); ++r) {
-          const int deg = lrowptr[r + 1] - lrowptr[r];
-          c += 1 + (deg >= kHeavyMin ? 0 : deg);
-        }
-        pre[t + 1] = pre[t] + c;
-      }
+      const int tiles = tbase[k + 1] - tbase[k];
+      // cost of the tiles before tile t
+      auto before = [&](int t) {
+        return static_cast<double>(wrow[std::min(rend, rbeg + t * tile_rows)] - wrow[rbeg]) + row_cost * tile_rows * t;
+      };
       const int V = blk_S[b] * kWaves;
       cuts[k].assign(static_cast<size_t>(V) + 1, tiles);
       cuts[k][0] = 0;
       int t = 0;
       for (int v = 1; v < V; ++v) {
-        const double want = pre[tiles] * v / V;
-        while (t < tiles && pre[t] < want) ++t;
+        const double want = before(tiles) * v / V;
+        while (t < tiles && before(t) < want) ++t;
         cuts[k][v] = t;
       }
     }
@@ -496,10 +492,10 @@ void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<
       WaveRun& run = wave_runs[b * kWaves + q];
       run.tile0 = cuts[k][v];
       run.tile1 = cuts[k][v + 1];
-      run.rbeg = part_rows[k];
-      run.rend = part_rows[k + 1];
-      run.e0 = wrow[std::min(run.rend, run.rbeg + run.tile0 * tile_rows)];
-      run.e1 = wrow[std::min(run.rend, run.rbeg + run.tile1 * tile_rows)];
+      run.rbeg = rbeg;
+      run.rend = rend;
+      run.e0 = wrow[std::min(rend, rbeg + run.tile0 * tile_rows)];
+      run.e1 = wrow[std::min(rend, rbeg + run.tile1 * tile_rows)];
       run.tglob = tbase[k];
     }
   }
@@ -538,8 +534,10 @@ void bucket_blocks(const std::vector<int>& blk_k, int num_sets, std::vector<int>
     if (blk_k[b] >= 0) list[cursor[num_sets == 1 ? 0 : blk_k[b]]++] = static_cast<int>(b);
 }
 
-// Builds the subgraph-naming arrays of `m` from the host copies: units of subgraphs with
-// active[k] == 0 are marked -1 and left out of the lists (active == nullptr: all take part).
+// Builds the subgraph-naming arrays of `m`: units of subgraphs with active[k] == 0 are marked -1
+// and left out of the lists (active == nullptr: all take part), and the runs of the wave kernels
+// are cut for the active subgraphs alone, so that these get all the workgroups a launch aims
+// at (6 of 64 subgraphs, 56 k rows of width 64, bf16: forward launch 30 -> 15 us).
 int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* active) {
   const gco_ctx::HostMaps& h = ctx->hm;
   const int P = ctx->P, Pw = ctx->Pw;
@@ -550,42 +548,50 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
         if (k >= 0 && !active[k]) k = -1;
     return out;
   };
-  const bool first = !m.allocated;
-  auto put = [&](int32_t*& dst, const std::vector<int>& v, size_t capacity) -> int {
-    if (first) GALLOC(dst, std::max<size_t>(1, capacity));
-    HIPCHK(h2d(ctx, dst, v.data(), v.size()));
-    return GCO_OK;
+  // all arrays one after another in one block, each from a 16-byte boundary
+  std::vector<int32_t> block;
+  std::vector<std::pair<const int32_t**, size_t>> places;
+  auto put = [&](const int32_t** dst, const int32_t* v, size_t count) {
+    block.resize((block.size() + 3) / 4 * 4);
+    places.push_back({dst, block.size()});
+    block.insert(block.end(), v, v + count);
+    if (count == 0) block.push_back(0);
   };
-  auto put_lists = [&](int32_t*& ptr, int32_t*& list, const std::vector<int>& ks, int sets) -> int {
+  auto put_lists = [&](const int32_t** ptr, const int32_t** list, const std::vector<int>& ks, int sets) {
     std::vector<int> pv, lv;
     bucket_blocks(ks, sets, pv, lv);
-    int rc = put(ptr, pv, pv.size());
-    if (rc != GCO_OK) return rc;
-    return put(list, lv, ks.size());
+    put(ptr, pv.data(), pv.size());
+    put(list, lv.data(), lv.size());
   };
-#define PUT(expr)                 \
-  do {                            \
-    const int rc_ = (expr);       \
-    if (rc_ != GCO_OK) return rc_; \
-  } while (0)
   const std::vector<int> blk_k = filtered(h.blk_k), nblk_k = filtered(h.nblk_k);
-  PUT(put(m.blk_k, blk_k, blk_k.size()));
-  PUT(put(m.nblk_k, nblk_k, nblk_k.size()));
-  PUT(put_lists(m.pbl_ptr, m.pbl_list, blk_k, Pw));
-  PUT(put_lists(m.nwbl_ptr, m.nwbl_list, nblk_k, Pw));
+  put(&m.blk_k, blk_k.data(), blk_k.size());
+  put(&m.nblk_k, nblk_k.data(), nblk_k.size());
+  put_lists(&m.pbl_ptr, &m.pbl_list, blk_k, Pw);
+  put_lists(&m.nwbl_ptr, &m.nwbl_list, nblk_k, Pw);
   std::vector<int> narrow;
+  const bool f32 = ctx->cfg.storage == GCO_STORAGE_FP32;
   for (int v = 0; v < kWaveMaps; ++v) {
-    const std::vector<int> wk = filtered(h.wblk_k[v]);
-    PUT(put(m.wblk_k[v], wk, wk.size()));
-    PUT(put_lists(m.wpbl_ptr[v], m.wpbl_list[v], wk, Pw));
+    // one decomposition per kernel kind (different cost per row)
+    const int target = f32 ? wave_blocks_f32(ctx->cfg.dim, v)
+                           : (ctx->cfg.dim == 128 ? kWaveBlocksFor128 : kWaveBlocksFor)[v];
+    std::vector<int> wk;
+    std::vector<WaveRun> runs;
+    build_wave_map(P, h.part_rows, h.wrow, f32 && v != WM_NARROW ? kTileRowsF32 : kWaveRows, target,
+                   (f32 ? kWaveRowCostF32 : kWaveRowCost)[v], h.grouping, wk, runs, active);
+    m.num_wblocks[v] = static_cast<int>(wk.size());
+    put(&m.wblk_k[v], wk.data(), wk.size());
+    static_assert(sizeof(WaveRun) % 16 == 0 && alignof(WaveRun) == 16, "runs lie at 16-byte boundaries of the block");
+    put(reinterpret_cast<const int32_t**>(&m.wave_runs[v]), reinterpret_cast<const int32_t*>(runs.data()),
+        runs.size() * (sizeof(WaveRun) / sizeof(int32_t)));
+    put_lists(&m.wpbl_ptr[v], &m.wpbl_list[v], wk, Pw);
     if (v == WM_NARROW) narrow = wk;
   }
   const std::vector<int> chunk_part = filtered(h.chunk_part), heavy_part = filtered(h.heavy_part);
-  PUT(put(m.chunk_part, chunk_part, chunk_part.size()));
+  put(&m.chunk_part, chunk_part.data(), chunk_part.size());
   std::vector<int> heavy_rows(h.heavy_rows);
   for (size_t q = 0; q < heavy_rows.size(); ++q)
     if (heavy_part[q] < 0) heavy_rows[q] = -1;
-  PUT(put(m.heavy_rows, heavy_rows, heavy_rows.size()));
+  put(&m.heavy_rows, heavy_rows.data(), heavy_rows.size());
   // loss partial slots: one per pre-reduced row, then one per workgroup of the width-1
   // kernels; with the one-launch scalar layer, one per subgraph; with the staged form, one
   // per workgroup of those launches
@@ -596,9 +602,20 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
     for (int& k : slot_k)
       if (active != nullptr && !active[k]) k = -1;
   }
-  PUT(put_lists(m.loss_ptr, m.loss_list, slot_k, P));
-#undef PUT
-  m.allocated = true;
+  put_lists(&m.loss_ptr, &m.loss_list, slot_k, P);
+  if (block.size() > m.capacity) {
+    HIPCHK(hipStreamSynchronize(ctx->st));  // launches that read the old block
+    if (m.block != nullptr) {
+      ctx->graph_allocs.erase(std::find(ctx->graph_allocs.begin(), ctx->graph_allocs.end(), static_cast<void*>(m.block)));
+      ctx->raw_free(m.block);
+      m.block = nullptr;
+      m.capacity = 0;
+    }
+    GALLOC(m.block, block.size());
+    m.capacity = block.size();
+  }
+  for (const auto& at : places) *at.first = m.block + at.second;
+  HIPCHK(h2d(ctx, m.block, block.data(), block.size()));
   return GCO_OK;
 }
 
@@ -607,7 +624,11 @@ GraphView view_with(const gco_ctx* ctx, const gco_ctx::ActiveMaps& m) {
   GraphView g = ctx->gv;
   g.blk_k = m.blk_k;
   g.nblk_k = m.nblk_k;
-  for (int v = 0; v < kWaveMaps; ++v) g.wblk_k[v] = m.wblk_k[v];
+  for (int v = 0; v < kWaveMaps; ++v) {
+    g.wblk_k[v] = m.wblk_k[v];
+    g.wave_runs[v] = m.wave_runs[v];
+    g.num_wblocks[v] = m.num_wblocks[v];
+  }
   g.chunk_part = m.chunk_part;
   g.heavy_rows = m.heavy_rows;
   g.loss_ptr = m.loss_ptr;
@@ -922,26 +943,17 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
 
   // work decomposition
   std::vector<int> blk_k, blk_s, blk_S, nblk_k, nblk_s, nblk_S;
-  // subgraph -> XCD affinity only when one feature matrix exceeds the 256 MB Infinity Cache
-  const bool group_by_xcd =
-      static_cast<double>(n) * ctx->cfg.dim * ctx->elem_bytes() > 256.0 * 1024 * 1024;
-  build_block_map(P, part_rows, lrowptr, kTileRows, kWideBlocks, kMaxTilesPerBlock, blk_k, blk_s, blk_S,
-                  group_by_xcd);
-  // one decomposition per kernel kind (different cost per row)
-  for (int v = 0; v < kWaveMaps; ++v) {
-    std::vector<WaveRun> wave_runs;
-    const bool f32 = ctx->cfg.storage == GCO_STORAGE_FP32;
-    const int target = f32 ? wave_blocks_f32(ctx->cfg.dim, v)
-                           : (ctx->cfg.dim == 128 ? kWaveBlocksFor128 : kWaveBlocksFor)[v];
-    build_wave_map(P, part_rows, lrowptr, f32 && v != WM_NARROW ? kTileRowsF32 : kWaveRows, target,
-                   (f32 ? kWaveRowCostF32 : kWaveRowCost)[v], group_by_xcd, ctx->hm.wblk_k[v], wave_runs);
-    ctx->num_wblocks[v] = static_cast<int>(ctx->hm.wblk_k[v].size());
-    GALLOC(ctx->d_wave_runs[v], wave_runs.size());
-    HIPCHK(h2d(ctx, ctx->d_wave_runs[v], wave_runs.data(), wave_runs.size()));
-  }
+  const double matrix_bytes = static_cast<double>(n) * ctx->cfg.dim * ctx->elem_bytes();
+  const Grouping grouping = matrix_bytes > 256.0 * 1024 * 1024 ? Grouping::kAlways
+                            : ctx->cfg.storage == GCO_STORAGE_FP32 && matrix_bytes > 32.0 * 1024 * 1024
+                                ? Grouping::kIfEven
+                                : Grouping::kNone;
+  std::vector<double> entries(P);
+  for (int k = 0; k < P; ++k) entries[k] = lrowptr[part_rows[k + 1]] - lrowptr[part_rows[k]];
+  build_block_map(P, part_rows, entries, kTileRows, kWideBlocks, kMaxTilesPerBlock, blk_k, blk_s, blk_S, grouping);
   // width-1 kernels: one 256-row tile per workgroup
-  build_block_map(P, part_rows, lrowptr, kNarrowRows, std::numeric_limits<int>::max() / 2, 1, nblk_k,
-                  nblk_s, nblk_S, group_by_xcd);
+  build_block_map(P, part_rows, entries, kNarrowRows, std::numeric_limits<int>::max() / 2, 1, nblk_k, nblk_s, nblk_S,
+                  grouping);
   GALLOC(ctx->d_blk_s, blk_s.size());
   GALLOC(ctx->d_nblk_s, nblk_s.size());
   GALLOC(ctx->d_blk_S, blk_S.size());
@@ -950,29 +962,31 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   HIPCHK(h2d(ctx, ctx->d_nblk_S, nblk_S.data(), nblk_S.size()));
   HIPCHK(h2d(ctx, ctx->d_blk_s, blk_s.data(), blk_s.size()));
   HIPCHK(h2d(ctx, ctx->d_nblk_s, nblk_s.data(), nblk_s.size()));
+  ctx->hm.part_rows = part_rows;
+  ctx->hm.grouping = grouping;
   ctx->hm.blk_k = blk_k;
   ctx->hm.nblk_k = nblk_k;
   // very long rows
   std::vector<int> heavy_of_row, heavy_rows, heavy_chunk_ptr(1, 0), chunk_begin, chunk_end, chunk_part;
+  std::vector<int>& wrow = ctx->hm.wrow;  // offset of every row in the light stream
+  wrow.resize(static_cast<size_t>(n) + 1);
+  wrow[0] = 0;
   int num_heavy = 0;
-  {
-    int k = 0;
-    for (int r = 0; r < n; ++r) {
-      while (r >= part_rows[k + 1]) ++k;
+  for (int k = 0; k < P; ++k)
+    for (int r = part_rows[k]; r < part_rows[k + 1]; ++r) {
       const int deg = lrowptr[r + 1] - lrowptr[r];
-      if (deg >= kHeavyMin) {
-        if (heavy_of_row.empty()) heavy_of_row.assign(n, -1);
-        heavy_of_row[r] = num_heavy++;
-        heavy_rows.push_back(r);
-        for (int e = lrowptr[r]; e < lrowptr[r + 1]; e += kChunk) {
-          chunk_begin.push_back(e);
-          chunk_end.push_back(std::min(e + kChunk, lrowptr[r + 1]));
-          chunk_part.push_back(k);
-        }
-        heavy_chunk_ptr.push_back(static_cast<int>(chunk_begin.size()));
+      wrow[r + 1] = wrow[r] + 1 + (deg >= kHeavyMin ? 0 : deg);
+      if (deg < kHeavyMin) continue;
+      if (heavy_of_row.empty()) heavy_of_row.assign(n, -1);
+      heavy_of_row[r] = num_heavy++;
+      heavy_rows.push_back(r);
+      for (int e = lrowptr[r]; e < lrowptr[r + 1]; e += kChunk) {
+        chunk_begin.push_back(e);
+        chunk_end.push_back(std::min(e + kChunk, lrowptr[r + 1]));
+        chunk_part.push_back(k);
       }
+      heavy_chunk_ptr.push_back(static_cast<int>(chunk_begin.size()));
     }
-  }
   const int num_chunks = static_cast<int>(chunk_begin.size());
   {  // subgraph of every pre-reduced row
     ctx->hm.heavy_part.clear();
@@ -983,7 +997,6 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     }
     ctx->hm.heavy_rows = heavy_rows;
     ctx->hm.chunk_part = chunk_part;
-    ctx->num_loss_slots = static_cast<int>(heavy_rows.size() + ctx->hm.wblk_k[WM_NARROW].size());
   }
   {  // Form of the scalar layer's three passes.
      // ONE launch (a workgroup per subgraph, vectors in LDS): if two vectors of the largest
@@ -996,11 +1009,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     std::vector<int64_t> light_of(P, 0);
     for (int kk = 0; kk < P; ++kk) {
       max_rows = std::max(max_rows, part_rows[kk + 1] - part_rows[kk]);
-      int64_t light = 0;
-      for (int r = part_rows[kk]; r < part_rows[kk + 1]; ++r) {
-        const int deg = lrowptr[r + 1] - lrowptr[r];
-        light += 1 + (deg >= kHeavyMin ? 0 : deg);
-      }
+      const int64_t light = wrow[part_rows[kk + 1]] - wrow[part_rows[kk]];
       light_of[kk] = light;
       total_light += light;
       max_light = std::max(max_light, light);
@@ -1087,26 +1096,26 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
       // light stream plus one per row), one per wavefront of its workgroups; a run is handed
       // over as its range of the stream
       std::vector<int2> cuts(static_cast<size_t>(num_wgs) * NW);
-      int64_t woff = 0;  // light-stream offset of the current row
       for (int kk = 0; kk < P; ++kk) {
         const int rb = part_rows[kk], re = part_rows[kk + 1];
         const int V = (wg_ptr[kk + 1] - wg_ptr[kk]) * NW;
-        std::vector<double> pre(static_cast<size_t>(re - rb) + 1, 0.0);
-        std::vector<int> off(static_cast<size_t>(re - rb) + 1, 0);
-        for (int r = rb; r < re; ++r) {
-          const int deg = lrowptr[r + 1] - lrowptr[r];
-          const int len = 1 + (deg >= kHeavyMin ? 0 : deg);
-          off[r - rb] = static_cast<int>(woff);
-          woff += len;
-          pre[r - rb + 1] = pre[r - rb] + 1 + len;
-        }
-        off[re - rb] = static_cast<int>(woff);
+        // cost of the subgraph's rows before row r
+        auto before = [&](int r) { return static_cast<double>(wrow[r] - wrow[rb]) + (r - rb); };
         int r = rb;
         for (int v = 0; v < V; ++v) {
           const int start = r;
-          const double want = pre[re - rb] * (v + 1) / V;
-          while (r < re && (v == V - 1 || pre[r - rb + 1] <= want)) ++r;
-          cuts[static_cast<size_t>(wg_ptr[kk]) * NW + v] = make_int2(off[start - rb], off[r - rb]);
+          if (v == V - 1) {
+            r = re;
+          } else {  // rows as long as their end is within the wavefront's share of the cost
+            const double want = before(re) * (v + 1) / V;
+            int lo = r, hi = re;
+            while (lo < hi) {
+              const int mid = (lo + hi) / 2;
+              if (before(mid + 1) <= want) lo = mid + 1; else hi = mid;
+            }
+            r = lo;
+          }
+          cuts[static_cast<size_t>(wg_ptr[kk]) * NW + v] = make_int2(wrow[start], wrow[r]);
         }
       }
       std::vector<int> heavy_ptr(static_cast<size_t>(P) + 1, 0);
@@ -1126,12 +1135,15 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
       HIPCHK(h2d(ctx, ctx->d_staged_ptr, wg_ptr.data(), wg_ptr.size()));
     }
   }
-  ctx->full.allocated = false;
-  ctx->sub.allocated = false;
+  ctx->full = gco_ctx::ActiveMaps{};  // their blocks went with the graph before
+  ctx->sub = gco_ctx::ActiveMaps{};
+  ctx->sub_active.clear();
   {
     const int rc = upload_active_maps(ctx, ctx->full, nullptr);
     if (rc != GCO_OK) return rc;
   }
+  if (!ctx->fused_scalar && !ctx->staged_scalar)
+    ctx->num_loss_slots = static_cast<int>(heavy_rows.size()) + ctx->full.num_wblocks[WM_NARROW];
   {  // pre-reduced rows per wave tile
     std::vector<int> tbase(P + 1, 0);
     for (int kk = 0; kk < P; ++kk)
@@ -1191,9 +1203,9 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   g.blk_S = ctx->d_blk_S;
   g.num_blocks = static_cast<int>(blk_k.size());
   for (int v = 0; v < kWaveMaps; ++v) {
-    g.wave_runs[v] = ctx->d_wave_runs[v];
+    g.wave_runs[v] = ctx->full.wave_runs[v];
     g.wblk_k[v] = ctx->full.wblk_k[v];
-    g.num_wblocks[v] = ctx->num_wblocks[v];
+    g.num_wblocks[v] = ctx->full.num_wblocks[v];
   }
   g.wrowptr = ctx->d_wrowptr;
   g.wtile_hptr = ctx->d_wtile_hptr;
@@ -1755,7 +1767,7 @@ int gco_train_subset(gco_ctx* ctx, int32_t epochs, const int32_t* parts, int32_t
   }
   // the maps of the previous call serve again when the same subgraphs are listed (the
   // fine-tuning rounds of Alg. 1 stage 3 come back with the same set many times)
-  if (!ctx->sub.allocated || ctx->sub_active != active) {
+  if (ctx->sub.block == nullptr || ctx->sub_active != active) {
     const int rc = upload_active_maps(ctx, ctx->sub, active.data());
     if (rc != GCO_OK) return rc;
     ctx->sub_active = active;

@@ -60,3 +60,32 @@ def test_tile_and_row_length_edges(gco, D, L, norm, share):
     ctx.set_params(E, Ws)
     assert np.array_equal(first, ctx.train(3))  # one fixed order of additions
     ctx.destroy()
+
+
+@pytest.mark.parametrize("storage,D", [("fp32", 32), ("bf16", 64)])
+def test_a_listed_subset_has_runs_of_its_own(gco, storage, D):
+    """A fine-tune cuts its wavefront runs for the listed subgraphs alone.  Listing all of them
+    gives the bits of gco_train; changing lists back and forth, also to longer ones, gives the
+    bits of a context that only ever saw that list."""
+    g, part, P = ragged_subgraphs(5)
+    E, Ws = inputs.init_params(g.n, part, P, 3, D, 3)
+
+    def context():
+        ctx = gco.Context(num_layers=3, dim=D, storage=storage, norm="mean")
+        ctx.set_scalar_layer_form("streams")
+        ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+        ctx.set_params(E, Ws)
+        return ctx
+
+    a, b = context(), context()
+    assert np.array_equal(a.train(3), b.train_subset(3, np.arange(P)))
+    assert np.array_equal(a.get_params()[0], b.get_params()[0])
+    for listed in ([11], [0, 4, 9, 10], [3], list(range(P)), [2, 11]):
+        c = context()
+        b.set_params(E, Ws)
+        assert np.array_equal(b.train_subset(4, listed), c.train_subset(4, listed))
+        (e1, w1), (e2, w2) = b.get_params(), c.get_params()
+        assert np.array_equal(e1, e2) and all(np.array_equal(x, y) for x, y in zip(w1, w2))
+        c.destroy()
+    a.destroy()
+    b.destroy()
