@@ -1923,13 +1923,30 @@ int gco_get_hidden(gco_ctx* ctx, int32_t layer, float* H) {
 // ---- read-out -------------------------------------------------------------------
 
 // Device buffers of one gco_round_repair call (n floats, three byte arrays of n rounded up
-// to a multiple of 4, 8 counters, 4 ints).
+// to a multiple of 4, 8 counters, 1 int).
 struct RepairBuffers {
   float* p_orig;
   uint8_t *state, *x_orig, *x_new;
   unsigned long long* counts;
   int* undecided;
 };
+
+// They lie in one block, every piece on a 256-byte boundary.
+static size_t repair_piece(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+static size_t repair_bytes(size_t n) { return 512 + repair_piece(n * sizeof(float)) + 3 * repair_piece((n + 3) / 4 * 4); }
+
+static RepairBuffers repair_buffers(unsigned char* q, size_t n) {
+  const size_t flags = repair_piece((n + 3) / 4 * 4);
+  RepairBuffers b{};
+  b.counts = reinterpret_cast<unsigned long long*>(q);
+  b.undecided = reinterpret_cast<int*>(q + 256);
+  b.p_orig = reinterpret_cast<float*>(q + 512);
+  b.state = q + 512 + repair_piece(n * sizeof(float));
+  b.x_orig = b.state + flags;
+  b.x_new = b.x_orig + flags;
+  return b;
+}
 
 static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, const RepairBuffers& b, uint8_t* x,
                              int64_t* objective, int64_t* conflicts_before, int64_t* conflicts_after) {
@@ -1942,23 +1959,22 @@ static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, cons
   launch_gather_rows(st, n, 1, ctx->p, ctx->d_inv, p_orig);
   launch_round(st, n, p_orig, thr, x_orig);  // 0/1 in original order
   launch_fill_u32(st, counts, 16, 0u);
-  launch_edge_counts(st, n, ctx->d_rowptr, ctx->d_col, x_orig, counts);
+  launch_edge_counts(st, n, ctx->nnz_full, ctx->d_rowptr, ctx->d_col, x_orig, counts);
   const bool repair = ctx->cfg.problem == GCO_PROBLEM_MIS && repair_scope != GCO_REPAIR_NONE;
   if (repair) {
     const bool local = repair_scope == GCO_REPAIR_LOCAL;
     if (local) launch_round(st, n, ctx->p, thr, state);
     else launch_round(st, n, p_orig, thr, state);
-    // each batch of four rounds ends with a count of the nodes still undecided
+    // each batch of four rounds ends with a word that says whether a node is still undecided
     for (int64_t guard = 0; guard <= static_cast<int64_t>(n) + 4; guard += 4) {
-      launch_fill_u32(st, undecided, 4, 0u);
+      launch_fill_u32(st, undecided, 1, 0u);
       for (int q = 0; q < 4; ++q) {
-        if (local)
-          launch_repair_round_local(st, n, ctx->d_lrowptr, ctx->d_lcol, ctx->p, state, undecided + q);
-        else
-          launch_repair_round_all(st, n, ctx->d_rowptr, ctx->d_col, p_orig, state, undecided + q);
+        int* last = q == 3 ? undecided : nullptr;
+        if (local) launch_repair_round_local(st, n, ctx->d_lrowptr, ctx->d_lcol, ctx->p, state, last);
+        else launch_repair_round_all(st, n, ctx->d_rowptr, ctx->d_col, p_orig, state, last);
       }
       int left = 0;
-      HIPCHK(d2h(ctx, &left, undecided + 3, 1));
+      HIPCHK(d2h(ctx, &left, undecided, 1));
       if (left == 0) break;
     }
     if (local) {
@@ -1968,7 +1984,7 @@ static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, cons
       launch_state_to_x(st, n, state, x_orig);
     }
   }
-  launch_edge_counts(st, n, ctx->d_rowptr, ctx->d_col, x_orig, counts + 4);
+  launch_edge_counts(st, n, ctx->nnz_full, ctx->d_rowptr, ctx->d_col, x_orig, counts + 4);
   unsigned long long h[8];
   HIPCHK(d2h(ctx, h, counts, 8));
   HIPCHK(d2h(ctx, x, x_orig, static_cast<size_t>(n)));
@@ -1986,19 +2002,11 @@ int gco_round_repair(gco_ctx* ctx, float thr, int32_t repair_scope, uint8_t* x, 
   NEED(x, GCO_EINVAL, "x is NULL");
   NEED(repair_scope >= GCO_REPAIR_NONE && repair_scope <= GCO_REPAIR_ALL, GCO_EINVAL,
        "bad repair_scope %d", repair_scope);
-  const int n = ctx->n;
   Scratch tmp(ctx);
-  const size_t npad = (static_cast<size_t>(n) + 3) / 4 * 4;
-  RepairBuffers b{};
-  b.p_orig = tmp.get<float>(static_cast<size_t>(n));
-  b.state = tmp.get<uint8_t>(npad);
-  b.x_orig = tmp.get<uint8_t>(npad);
-  b.x_new = tmp.get<uint8_t>(npad);
-  b.counts = tmp.get<unsigned long long>(8);
-  b.undecided = tmp.get<int>(4);
-  NEED(b.p_orig && b.state && b.x_orig && b.x_new && b.counts && b.undecided, GCO_ENOMEM,
-       "device scratch allocation failed");
-  return round_repair_impl(ctx, thr, repair_scope, b, x, objective, conflicts_before, conflicts_after);
+  unsigned char* base = tmp.get<unsigned char>(repair_bytes(static_cast<size_t>(ctx->n)));
+  NEED(base, GCO_ENOMEM, "device scratch allocation failed");
+  return round_repair_impl(ctx, thr, repair_scope, repair_buffers(base, static_cast<size_t>(ctx->n)), x, objective,
+                           conflicts_before, conflicts_after);
 }
 
 int gco_round_repair_static(gco_ctx* ctx, float thr, int32_t repair_scope, uint8_t* x, int64_t* objective,
@@ -2013,52 +2021,38 @@ int gco_round_repair_static(gco_ctx* ctx, float thr, int32_t repair_scope, uint8
        kStaticMaxNodes);
   void* base = nullptr;
   HIPCHK(static_scratch_for_current_device(&base));
-  // carve the block: every piece starts on a 256-byte boundary
-  const size_t n = static_cast<size_t>(ctx->n);
-  const size_t npad = (n + 3) / 4 * 4;
-  auto up = [](size_t v) { return (v + 255) / 256 * 256; };
-  unsigned char* q = static_cast<unsigned char*>(base);
-  RepairBuffers b{};
-  b.counts = reinterpret_cast<unsigned long long*>(q);
-  q += 256;
-  b.undecided = reinterpret_cast<int*>(q);
-  q += 256;
-  b.p_orig = reinterpret_cast<float*>(q);
-  q += up(n * sizeof(float));
-  b.state = q;
-  q += up(npad);
-  b.x_orig = q;
-  q += up(npad);
-  b.x_new = q;
-  q += up(npad);
-  NEED(static_cast<size_t>(q - static_cast<unsigned char*>(base)) <= kStaticScratchBytes, GCO_ERANGE,
+  NEED(repair_bytes(static_cast<size_t>(ctx->n)) <= kStaticScratchBytes, GCO_ERANGE,
        "static work area too small for n = %d", ctx->n);
-  return round_repair_impl(ctx, thr, repair_scope, b, x, objective, conflicts_before, conflicts_after);
+  return round_repair_impl(ctx, thr, repair_scope,
+                           repair_buffers(static_cast<unsigned char*>(base), static_cast<size_t>(ctx->n)), x,
+                           objective, conflicts_before, conflicts_after);
 }
 
 static int cross_edges_impl(gco_ctx* ctx, const uint8_t* d_x, int64_t* count, int32_t* u, int32_t* v,
                             uint8_t* cross_host) {
   const int n = ctx->n;
+  const int64_t nnz = ctx->nnz_full;
   hipStream_t st = ctx->st;
   Scratch tmp(ctx);
-  int64_t* cnt = tmp.get<int64_t>(static_cast<size_t>(n) + 1);
-  int64_t* offs = tmp.get<int64_t>(static_cast<size_t>(n) + 1);
-  int64_t* scan = tmp.get<int64_t>(scan_temp_elems(static_cast<int64_t>(n) + 1));
-  NEED(cnt && offs && scan, GCO_ENOMEM, "device scratch allocation failed");
-  launch_fill_u32(st, cnt + n, 2, 0u);
-  launch_cut_count(st, n, ctx->d_rowptr, ctx->d_col, ctx->d_part, d_x, cnt);
-  exclusive_scan_i64(st, cnt, offs, static_cast<int64_t>(n) + 1, scan);
-  int64_t total = 0;
-  HIPCHK(d2h(ctx, &total, offs + n, 1));
   if (cross_host) {
     const size_t npad = (static_cast<size_t>(n) + 3) / 4 * 4;
     uint8_t* cross = tmp.get<uint8_t>(npad);
     NEED(cross, GCO_ENOMEM, "device scratch allocation failed");
     launch_fill_u32(st, cross, static_cast<int64_t>(npad / 4), 0u);
-    launch_cut_fill(st, n, ctx->d_rowptr, ctx->d_col, ctx->d_part, d_x, offs, nullptr, nullptr, cross);
+    launch_cross_mark(st, n, nnz, ctx->d_rowptr, ctx->d_col, ctx->d_part, cross);
     HIPCHK(d2h(ctx, cross_host, cross, static_cast<size_t>(n)));
     return GCO_OK;
   }
+  const int64_t chunks = entry_chunks(nnz);
+  const size_t slots = static_cast<size_t>(chunks) + 1;
+  int64_t* cnt = tmp.get<int64_t>(2 * slots + scan_temp_elems(chunks + 1));
+  NEED(cnt, GCO_ENOMEM, "device scratch allocation failed");
+  int64_t *offs = cnt + slots, *scan = offs + slots;
+  launch_fill_u32(st, cnt + chunks, 2, 0u);
+  launch_cut_count(st, n, nnz, ctx->d_rowptr, ctx->d_col, ctx->d_part, d_x, cnt);
+  exclusive_scan_i64(st, cnt, offs, chunks + 1, scan);
+  int64_t total = 0;
+  HIPCHK(d2h(ctx, &total, offs + chunks, 1));
   if (!u && !v) {
     *count = total;
     return GCO_OK;
@@ -2069,7 +2063,7 @@ static int cross_edges_impl(gco_ctx* ctx, const uint8_t* d_x, int64_t* count, in
   int32_t* du = tmp.get<int32_t>(static_cast<size_t>(total));
   int32_t* dv = tmp.get<int32_t>(static_cast<size_t>(total));
   NEED(du && dv, GCO_ENOMEM, "device scratch allocation failed");
-  launch_cut_fill(st, n, ctx->d_rowptr, ctx->d_col, ctx->d_part, d_x, offs, du, dv, nullptr);
+  launch_cut_fill(st, n, nnz, ctx->d_rowptr, ctx->d_col, ctx->d_part, d_x, offs, du, dv);
   HIPCHK(d2h(ctx, u, du, static_cast<size_t>(total)));
   HIPCHK(d2h(ctx, v, dv, static_cast<size_t>(total)));
   *count = total;

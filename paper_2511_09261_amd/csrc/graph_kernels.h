@@ -44,13 +44,16 @@ void launch_gather_rows(hipStream_t st, int64_t rows, int width, const void* src
                         void* dst);
 void launch_gather_bytes(hipStream_t st, int n, const uint8_t* src, const int32_t* map, uint8_t* dst);
 
-// Cross edges: per-row counts, then the fill at scanned offsets.  x (optional)
-// restricts to edges with both ends selected.  u, v, cross may each be nullptr.
-void launch_cut_count(hipStream_t st, int n, const int64_t* rowptr, const int32_t* col,
+// Cross edges: counts per chunk of entries (entry_chunks(nnz) of them), then the fill at scanned
+// offsets.  x (optional) restricts to edges with both ends selected.  launch_cross_mark sets
+// cross[i] = 1 for every end of a cross edge.
+int64_t entry_chunks(int64_t nnz);
+void launch_cut_count(hipStream_t st, int n, int64_t nnz, const int64_t* rowptr, const int32_t* col,
                       const int32_t* part, const uint8_t* x, int64_t* count);
-void launch_cut_fill(hipStream_t st, int n, const int64_t* rowptr, const int32_t* col,
-                     const int32_t* part, const uint8_t* x, const int64_t* offs, int32_t* u,
-                     int32_t* v, uint8_t* cross);
+void launch_cut_fill(hipStream_t st, int n, int64_t nnz, const int64_t* rowptr, const int32_t* col,
+                     const int32_t* part, const uint8_t* x, const int64_t* offs, int32_t* u, int32_t* v);
+void launch_cross_mark(hipStream_t st, int n, int64_t nnz, const int64_t* rowptr, const int32_t* col,
+                       const int32_t* part, uint8_t* cross);
 
 // Binarisation and one round of the parallel greedy repair (see the kernel).
 void launch_round(hipStream_t st, int n, const float* p, float thr, uint8_t* state);
@@ -61,7 +64,7 @@ void launch_repair_round_all(hipStream_t st, int n, const int64_t* rowptr, const
 void launch_state_to_x(hipStream_t st, int n, const uint8_t* state, uint8_t* x);
 // counts[0] += selected nodes, counts[1] += edges with both ends selected,
 // counts[2] += edges whose ends differ.
-void launch_edge_counts(hipStream_t st, int n, const int64_t* rowptr, const int32_t* col,
+void launch_edge_counts(hipStream_t st, int n, int64_t nnz, const int64_t* rowptr, const int32_t* col,
                         const uint8_t* x, unsigned long long* counts);
 void launch_fill_u32(hipStream_t st, void* dst, int64_t count, uint32_t value);
 
