@@ -1,5 +1,5 @@
-// Device code shared by the wide (feature-matrix) kernels: the sources of
-// gathered rows and the fixed-order row gather.
+// Pre-reduction of the rows with very many neighbours (fp32 storage): the sources of
+// gathered rows, the fixed-order row gather and the kernel over the chunks.
 #pragma once
 
 #include "device_utils.h"

@@ -1,18 +1,13 @@
-// Training-step kernels for gfx950: fused aggregate+transform layers (Eq. 3),
-// read-out (Eq. 4), loss and its gradient (Eq. 5), backward passes and Adam.
+// Training-step kernels for gfx950 outside the hidden layers and the scalar layer's stream passes:
+// the scalar layer of a one-layer model (fwd_gemv, bwd_single), loss reduction, Adam on the
+// weights, best snapshots, conversions, and the launchers that choose between the fp32 and the
+// bf16 layer kernels.
 //
-// Work decomposition.  Nodes are stored subgraph by subgraph.  A workgroup is
-// bound to one subgraph k (so its weight matrix W^k sits in LDS once) and walks
-// that subgraph's row tiles s, s+S, s+2S, ...  Within a tile:
-//   phase 1  gather: A_hat rows times the feature matrix, fp32 accumulation,
-//            result left in an LDS tile.  Short rows are taken by small lane
-//            groups (one 16-byte slice of the feature row per lane), long rows by
-//            the whole workgroup, very long rows come pre-reduced in chunks;
-//   phase 2  dense transform of the LDS tile with W^k and the fused epilogue.
+// Nodes are stored subgraph by subgraph and a workgroup is bound to one subgraph k, whose tiles
+// s, s+S, s+2S, ... it walks.
 // Every sum is taken in an order fixed by the launch shape, so results are
 // bit-identical from run to run.
 #include "device_utils.h"
-#include "gather.h"
 #include "gco_internal.h"
 #include "heavy_chunk.h"
 

@@ -201,7 +201,8 @@ __device__ __forceinline__ auto& select_array(A& a, B& b) {
 // that step's rows are parked in LDS (their registers are free again), together with the
 // entries of the step after; the products and tile epilogues of a step then run beside the
 // next step's round trip.  The rows in flight occupy 32 registers through the epilogue and
-// the entries another 16: for the kernel that has them to spare (forward, width 128).
+// the entries another 16: for the kernel that has them to spare (forward, width 128, and width 64
+// where few workgroups run).
 // LDS_ENTRIES (not with EARLY_ROWS): the entries of the next step are copied straight into
 // ent_lds (8 * SE bytes of this wavefront's LDS) instead of into 16 registers that stay live
 // through the whole step, and are read from there when the step ends.  The copy is issued
@@ -478,8 +479,8 @@ constexpr size_t fwd_wave_lds() {
 // ---------------------------------------------------------------------------
 // Forward: Y = relu((A_hat X) W^k)  [+ t = Y w_out^k]
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(kBlock, D == 64 ? 3 : 2) void fwd_wave_kernel(
+template <int D, bool EARLY>
+__global__ __launch_bounds__(kBlock, D == 64 && !EARLY ? 3 : 2) void fwd_wave_kernel(
     GraphView g, const bf16_t* __restrict__ X, const float* __restrict__ W, int w_stride,
     bf16_t* __restrict__ Y, const float* __restrict__ w_out, int wout_stride, float* __restrict__ t,
     const float* __restrict__ heavy_partial) {
@@ -505,7 +506,7 @@ __global__ __launch_bounds__(kBlock, D == 64 ? 3 : 2) void fwd_wave_kernel(
   if (run.tile0 >= run.tile1) return;
   unsigned char* my_lds = wave_mem + wave * G_::wave_bytes;
   bf16_t* ot = reinterpret_cast<bf16_t*>(my_lds);  // overlays the row buffer
-  stream_tiles<D, D == 128, false>(g, g.went, X, run, my_lds,
+  stream_tiles<D, EARLY, false>(g, g.went, X, run, my_lds,
                   reinterpret_cast<uint32_t*>(my_lds + G_::xf_bytes), pair_mask, heavy_partial, nullptr,
                   [&](int row0, int nrows, const floatx16 (&agg)[G_::NT]) {
     // Z^T = W^T AGG^T: the rounded aggregate is the B operand as it stands
@@ -1167,18 +1168,19 @@ void launch_bwd_hidden_wave(const Launch& ln, int D, bool to_embed, const GraphV
 void launch_fwd_hidden_wave(const Launch& ln, int D, const GraphView& g, const void* X, const float* W,
                             int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
                             float* heavy_partial) {
+  auto run = [&](auto kernel, size_t lds) {
+    allow_lds(kernel, lds);
+    kernel<<<g.num_wblocks[WM_FWD], kBlock, lds, ln.st>>>(g, static_cast<const bf16_t*>(X), W, w_stride,
+                                                          static_cast<bf16_t*>(Y), w_out, wout_stride, t, heavy_partial);
+  };
+  // Width 64: up to two workgroups per CU the registers of EARLY_ROWS are there for nothing else
+  // and a step's round trip counts (4 k nodes 19.1 -> 17.1 us, 6 listed subgraphs of 9 k nodes
+  // 14.7 -> 12.6); above, a third workgroup per CU hides more (1.1 M nodes 84 against 102 us,
+  // 300 k nodes 42 against 48).
   ln.begin(KK_FWD_HIDDEN);
-  if (D == 64) {
-    allow_lds(fwd_wave_kernel<64>, fwd_wave_lds<64>());
-    fwd_wave_kernel<64><<<g.num_wblocks[WM_FWD], kBlock, fwd_wave_lds<64>(), ln.st>>>(
-        g, static_cast<const bf16_t*>(X), W, w_stride, static_cast<bf16_t*>(Y), w_out, wout_stride, t,
-        heavy_partial);
-  } else if (D == 128) {
-    allow_lds(fwd_wave_kernel<128>, fwd_wave_lds<128>());
-    fwd_wave_kernel<128><<<g.num_wblocks[WM_FWD], kBlock, fwd_wave_lds<128>(), ln.st>>>(
-        g, static_cast<const bf16_t*>(X), W, w_stride, static_cast<bf16_t*>(Y), w_out, wout_stride, t,
-        heavy_partial);
-  }
+  if (D == 64 && g.num_wblocks[WM_FWD] <= 512) run(fwd_wave_kernel<64, true>, fwd_wave_lds<64>());
+  else if (D == 64) run(fwd_wave_kernel<64, false>, fwd_wave_lds<64>());
+  else if (D == 128) run(fwd_wave_kernel<128, true>, fwd_wave_lds<128>());
   ln.end(KK_FWD_HIDDEN);
 }
 
