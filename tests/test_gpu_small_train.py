@@ -1,5 +1,5 @@
 """GPU parity of the kernel that trains small subgraphs for whole epochs in one launch: loss
-trajectories and parameters against the fp64 checker where its tiles, wavefront rounds and
+trajectories and parameters against the fp64 oracle where its tiles, wavefront rounds and
 launches begin and end; forward, loss and training agree bit for bit.
 
 Tolerances: fp32 1e-4 over ten epochs and bf16 2e-2, as in test_gpu_parity."""
