@@ -94,16 +94,21 @@ __device__ __forceinline__ void wave_lds_handoff() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One Adam step on one value (constants of AdamStep).  v_sqrt_f32 and v_rcp_f32 are within 1 ulp
-// each: two units in the last place of the update, which is far below those of the value it is
-// taken from; the IEEE sequences cost 25 more instructions.  The denominator is kept out of the
-// subnormal range, whose reciprocal would overflow.
+// One Adam step on one embedding value or one weight (constants of AdamStep), with the correctly
+// rounded square root and division: every launch that may update a parameter in fp32 takes the
+// same step, and a subgraph does not train differently because other kernels were chosen for it.
 template <class Step>
 __device__ __forceinline__ void adam_value(const Step& ad, float g, float& e, float& m, float& v) {
   m = ad.b1 * m + (1.f - ad.b1) * g;
   v = ad.b2 * v + (1.f - ad.b2) * g * g;
-  const float d = fmaxf(__builtin_amdgcn_sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps, 1.17549435e-38f);
-  e -= ad.lr * ((m * ad.inv_bc1) * __builtin_amdgcn_rcpf(d));
+  const float upd = (m * ad.inv_bc1) / (sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps);
+  e -= ad.lr * upd;
+}
+template <class Step>
+__device__ __forceinline__ void adam_weight(const Step& ad, float g, float& w, float& m, float& v) {
+  m = ad.b1 * m + (1.f - ad.b1) * g;
+  v = ad.b2 * v + (1.f - ad.b2) * g * g;
+  w -= ad.lr * (m * ad.inv_bc1) / (sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps);
 }
 
 // Sum over the 64 lanes of a wavefront in a fixed butterfly order; every lane

@@ -263,7 +263,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     float w = W[idx], m = mW[idx], v = vW[idx], s = 0.f;
 #pragma unroll
     for (int q = 0; q < kSlots; ++q) s += slots[q * DP * DP + r * DP + c];
-    adam_value(adW, s, w, m, v);
+    adam_weight(adW, s, w, m, v);
     W[idx] = w;
     mW[idx] = m;
     vW[idx] = v;
@@ -274,7 +274,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     float w = a.W[L - 1][idx], m = a.mW[L - 1][idx], v = a.vW[L - 1][idx], s = 0.f;
 #pragma unroll
     for (int q = 0; q < NW; ++q) s += smem[cv.gwo + q * DP + tid];
-    adam_value(adW, s, w, m, v);
+    adam_weight(adW, s, w, m, v);
     a.W[L - 1][idx] = w;
     a.mW[L - 1][idx] = m;
     a.vW[L - 1][idx] = v;

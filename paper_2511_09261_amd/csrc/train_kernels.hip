@@ -62,10 +62,8 @@ __global__ __launch_bounds__(kBlock) void bwd_single_kernel(GraphView g, BwdArgs
       if (a.mode == EMBED_WRITE_GRAD) {
         a.gE[idx] = gq;
       } else if (a.mode == EMBED_ADAM) {
-        const float m = ad.b1 * a.mE[idx] + (1.f - ad.b1) * gq;
-        const float v = ad.b2 * a.vE[idx] + (1.f - ad.b2) * gq * gq;
-        const float upd = (m * ad.inv_bc1) / (sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps);
-        const float e = a.E[idx] - ad.lr * upd;
+        float e = a.E[idx], m = a.mE[idx], v = a.vE[idx];
+        adam_value(ad, gq, e, m, v);
         a.mE[idx] = m;
         a.vE[idx] = v;
         a.E[idx] = e;
@@ -261,11 +259,11 @@ __device__ inline void adam_on_weight(const WeightTensor& wt, int64_t gid, float
                                       int update) {
   if (wt.grad_out != nullptr) wt.grad_out[gid] = gsum;
   if (update) {
-    const float m = adk.b1 * wt.m[gid] + (1.f - adk.b1) * gsum;
-    const float v = adk.b2 * wt.v[gid] + (1.f - adk.b2) * gsum * gsum;
+    float w = wt.W[gid], m = wt.m[gid], v = wt.v[gid];
+    adam_weight(adk, gsum, w, m, v);
     wt.m[gid] = m;
     wt.v[gid] = v;
-    wt.W[gid] -= adk.lr * (m * adk.inv_bc1) / (sqrtf(v) * adk.inv_sqrt_bc2 + adk.eps);
+    wt.W[gid] = w;
   }
 }
 
