@@ -1035,8 +1035,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     // 64 subgraphs of 24 k entries 58 / 36, 16 subgraphs of 2 k entries 9 / 25, 256 of 25 k 71 / 110.
     const double steps = static_cast<double>((max_light + 1023) / 1024);
     const bool fused_pays = 6.0 + 2.3 * steps * ((P + 255) / 256) <= 27.0 + 13e-6 * static_cast<double>(total_light);
-    ctx->fused_scalar = form == GCO_SCALAR_ONE_LAUNCH ||
-                        (form == GCO_SCALAR_AUTO && fused_fits && (fused_pays || !staged_fits));
+    ctx->fused_scalar = form == GCO_SCALAR_ONE_LAUNCH || (form == GCO_SCALAR_AUTO && fused_fits && fused_pays);
     ctx->staged_scalar = form == GCO_SCALAR_STAGED || (form == GCO_SCALAR_AUTO && !ctx->fused_scalar && staged_fits);
     // Whole epochs in one launch: where the scalar layer is one launch anyway, every subgraph has
     // weights of its own and fits the LDS with its stream, and that is the faster way
