@@ -1030,11 +1030,14 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
          "the staged scalar layer needs the largest subgraph's vector (%d rows) twice in %zu bytes of LDS and at "
          "most %d rows", max_rows, kLdsPerComputeUnit, scalar_staged_max_cap() - 3);
     // ONE launch takes 6 us and 2.3 per 1024 entries of the largest subgraph (a step of its
-    // wavefronts) for every 256 subgraphs, three staged ones 27 and 13 per million entries of all;
+    // wavefronts) for every 256 subgraphs, three staged ones 27 and 13 per million entries of all,
+    // and 14 for every thousand workgroups beyond 512 (each subgraph has one);
     // measured, one / staged: 64 subgraphs of 41 k entries 121 / 57, of 31 k entries 64 / 45, 6 of
-    // 64 subgraphs of 24 k entries 58 / 36, 16 subgraphs of 2 k entries 9 / 25, 256 of 25 k 71 / 110.
+    // 64 subgraphs of 24 k entries 58 / 36, 16 subgraphs of 2 k entries 9 / 25, 256 of 25 k 71 / 110;
+    // tiny subgraphs: 1000 of them 13 / 31, 4000 33 / 74, 16000 113 / 253.
     const double steps = static_cast<double>((max_light + 1023) / 1024);
-    const bool fused_pays = 6.0 + 2.3 * steps * ((P + 255) / 256) <= 27.0 + 13e-6 * static_cast<double>(total_light);
+    const bool fused_pays = 6.0 + 2.3 * steps * ((P + 255) / 256) <=
+                            27.0 + 13e-6 * static_cast<double>(total_light) + 0.014 * std::max(0, P - 512);
     ctx->fused_scalar = form == GCO_SCALAR_ONE_LAUNCH || (form == GCO_SCALAR_AUTO && fused_fits && fused_pays);
     ctx->staged_scalar = form == GCO_SCALAR_STAGED || (form == GCO_SCALAR_AUTO && !ctx->fused_scalar && staged_fits);
     // Whole epochs in one launch: where the scalar layer is one launch anyway, every subgraph has

@@ -9,6 +9,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("P,rows,edges_per_row,form", [
     (16, 125, 2, "one_launch"),
+    (4000, 3, 1, "one_launch"),   # staged: three launches of a workgroup per subgraph, 74 us against 33
+    (12000, 3, 1, "one_launch"),
     (1, 5000, 3, "staged"),       # one workgroup: 66 us against 26
     (16, 5000, 5, "staged"),      # 96 us against 29
     (1, 20455, 15, "streams"),    # three rows too long for the staged form: 51 us, one workgroup 956
