@@ -223,6 +223,14 @@ int gco_loss(gco_ctx* ctx, double* total, double* per_part);
  * target < 0 or lo[k] > hi[k]. */
 int gco_apportion(const double* work, int32_t n, int64_t target, const int32_t* lo, const int32_t* hi,
                   int32_t* share);
+/* Test hook for the host side of the work decomposition (no device call): the subgraph that
+ * each workgroup of a hidden layer's launch serves (-1: none), for storage and dim as in
+ * gco_config and subgraphs of rows[k] nodes with entries[k] local CSR entries spread evenly
+ * over them.  kind 0: forward, 1: backward of a layer that is not the first, 2: backward of the first.
+ * Two-call pattern: with part = NULL only *count is written; otherwise *count is the
+ * capacity of part on entry.  Host memory. */
+int gco_workgroup_parts(int32_t storage, int32_t dim, int32_t kind, const int32_t* rows, const int32_t* entries,
+                        int32_t num_parts, int64_t* count, int32_t* part);
 
 /* Forward + backward at the current parameters without an update (test hook):
  * gradients shaped like the parameters. */

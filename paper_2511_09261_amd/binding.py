@@ -59,6 +59,8 @@ _PROTOTYPES = {
     "gco_get_config": (C.c_int, [C.c_void_p, C.POINTER(Config)]),
     "gco_apportion": (C.c_int, [C.POINTER(C.c_double), C.c_int32, C.c_int64, C.POINTER(C.c_int32),
                                 C.POINTER(C.c_int32), C.POINTER(C.c_int32)]),
+    "gco_workgroup_parts": (C.c_int, [C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_int32,
+                                      C.POINTER(C.c_int64), C.c_void_p]),
     "gco_set_scalar_layer_form": (C.c_int, [C.c_void_p, C.c_int]),
     "gco_get_scalar_layer_form": (C.c_int, [C.c_void_p, C.POINTER(C.c_int)]),
     "gco_last_error": (C.c_char_p, [C.c_void_p]),
@@ -152,6 +154,23 @@ def apportion(work, target, lo, hi):
     if rc != 0:
         raise GcoError(rc, "gco_apportion failed (bad bounds or sizes)")
     return share
+
+
+def workgroup_parts(storage, dim, kind, rows, entries):
+    """gco_workgroup_parts: the subgraph that each workgroup of a hidden layer's launch serves (-1: none).
+    kind: "forward", "hidden" or "embed".  Host only."""
+    lib = load()
+    rows = np.ascontiguousarray(rows, dtype=np.int32)
+    entries = np.ascontiguousarray(entries, dtype=np.int32)
+    args = (STORAGE[storage], dim, {"forward": 0, "hidden": 1, "embed": 2}[kind], _ptr(rows), _ptr(entries), rows.shape[0])
+    count = C.c_int64()
+    rc = lib.gco_workgroup_parts(*args, C.byref(count), None)
+    part = np.empty(count.value, dtype=np.int32)
+    if rc == 0:
+        rc = lib.gco_workgroup_parts(*args, C.byref(count), _ptr(part))
+    if rc != 0:
+        raise GcoError(rc, "gco_workgroup_parts failed (bad sizes)")
+    return part
 
 
 def louvain(n, rowptr, col, max_levels=32):

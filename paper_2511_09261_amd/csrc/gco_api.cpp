@@ -132,7 +132,6 @@ struct gco_ctx {
     // what the runs of the wave kernels are cut from: first row of every subgraph, offset of
     // every row in the light stream
     std::vector<int> part_rows, wrow;
-    Grouping grouping = Grouping::kNone;
   } hm;
   struct ActiveMaps {
     int32_t* block = nullptr;  // one allocation and one copy hold all of the following
@@ -319,19 +318,6 @@ int w_elems(const gco_ctx* ctx, int l /*1..L*/) {
   return l < ctx->cfg.num_layers ? D * D : D;
 }
 
-// Workgroup -> (subgraph k, first tile s, stride S_k) tables: workgroup b walks
-// tiles s, s + S_k, s + 2 S_k, ... of subgraph k.  S_k is proportional to the
-// subgraph's share of the work (rows and entries), at least
-// ceil(tiles_k / max_tiles_per_block), at most tiles_k.  With grouping, all
-// workgroups of a subgraph get ids that are equal modulo 8, so that they land on
-// one XCD and share its L2 (workgroups are dealt to the 8 XCDs round-robin by id);
-// subgraphs are spread over the XCDs longest-first.
-// kAlways: one feature matrix exceeds the 256 MB Infinity Cache.  kIfEven: fp32 rows that
-// exceed the L2s together, which without grouping each fetch all of it (700 k rows of width 16 in
-// 48 subgraphs: forward 45 -> 39 us, embedding backward 91 -> 76) -- but only if no XCD gets 5 %
-// more workgroups than the mean (150 k rows of width 64 in 24 uneven subgraphs: 78 -> 91 us).  bf16
-// rows within the Infinity Cache gain nothing measurable (c4: 0.977 against 0.973 ms per epoch).
-// Runs over some of the subgraphs only are never grouped (active != nullptr).
 // Shares of `target` units in proportion to work[k], share k within [lo[k], hi[k]].  The
 // shares add up to exactly `target` whenever the bounds allow it: a launch sized to a whole
 // number of rounds of resident workgroups must not spill a handful of workgroups into one
@@ -377,6 +363,15 @@ std::vector<int> apportion(const std::vector<double>& work, int64_t target, cons
   return share;
 }
 
+// Workgroup -> (subgraph k, first tile s, stride S_k) tables: workgroup b walks
+// tiles s, s + S_k, s + 2 S_k, ... of subgraph k.  S_k is proportional to the
+// subgraph's share of the work (rows and entries), at least
+// ceil(tiles_k / max_tiles_per_block), at most tiles_k.  With grouping, all
+// workgroups of a subgraph get ids that are equal modulo 8, so that they land on
+// one XCD and share its L2 (workgroups are dealt to the 8 XCDs round-robin by id);
+// subgraphs are spread over the XCDs longest-first.  kIfEven: only if no XCD gets 5 % more
+// workgroups than the mean.
+// Runs over some of the subgraphs only are never grouped (active != nullptr).
 void build_block_map(int P, const std::vector<int>& part_rows, const std::vector<double>& entries, int tile_rows,
                      int target_blocks, int max_tiles_per_block, std::vector<int>& blk_k, std::vector<int>& blk_s,
                      std::vector<int>& blk_S, Grouping grouping, double row_cost = 2.0,
@@ -501,6 +496,32 @@ void build_wave_map(int P, const std::vector<int>& part_rows, const std::vector<
   }
 }
 
+// The wavefront runs of kernel kind v (one decomposition per kind: the cost of a row differs), and
+// whether they are grouped by XCD.  Always: one feature matrix exceeds the 256 MB Infinity Cache.
+// If even: fp32 rows of width 8 to 32 that exceed the L2s together, which without grouping each
+// fetch all of it.  Width 16, 600 k rows in 24 to 64 subgraphs of spread 0 to 0.5: epochs of 213-238
+// us become 185-211; width 32, 300 k rows: 188-233 -> 181-226.  Not from width 64 on: the launch is
+// one round of resident workgroups, and an XCD with a few more than it holds runs a second
+// one; 150 k rows of width 64 in 24 subgraphs of spread 0.5: 465-475 -> 566 us, width 128, 100 k
+// rows: 466 -> 611 (in equal subgraphs 465 -> 453 and 403 -> 389).  bf16 rows within the Infinity Cache
+// gain nothing measurable (1.1 M rows of width 64: 0.977 against 0.973 ms per epoch).
+Grouping grouping_of(int storage, int dim, int n, int v) {
+  const bool f32 = storage == GCO_STORAGE_FP32;
+  const double bytes = static_cast<double>(n) * dim * (f32 ? 4 : 2);
+  if (bytes > 256.0 * 1024 * 1024) return Grouping::kAlways;
+  const bool gathers_rows = v == WM_FWD || v == WM_BWD || v == WM_EMBED;
+  return f32 && dim <= 32 && gathers_rows && bytes > 32.0 * 1024 * 1024 ? Grouping::kIfEven : Grouping::kNone;
+}
+
+void wave_map_of(int storage, int dim, int v, int P, const std::vector<int>& part_rows, const std::vector<int>& wrow,
+                 const uint8_t* active, std::vector<int>& wblk_k, std::vector<WaveRun>& wave_runs) {
+  const bool f32 = storage == GCO_STORAGE_FP32;
+  const int target = f32 ? wave_blocks_f32(dim, v) : (dim == 128 ? kWaveBlocksFor128 : kWaveBlocksFor)[v];
+  build_wave_map(P, part_rows, wrow, f32 && v != WM_NARROW ? kTileRowsF32 : kWaveRows, target,
+                 (f32 ? kWaveRowCostF32 : kWaveRowCost)[v], grouping_of(storage, dim, part_rows[P], v), wblk_k,
+                 wave_runs, active);
+}
+
 // Whether training runs faster with a workgroup per subgraph for whole epochs (small_train.hip)
 // than with four to eight launches per epoch over the whole chip; microseconds per epoch, from a
 // sweep over 1 .. 512 subgraphs of 60 .. 2500 rows with 3 .. 8 neighbours.  One compute unit is
@@ -569,15 +590,10 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
   put_lists(&m.pbl_ptr, &m.pbl_list, blk_k, Pw);
   put_lists(&m.nwbl_ptr, &m.nwbl_list, nblk_k, Pw);
   std::vector<int> narrow;
-  const bool f32 = ctx->cfg.storage == GCO_STORAGE_FP32;
   for (int v = 0; v < kWaveMaps; ++v) {
-    // one decomposition per kernel kind (different cost per row)
-    const int target = f32 ? wave_blocks_f32(ctx->cfg.dim, v)
-                           : (ctx->cfg.dim == 128 ? kWaveBlocksFor128 : kWaveBlocksFor)[v];
     std::vector<int> wk;
     std::vector<WaveRun> runs;
-    build_wave_map(P, h.part_rows, h.wrow, f32 && v != WM_NARROW ? kTileRowsF32 : kWaveRows, target,
-                   (f32 ? kWaveRowCostF32 : kWaveRowCost)[v], h.grouping, wk, runs, active);
+    wave_map_of(ctx->cfg.storage, ctx->cfg.dim, v, P, h.part_rows, h.wrow, active, wk, runs);
     m.num_wblocks[v] = static_cast<int>(wk.size());
     put(&m.wblk_k[v], wk.data(), wk.size());
     static_assert(sizeof(WaveRun) % 16 == 0 && alignof(WaveRun) == 16, "runs lie at 16-byte boundaries of the block");
@@ -943,11 +959,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
 
   // work decomposition
   std::vector<int> blk_k, blk_s, blk_S, nblk_k, nblk_s, nblk_S;
-  const double matrix_bytes = static_cast<double>(n) * ctx->cfg.dim * ctx->elem_bytes();
-  const Grouping grouping = matrix_bytes > 256.0 * 1024 * 1024 ? Grouping::kAlways
-                            : ctx->cfg.storage == GCO_STORAGE_FP32 && matrix_bytes > 32.0 * 1024 * 1024
-                                ? Grouping::kIfEven
-                                : Grouping::kNone;
+  const Grouping grouping = grouping_of(ctx->cfg.storage, D, n, WM_NARROW);
   std::vector<double> entries(P);
   for (int k = 0; k < P; ++k) entries[k] = lrowptr[part_rows[k + 1]] - lrowptr[part_rows[k]];
   build_block_map(P, part_rows, entries, kTileRows, kWideBlocks, kMaxTilesPerBlock, blk_k, blk_s, blk_S, grouping);
@@ -963,7 +975,6 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   HIPCHK(h2d(ctx, ctx->d_blk_s, blk_s.data(), blk_s.size()));
   HIPCHK(h2d(ctx, ctx->d_nblk_s, nblk_s.data(), nblk_s.size()));
   ctx->hm.part_rows = part_rows;
-  ctx->hm.grouping = grouping;
   ctx->hm.blk_k = blk_k;
   ctx->hm.nblk_k = nblk_k;
   // very long rows
@@ -2119,6 +2130,36 @@ int gco_apportion(const double* work, int32_t n, int64_t target, const int32_t* 
   const std::vector<int> got = apportion(std::vector<double>(work, work + n), target, std::vector<int>(lo, lo + n),
                                          std::vector<int>(hi, hi + n));
   std::copy(got.begin(), got.end(), share);
+  return GCO_OK;
+}
+
+int gco_workgroup_parts(int32_t storage, int32_t dim, int32_t kind, const int32_t* rows, const int32_t* entries,
+                        int32_t num_parts, int64_t* count, int32_t* part) {
+  const bool dim_ok = dim == 64 || dim == 128 || (storage == GCO_STORAGE_FP32 && (dim == 8 || dim == 16 || dim == 32));
+  if (!rows || !entries || !count || num_parts < 1 || !dim_ok || kind < WM_FWD || kind > WM_EMBED ||
+      (storage != GCO_STORAGE_FP32 && storage != GCO_STORAGE_BF16))
+    return GCO_EINVAL;
+  int64_t n = 0, nnz = 0;
+  for (int k = 0; k < num_parts; ++k) {
+    if (rows[k] < 0 || entries[k] < 0 || (rows[k] == 0 && entries[k] > 0)) return GCO_EINVAL;
+    n += rows[k];
+    nnz += entries[k];
+  }
+  if (n + nnz + kEntPad >= std::numeric_limits<int32_t>::max()) return GCO_ERANGE;
+  std::vector<int> part_rows(1, 0), wrow(1, 0), wblk_k;
+  for (int k = 0; k < num_parts; ++k) {
+    const int first = wrow.back();
+    for (int64_t r = 1; r <= rows[k]; ++r)
+      wrow.push_back(first + static_cast<int>(r + entries[k] * r / rows[k]));
+    part_rows.push_back(static_cast<int>(wrow.size()) - 1);
+  }
+  std::vector<WaveRun> runs;
+  wave_map_of(storage, dim, kind, num_parts, part_rows, wrow, nullptr, wblk_k, runs);
+  const int64_t room = *count;
+  *count = static_cast<int64_t>(wblk_k.size());
+  if (!part) return GCO_OK;
+  if (room < *count) return GCO_ERANGE;
+  std::copy(wblk_k.begin(), wblk_k.end(), part);
   return GCO_OK;
 }
 

@@ -78,7 +78,7 @@ def make_case(kind, seed):
         part[50000:75000] = 1
         part[75000:] = 2
         return inputs.from_edges(n, u, v), part, 3
-    if kind == "bfs12":         # more than 8 subgraphs: the XCD-grouped block map
+    if kind == "bfs12":         # a regular graph in a dozen subgraphs as a partitioner cuts them
         g = inputs.random_regular(3000, 6, seed)
         return g, inputs.bfs_partition(g, 12, seed), 12
     raise ValueError(kind)

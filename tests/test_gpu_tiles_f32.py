@@ -62,6 +62,43 @@ def test_tile_and_row_length_edges(gco, D, L, norm, share):
     ctx.destroy()
 
 
+def test_workgroups_grouped_by_xcd(gco):
+    """Rows of more than 32 MB in more than eight subgraphs: the launches whose workgroups are
+    grouped by XCD, with idle workgroups among them, against the oracle."""
+    P, D = 24, 16
+    rs = np.random.RandomState(3)
+    sizes = (23_000 * (0.7 + 0.6 * rs.random_sample(P))).astype(np.int32)
+    n = int(sizes.sum())
+    part = np.repeat(np.arange(P), sizes).astype(np.int32)
+    u = rs.randint(0, n, 2 * n)
+    v = np.clip(u + rs.randint(-30, 31, 2 * n), 0, n - 1)
+    name = rs.permutation(n)
+    ids = np.empty(n, dtype=np.int32)
+    ids[name] = part
+    g = inputs.from_edges(n, name[u], name[v])
+    row = np.repeat(np.arange(n), np.diff(g.rowptr))
+    inside = ids[row] == ids[g.col]
+    served = [gco.workgroup_parts("fp32", D, kind, sizes, np.bincount(ids[row[inside]], minlength=P))
+              for kind in ("forward", "hidden", "embed")]
+    assert all(np.any(np.diff(w) < 0) for w in served)       # out of the subgraphs' order: grouped
+    assert any((w < 0).any() for w in served)                # workgroups with nothing to do
+    E, Ws = inputs.init_params(n, ids, P, 3, D, 3)
+    E, Ws = (E * 5).astype(np.float32), [W * 1.5 for W in Ws]
+    ctx = gco.Context(num_layers=3, dim=D)
+    ctx.upload_graph(n, g.rowptr, g.col, ids, P)
+    ctx.set_params(E, Ws)
+    spec = gcn.Spec(num_layers=3)
+    lg = gcn.local_graph(n, g.rowptr, g.col, ids, P, "sym")
+    cache = gcn.forward(lg, E, Ws, spec)
+    gE, gWs = gcn.backward(lg, cache, Ws, spec)
+    dE, dWs = ctx.get_grads()
+    assert rel(ctx.get_probs(), cache["p"]) <= 1e-5
+    assert rel(dE, gE) <= 1e-5
+    for l in range(3):
+        assert rel(dWs[l], gWs[l]) <= 1e-5, f"layer {l + 1}"
+    ctx.destroy()
+
+
 @pytest.mark.parametrize("storage,D", [("fp32", 32), ("bf16", 64)])
 def test_a_listed_subset_has_runs_of_its_own(gco, storage, D):
     """A fine-tune cuts its wavefront runs for the listed subgraphs alone.  Listing all of them
