@@ -1562,6 +1562,12 @@ static void run_small(gco_ctx* ctx, const GraphView& gv, int passes, int epochs,
     const AdamStep ad = adam_constants(c, steps + e + 1);
     a.bc[e] = make_float2(ad.inv_bc1, ad.inv_sqrt_bc2);
   }
+  if (passes == 3 && ctx->best_on) {
+    a.best_loss = ctx->d_best_loss;
+    a.has_best = ctx->d_has_best;
+    a.E_best = ctx->E_best;
+    std::copy(ctx->W_best, ctx->W_best + c.num_layers, a.W_best);
+  }
   a.epochs = epochs;
   a.passes = passes;
   a.train_embed = c.train_embed;
@@ -1697,13 +1703,6 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
   for (int64_t t : ctx->stepE) uniform = uniform && t == ctx->stepE[0];
   for (int64_t t : ctx->stepW) uniform = uniform && t == ctx->stepE[0];
   const gco_config& c = ctx->cfg;
-  // the losses of set e against the lowest so far, while the parameters still are the ones they
-  // belong to
-  auto offer_snapshot = [&](int e) {
-    launch_best_update(ctx->launch(), gv, ctx->loss_partial + static_cast<size_t>(e) * gv.num_loss_slots, Pw,
-                       ctx->d_best_loss, ctx->d_improved, ctx->d_has_best);
-    copy_params(ctx, gv, ctx->d_improved, /*to_best=*/true);
-  };
   std::vector<float2> bc;
   // the loss partials of up to kLossSets epochs are reduced by one launch; so are the
   // per-subgraph bias corrections of those epochs uploaded at once
@@ -1722,13 +1721,7 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
       HIPCHK(h2d(ctx, ctx->d_bc, bc.data(), bc.size()));
     }
     if (ctx->small_train_lds != 0) {
-      const int64_t steps = ctx->stepE.empty() ? 0 : ctx->stepE[0] + e0;
-      if (!ctx->best_on) run_small(ctx, gv, 3, ne, 0, uniform, steps, ctx->d_bc);
-      for (int e = 0; ctx->best_on && e < ne; ++e) {
-        run_small(ctx, gv, 2, 1, e, true, 0, nullptr);
-        offer_snapshot(e);
-        run_small(ctx, gv, 3, 1, e, uniform, steps + e, ctx->d_bc + static_cast<size_t>(e) * (P + Pw));
-      }
+      run_small(ctx, gv, 3, ne, 0, uniform, ctx->stepE.empty() ? 0 : ctx->stepE[0] + e0, ctx->d_bc);
       launch_loss_reduce(ctx->launch(), gv, ctx->loss_partial, ne, gv.num_loss_slots, nullptr, ctx->loss_hist + e0);
       continue;
     }
@@ -1740,7 +1733,12 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
       }
       run_hidden_forward(ctx, gv);
       run_scalar_layer(ctx, gv, 3, e);
-      if (ctx->best_on) offer_snapshot(e);
+      if (ctx->best_on) {
+        // the parameters still are the ones this loss belongs to
+        launch_best_update(ctx->launch(), gv, ctx->loss_partial + static_cast<size_t>(e) * gv.num_loss_slots, Pw,
+                           ctx->d_best_loss, ctx->d_improved, ctx->d_has_best);
+        copy_params(ctx, gv, ctx->d_improved, /*to_best=*/true);
+      }
       run_backward(ctx, gv, maps, true, adE, adW, nullptr, nullptr);
     }
     launch_loss_reduce(ctx->launch(), gv, ctx->loss_partial, ne, gv.num_loss_slots, nullptr, ctx->loss_hist + e0);

@@ -401,6 +401,10 @@ struct SmallTrain {
   double* loss_partial = nullptr;  // set e at loss_partial + e * num_loss_slots
   AdamStep adam{};                 // per_part, if set: [epochs][2 P] (embeddings, then weights)
   float2 bc[kLossSets];            // else the two bias corrections of every epoch
+  // best-by-loss snapshot of every subgraph (nullptr: not tracked)
+  double* best_loss = nullptr;
+  int* has_best = nullptr;
+  float *E_best = nullptr, *W_best[3] = {};
   int epochs = 0;
   int passes = 3;  // 1: forward only (p of one epoch); 2: and the loss; 3: whole epochs
   int train_embed = 1;

@@ -14,6 +14,9 @@
 // its own do (stored features and gradients, the operands of the dense products) and multiplies
 // the rounded values on the fp32 matrix instructions, which is exact per product.
 //
+// Best-by-loss snapshots are taken inside the epoch, between the loss and the update, so that tracking
+// them costs no second forward pass and no launch.
+//
 // What bounds it: the chain of dependent phases -- per epoch about ten barriers, and per tile the
 // latency of its gather and of its products.
 #include "device_utils.h"
@@ -63,7 +66,7 @@ struct Carve {
     rp = take(r);
     ent = take(2 * e);
     valt = mean ? take(e) : 0;
-    red = take(2 * SK<D>::NW);
+    red = take(2 * SK<D>::NW + 4);  // the wavefronts' shares of the loss, the lowest loss, whether this one is lower
     end = at;
   }
 };
@@ -283,6 +286,17 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
   __syncthreads();
 }
 
+// Copies the weight sets of subgraph k to the snapshot.
+template <int D, int L>
+__device__ __forceinline__ void keep_weights(const SmallTrain& a, int k) {
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    const int elems = l < L - 1 ? D * D : D;
+    for (int i = threadIdx.x; i < elems; i += SK<D>::NT)
+      a.W_best[l][static_cast<size_t>(k) * elems + i] = a.W[l][static_cast<size_t>(k) * elems + i];
+  }
+}
+
 template <typename T, int D, int L>
 __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, SmallTrain a) {
   using K = SK<D>;
@@ -294,6 +308,14 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   if (R == 0) {  // no rows: a loss of nothing
     if (a.passes == 1) return;
     for (int ep = threadIdx.x; ep < a.epochs; ep += NT) a.loss_partial[static_cast<size_t>(ep) * g.num_loss_slots + k] = 0.0;
+    if (a.best_loss != nullptr && a.best_loss[k] > 0.0) {  // its one model, whose loss is 0 from the first epoch on
+      __syncthreads();
+      keep_weights<D, L>(a, k);
+      if (threadIdx.x == 0) {
+        a.best_loss[k] = 0.0;
+        a.has_best[k] = 1;
+      }
+    }
     return;
   }
   const size_t first = rbeg;
@@ -305,6 +327,8 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   int* rp = reinterpret_cast<int*>(smem + cv.rp);
   uint2* ent = reinterpret_cast<uint2*>(smem + cv.ent);
   double* dred = reinterpret_cast<double*>(smem + cv.red);
+  double* lowest = dred + NW;
+  int* lower = reinterpret_cast<int*>(lowest + 1);
 
   for (int i = tid; i <= R; i += NT) rp[i] = g.wrowptr[rbeg + i] - es;
   for (int i = tid; i < R; i += NT) smem[cv.c + i] = a.c[rbeg + i];
@@ -325,6 +349,7 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
           r < D && c < D ? Store<T>::as_stored(a.W[l - 1][static_cast<size_t>(k) * D * D + r * D + c]) : 0.f;
     }
   if (tid < DP) smem[cv.wo + tid] = tid < D ? a.W[L - 1][static_cast<size_t>(k) * D + tid] : 0.f;
+  if (tid == 0) *lowest = a.best_loss != nullptr ? a.best_loss[k] : 0.0;
   __syncthreads();
   const StreamInLds fwd{ent, nullptr, rp};
   const StreamInLds bwd{ent, mean ? smem + cv.valt : nullptr, rp};
@@ -422,11 +447,24 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
 #pragma unroll
       for (int w = 0; w < NW; ++w) total += dred[w];
       a.loss_partial[static_cast<size_t>(ep) * g.num_loss_slots + k] = total;
+      *lower = a.best_loss != nullptr && total < *lowest;
+      if (*lower) {
+        *lowest = total;
+        a.best_loss[k] = total;
+        a.has_best[k] = 1;
+      }
     }
     if (a.passes == 2) return;
     scan_rows(bwd, e0, e1, [&](const Entry& en) { return en.val * tv[en.col]; },
               [&](int row, float s) { pv[row] = s; });
     __syncthreads();
+    if (*lower) {  // the parameters this loss belongs to, before they change
+      const float4* from = reinterpret_cast<const float4*>(a.E + first * D);
+      float4* to = reinterpret_cast<float4*>(a.E_best + first * D);
+      for (int i = tid; i < R * (D / 4); i += NT) to[i] = from[i];
+      keep_weights<D, L>(a, k);
+      __syncthreads();
+    }
     if constexpr (L == 2) {
       backward_layer<T, D, L, true, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
     } else {

@@ -84,19 +84,49 @@ def test_whole_epochs_of_small_subgraphs(gco, D, L, norm, storage):
     ctx.destroy()
 
 
-def test_snapshots_of_small_subgraphs_cost_no_bit(gco):
-    g, part, P = ragged([40] * 50 + [0, 1], 9)
-    E, Ws = inputs.init_params(g.n, part, P, 2, 16, 5)
-    ctx = gco.Context(num_layers=2, dim=16, lr=5e-2)
+@pytest.mark.parametrize("D,L,storage", [(16, 2, "fp32"), (8, 3, "fp32"), (32, 2, "fp32"), (64, 2, "bf16")])
+def test_snapshots_of_small_subgraphs_cost_no_bit(gco, D, L, storage):
+    """Tracking the best parameters changes no result and needs no launch of its own."""
+    g, part, P = ragged([64 if D == 64 else 40] * 240 + [0, 1], 9, 1)
+    E, Ws = inputs.init_params(g.n, part, P, L, D, 5)
+    ctx = gco.Context(num_layers=L, dim=D, storage=storage, lr=0.3)   # large enough that losses go up and down
     ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
     ctx.set_params(E, Ws)
     plain = ctx.train(12)
     ctx.set_params(E, Ws)
     ctx.keep_best(True)
+    ctx.set_profiling(1)
     assert np.array_equal(plain, ctx.train(12))
+    assert used(ctx) == 1 and ctx.get_timing()["best_snapshot"]["launches"] == 0
+    ctx.set_profiling(0)
     best = ctx.get_best_loss()
+    assert best[P - 2] == 0.0 and np.isfinite(best).all()             # P - 2: no nodes
     ctx.restore_best()
     _, per = ctx.loss()
-    has = np.isfinite(best)
-    assert np.array_equal(per[has], best[has])
+    assert np.array_equal(per, best)
+    kept = ctx.get_params()
+    # the parameters of the epoch of the lowest loss, for every subgraph
+    ctx.set_params(E, Ws)
+    ctx.keep_best(False)
+    losses, states = [], []
+    for _ in range(12):
+        losses.append(ctx.loss()[1])
+        states.append(ctx.get_params())
+        ctx.train(1, return_loss=False)
+    at = np.argmin(np.stack(losses), axis=0)
+    assert len(set(at.tolist())) > 2
+    for k in range(P):
+        assert np.array_equal(kept[0][part == k], states[at[k]][0][part == k])
+        for l in range(L):
+            assert np.array_equal(kept[1][l][k], states[at[k]][1][l][k])
+    # a subset is compared with what it had before; the others keep their snapshots
+    ctx.set_params(E, Ws)
+    ctx.keep_best(True)
+    ctx.train(3, return_loss=False)
+    first = ctx.get_best_loss()
+    listed = np.arange(0, P, 2, dtype=np.int32)
+    ctx.train_subset(9, listed, return_loss=False)
+    second = ctx.get_best_loss()
+    on = np.isin(np.arange(P), listed)
+    assert np.array_equal(second[~on], first[~on]) and np.array_equal(second[on], best[on])
     ctx.destroy()
