@@ -96,13 +96,18 @@ int gco_get_config(gco_ctx* ctx, gco_config* out);
  *   STAGED      three launches, each workgroup first copies its subgraph's vector into LDS
  *               (the largest subgraph's float vector must fit a compute unit's LDS twice);
  *   ONE_LAUNCH  one launch with a workgroup per subgraph (two such vectors must fit once).
+ * With AUTO, graphs of small subgraphs (weights of their own, at most 64 wide) may go further
+ * than ONE_LAUNCH: forward, loss and training then run in one kernel with a workgroup per
+ * subgraph that takes the scalar layer along, whole epochs at a time (kernel kind
+ * "small_train").  Forcing a form switches that kernel off.
  * All forms compute the same sums; where a row's entries fall into the 64-entry steps of
  * the kernels differs, so results agree to fp32 rounding, not bit for bit.  Call before
  * gco_upload_graph, which returns GCO_ERANGE if the subgraphs do not fit a forced form.
  * EINVAL for an unknown value. */
 enum { GCO_SCALAR_AUTO = 0, GCO_SCALAR_STREAMS = 1, GCO_SCALAR_STAGED = 2, GCO_SCALAR_ONE_LAUNCH = 3 };
 int gco_set_scalar_layer_form(gco_ctx* ctx, int form);
-/* The form in use for the uploaded graph (one of the three; ESTATE before upload). */
+/* The form in use for the uploaded graph (one of the three; ESTATE before upload).  ONE_LAUNCH
+ * also where AUTO has chosen the kernel for whole epochs. */
 int gco_get_scalar_layer_form(gco_ctx* ctx, int* form);
 
 /* Text of the last failure on ctx (valid until the next call on ctx). */

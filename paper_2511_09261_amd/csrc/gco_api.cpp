@@ -1051,10 +1051,11 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
                             27.0 + 13e-6 * static_cast<double>(total_light) + 0.014 * std::max(0, P - 512);
     ctx->fused_scalar = form == GCO_SCALAR_ONE_LAUNCH || (form == GCO_SCALAR_AUTO && fused_fits && fused_pays);
     ctx->staged_scalar = form == GCO_SCALAR_STAGED || (form == GCO_SCALAR_AUTO && !ctx->fused_scalar && staged_fits);
-    // Whole epochs in one launch: where the scalar layer is one launch anyway, every subgraph has
-    // weights of its own and fits the LDS with its stream, and that is the faster way
+    // Whole epochs in one launch: where the scalar layer is one launch by choice, every subgraph has
+    // weights of its own and fits the LDS with its stream, and that is the faster way.  A forced
+    // form is what runs.
     ctx->small_train_lds = 0;
-    if (ctx->fused_scalar && ctx->Pw == P && L >= 2 && D <= 64 && num_heavy == 0 &&
+    if (form == GCO_SCALAR_AUTO && ctx->fused_scalar && ctx->Pw == P && L >= 2 && D <= 64 && num_heavy == 0 &&
         small_train_pays(ctx->cfg, P, n, total_light, max_rows, max_light)) {
       size_t lds = 0;
       for (int kk = 0; kk < P; ++kk)

@@ -130,3 +130,23 @@ def test_snapshots_of_small_subgraphs_cost_no_bit(gco, D, L, storage):
     on = np.isin(np.arange(P), listed)
     assert np.array_equal(second[~on], first[~on]) and np.array_equal(second[on], best[on])
     ctx.destroy()
+
+
+@pytest.mark.parametrize("form", ["auto", "streams", "staged", "one_launch"])
+def test_a_forced_form_of_the_scalar_layer_is_what_runs(gco, form):
+    g, part, P = ragged([60] * 30, 3)
+    E, Ws = inputs.init_params(g.n, part, P, 2, 16, 5)
+    ctx = gco.Context(num_layers=2, dim=16)
+    ctx.set_scalar_layer_form(form)
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    ctx.set_profiling(1)
+    ctx.forward()
+    ctx.loss()
+    ctx.train(2)
+    t = {k: v["launches"] for k, v in ctx.get_timing().items()}
+    assert ctx.get_scalar_layer_form() == ("one_launch" if form == "auto" else form)
+    assert t["small_train"] == (3 if form == "auto" else 0)
+    assert t["scalar_layer"] == (4 if form == "one_launch" else 0)
+    assert t["fwd_readout"] == (4 if form in ("streams", "staged") else 0)
+    ctx.destroy()
