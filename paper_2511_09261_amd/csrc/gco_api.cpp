@@ -1536,10 +1536,11 @@ static AdamStep adam_constants(const gco_config& c, int64_t step) {
 
 // Small subgraphs (small_train_lds != 0).  passes = 1: forward; 2: forward and loss, to set `slot`
 // of the loss partials; 3: `epochs` (at most kLossSets) epochs in one launch, their losses to the
-// sets from `slot` on.  uniform: the step counts of all models are `steps` before it; else bc
-// holds the bias corrections.  Forward, loss and training take every sum in the same order.
+// sets from `slot` on; 4: the gradients of one epoch to gE and gW.  uniform: the step counts of all models are `steps` before it; else bc
+// holds the bias corrections.  Forward, loss, gradients and training take every sum in the same
+// order.
 static void run_small(gco_ctx* ctx, const GraphView& gv, int passes, int epochs, int slot, bool uniform,
-                      int64_t steps, const float2* bc) {
+                      int64_t steps, const float2* bc, float* gE = nullptr, float* const* gW = nullptr) {
   const gco_config& c = ctx->cfg;
   SmallTrain a;
   for (int l = 0; l < c.num_layers; ++l) {
@@ -1568,6 +1569,10 @@ static void run_small(gco_ctx* ctx, const GraphView& gv, int passes, int epochs,
     a.has_best = ctx->d_has_best;
     a.E_best = ctx->E_best;
     std::copy(ctx->W_best, ctx->W_best + c.num_layers, a.W_best);
+  }
+  if (passes == 4) {
+    a.gE = gE;
+    std::copy(gW, gW + c.num_layers, a.gW);
   }
   a.epochs = epochs;
   a.passes = passes;
@@ -1900,9 +1905,13 @@ int gco_get_grads(gco_ctx* ctx, float* gE, float* const* gW) {
     d_gW[l - 1] = tmp.get<float>(static_cast<size_t>(ctx->Pw) * w_elems(ctx, l));
     NEED(d_gW[l - 1], GCO_ENOMEM, "device scratch allocation failed");
   }
-  run_hidden_forward(ctx, ctx->gv);
-  run_scalar_layer(ctx, ctx->gv, 3, 0);
-  run_backward(ctx, ctx->gv, ctx->full, false, AdamStep{}, AdamStep{}, d_gE, d_gW);
+  if (ctx->small_train_lds != 0) {
+    run_small(ctx, ctx->gv, 4, 1, 0, true, 0, nullptr, d_gE, d_gW);
+  } else {
+    run_hidden_forward(ctx, ctx->gv);
+    run_scalar_layer(ctx, ctx->gv, 3, 0);
+    run_backward(ctx, ctx->gv, ctx->full, false, AdamStep{}, AdamStep{}, d_gE, d_gW);
+  }
   HIPCHK(hipGetLastError());
   if (gE) {
     int rc = download_node_matrix(ctx, gE, d_gE);

@@ -406,7 +406,8 @@ struct SmallTrain {
   int* has_best = nullptr;
   float *E_best = nullptr, *W_best[3] = {};
   int epochs = 0;
-  int passes = 3;  // 1: forward only (p of one epoch); 2: and the loss; 3: whole epochs
+  int passes = 3;  // 1: forward only (p of one epoch); 2: and the loss; 3: whole epochs; 4: gradients, no update
+  float *gE = nullptr, *gW[3] = {};  // passes = 4 (gE may be nullptr)
   int train_embed = 1;
 };
 size_t small_train_lds_bytes(int D, int L, int rows, int entries, bool mean);

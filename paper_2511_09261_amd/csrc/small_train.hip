@@ -114,7 +114,7 @@ __device__ __forceinline__ void scan_rows(const StreamInLds& s, int e0, int e1, 
 }
 
 // Backward of hidden layer l (see BwdArgs), then Adam on W_l (and on w_out by the last layer).
-template <typename T, int D, int L, bool LAST, bool TO_EMBED>
+template <typename T, int D, int L, bool GRADS, bool LAST, bool TO_EMBED>
 __device__ __forceinline__ void backward_layer(const SmallTrain& a, const StreamInLds& st, const GraphView& g, float* smem,
                                const Carve<D>& cv, const int k, const int R, const size_t first, const AdamStep& adE,
                                const AdamStep& adW) {
@@ -186,7 +186,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
         for (int tb = 0; tb < NQ; ++tb) gw[ta][tb] = mfma(av[s][ta], bv[tb], gw[ta][tb]);
     }
     wave_lds_handoff();
-    if (TO_EMBED && !a.train_embed) continue;
+    if (TO_EMBED && (GRADS ? a.gE == nullptr : !a.train_embed)) continue;
     const int on = operand_lane<D>(n);
 #pragma unroll
     for (int ta = 0; ta < NQ; ++ta) {
@@ -206,7 +206,9 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
         for (int j = 0; j < 4; ++j) z = mfma(w[j], acc[q][j], z);
       }
       if (row < R) {
-        if constexpr (TO_EMBED) {
+        if constexpr (TO_EMBED && GRADS) {
+          store4<D>(a.gE + first * D, row, ta, h, z);
+        } else if constexpr (TO_EMBED) {
 #pragma unroll
           for (int x = 0; x < 4; ++x) {
             float ex = e[x], mx = m[x], vx = v[x];
@@ -258,6 +260,22 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     if (wave < kSlots) each([](float& place, float x) { place = x + place; });
     __syncthreads();
   }
+  if constexpr (GRADS) {
+    for (int idx = tid; idx < D * D; idx += K::NT) {
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < kSlots; ++q) s += slots[q * DP * DP + idx / D * DP + idx % D];
+      a.gW[l - 1][static_cast<size_t>(k) * D * D + idx] = s;
+    }
+    if (LAST && tid < D) {
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) s += smem[cv.gwo + q * DP + tid];
+      a.gW[L - 1][static_cast<size_t>(k) * D + tid] = s;
+    }
+    __syncthreads();
+    return;
+  }
   float* W = a.W[l - 1] + static_cast<size_t>(k) * D * D;
   float* mW = a.mW[l - 1] + static_cast<size_t>(k) * D * D;
   float* vW = a.vW[l - 1] + static_cast<size_t>(k) * D * D;
@@ -297,7 +315,8 @@ __device__ __forceinline__ void keep_weights(const SmallTrain& a, int k) {
   }
 }
 
-template <typename T, int D, int L>
+// GRADS: passes = 4, compiled by itself so that training does not carry it.
+template <typename T, int D, int L, bool GRADS>
 __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, SmallTrain a) {
   using K = SK<D>;
   constexpr int NQ = K::NQ, DP = K::DP, NW = K::NW, NT = K::NT, WP = K::WP;
@@ -307,6 +326,14 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   const int rbeg = g.part_rows[k], R = g.part_rows[k + 1] - rbeg;
   if (R == 0) {  // no rows: a loss of nothing
     if (a.passes == 1) return;
+    if constexpr (GRADS) {
+#pragma unroll
+      for (int l = 0; l < L; ++l) {
+        const int elems = l < L - 1 ? D * D : D;
+        for (int i = threadIdx.x; i < elems; i += NT) a.gW[l][static_cast<size_t>(k) * elems + i] = 0.f;
+      }
+      return;
+    }
     for (int ep = threadIdx.x; ep < a.epochs; ep += NT) a.loss_partial[static_cast<size_t>(ep) * g.num_loss_slots + k] = 0.0;
     if (a.best_loss != nullptr && a.best_loss[k] > 0.0) {  // its one model, whose loss is 0 from the first epoch on
       __syncthreads();
@@ -466,19 +493,23 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
       __syncthreads();
     }
     if constexpr (L == 2) {
-      backward_layer<T, D, L, true, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
+      backward_layer<T, D, L, GRADS, true, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
     } else {
-      backward_layer<T, D, L, true, false>(a, bwd, g, smem, cv, k, R, first, adE, adW);
-      backward_layer<T, D, L, false, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
+      backward_layer<T, D, L, GRADS, true, false>(a, bwd, g, smem, cv, k, R, first, adE, adW);
+      backward_layer<T, D, L, GRADS, false, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
     }
   }
 }
 
 template <typename T, int D, int L>
 void launch_t(const Launch& ln, const GraphView& g, const SmallTrain& a, size_t lds) {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(small_train_kernel<T, D, L>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-  small_train_kernel<T, D, L><<<g.P, SK<D>::NT, lds, ln.st>>>(g, a);
+  auto run = [&](auto kernel) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              static_cast<int>(lds));
+    kernel<<<g.P, SK<D>::NT, lds, ln.st>>>(g, a);
+  };
+  if (a.passes == 4) run(small_train_kernel<T, D, L, true>);
+  else run(small_train_kernel<T, D, L, false>);
 }
 
 template <typename T, int D>

@@ -8,7 +8,7 @@ import pytest
 
 from oracle import gcn
 from paper_2511_09261_amd import inputs
-from tests.parity import rel_l2
+from tests.parity import rel, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -149,4 +149,33 @@ def test_a_forced_form_of_the_scalar_layer_is_what_runs(gco, form):
     assert t["small_train"] == (3 if form == "auto" else 0)
     assert t["scalar_layer"] == (4 if form == "one_launch" else 0)
     assert t["fwd_readout"] == (4 if form in ("streams", "staged") else 0)
+    ctx.destroy()
+
+
+@pytest.mark.parametrize("D,L,norm,problem", [(8, 2, "mean", "mis"), (16, 3, "sym", "maxcut"), (32, 2, "sym", "maxcut"),
+                                              (64, 3, "mean", "mis")])
+def test_gradients_come_from_the_kernel_that_trains(gco, D, L, norm, problem):
+    """fp32 sums of at most a few hundred terms against fp64, norm-wise 1e-5; the forward pass of
+    gco_get_grads is that of gco_forward, bit for bit."""
+    g, part, P = ragged([1, 0, 15, 16, 17, 33, 63, 64] + [60] * 200, D + L, 1)
+    E, Ws = inputs.init_params(g.n, part, P, L, D, 5)
+    E, Ws = (E * 5).astype(np.float32), [W * 1.5 for W in Ws]
+    ctx = gco.Context(problem=problem, num_layers=L, dim=D, norm=norm)
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    ctx.forward()
+    p, H = ctx.get_probs(), [ctx.get_hidden(l) for l in range(1, L)]
+    ctx.set_profiling(1)
+    dE, dWs = ctx.get_grads()
+    assert used(ctx) == 1
+    assert np.array_equal(ctx.get_probs(), p)
+    assert all(np.array_equal(ctx.get_hidden(l), H[l - 1]) for l in range(1, L))
+    spec = gcn.Spec(problem=problem, num_layers=L, norm=norm)
+    lg = gcn.local_graph(g.n, g.rowptr, g.col, part, P, norm)
+    gE, gWs = gcn.backward(lg, gcn.forward(lg, E, Ws, spec), Ws, spec)
+    assert rel(dE, gE) <= 1e-5
+    for l in range(L):
+        assert rel(dWs[l], gWs[l]) <= 1e-5, f"layer {l + 1}"
+    E1, W1 = ctx.get_params()                  # nothing was updated
+    assert np.array_equal(E1, E) and all(np.array_equal(a, b.astype(np.float32)) for a, b in zip(W1, Ws))
     ctx.destroy()
