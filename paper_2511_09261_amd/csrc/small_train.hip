@@ -113,6 +113,20 @@ __device__ __forceinline__ void scan_rows(const StreamInLds& s, int e0, int e1, 
   }
 }
 
+// The thread's number.  HIDE: unknown to the compiler at the places where it is asked for, so that
+// addresses made from it are worked out again in every phase of an epoch.  Known, they are all made
+// ahead of the loop over the epochs, and held in registers across it they and others spill (three
+// layers of width 32: 75 registers, 33 with this), each reload waiting for every load in flight:
+// 256 subgraphs of 200 rows of width 32, three layers, 47.6 -> 43.9 us per epoch, of 128 rows of width
+// 64 65.2 -> 60.9.  Two layers of width 8 or 16 spill twelve at most, and working the addresses out costs
+// more (200 rows: 14.3 us against 15.0).
+template <bool HIDE>
+__device__ __forceinline__ int thread_number() {
+  int tid = threadIdx.x;
+  if (HIDE) asm volatile("" : "+v"(tid));
+  return tid;
+}
+
 // Backward of hidden layer l (see BwdArgs), then Adam on W_l (and on w_out by the last layer).
 template <typename T, int D, int L, bool GRADS, bool LAST, bool TO_EMBED>
 __device__ __forceinline__ void backward_layer(const SmallTrain& a, const StreamInLds& st, const GraphView& g, float* smem,
@@ -123,7 +137,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
   constexpr int l = LAST ? L - 1 : 1;
   static_assert(TO_EMBED == (l == 1), "the layer's number");
   using Rows = std::conditional_t<LAST, LastRows<D, T>, PlainRows<D, T>>;
-  const int tid = threadIdx.x, lane = tid % 64, n = lane % 16, h = lane / 16;
+  const int tid = thread_number<(L == 3 || D >= 32)>(), lane = tid % 64, n = lane % 16, h = lane / 16;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   float* gt = smem + cv.sums + wave * K::kWaveLds;
   float* wl = smem + cv.w[l - 1];
@@ -395,6 +409,7 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   float *tv = smem + cv.t, *pv = smem + cv.p;
 
   for (int ep = 0; ep < a.epochs; ++ep) {
+    const int tid = thread_number<(L == 3 || D == 64)>(), lane = tid % 64, n = lane % 16, h = lane / 16;
     AdamStep adE = a.adam, adW = a.adam;
     if (a.adam.per_part != nullptr) {
       const float2* bc = a.adam.per_part + static_cast<size_t>(ep) * (2 * g.P);  // [P] embeddings, [P] weights
