@@ -50,7 +50,23 @@ __device__ __forceinline__ void store4(bf16_t* X, int j, int q, int h, const f32
       make_uint2(f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]));
 }
 
-// ---- sources of gathered rows: request() starts the loads of a row, add() uses them ----
+// The same of a gathered row.  Width 8: the lanes of the upper half, which such a row does not have, load
+// the lower one again instead of branching around the load; aggregate() drops what they sum.
+template <int D>
+__device__ __forceinline__ f32x4 gather4(const float* X, int j, int q, int h) {
+  return *reinterpret_cast<const f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * (D == 8 ? h % 2 : h));
+}
+template <int D>
+__device__ __forceinline__ f32x4 gather4(const bf16_t* X, int j, int q, int h) {
+  return load4<D>(X, j, q, h);
+}
+
+// Loads before it are issued before it.  Without it the compiler moves a load whose value is used under
+// a condition down to that use, where it is issued late and waited for with everything in flight.
+__device__ __forceinline__ void loads_stay_here() { asm volatile("" ::: "memory"); }
+
+// ---- sources of gathered rows: request() starts the loads of a row (this lane's features of it:
+// 16 q + 4 h + j, h = lane % 4), add() uses them ----
 template <int D, typename T = float>
 struct PlainRows {
   struct Row {
@@ -59,7 +75,7 @@ struct PlainRows {
   const T* X;
   __device__ __forceinline__ void request(Row& r, int j, int h) const {
 #pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = load4<D>(X, j, q, h);
+    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = gather4<D>(X, j, q, h);
   }
   __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
 #pragma unroll
@@ -84,10 +100,10 @@ struct LastRows {
   __device__ __forceinline__ void request(Row& r, int j, int h) const {
     r.gt = g_t[j];
 #pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = load4<D>(H, j, q, h);
+    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = gather4<D>(H, j, q, h);
   }
   __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
-    int off = 4 * (threadIdx.x % 64 / 16);
+    int off = 4 * (threadIdx.x % 4);
     if (D > 64) asm volatile("" : "+v"(off));  // not read ahead of the loop over the entries
 #pragma unroll
     for (int q = 0; q < TF<D>::NQ; ++q) {
@@ -115,6 +131,17 @@ __device__ __forceinline__ float row16_sum(float v) {
   GCO_ROR(8) GCO_ROR(4) GCO_ROR(2) GCO_ROR(1)
 #undef GCO_ROR
   return v;
+}
+
+// Sum over the lanes of equal number modulo 4 (a gathered row's sixteen groups); every lane ends with
+// the total, in a fixed order.
+__device__ __forceinline__ float groups_sum(float v) {
+#define GCO_ROR(N) \
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+  GCO_ROR(8) GCO_ROR(4)
+#undef GCO_ROR
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
 }
 
 // What the aggregation of a tile starts from, requested a tile ahead: the tile's range of the
@@ -149,6 +176,7 @@ struct TileFacts {
   }
   int share;    // entries per lane group (uniform)
   bool by_row;  // every lane group sums the row of its own number (uniform)
+  int e0, e1;   // this lane's group's share
   // How the tile's entries are dealt to the lane groups.  Row by row the tile takes its longest
   // row, but an entry costs a third of the instructions (no row to watch for, no sums through
   // LDS).  From memory every batch of entries is a round trip: taken up to 1.5 times the mean and
@@ -165,15 +193,18 @@ struct TileFacts {
     longest = __builtin_amdgcn_readfirstlane(longest);
     share = (E1() - E0() + 15) / 16;
     by_row = 2 * longest <= Stream::kByRow * (share + 1) + 1;
-    if (by_row) share = longest;
+    const int group = threadIdx.x % 64 / 4;
+    if (by_row) {
+      share = longest;
+      e0 = __shfl(a, group, 64);
+      e1 = __shfl(b, group, 64);
+    } else {
+      e0 = E0() + group * share;
+      e1 = min(e0 + share, E1());
+    }
   }
   __device__ __forceinline__ int E0() const { return __builtin_amdgcn_readlane(a, 0); }
   __device__ __forceinline__ int E1() const { return __builtin_amdgcn_readlane(b, 15); }
-  // first entry of this lane's group, and the end of its share
-  __device__ __forceinline__ int begin() const {
-    return by_row ? a : E0() + static_cast<int>(threadIdx.x % 16) * share;
-  }
-  __device__ __forceinline__ int end() const { return by_row ? b : min(begin() + share, E1()); }
   // No branches around the loads, here and for the rows: a group whose share has ended reads on
   // into the next one's (the stream is padded), and fetches its own row again.
   template <class Stream>
@@ -184,13 +215,19 @@ struct TileFacts {
   template <class Stream>
   __device__ __forceinline__ void request_entries(const Stream& s) {
     deal(s);
-    request_entries_at(s, begin(), first);
+    request_entries_at(s, e0, first);
   }
 };
 
 // acc = (A_hat x)(row n of the tile at r0, this lane's features); zero for rows past r1.
 // `sums` is kWaveLds floats of this wavefront's LDS.  on_own(x) is called by one lane group
 // for every row of the tile with the gathered row itself.
+//
+// The lanes of a group that gathers a row are neighbours (lane 4 group + h holds features
+// 16 q + 4 h + j), because the cache looks at four neighbouring lanes at once: a row or a stream
+// entry is one look-up per group.  With the groups in the layout of the products (lane n + 16 h) every lane
+// was one of its own, and these bounded the kernels where rows are not short: 19 000 rows of width 16
+// with 30 neighbours, 6.5 million look-ups a launch.  The sums change layout on their way through LDS.
 template <int D, class Stream, class Rows, class OnOwn>
 __device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stream, const Rows& rows,
                                           const TileFacts<D>& f, int r0, int r1,
@@ -198,39 +235,41 @@ __device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stre
                                           f32x4 (&acc)[TF<D>::NQ], OnOwn&& on_own) {
   constexpr int NQ = TF<D>::NQ, U = TF<D>::U, PT = TF<D>::PT;
   const int lane = threadIdx.x % 64, n = lane % 16, h = lane / 16;
+  const int group = lane / 4, gh = lane % 4;
   float* carries = sums + kTile * PT;
-  const int E0 = f.E0(), share = f.share, e1 = f.end();
+  const int E0 = f.E0(), share = f.share, e1 = f.e1;
   if (share == 0) {  // no rows (a wavefront that keeps step with its workgroup)
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     return;
   }
-  int e = f.begin();
+  int e = f.e0;
   Entry en[U];
   typename Rows::Row x[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     en[u] = f.first[u];
-    rows.request(x[u], e + u < e1 ? en[u].col : r0, h);
+    rows.request(x[u], e + u < e1 ? en[u].col : r0, gh);
   }
+  loads_stay_here();
 #pragma unroll
   for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
   bool pre_reduced = false;  // such a row is among this group's
-  const bool valid = r0 + n < r1;
   // The row in hand (by_row: the group's own throughout) and the place of its sum.
-  int cur = f.by_row ? r0 + n : -1;
-  float* place = carries;
+  int cur = f.by_row ? r0 + group : -1;
+  float* place = f.by_row ? sums + group * PT : carries;
   auto leave = [&]() {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(place + 16 * q + 4 * h) = acc[q];
+    for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(place + 16 * q + 4 * gh) = acc[q];
   };
-  if (f.by_row && valid) {  // a row begins with its diagonal entry
+  if (f.by_row && cur < r1) {  // a row begins with its diagonal entry
     on_own(x[0]);
     if (Stream::kPreReduced) pre_reduced = en[0].row < 0;
   }
   for (int b = 0; b < share; b += U, e += U) {
     Entry nx[U];
     TileFacts<D>::request_entries_at(stream, e + U, nx);
+    loads_stay_here();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (e + u < e1) {
@@ -242,7 +281,7 @@ __device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stre
           for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
           cur = row;
           if (Stream::kPreReduced) pre_reduced |= en[u].row < 0;
-          place = carries + n * PT;
+          place = carries + group * PT;
           if (en[u].col == row) {  // the row's diagonal entry
             place = sums + (row - r0) * PT;
             on_own(x[u]);
@@ -255,32 +294,35 @@ __device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stre
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         en[u] = nx[u];
-        rows.request(x[u], e + U + u < e1 ? en[u].col : r0, h);
+        rows.request(x[u], e + U + u < e1 ? en[u].col : r0, gh);
       }
+      loads_stay_here();
     }
   }
+  if (cur >= 0) leave();
+  wave_lds_handoff();
+  const bool valid = r0 + n < r1;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(sums + n * PT + 16 * q + 4 * h);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) acc[q][y] = valid && (D > 8 || h < 2) ? v[y] : 0.f;
+  }
   if (!f.by_row) {
-    if (cur >= 0) leave();
-    wave_lds_handoff();
     // the row's sum: its place, then the carries of the groups it ran through.  Shares are far
     // below 2^20 entries, so the float quotients of half-integers are on the right side.
     const float inv = 1.f / static_cast<float>(share);
     int grp = static_cast<int>((static_cast<float>(f.a - E0) + 0.5f) * inv);
     const int last = static_cast<int>((static_cast<float>(f.b - E0) - 0.5f) * inv);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(sums + n * PT + 16 * q + 4 * h);
-#pragma unroll
-      for (int y = 0; y < 4; ++y) acc[q][y] = valid ? v[y] : 0.f;
-    }
     for (++grp; __any(valid && grp <= last); ++grp) {
       if (valid && grp <= last) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) acc[q] += *reinterpret_cast<const f32x4*>(carries + grp * PT + 16 * q + 4 * h);
+        for (int q = 0; q < NQ; ++q)
+          if (D > 8 || h < 2) acc[q] += *reinterpret_cast<const f32x4*>(carries + grp * PT + 16 * q + 4 * h);
       }
     }
-    wave_lds_handoff();
   }
+  wave_lds_handoff();
   if (Stream::kPreReduced && __any(pre_reduced)) {  // pre-reduced rows: lane group n adds chunks n, n + 16, ...
     const int hh = valid ? g.heavy_of_row[r0 + n] : -1;
     unsigned todo = static_cast<unsigned>(__ballot(hh >= 0)) & 0xffffu;

@@ -147,7 +147,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     rows.H = static_cast<const T*>(a.H[l]) + first * D;
     rows.g_t = smem + cv.p;  // g_t has taken the place of p
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) rows.w[q] = *reinterpret_cast<const f32x4*>(smem + cv.wo + 16 * q + 4 * h);
+    for (int q = 0; q < NQ; ++q) rows.w[q] = *reinterpret_cast<const f32x4*>(smem + cv.wo + 16 * q + 4 * (lane % 4));
   } else {
     rows.X = static_cast<const T*>(a.GZ) + first * D;
   }
@@ -250,8 +250,8 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
       for (int y = 0; y < 4; ++y) {
-        const float s = row16_sum(gwo[q][y]);
-        if (n == 0) smem[cv.gwo + wave * DP + 16 * q + 4 * h + y] = s;
+        const float s = groups_sum(gwo[q][y]);
+        if (lane < 4) smem[cv.gwo + wave * DP + 16 * q + 4 * lane + y] = s;
       }
   }
   __syncthreads();  // the row sums have served

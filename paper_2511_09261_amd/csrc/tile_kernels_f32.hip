@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
     const float* wk = a.w_out + static_cast<size_t>(k) * a.wout_stride;
     if (D <= 64) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) rows.w[D <= 64 ? q : 0] = load4<D>(wk, 0, q, h);
+      for (int q = 0; q < NQ; ++q) rows.w[D <= 64 ? q : 0] = load4<D>(wk, 0, q, lane % 4);
     } else {
       if (tid < D) last[tid] = wk[tid];  // that place receives the gradient of w_out at the end
       rows.w_lds = last;
@@ -373,8 +373,8 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
     for (int q = 0; q < NQ; ++q)
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const float s = row16_sum(gwo[q][x]);
-        if (n == 0) last[wave * DP + 16 * q + 4 * h + x] = s;
+        const float s = groups_sum(gwo[q][x]);
+        if (lane < 4) last[wave * DP + 16 * q + 4 * lane + x] = s;
       }
   }
   if constexpr (T::SHARED_GW) {
