@@ -156,7 +156,7 @@ struct StreamInMemory {
   const int* wrowid;
   const int* wrowptr;
   static constexpr bool kPreReduced = true;
-  static constexpr int kByRow = 3;  // halves, see TileFacts::deal
+  static __device__ __forceinline__ bool by_row(int longest, int share) { return longest <= share + 4; }
   __device__ __forceinline__ int begin_of(int row) const { return wrowptr[row]; }
   __device__ __forceinline__ Entry at(int e) const {
     const int2 c = went[e];
@@ -178,10 +178,11 @@ struct TileFacts {
   bool by_row;  // every lane group sums the row of its own number (uniform)
   int e0, e1;   // this lane's group's share
   // How the tile's entries are dealt to the lane groups.  Row by row the tile takes its longest
-  // row, but an entry costs a third of the instructions (no row to watch for, no sums through
-  // LDS).  From memory every batch of entries is a round trip: taken up to 1.5 times the mean and
-  // two (150 k rows of width 64 with hubs: 9.6 ms per 20 epochs, with 3 times and four 10.5); with the
-  // stream in LDS and one compute unit's instructions the limit, up to 3 times and four (1250
+  // row, but there is no row to watch for and no carry.  From memory every batch of entries is a
+  // round trip: taken up to one batch more than equal shares (700 k rows of width 16 with 5
+  // neighbours: forward 48.5 us, with up to 1.5 times the mean 51; 19 000 rows of width 64 with 30
+  // neighbours: 34.7, 36.6; 512 subgraphs of 60 rows of width 16: 9.3, never by row 9.8).  With the
+  // stream in LDS and one compute unit's instructions the limit, up to 3 times and three (1250
   // rows of width 16: 40.3 -> 37.0 us per epoch against equal shares throughout).
   template <class Stream>
   __device__ __forceinline__ void deal(const Stream&) {
@@ -192,7 +193,7 @@ struct TileFacts {
 #undef GCO_ROR
     longest = __builtin_amdgcn_readfirstlane(longest);
     share = (E1() - E0() + 15) / 16;
-    by_row = 2 * longest <= Stream::kByRow * (share + 1) + 1;
+    by_row = Stream::by_row(longest, share);
     const int group = threadIdx.x % 64 / 4;
     if (by_row) {
       share = longest;

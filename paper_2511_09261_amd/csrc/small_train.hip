@@ -78,7 +78,7 @@ struct StreamInLds {
   const float* valt;  // nullptr: the values of ent
   const int* rp;
   static constexpr bool kPreReduced = false;
-  static constexpr int kByRow = 6;
+  static __device__ __forceinline__ bool by_row(int longest, int share) { return longest <= 3 * (share + 1); }
   __device__ __forceinline__ int begin_of(int row) const { return rp[row]; }
   __device__ __forceinline__ Entry at(int e) const {
     const uint2 x = ent[e];

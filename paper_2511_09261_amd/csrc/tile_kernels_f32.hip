@@ -51,9 +51,11 @@ __device__ __forceinline__ void run_rows(const WaveRun& run, int& r0, int& r1) {
 }
 
 // operand(ta, q, lane) of all tiles to LDS, wl[(ta NQ + q) 64 + lane]: all loads first, one wait.
-template <int D, class Operand>
-__device__ __forceinline__ void fill_operands(f32x4* wl, const Operand& operand) {
+// While they are on their way, request() starts what needs only the loads before.
+template <int D, class Operand, class Request>
+__device__ __forceinline__ void fill_operands(f32x4* wl, const Operand& operand, Request&& request) {
   constexpr int NQ = TK<D>::NQ;
+  if constexpr (!TK<D>::W_IN_LDS) request();
   if constexpr (TK<D>::W_IN_LDS) {
     constexpr int kPer = (NQ * NQ * 64 + kBlock - 1) / kBlock;
     f32x4 v[kPer];
@@ -62,6 +64,9 @@ __device__ __forceinline__ void fill_operands(f32x4* wl, const Operand& operand)
       const int idx = min(static_cast<int>(threadIdx.x) + i * kBlock, NQ * NQ * 64 - 1);
       v[i] = operand(idx / 64 / NQ, (idx / 64) % NQ, idx % 64);
     }
+    loads_stay_here();
+    request();
+    loads_stay_here();
 #pragma unroll
     for (int i = 0; i < kPer; ++i)
       if (static_cast<int>(threadIdx.x) + i * kBlock < NQ * NQ * 64) wl[threadIdx.x + i * kBlock] = v[i];
@@ -87,10 +92,11 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
   constexpr int kTaUnroll = D <= 64 ? NQ : 1;
   extern __shared__ __align__(16) unsigned char smem[];
   f32x4* wl = reinterpret_cast<f32x4*>(smem);
-  const int k = g.wblk_k[WM_FWD][blockIdx.x];
-  if (k < 0) return;
   const int tid = threadIdx.x, lane = tid % 64, n = lane % 16, h = lane / 16;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int k = g.wblk_k[WM_FWD][blockIdx.x];
+  const WaveRun run = g.wave_runs[WM_FWD][blockIdx.x * kWavesPerBlock + wave];
+  if (k < 0) return;
   // A operands of Z^T = W^T AGG^T: wl[(ta NQ + q) 64 + lane][j] = W[16 q + 4 h + j][16 ta + n]
   const float* Wk = W + static_cast<size_t>(k) * w_stride;
   auto w_operand = [&](int ta, int q, int l) {
@@ -103,13 +109,12 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
     return v;
   };
   // the wavefront's first tile is on its way while W is
-  const WaveRun run = g.wave_runs[WM_FWD][blockIdx.x * kWavesPerBlock + wave];
   int r0, r1;
   run_rows(run, r0, r1);
   TileFacts<D> f, nf;
   const StreamInMemory stream{g.went, g.wrowid, g.wrowptr};
   f.request(stream, r0, r1);
-  fill_operands<D>(wl, w_operand);
+  fill_operands<D>(wl, w_operand, [&]() { f.request_entries(stream); });
   float* wo = reinterpret_cast<float*>(smem + fwd_tile_lds<D>()) - TK<D>::DP;  // w_out^k
   const bool last = w_out != nullptr;
   if (last && tid < TK<D>::DP) wo[tid] = tid < D ? w_out[static_cast<size_t>(k) * wout_stride + tid] : 0.f;
@@ -117,7 +122,6 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
   float* sums = reinterpret_cast<float*>(smem) + (TK<D>::W_IN_LDS ? TK<D>::DP * TK<D>::DP : 0) + wave * TK<D>::kWaveLds;
   if (r0 >= r1) return;
   const PlainRows<D> rows{X};
-  f.request_entries(stream);
   for (; r0 < r1; r0 += kTile) {
     const int row = r0 + n;
     nf.request(stream, r0 + kTile, r1);
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   fill_operands<D>(wl, [&](int ta, int q, int l) {
     const int o = 16 * ta + l % 16;
     return D >= 16 || o < D ? load4<D>(Wk, o, q, l / 16) : f32x4{0.f, 0.f, 0.f, 0.f};
-  });
+  }, [&]() { f.request_entries(stream); });
   __syncthreads();
   Rows rows;
   if constexpr (LAST) {
@@ -238,7 +242,6 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
 #pragma unroll
   for (int q = 0; q < (LAST ? NQ : 1); ++q) gwo[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  f.request_entries(stream);
   // what the epilogue needs of the row: Adam's E, m, v, or the row of Hprev for its mask
   const bool adam = TO_EMBED && a.mode == EMBED_ADAM;
   f32x4 s_e[NS], s_m[TO_EMBED ? NS : 1], s_v[TO_EMBED ? NS : 1];
