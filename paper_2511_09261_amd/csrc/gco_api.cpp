@@ -1991,8 +1991,8 @@ static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, cons
       launch_fill_u32(st, undecided, 1, 0u);
       for (int q = 0; q < 4; ++q) {
         int* last = q == 3 ? undecided : nullptr;
-        if (local) launch_repair_round_local(st, n, ctx->d_lrowptr, ctx->d_lcol, ctx->p, state, last);
-        else launch_repair_round_all(st, n, ctx->d_rowptr, ctx->d_col, p_orig, state, last);
+        if (local) launch_repair_round_local(st, n, ctx->nnz_loc, ctx->d_lrowptr, ctx->d_lcol, ctx->p, state, last);
+        else launch_repair_round_all(st, n, ctx->nnz_full, ctx->d_rowptr, ctx->d_col, p_orig, state, last);
       }
       int left = 0;
       HIPCHK(d2h(ctx, &left, undecided, 1));

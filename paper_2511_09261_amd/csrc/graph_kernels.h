@@ -57,9 +57,9 @@ void launch_cross_mark(hipStream_t st, int n, int64_t nnz, const int64_t* rowptr
 
 // Binarisation and one round of the parallel greedy repair (see the kernel).
 void launch_round(hipStream_t st, int n, const float* p, float thr, uint8_t* state);
-void launch_repair_round_local(hipStream_t st, int n, const int32_t* lrowptr, const int32_t* lcol,
+void launch_repair_round_local(hipStream_t st, int n, int64_t nnz, const int32_t* lrowptr, const int32_t* lcol,
                                const float* p, uint8_t* state, int* undecided);
-void launch_repair_round_all(hipStream_t st, int n, const int64_t* rowptr, const int32_t* col,
+void launch_repair_round_all(hipStream_t st, int n, int64_t nnz, const int64_t* rowptr, const int32_t* col,
                              const float* p, uint8_t* state, int* undecided);
 void launch_state_to_x(hipStream_t st, int n, const uint8_t* state, uint8_t* x);
 // counts[0] += selected nodes, counts[1] += edges with both ends selected,

@@ -497,27 +497,31 @@ __global__ __launch_bounds__(kBlock) void round_kernel(int n, const float* __res
   if (i < n) state[i] = p[i] >= thr ? 1 : 0;
 }
 
-// Eight lanes per undecided node; the whole workgroup, afterwards, for nodes with more than
-// kRepairOwn neighbours.  A node is removed once a kept neighbour
+// kLanes lanes per undecided node; the whole workgroup, afterwards, for nodes with more than
+// kRepairOwn kLanes neighbours.  A node is removed once a kept neighbour
 // of higher priority exists, kept once every selected neighbour of higher
 // priority has been removed.  Priority: p descending, then index ascending.
 // States only move 1 -> 0 or 1 -> 2 and every decision rests on final facts,
 // so the fixed point does not depend on the interleaving.
 // Bound by latency: column, then its state and probability.  With a wavefront per node and an
 // atomic count of the undecided, the first round over 1.1 M nodes took 416 us, now 56; the mean of
-// eight rounds 153 against 22.
-constexpr int kRepairOwn = 128;
+// eight rounds 153 against 22.  Eight lanes suit rows of a few neighbours; where most nodes have more
+// than their share of 128 and would fall to the workgroup, one after another, a node takes a wavefront
+// (repair over all edges, 4 k nodes of 200 neighbours: 448 -> 281 us, 3 k of 1000: 438 -> 308; but
+// 20 k of 100: 330 with eight lanes, 418 with a wavefront).
+constexpr int kRepairOwn = 16;
 
-template <typename PtrT>
+template <int kLanes, typename PtrT>
 __global__ __launch_bounds__(kBlock) void repair_round_kernel(int n, const PtrT* __restrict__ rowptr,
                                                               const int32_t* __restrict__ col,
                                                               const float* __restrict__ p,
                                                               volatile uint8_t* state,
                                                               int* __restrict__ undecided) {
-  __shared__ int longs[kBlock / 8];
+  constexpr int kAtOnce = kLanes == 64 ? 4 : 2;  // entries of a lane in flight
+  __shared__ int longs[kBlock / kLanes];
   __shared__ int num_longs;
-  const int tid = threadIdx.x, lane = tid % 64, sub = tid % 8;
-  const int i = blockIdx.x * (kBlock / 8) + tid / 8;
+  const int tid = threadIdx.x, lane = tid % 64, sub = tid % kLanes;
+  const int i = blockIdx.x * (kBlock / kLanes) + tid / kLanes;
   if (tid == 0) num_longs = 0;
   __syncthreads();
   const bool open = i < n && state[i] == 1;
@@ -548,10 +552,13 @@ __global__ __launch_bounds__(kBlock) void repair_round_kernel(int n, const PtrT*
       wait |= above && sj[u] != 2;
     }
   };
-  const bool own = e1 - e0 <= kRepairOwn;
+  const bool own = e1 - e0 <= kRepairOwn * kLanes;
   const PtrT end = own ? e1 : e0;
-  for (PtrT e = e0 + sub; __any(e < end); e += 16) look(e, end, 8, i, pi, std::integral_constant<int, 2>{});
-  const unsigned long long group = 0xffull << (lane - sub);
+  for (PtrT e = e0 + sub; __any(e < end); e += kAtOnce * kLanes) {
+    look(e, end, kLanes, i, pi, std::integral_constant<int, kAtOnce>{});
+    if (kLanes == 64 && __any(kill)) break;
+  }
+  const unsigned long long group = kLanes == 64 ? ~0ull : ((1ull << (kLanes % 64)) - 1ull) << (lane - sub);
   const bool any_kill = (__ballot(kill) & group) != 0, any_wait = (__ballot(wait) & group) != 0;
   bool left = false;
   if (open && sub == 0) {
@@ -729,14 +736,23 @@ void launch_round(hipStream_t st, int n, const float* p, float thr, uint8_t* sta
   round_kernel<<<blocks_for(n, kBlock), kBlock, 0, st>>>(n, p, thr, state);
 }
 
-void launch_repair_round_local(hipStream_t st, int n, const int32_t* lrowptr, const int32_t* lcol,
-                               const float* p, uint8_t* state, int* undecided) {
-  repair_round_kernel<int32_t><<<blocks_for(n, kBlock / 8), kBlock, 0, st>>>(n, lrowptr, lcol, p, state, undecided);
+template <typename PtrT>
+static void repair_round(hipStream_t st, int n, int64_t nnz, const PtrT* rowptr, const int32_t* col, const float* p,
+                         uint8_t* state, int* undecided) {
+  if (nnz < 8 * kRepairOwn * static_cast<int64_t>(n))
+    repair_round_kernel<8><<<blocks_for(n, kBlock / 8), kBlock, 0, st>>>(n, rowptr, col, p, state, undecided);
+  else
+    repair_round_kernel<64><<<blocks_for(n, kBlock / 64), kBlock, 0, st>>>(n, rowptr, col, p, state, undecided);
 }
 
-void launch_repair_round_all(hipStream_t st, int n, const int64_t* rowptr, const int32_t* col,
+void launch_repair_round_local(hipStream_t st, int n, int64_t nnz, const int32_t* lrowptr, const int32_t* lcol,
+                               const float* p, uint8_t* state, int* undecided) {
+  repair_round(st, n, nnz, lrowptr, lcol, p, state, undecided);
+}
+
+void launch_repair_round_all(hipStream_t st, int n, int64_t nnz, const int64_t* rowptr, const int32_t* col,
                              const float* p, uint8_t* state, int* undecided) {
-  repair_round_kernel<int64_t><<<blocks_for(n, kBlock / 8), kBlock, 0, st>>>(n, rowptr, col, p, state, undecided);
+  repair_round(st, n, nnz, rowptr, col, p, state, undecided);
 }
 
 void launch_state_to_x(hipStream_t st, int n, const uint8_t* state, uint8_t* x) {

@@ -16,10 +16,15 @@ def circulant(n, half):
     return inputs.from_edges(n, u, (u + np.tile(np.arange(1, half + 1), n)) % n)
 
 
-def spokes(n, degrees, rs):
-    """Node 7 (i + 1) has degrees[i] neighbours among the last nodes."""
+def spokes(n, degrees, rs, core=None):
+    """Node 7 (i + 1) has degrees[i] neighbours among the last nodes; the last nodes of all are joined as
+    the upper triangle `core` says."""
     us = [np.full(d, 7 * (i + 1)) for i, d in enumerate(degrees)]
     vs = [n - 1 - rs.permutation(n - 7 * (len(degrees) + 2))[:d] for d in degrees]
+    if core is not None:
+        u, v = np.nonzero(core)
+        us.append(n - 1 - u)
+        vs.append(n - 1 - v)
     return inputs.from_edges(n, np.concatenate(us), np.concatenate(vs))
 
 
@@ -36,6 +41,10 @@ def graph(kind):
         return spokes(900, [1, 7, 8, 9, 15, 16, 17, 127, 128, 129, 255, 256, 257, 600], rs)
     if kind == "hubs":                    # rows longer than a chunk and than two
         return spokes(9000, [2048, 2049, 4500, 7000], rs)
+    if kind == "dense":                   # more than 128 neighbours on average: a wavefront per node
+        return spokes(1500, [1, 255, 256, 257, 1024, 1025], rs, np.triu(rs.random_sample((700, 700)) < 0.9, 1))
+    if kind == "dense_hubs":              # and rows beyond a wavefront's 1024
+        return spokes(3000, [1023, 1024, 1025, 2500], rs, np.triu(rs.random_sample((1000, 1000)) < 0.5, 1))
     if kind == "gap":                     # 30 000 rows without entries between two that have some
         u = np.concatenate([rs.randint(0, 400, 1500), 30400 + rs.randint(0, 400, 1500)])
         v = np.concatenate([rs.randint(0, 400, 1500), 30400 + rs.randint(0, 400, 1500)])
@@ -44,8 +53,8 @@ def graph(kind):
     return inputs.from_edges(300, np.array([0]), np.array([299]))  # two entries, at both ends
 
 
-@pytest.mark.parametrize("kind", ["whole_chunks", "rows_over_edges", "one_entry_more", "row_lengths", "hubs", "gap",
-                                  "two_entries"])
+@pytest.mark.parametrize("kind", ["whole_chunks", "rows_over_edges", "one_entry_more", "row_lengths", "hubs", "dense",
+                                  "dense_hubs", "gap", "two_entries"])
 def test_read_out_edges(gco, kind):
     g = graph(kind)
     rs = np.random.RandomState(6)
