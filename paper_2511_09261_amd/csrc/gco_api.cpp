@@ -619,17 +619,14 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
       if (active != nullptr && !active[k]) k = -1;
   }
   put_lists(&m.loss_ptr, &m.loss_list, slot_k, P);
-  if (block.size() > m.capacity) {
-    HIPCHK(hipStreamSynchronize(ctx->st));  // launches that read the old block
-    if (m.block != nullptr) {
-      ctx->graph_allocs.erase(std::find(ctx->graph_allocs.begin(), ctx->graph_allocs.end(), static_cast<void*>(m.block)));
-      ctx->raw_free(m.block);
-      m.block = nullptr;
-      m.capacity = 0;
-    }
-    GALLOC(m.block, block.size());
-    m.capacity = block.size();
+  // A subset's arrays are never longer than those of all subgraphs (its launches have no more
+  // workgroups: the sum of the shares is the target held between the sums of the bounds, and both sums are
+  // over fewer subgraphs), so one block serves every later list: no allocation, no wait.
+  if (m.block == nullptr) {
+    m.capacity = std::max(block.size(), ctx->full.capacity);
+    GALLOC(m.block, m.capacity);
   }
+  NEED(block.size() <= m.capacity, GCO_ERANGE, "tables of the subgraphs listed exceed those of all");
   for (const auto& at : places) *at.first = m.block + at.second;
   HIPCHK(h2d(ctx, m.block, block.data(), block.size()));
   return GCO_OK;

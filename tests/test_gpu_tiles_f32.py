@@ -126,3 +126,36 @@ def test_a_listed_subset_has_runs_of_its_own(gco, storage, D):
         c.destroy()
     a.destroy()
     b.destroy()
+
+
+@pytest.mark.parametrize("storage,D,sizes", [("fp32", 16, [40] * 300), ("bf16", 64, [33, 400, 0, 2000, 7] * 12),
+                                             ("fp32", 32, [30_000] * 9)])
+def test_a_longer_list_allocates_nothing(gco, storage, D, sizes):
+    """The tables of a subset of the subgraphs lie in one block for every list after the first."""
+    rs = np.random.RandomState(1)
+    n, P = sum(sizes), len(sizes)
+    part = np.repeat(np.arange(P), sizes).astype(np.int32)
+    u = rs.randint(0, n, 3 * n)
+    g = inputs.from_edges(n, u, np.clip(u + rs.randint(-20, 21, 3 * n), 0, n - 1))
+    E, Ws = inputs.init_params(n, part, P, 3, D, 3)
+    ctx = gco.Context(num_layers=3, dim=D, storage=storage)
+    ctx.set_scalar_layer_form("streams")
+    ctx.upload_graph(n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    ctx.train_subset(2, [0])
+    asked = []
+    empty = ctx._allocator.torch.empty
+
+    class Counting:
+        uint8 = ctx._allocator.torch.uint8
+
+        @staticmethod
+        def empty(*args, **more):
+            asked.append(args)
+            return empty(*args, **more)
+
+    ctx._allocator.torch = Counting
+    for listed in ([1, 2], [P - 1], list(range(0, P, 2)), list(range(P)), list(range(P - 1)), [3]):
+        ctx.train_subset(2, listed)
+    assert not asked
+    ctx.destroy()
