@@ -572,12 +572,15 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
   // all arrays one after another in one block, each from a 16-byte boundary
   std::vector<int32_t> block;
   std::vector<std::pair<const int32_t**, size_t>> places;
-  auto put = [&](const int32_t** dst, const int32_t* v, size_t count) {
+  auto append = [&](const int32_t* v, size_t count) {  // returns the array's place in the block
     block.resize((block.size() + 3) / 4 * 4);
-    places.push_back({dst, block.size()});
+    const size_t at = block.size();
     block.insert(block.end(), v, v + count);
     if (count == 0) block.push_back(0);
+    return at;
   };
+  auto put = [&](const int32_t** dst, const int32_t* v, size_t count) { places.push_back({dst, append(v, count)}); };
+  size_t runs_at[kWaveMaps] = {};
   auto put_lists = [&](const int32_t** ptr, const int32_t** list, const std::vector<int>& ks, int sets) {
     std::vector<int> pv, lv;
     bucket_blocks(ks, sets, pv, lv);
@@ -597,8 +600,9 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
     m.num_wblocks[v] = static_cast<int>(wk.size());
     put(&m.wblk_k[v], wk.data(), wk.size());
     static_assert(sizeof(WaveRun) % 16 == 0 && alignof(WaveRun) == 16, "runs lie at 16-byte boundaries of the block");
-    put(reinterpret_cast<const int32_t**>(&m.wave_runs[v]), reinterpret_cast<const int32_t*>(runs.data()),
-        runs.size() * (sizeof(WaveRun) / sizeof(int32_t)));
+    std::vector<int32_t> words(runs.size() * (sizeof(WaveRun) / sizeof(int32_t)));
+    if (!runs.empty()) std::memcpy(words.data(), runs.data(), runs.size() * sizeof(WaveRun));
+    runs_at[v] = append(words.data(), words.size());
     put_lists(&m.wpbl_ptr[v], &m.wpbl_list[v], wk, Pw);
     if (v == WM_NARROW) narrow = wk;
   }
@@ -628,6 +632,7 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
   }
   NEED(block.size() <= m.capacity, GCO_ERANGE, "tables of the subgraphs listed exceed those of all");
   for (const auto& at : places) *at.first = m.block + at.second;
+  for (int v = 0; v < kWaveMaps; ++v) m.wave_runs[v] = reinterpret_cast<const WaveRun*>(m.block + runs_at[v]);
   HIPCHK(h2d(ctx, m.block, block.data(), block.size()));
   return GCO_OK;
 }
