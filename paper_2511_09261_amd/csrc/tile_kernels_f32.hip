@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   const int tid = threadIdx.x, lane = tid % 64, n = lane % 16, h = lane / 16;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   float* gt = gt_all + wave * T::kWaveLds;  // row sums and carries, then the G_T tile
-  const float* __restrict__ Hprev = static_cast<const float*>(a.Hprev);
+  const float* Hprev = static_cast<const float*>(a.Hprev);  // of the first layer: E itself, which the epilogue writes
   const float* __restrict__ Wk = a.W + static_cast<size_t>(k) * a.w_stride;
   // Rows of this wavefront, kStep apart; with shared accumulators the workgroup's wavefronts
   // take turns and all of them go through the same number of tiles.
