@@ -964,7 +964,8 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   const Grouping grouping = grouping_of(ctx->cfg.storage, D, n, WM_NARROW);
   std::vector<double> entries(P);
   for (int k = 0; k < P; ++k) entries[k] = lrowptr[part_rows[k + 1]] - lrowptr[part_rows[k]];
-  build_block_map(P, part_rows, entries, kTileRows, kWideBlocks, kMaxTilesPerBlock, blk_k, blk_s, blk_S, grouping);
+  if (L == 1)  // the backward launch of the one-layer model
+    build_block_map(P, part_rows, entries, kTileRows, kWideBlocks, kMaxTilesPerBlock, blk_k, blk_s, blk_S, grouping);
   // width-1 kernels: one 256-row tile per workgroup
   build_block_map(P, part_rows, entries, kNarrowRows, std::numeric_limits<int>::max() / 2, 1, nblk_k, nblk_s, nblk_S,
                   grouping);
@@ -1280,7 +1281,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     GALLOC(q, nd * eb);
     ctx->H[l] = q;
     GALLOC(ctx->gW_partial[l - 1],
-           static_cast<size_t>(std::max({g.num_blocks, g.num_wblocks[WM_BWD], g.num_wblocks[WM_EMBED], g.num_wblocks[WM_GRADW]})) * D * D);
+           static_cast<size_t>(std::max({g.num_wblocks[WM_BWD], g.num_wblocks[WM_EMBED], g.num_wblocks[WM_GRADW]})) * D * D);
   }
   // G_Z between two hidden layers; the wave-per-tile kernels also store that of the last one
   for (int l = 1; l <= (ctx->wave_path() ? L - 1 : L - 2); ++l) {

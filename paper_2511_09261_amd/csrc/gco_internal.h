@@ -96,7 +96,7 @@ struct GraphView {
   const int2* ent_t = nullptr;    // [nnz]
   const float* diag = nullptr;    // [n]
   const int* part_rows = nullptr; // [P+1] first row of each subgraph
-  // wide kernels: workgroup b works on tiles blk_s[b], + blk_S[b], + 2 blk_S[b], ...
+  // backward of the one-layer model (nullptr with hidden layers): workgroup b works on tiles blk_s[b], + blk_S[b], + 2 blk_S[b], ...
   // of subgraph blk_k[b] (blk_k[b] < 0: nothing to do)
   const int* blk_k = nullptr;
   const int* blk_s = nullptr;
@@ -307,11 +307,11 @@ struct BwdArgs {
   const float* g_t = nullptr;    // [n] (last)
   const float* w_out = nullptr;  // [Pw, D] (last)
   int wout_stride = 0;
-  float* gwout_partial = nullptr;  // [num_blocks, D] (last)
+  float* gwout_partial = nullptr;  // [workgroups of the launch that forms it, D] (last)
   const void* Hprev = nullptr;   // [n, D] storage type
   const float* W = nullptr;      // [Pw, D, D]
   int w_stride = 0;
-  float* gW_partial = nullptr;   // [num_blocks, D*D]
+  float* gW_partial = nullptr;   // [workgroups of the launch that forms it, D*D]
   void* GZ_out = nullptr;        // [n, D] storage type (not to_embed)
   void* GT = nullptr;            // [n, D] bf16: rows of G_T = A_hat^T G_Z (wave-per-tile path, width 128)
   // to_embed

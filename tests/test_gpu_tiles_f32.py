@@ -159,3 +159,16 @@ def test_a_longer_list_allocates_nothing(gco, storage, D, sizes):
         ctx.train_subset(2, listed)
     assert not asked
     ctx.destroy()
+
+
+def test_partial_sums_take_the_memory_of_the_workgroups_there_are(gco):
+    """Width 128: 512 backward workgroups, 32 MB of partial weight gradients per hidden layer."""
+    n, D, L = 140_000, 128, 3
+    u = np.arange(n - 1)
+    g = inputs.from_edges(n, u, u + 1)
+    ctx = gco.Context(num_layers=L, dim=D)
+    ctx.upload_graph(n, g.rowptr, g.col)
+    total = sum(t.numel() for t in ctx._allocator.live.values())
+    rows = (3 + (L - 1) + (L - 2)) * n * D * 4       # E, m, v, the hidden layers, the gradient between two
+    assert total <= rows + (L - 1) * 512 * D * D * 4 + 200 * n
+    ctx.destroy()
