@@ -329,8 +329,12 @@ __device__ __forceinline__ void keep_weights(const SmallTrain& a, int k) {
   }
 }
 
-// GRADS: passes = 4, compiled by itself so that training does not carry it.
-template <typename T, int D, int L, bool GRADS>
+// What a launch is for; each is compiled by itself.  Training does not carry the gradients' stores, and
+// forward and loss not the registers of the backward pass (which spill, so that a launch of its own started
+// later: 512 subgraphs of 60 rows of width 16, forward 17.6 -> 11.2 us).
+enum class Purpose { kForward, kTrain, kGradients };  // passes 1 and 2; 3; 4
+
+template <typename T, int D, int L, Purpose FOR>
 __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, SmallTrain a) {
   using K = SK<D>;
   constexpr int NQ = K::NQ, DP = K::DP, NW = K::NW, NT = K::NT, WP = K::WP;
@@ -340,7 +344,7 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   const int rbeg = g.part_rows[k], R = g.part_rows[k + 1] - rbeg;
   if (R == 0) {  // no rows: a loss of nothing
     if (a.passes == 1) return;
-    if constexpr (GRADS) {
+    if constexpr (FOR == Purpose::kGradients) {
 #pragma unroll
       for (int l = 0; l < L; ++l) {
         const int elems = l < L - 1 ? D * D : D;
@@ -363,7 +367,7 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   const bool mean = g.wval != g.wval_t;
   const int es = g.wrowptr[rbeg], En = g.wrowptr[rbeg + R] - es;
   const Carve<D> cv(L, R, En, mean);
-  const int tid = threadIdx.x, lane = tid % 64, n = lane % 16, h = lane / 16;
+  const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   int* rp = reinterpret_cast<int*>(smem + cv.rp);
   uint2* ent = reinterpret_cast<uint2*>(smem + cv.ent);
@@ -471,7 +475,7 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
                 pv[row] = p;
                 if (keep_p) a.p[rbeg + row] = p;
               });
-    if (a.passes == 1) return;
+    if (FOR == Purpose::kForward && a.passes == 1) return;
     __syncthreads();
     double lsum = 0.0;
     scan_rows(fwd, e0, e1, [&](const Entry& en) { return en.col == en.row ? 0.f : pv[en.col]; },
@@ -496,7 +500,9 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
         a.has_best[k] = 1;
       }
     }
-    if (a.passes == 2) return;
+    if constexpr (FOR == Purpose::kForward) {
+      return;
+    } else {
     scan_rows(bwd, e0, e1, [&](const Entry& en) { return en.val * tv[en.col]; },
               [&](int row, float s) { pv[row] = s; });
     __syncthreads();
@@ -507,11 +513,13 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
       keep_weights<D, L>(a, k);
       __syncthreads();
     }
+    constexpr bool kGrads = FOR == Purpose::kGradients;
     if constexpr (L == 2) {
-      backward_layer<T, D, L, GRADS, true, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
+      backward_layer<T, D, L, kGrads, true, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
     } else {
-      backward_layer<T, D, L, GRADS, true, false>(a, bwd, g, smem, cv, k, R, first, adE, adW);
-      backward_layer<T, D, L, GRADS, false, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
+      backward_layer<T, D, L, kGrads, true, false>(a, bwd, g, smem, cv, k, R, first, adE, adW);
+      backward_layer<T, D, L, kGrads, false, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
+    }
     }
   }
 }
@@ -523,8 +531,9 @@ void launch_t(const Launch& ln, const GraphView& g, const SmallTrain& a, size_t 
                               static_cast<int>(lds));
     kernel<<<g.P, SK<D>::NT, lds, ln.st>>>(g, a);
   };
-  if (a.passes == 4) run(small_train_kernel<T, D, L, true>);
-  else run(small_train_kernel<T, D, L, false>);
+  if (a.passes <= 2) run(small_train_kernel<T, D, L, Purpose::kForward>);
+  else if (a.passes == 3) run(small_train_kernel<T, D, L, Purpose::kTrain>);
+  else run(small_train_kernel<T, D, L, Purpose::kGradients>);
 }
 
 template <typename T, int D>
