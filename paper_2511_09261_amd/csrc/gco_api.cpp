@@ -1648,9 +1648,12 @@ static void run_backward(gco_ctx* ctx, const GraphView& gv, const gco_ctx::Activ
     wt[l - 1].blk_ptr = L == 1 ? maps.pbl_ptr : (narrow ? maps.nwbl_ptr : maps.wpbl_ptr[wm]);
     wt[l - 1].blk_list = L == 1 ? maps.pbl_list : (narrow ? maps.nwbl_list : maps.wpbl_list[wm]);
   }
-  const int writers = L == 1 ? gv.num_blocks
-                             : std::max({gv.num_wblocks[WM_BWD], gv.num_wblocks[WM_EMBED],
-                                         ctx->wave_path() ? gv.num_nblocks : 0});
+  // of the run over all subgraphs: a subset with a few hundred partials per weight set is no
+  // case for one thread per weight either (400 partials: 18 us, split 7.5; 103: 10.8, 8.4)
+  const GraphView& all = ctx->gv;
+  const int writers = L == 1 ? all.num_blocks
+                             : std::max({all.num_wblocks[WM_BWD], all.num_wblocks[WM_EMBED],
+                                         ctx->wave_path() ? all.num_nblocks : 0});
   const bool many_partials = writers / ctx->Pw >= 512;
   // the last launch of an epoch also pre-reduces the long rows of the new embeddings
   ChunkTail tail;
