@@ -217,6 +217,10 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
     return D >= 16 || o < D ? load4<D>(Wk, o, q, l / 16) : f32x4{0.f, 0.f, 0.f, 0.f};
   }, [&]() { f.request_entries(stream); });
   __syncthreads();
+  // tiny subgraphs: all rows are the first wavefront's, and its sums are the workgroup's (8000 subgraphs of 3
+  // rows of width 8: 32.7 -> 24.6 us, embeddings 29.4 -> 24.0)
+  const bool alone = !T::SHARED_GW && runs[0].tile1 == runs[kWavesPerBlock - 1].tile1;
+  if (alone && wave > 0) return;
   Rows rows;
   if constexpr (LAST) {
     rows.H = static_cast<const float*>(a.Hcur);
@@ -389,6 +393,14 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
         for (int r = 0; r < 4; ++r)
           out[(16 * ta + 4 * h + r) * D + 16 * (wave * TB + tb) + n] = gw[ta][tb][r];
     __syncthreads();
+  } else if (alone) {
+#pragma unroll
+    for (int ta = 0; ta < NQ; ++ta)
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (D >= 16 || (4 * h + r < D && n < D)) out[(16 * ta + 4 * h + r) * D + 16 * tb + n] = gw[ta][tb][r];
   } else {
     // (wave 0 + wave 2) + (wave 1 + wave 3)
     float* buf = gt_all;
@@ -413,10 +425,12 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
       out[idx] = buf[p] + buf[DP * DP + p];
     }
   }
+  if (LAST && alone) wave_lds_handoff();
   if (LAST && tid < D) {
     float s = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) s += last[w * DP + tid];
+    for (int w = 0; w < kWavesPerBlock; ++w)
+      if (w == 0 || !alone) s += last[w * DP + tid];
     a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + tid] = s;
   }
 }
