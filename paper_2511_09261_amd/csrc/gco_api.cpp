@@ -523,22 +523,40 @@ void wave_map_of(int storage, int dim, int v, int P, const std::vector<int>& par
 }
 
 // Whether training runs faster with a workgroup per subgraph for whole epochs (small_train.hip)
-// than with four to eight launches per epoch over the whole chip; microseconds per epoch, from a
-// sweep over 1 .. 512 subgraphs of 60 .. 2500 rows with 3 .. 8 neighbours.  One compute unit is
-// bound by its instructions: a round of tiles (one per wavefront) takes a fixed time and one per
-// entry.  Measured, one / launches (us): 200 rows of width 16: 9.4 / 26 (1 subgraph), 22 / 55 (512);
-// 1250 rows: 37 / 44 and 94 / 184; width 32, 200 rows: 19 / 30, 1250 rows: 83 / 48 (1), 102 / 164
-// (256); width 64, 200 rows: 41 / 36 (1), 48 / 82 (256); bf16, 200 rows: 50 / 37, 59 / 71.
+// than with four to eight launches per epoch over the whole chip; microseconds per epoch, fitted to
+// 504 measured pairs (1 .. 1500 subgraphs of 12 .. 2500 rows with 3 and 8 neighbours, two and three
+// layers).  One compute unit is bound by its instructions: a round of tiles (one per wavefront) takes a
+// fixed time and one per entry, the width-1 passes a time per entry; beyond 256 subgraphs compute units
+// take them in turn, narrow ones two at once.  Both estimates are within 0.67 .. 1.38 of what was measured; the
+// choice was more than 5 % off the faster way in 14 of the pairs, by 31 % at most.  A forward pass alone gains
+// less than an epoch, and beyond 256 subgraphs it loses (512 x 200 rows of width 64, bf16: 42 us against
+// 24), so there the epoch has to gain more.
+// Measured, one launch / several (us): width 16, two layers: 200 rows with 8 neighbours 13 / 28, 64 x 600
+// rows with 4 24 / 41; width 32: 8 x 60 rows with 8 15 / 34, 8 x 500 rows with 3 35 / 37; width 64: 200 x 60
+// rows 25 / 50, three layers of 64 x 200 rows 72 / 65; bf16: 60 rows 22 / 36, 512 x 500 rows 397 / 304.
 bool small_train_pays(const gco_config& c, int P, int n, int64_t entries, int max_rows, int64_t max_entries) {
-  const bool bf16 = c.storage == GCO_STORAGE_BF16;
-  const double e = static_cast<double>(entries) / n;  // entries per row, the diagonal included
-  const double round = c.dim <= 16 ? 2.1 + 1.07 * e : c.dim == 32 ? 8.2 + 1.7 * e : (bf16 ? 17.0 : 11.0) + 1.4 * e;
-  const int tiles = (max_rows + kTileRowsF32 - 1) / kTileRowsF32, waves = c.dim <= 32 ? 16 : 8;
-  const double one = ((P + 255) / 256) * (8.0 + (c.num_layers - 1) * ((tiles + waves - 1) / waves) * round);
-  const double row_ns = c.dim <= 16 ? 0.1 + 0.04 * e : (bf16 ? 0.0095 : 0.0125) * c.dim;
-  const double launches = (c.num_layers == 2 ? 26.0 : 38.0) + 1.5e-3 * static_cast<double>(max_entries) +
-                          (c.num_layers - 1) * row_ns * 1e-3 * n;
-  return one < 0.9 * launches;
+  struct Cost {
+    double start, layer, round, entry, narrow;                    // one launch
+    double launches, more, narrow_pass, per_row, per_entry, adam;  // several
+  };
+  static constexpr Cost kCost[] = {
+      {3.9, 0.8, 3.2, 0.20, 3.65, 15.1, 10.8, 2.3, 0.097, 0.013, 22.5},  // width 8, 16
+      {2.8, 2.0, 7.2, 0.10, 8.2, 14.9, 12.7, 2.9, 0.206, 0.020, 11.7},   // 32
+      {4.6, 0.0, 12.4, 0.47, 7.1, 14.2, 18.0, 4.6, 0.509, 0.031, 9.6},   // 64
+      {2.5, 0.0, 15.6, 0.65, 11.6, 16.5, 16.6, 6.8, 0.330, 0.024, 8.5},  // 64, bf16
+  };
+  const Cost& k = kCost[c.storage == GCO_STORAGE_BF16 ? 3 : (c.dim <= 16 ? 0 : (c.dim == 32 ? 1 : 2))];
+  const int hidden = c.num_layers - 1, waves = c.dim <= 32 ? 16 : 8;
+  const int rounds = ((max_rows + kTileRowsF32 - 1) / kTileRowsF32 + waves - 1) / waves;
+  const double per_row = static_cast<double>(entries) / n;  // entries of a row, the diagonal included
+  const double thousands = 1e-3 * static_cast<double>(max_entries);
+  const double turns = P <= 256 ? 1.0 : P / 256.0 * (c.dim <= 32 ? 0.85 : 1.0);
+  const double one =
+      turns * (k.start + hidden * (k.layer + rounds * (k.round + k.entry * per_row)) + k.narrow * thousands);
+  const double several = k.launches + k.narrow_pass * thousands * ((P + 255) / 256) +
+                         hidden * (k.more + 1e-3 * (k.per_row * n + k.per_entry * static_cast<double>(entries)) +
+                                   k.adam * 1e-6 * P * c.dim * c.dim);
+  return one < (P <= 256 ? 0.92 : 0.8) * several;
 }
 
 // Workgroup ids grouped by the subgraph they work on (ascending within a group);
