@@ -32,8 +32,8 @@ pytestmark = pytest.mark.gpu
 
 
 def graph_with_long_rows(n, seed, hubs=(2500, 700, 90), base_deg=4):
-    """Sparse random graph plus a few hub nodes whose degrees span the three
-    row classes of the gather (short, workgroup-wide, pre-reduced)."""
+    """Sparse random graph plus a few hub nodes whose degrees span the
+    row classes of the gather (short, long, pre-reduced)."""
     rs = np.random.RandomState(seed)
     m = n * base_deg // 2
     u = rs.randint(0, n, m)
@@ -319,7 +319,7 @@ def test_frozen_embeddings_and_shared_weights_train(gco):
 # ------------------------------------------------------------------ subset fine-tune
 
 @pytest.mark.parametrize("kind,L,D,storage,share,lr", [
-    ("bfs12", 2, 16, "fp32", False, 1e-2),     # block kernels
+    ("bfs12", 2, 16, "fp32", False, 1e-2),     # whole epochs in one launch
     ("bfs12", 3, 64, "bf16", False, 1e-2),     # wave-per-tile kernels
     ("hubs_parts", 3, 64, "bf16", False, 1e-2),  # with pre-reduced rows in a subgraph that sits out
     # wave-per-tile kernels with the separate weight-gradient kernel (at 1e-2 this model
@@ -394,7 +394,7 @@ def test_subset_errors_and_empty_list(gco):
 # ------------------------------------------------------------------ best-by-loss snapshot
 
 @pytest.mark.parametrize("kind,L,D,storage,share,lr", [
-    ("bfs12", 2, 16, "fp32", False, 0.05),       # block kernels; best epochs differ per subgraph
+    ("bfs12", 2, 16, "fp32", False, 0.05),       # whole epochs in one launch; best epochs differ per subgraph
     ("bfs12", 3, 64, "bf16", False, 0.02),       # wave-per-tile kernels
     ("hubs_parts", 3, 64, "bf16", False, 0.02),  # long rows
     ("bfs12", 3, 128, "bf16", False, 0.02),      # width 128

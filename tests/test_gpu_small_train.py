@@ -33,19 +33,24 @@ def used(ctx):
     return ctx.get_timing()["small_train"]["launches"]
 
 
-@pytest.mark.parametrize("D,L,norm,storage", [(8, 2, "sym", "fp32"), (16, 3, "mean", "fp32"), (32, 2, "mean", "fp32"),
-                                              (32, 3, "sym", "fp32"), (64, 2, "sym", "fp32"), (64, 3, "mean", "fp32"),
-                                              (64, 2, "mean", "bf16"), (64, 3, "sym", "bf16")])
-def test_whole_epochs_of_small_subgraphs(gco, D, L, norm, storage):
+@pytest.mark.parametrize("D,L,norm,storage,problem,train_embed", [
+    (8, 2, "sym", "fp32", "mis", True), (16, 3, "mean", "fp32", "mis", True), (32, 2, "mean", "fp32", "mis", True),
+    (32, 3, "sym", "fp32", "mis", True), (64, 2, "sym", "fp32", "mis", True), (64, 3, "mean", "fp32", "mis", True),
+    (64, 2, "mean", "bf16", "mis", True), (64, 3, "sym", "bf16", "mis", True),
+    (8, 3, "sym", "fp32", "maxcut", True), (16, 2, "sym", "fp32", "maxcut", True), (32, 2, "mean", "fp32", "maxcut", True),
+    (64, 2, "sym", "bf16", "maxcut", True),
+    (16, 2, "mean", "fp32", "mis", False), (32, 3, "sym", "fp32", "maxcut", False), (64, 2, "mean", "bf16", "mis", False)])
+def test_whole_epochs_of_small_subgraphs(gco, D, L, norm, storage, problem, train_embed):
     # one row, tile edges, and one to two rounds of tiles; enough subgraphs that this is the chosen way
     sizes = [1, 0, 15, 16, 17, 33, 63, 64] + [64] * 240 if D >= 32 else [1, 0, 15, 16, 17, 33, 255, 256, 257] + [60] * 60
     g, part, P = ragged(sizes, D + L, 1 if D == 64 else 2)
     E, Ws = inputs.init_params(g.n, part, P, L, D, 5)
     E = (E * 3).astype(np.float32)
-    ctx = gco.Context(num_layers=L, dim=D, norm=norm, storage=storage, lr=1e-2)
+    ctx = gco.Context(problem=problem, num_layers=L, dim=D, norm=norm, storage=storage, train_embed=train_embed, lr=1e-2)
     ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
     ctx.set_params(E, Ws)
-    spec = gcn.Spec(num_layers=L, norm=norm, lr=1e-2, storage="bf16" if storage == "bf16" else "exact")
+    spec = gcn.Spec(problem=problem, num_layers=L, norm=norm, train_embed=train_embed, lr=1e-2,
+                    storage="bf16" if storage == "bf16" else "exact")
     lg = gcn.local_graph(g.n, g.rowptr, g.col, part, P, norm)
     tol = 1e-4 if storage == "fp32" else 2e-2
     extra = (np.arange(g.n) % 7 == 0).astype(np.float32) * 0.5
@@ -65,7 +70,7 @@ def test_whole_epochs_of_small_subgraphs(gco, D, L, norm, storage):
     # that kind, moved by lr per epoch on values of about 0.15, the 2-norms are within
     # sqrt(1e-4) * 0.1 / 0.15 < 1e-2 (fp32) and sqrt(1/30) * 0.1 / 0.15 < 0.13 (bf16).
     bound = 1e-2 if storage == "fp32" else 0.13
-    assert rel_l2(dE, st.E) <= bound
+    assert rel_l2(dE, st.E) <= bound and (train_embed or np.array_equal(dE, E))
     for l in range(L):
         assert rel_l2(dW[l], st.Ws[l]) <= bound
     # a subset with step counts of its own, the others bit for bit as they were
