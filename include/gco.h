@@ -182,6 +182,8 @@ int gco_train(gco_ctx* ctx, int32_t epochs, double* loss_per_epoch);
  * gradients of the listed subgraphs only.  loss_per_epoch[e] is the sum of the listed
  * subgraphs' losses.  Every subgraph (and weight set) counts its own Adam steps, so the
  * bias correction of a subgraph depends only on how often that subgraph was trained.
+ * The order in which a listed subgraph's sums are taken, and with it their last bits, follows
+ * the list: the work is cut for the subgraphs listed.  The same list gives the same bits.
  * ERANGE for an id outside [0, num_parts). */
 int gco_train_subset(gco_ctx* ctx, int32_t epochs, const int32_t* parts, int32_t num_listed,
                      double* loss_per_epoch);

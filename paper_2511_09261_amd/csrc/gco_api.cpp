@@ -727,6 +727,7 @@ void traffic_model(gco_ctx* ctx) {
   kb[KK_LOSS_REDUCE] = ctx->P * 8.0;
   kb[KK_HEAVY] = 0;  // reported by time only
   kb[KK_BEST] = 0;   // depends on how many models improved
+  kb[KK_SMALL_TRAIN] = 0;  // one to 64 epochs a launch: reported by time only
   if (!split) kb[KK_GRAD_W] = 0;
 }
 

@@ -31,9 +31,14 @@ constexpr int kWaveBlocksFor[kWaveMaps] = {768, 512, 3072, 2048, 256};
 // embedding backward twelve
 constexpr int kWaveBlocksFor128[kWaveMaps] = {1024, 1024, 6144, 2048, 256};
 // fp32 storage: rows of a tile; workgroups aimed at, in rounds of those resident at once.  Up to
-// width 32 two rounds (700 k rows of width 16, forward / embedding backward: 45 / 91 us against
-// 47 / 99 with one), from width 64 on, where W and the first tile cost more per workgroup, one
-// (150 k rows of width 64: 78 / 125 us against 80 / 131 with two); and the cost of a row.
+// width 32 two rounds, from width 64 on, where W and the first tile cost more per workgroup, one.
+// Forward / hidden / embedding backward in us, three layers (the figure taken first):
+//   width 16, 700 k rows:  37.5 / 64.9 / 87.2, one round 42.6 / 73.9 / 97.5
+//   width 32, 300 k rows:  37.2 / 62.4 / 84.9, one round 36.1 / 67.8 / 92.7
+//   width 64, 150 k rows:  70.3 / 94.1 / 117.7, two rounds 62.8 / 98.6 / 118.6 (forward of 60 k rows 35.7, 37.8)
+//   width 128, 100 k rows: 122.8 / 207 / 241, two rounds 119.7 / 224 / 250
+// The cost of a row beside an entry of the stream hardly matters: a quarter to four times these move the
+// launches by 3 % (width 16, forward at 1: 39.7).
 constexpr int kTileRowsF32 = 16;
 inline int wave_blocks_f32(int dim, int map) {
   if (map == WM_FWD) return dim <= 16 ? 2 * 1536 : (dim == 32 ? 2 * 1024 : (dim == 64 ? 768 : 512));
