@@ -94,21 +94,59 @@ __device__ __forceinline__ void wave_lds_handoff() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One Adam step on one embedding value or one weight (constants of AdamStep), with the correctly
+// Square root of x in [2^-100, 2^100] and quotient for a denominator in [2^-30, 2^60], correctly rounded, in
+// 6 and 8 instructions (of which one each at a quarter of the rate) where sqrtf() and the division take 17
+// and 11 for the ranges beyond.
+// sqrt: s = x rsq(x), within two ulps, corrected by its exact residual; equal to sqrtf() for every mantissa
+// of both parities of the exponent, all of which were tried.  Quotient: the reciprocal after one Newton step,
+// then two corrections by the exact residual: the first leaves the quotient within an ulp, after which the
+// second rounds correctly (Markstein, "Computation of elementary functions on the IBM RISC System/6000
+// processor", 1990); tiny quotients (below 2^-70), whose residual is no longer exact, may be an ulp off.
+__device__ __forceinline__ float sqrt_in_range(float x) {
+  const float y = __builtin_amdgcn_rsqf(x), s = x * y, h = 0.5f * y;
+  return fmaf(fmaf(-s, s, x), h, s);
+}
+__device__ __forceinline__ float quotient_in_range(float n, float d) {
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.f), r, r);
+  float q = n * r;
+  q = fmaf(fmaf(-d, q, n), r, q);
+  return fmaf(fmaf(-d, q, n), r, q);
+}
+
+// One Adam step on N embedding values or weights (constants of AdamStep), with the correctly
 // rounded square root and division: every launch that may update a parameter in fp32 takes the
 // same step, and a subgraph does not train differently because other kernels were chosen for it.
-template <class Step>
-__device__ __forceinline__ void adam_value(const Step& ad, float g, float& e, float& m, float& v) {
-  m = ad.b1 * m + (1.f - ad.b1) * g;
-  v = ad.b2 * v + (1.f - ad.b2) * g * g;
-  const float upd = (m * ad.inv_bc1) / (sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps);
-  e -= ad.lr * upd;
+// With a usual eps, v is taken as at least 2^-100 for its square root, 2^-50, which eps swallows: the same
+// sum.  Beyond the ranges (uniform over the wavefront) the general functions serve.
+template <int N, class Step>
+__device__ __forceinline__ void adam_values(const Step& ad, const float (&g)[N], float (&e)[N], float (&m)[N],
+                                            float (&v)[N]) {
+  float top = 0.f;
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    m[x] = ad.b1 * m[x] + (1.f - ad.b1) * g[x];
+    v[x] = ad.b2 * v[x] + (1.f - ad.b2) * g[x] * g[x];
+    top = fmaxf(top, v[x]);
+  }
+  if (ad.eps >= 1e-9f && ad.eps <= 1.f && ad.inv_sqrt_bc2 <= 64.f && !__any(top > 0x1p100f)) {
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      const float root = sqrt_in_range(fmaxf(v[x], 0x1p-100f));
+      e[x] -= ad.lr * quotient_in_range(m[x] * ad.inv_bc1, root * ad.inv_sqrt_bc2 + ad.eps);
+    }
+  } else {
+#pragma unroll
+    for (int x = 0; x < N; ++x) e[x] -= ad.lr * ((m[x] * ad.inv_bc1) / (sqrtf(v[x]) * ad.inv_sqrt_bc2 + ad.eps));
+  }
 }
 template <class Step>
-__device__ __forceinline__ void adam_weight(const Step& ad, float g, float& w, float& m, float& v) {
-  m = ad.b1 * m + (1.f - ad.b1) * g;
-  v = ad.b2 * v + (1.f - ad.b2) * g * g;
-  w -= ad.lr * (m * ad.inv_bc1) / (sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps);
+__device__ __forceinline__ void adam_value(const Step& ad, float g, float& e, float& m, float& v) {
+  float g1[1] = {g}, e1[1] = {e}, m1[1] = {m}, v1[1] = {v};
+  adam_values<1>(ad, g1, e1, m1, v1);
+  e = e1[0];
+  m = m1[0];
+  v = v1[0];
 }
 
 // Sum over the 64 lanes of a wavefront in a fixed butterfly order; every lane

@@ -61,6 +61,17 @@ __device__ __forceinline__ f32x4 gather4(const bf16_t* X, int j, int q, int h) {
   return load4<D>(X, j, q, h);
 }
 
+// One Adam step on a lane's four features.
+template <class Step>
+__device__ __forceinline__ void adam_rows(const Step& ad, const f32x4& g, f32x4& e, f32x4& m, f32x4& v) {
+  const float gx[4] = {g[0], g[1], g[2], g[3]};
+  float ex[4] = {e[0], e[1], e[2], e[3]}, mx[4] = {m[0], m[1], m[2], m[3]}, vx[4] = {v[0], v[1], v[2], v[3]};
+  adam_values<4>(ad, gx, ex, mx, vx);
+  e = f32x4{ex[0], ex[1], ex[2], ex[3]};
+  m = f32x4{mx[0], mx[1], mx[2], mx[3]};
+  v = f32x4{vx[0], vx[1], vx[2], vx[3]};
+}
+
 // Loads before it are issued before it.  Without it the compiler moves a load whose value is used under
 // a condition down to that use, where it is issued late and waited for with everything in flight.
 __device__ __forceinline__ void loads_stay_here() { asm volatile("" ::: "memory"); }

@@ -223,14 +223,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
         if constexpr (TO_EMBED && GRADS) {
           store4<D>(a.gE + first * D, row, ta, h, z);
         } else if constexpr (TO_EMBED) {
-#pragma unroll
-          for (int x = 0; x < 4; ++x) {
-            float ex = e[x], mx = m[x], vx = v[x];
-            adam_value(adE, z[x], ex, mx, vx);
-            e[x] = ex;
-            m[x] = mx;
-            v[x] = vx;
-          }
+          adam_rows(adE, z, e, m, v);
           store4<D>(a.mE + first * D, row, ta, h, m);
           store4<D>(a.vE + first * D, row, ta, h, v);
           store4<D>(a.E + first * D, row, ta, h, e);
@@ -298,7 +291,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     float w = W[idx], m = mW[idx], v = vW[idx], s = 0.f;
 #pragma unroll
     for (int q = 0; q < kSlots; ++q) s += slots[q * DP * DP + r * DP + c];
-    adam_weight(adW, s, w, m, v);
+    adam_value(adW, s, w, m, v);
     W[idx] = w;
     mW[idx] = m;
     vW[idx] = v;
@@ -309,7 +302,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     float w = a.W[L - 1][idx], m = a.mW[L - 1][idx], v = a.vW[L - 1][idx], s = 0.f;
 #pragma unroll
     for (int q = 0; q < NW; ++q) s += smem[cv.gwo + q * DP + tid];
-    adam_weight(adW, s, w, m, v);
+    adam_value(adW, s, w, m, v);
     a.W[L - 1][idx] = w;
     a.mW[L - 1][idx] = m;
     a.vW[L - 1][idx] = v;

@@ -350,15 +350,8 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
             if (!adam) {
               store4<D>(a.gE, row, ta, h, z);
             } else {
-              f32x4 e;
-#pragma unroll
-              for (int x = 0; x < 4; ++x) {
-                float ex = hold_e[x], mx = m[x], vx = v[x];
-                adam_value(ad, z[x], ex, mx, vx);
-                e[x] = ex;
-                m[x] = mx;
-                v[x] = vx;
-              }
+              f32x4 e = hold_e;
+              adam_rows(ad, z, e, m, v);
               store4<D>(a.mE, row, ta, h, m);
               store4<D>(a.vE, row, ta, h, v);
               store4<D>(a.E, row, ta, h, e);
