@@ -159,8 +159,9 @@ struct gco_ctx {
   int staged_wgs = 0, staged_cap = 0;
   int32_t *d_staged_k = nullptr, *d_staged_ptr = nullptr, *d_staged_launch = nullptr;
   int scalar_form_wanted = GCO_SCALAR_AUTO;
-  // whole epochs in one launch, a workgroup per subgraph (small_train.hip); its LDS, 0 = not used
-  size_t small_train_lds = 0;
+  // whole epochs in one launch, a workgroup per subgraph (small_train.hip), and its LDS
+  bool small_train = false;
+  SmallLds small_lds;
   int2* d_fused_cuts = nullptr;
   int32_t* d_heavy_ptr = nullptr;
   int2 *d_went = nullptr, *d_went_t = nullptr;
@@ -524,39 +525,41 @@ void wave_map_of(int storage, int dim, int v, int P, const std::vector<int>& par
 
 // Whether training runs faster with a workgroup per subgraph for whole epochs (small_train.hip)
 // than with four to eight launches per epoch over the whole chip; microseconds per epoch, fitted to
-// 504 measured pairs (1 .. 1500 subgraphs of 12 .. 2500 rows with 3 and 8 neighbours, two and three
-// layers).  One compute unit is bound by its instructions: a round of tiles (one per wavefront) takes a
-// fixed time and one per entry, the width-1 passes a time per entry; beyond 256 subgraphs compute units
-// take them in turn, narrow ones two at once.  Both estimates are within 0.67 .. 1.38 of what was measured; the
-// choice was more than 5 % off the faster way in 14 of the pairs, by 31 % at most.  A forward pass alone gains
-// less than an epoch, and beyond 256 subgraphs it loses (512 x 200 rows of width 64, bf16: 42 us against
-// 24), so there the epoch has to gain more.
-// Measured, one launch / several (us): width 16, two layers: 200 rows with 8 neighbours 13 / 28, 64 x 600
-// rows with 4 24 / 41; width 32: 8 x 60 rows with 8 15 / 34, 8 x 500 rows with 3 35 / 37; width 64: 200 x 60
-// rows 25 / 50, three layers of 64 x 200 rows 72 / 65; bf16: 60 rows 22 / 36, 512 x 500 rows 397 / 304.
-bool small_train_pays(const gco_config& c, int P, int n, int64_t entries, int max_rows, int64_t max_entries) {
+// 738 measured pairs (1 .. 600 subgraphs of 30 .. 1250 rows with 3, 8 and 20 neighbours, those with 8
+// of uneven degree; two and three layers).  One compute unit is bound by its instructions: a round of tiles
+// (one per wavefront) takes a time, so do the width-1 passes per entry and the longest row; beyond 256
+// subgraphs compute units take them in turn.  bf16: `matrix` says that the gather runs on the matrix cores.
+// Both estimates are within 0.63 .. 1.36 of what was measured; the choice was more than 5 % off the faster
+// way in 5 of the pairs, by 18 % at most.  A forward pass alone gains less than an epoch, so beyond 256
+// subgraphs the epoch has to gain more.
+// Measured, one launch / several (us): width 16, two layers: 200 rows with 8 neighbours 10 / 31, 8 x 1250 with 3
+// 32 / 38, three layers 53 / 51; width 32, two layers: 8 x 500 rows with 3 24 / 38, 8 x 1250 55 / 43; width 64: 8 x 60
+// rows 16 / 43, 8 x 500 63 / 50; bf16: 8 x 60 rows 13 / 36, 8 x 250 24 / 50, 8 x 800 71 / 51, 600 x 250 81 / 158.
+bool small_train_pays(const gco_config& c, int P, int n, int64_t entries, int max_rows, int64_t max_entries,
+                      int max_degree, bool matrix) {
   struct Cost {
-    double start, layer, round, entry, narrow;                    // one launch
-    double launches, more, narrow_pass, per_row, per_entry, adam;  // several
+    double start, layer, round, entry, narrow, longest;                           // one launch
+    double launches, narrow_pass, more, per_row, per_entry, adam, longest_there;  // several
   };
   static constexpr Cost kCost[] = {
-      {3.9, 0.8, 3.2, 0.20, 3.65, 15.1, 10.8, 2.3, 0.097, 0.013, 22.5},  // width 8, 16
-      {2.8, 2.0, 7.2, 0.10, 8.2, 14.9, 12.7, 2.9, 0.206, 0.020, 11.7},   // 32
-      {4.6, 0.0, 12.4, 0.47, 7.1, 14.2, 18.0, 4.6, 0.509, 0.031, 9.6},   // 64
-      {2.5, 0.0, 15.6, 0.65, 11.6, 16.5, 16.6, 6.8, 0.330, 0.024, 8.5},  // 64, bf16
+      {2.0, 0.0, 3.3, 0.0, 1.8, 1.2, 16.0, 2.8, 9.5, 0.125, 0.014, 10.4, 0.9},      // width 8, 16
+      {0.3, 0.0, 6.8, 0.0, 3.6, 1.65, 15.5, 3.4, 12.9, 0.253, 0.021, 5.9, 1.3},     // 32
+      {3.2, 0.0, 12.0, 0.0, 5.6, 4.0, 13.9, 7.05, 20.7, 0.473, 0.029, 9.8, 0.3},    // 64
+      {4.1, 3.1, 8.2, 0.54, 2.2, 1.85, 13.6, 9.6, 20.5, 0.212, 0.027, 10.9, 1.55},  // 64, bf16
+      {4.1, 3.1, 5.55, 0.05, 2.2, 1.85, 13.6, 9.6, 20.5, 0.212, 0.027, 10.9, 1.55}, // 64, bf16, matrix
   };
-  const Cost& k = kCost[c.storage == GCO_STORAGE_BF16 ? 3 : (c.dim <= 16 ? 0 : (c.dim == 32 ? 1 : 2))];
+  const Cost& k = kCost[c.storage == GCO_STORAGE_BF16 ? (matrix ? 4 : 3) : (c.dim <= 16 ? 0 : (c.dim == 32 ? 1 : 2))];
   const int hidden = c.num_layers - 1, waves = c.dim <= 32 ? 16 : 8;
   const int rounds = ((max_rows + kTileRowsF32 - 1) / kTileRowsF32 + waves - 1) / waves;
   const double per_row = static_cast<double>(entries) / n;  // entries of a row, the diagonal included
-  const double thousands = 1e-3 * static_cast<double>(max_entries);
-  const double turns = P <= 256 ? 1.0 : P / 256.0 * (c.dim <= 32 ? 0.85 : 1.0);
-  const double one =
-      turns * (k.start + hidden * (k.layer + rounds * (k.round + k.entry * per_row)) + k.narrow * thousands);
+  const double thousands = 1e-3 * static_cast<double>(max_entries), longest = max_degree / 32.0;
+  const double turns = P <= 256 ? 1.0 : 1.07 * P / 256.0;
+  const double one = turns * (k.start + hidden * (k.layer + rounds * (k.round + k.entry * per_row) + k.longest * longest) +
+                              k.narrow * thousands);
   const double several = k.launches + k.narrow_pass * thousands * ((P + 255) / 256) +
                          hidden * (k.more + 1e-3 * (k.per_row * n + k.per_entry * static_cast<double>(entries)) +
-                                   k.adam * 1e-6 * P * c.dim * c.dim);
-  return one < (P <= 256 ? 0.92 : 0.8) * several;
+                                   k.adam * 1e-6 * P * c.dim * c.dim + k.longest_there * longest);
+  return one < (P <= 256 ? 0.95 : 0.85) * several;
 }
 
 // Workgroup ids grouped by the subgraph they work on (ascending within a group);
@@ -1076,14 +1079,20 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     // Whole epochs in one launch: where the scalar layer is one launch by choice, every subgraph has
     // weights of its own and fits the LDS with its stream, and that is the faster way.  A forced
     // form is what runs.
-    ctx->small_train_lds = 0;
-    if (form == GCO_SCALAR_AUTO && ctx->fused_scalar && ctx->Pw == P && L >= 2 && D <= 64 && num_heavy == 0 &&
-        small_train_pays(ctx->cfg, P, n, total_light, max_rows, max_light)) {
-      size_t lds = 0;
-      for (int kk = 0; kk < P; ++kk)
-        lds = std::max(lds, small_train_lds_bytes(D, L, part_rows[kk + 1] - part_rows[kk],
-                                                  static_cast<int>(light_of[kk]), ctx->cfg.norm != GCO_NORM_SYM));
-      if (lds <= kLdsPerComputeUnit) ctx->small_train_lds = lds;
+    ctx->small_train = false;
+    if (form == GCO_SCALAR_AUTO && ctx->fused_scalar && ctx->Pw == P && L >= 2 && D <= 64 && num_heavy == 0) {
+      SmallLds& lds = ctx->small_lds;
+      for (int kk = 0; kk < P; ++kk) {
+        const SmallLds one = small_train_lds(ctx->cfg.storage, D, L, part_rows[kk + 1] - part_rows[kk],
+                                             static_cast<int>(light_of[kk]), ctx->cfg.norm != GCO_NORM_SYM,
+                                             kLdsPerComputeUnit);
+        auto both = [kk](size_t x, size_t y) { return kk == 0 ? y : (x == 0 || y == 0 ? 0 : std::max(x, y)); };
+        lds = SmallLds{both(lds.unstaged, one.unstaged), both(lds.rows, one.rows), both(lds.all_rows, one.all_rows)};
+      }
+      int max_degree = 0;
+      for (int r = 0; r < n; ++r) max_degree = std::max(max_degree, lrowptr[r + 1] - lrowptr[r]);
+      ctx->small_train = lds.unstaged != 0 && small_train_pays(ctx->cfg, P, n, total_light, max_rows, max_light,
+                                                               max_degree, lds.rows != 0);
     }
     ctx->fused_waves = fused_nw;
     ctx->fused_cap = cap;
@@ -1556,7 +1565,7 @@ static AdamStep adam_constants(const gco_config& c, int64_t step) {
   return ad;
 }
 
-// Small subgraphs (small_train_lds != 0).  passes = 1: forward; 2: forward and loss, to set `slot`
+// Small subgraphs (ctx->small_train).  passes = 1: forward; 2: forward and loss, to set `slot`
 // of the loss partials; 3: `epochs` (at most kLossSets) epochs in one launch, their losses to the
 // sets from `slot` on; 4: the gradients of one epoch to gE and gW.  uniform: the step counts of all models are `steps` before it; else bc
 // holds the bias corrections.  Forward, loss, gradients and training take every sum in the same
@@ -1599,12 +1608,12 @@ static void run_small(gco_ctx* ctx, const GraphView& gv, int passes, int epochs,
   a.epochs = epochs;
   a.passes = passes;
   a.train_embed = c.train_embed;
-  launch_small_train(ctx->launch(), c.storage, c.dim, c.num_layers, gv, a, ctx->small_train_lds);
+  launch_small_train(ctx->launch(), c.storage, c.dim, c.num_layers, gv, a, ctx->small_lds);
   ctx->probs_valid = true;
 }
 
 static void run_forward(gco_ctx* ctx) {
-  if (ctx->small_train_lds != 0) return run_small(ctx, ctx->gv, 1, 1, 0, true, 0, nullptr);
+  if (ctx->small_train) return run_small(ctx, ctx->gv, 1, 1, 0, true, 0, nullptr);
   run_hidden_forward(ctx, ctx->gv);
   run_scalar_layer(ctx, ctx->gv, 1, 0);
 }
@@ -1751,7 +1760,7 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
         }
       HIPCHK(h2d(ctx, ctx->d_bc, bc.data(), bc.size()));
     }
-    if (ctx->small_train_lds != 0) {
+    if (ctx->small_train) {
       run_small(ctx, gv, 3, ne, 0, uniform, ctx->stepE.empty() ? 0 : ctx->stepE[0] + e0, ctx->d_bc);
       launch_loss_reduce(ctx->launch(), gv, ctx->loss_partial, ne, gv.num_loss_slots, nullptr, ctx->loss_hist + e0);
       continue;
@@ -1904,7 +1913,7 @@ int gco_get_probs(gco_ctx* ctx, float* p) {
 int gco_loss(gco_ctx* ctx, double* total, double* per_part) {
   if (!ctx) return GCO_EINVAL;
   NEED(ctx->has_params, GCO_ESTATE, "set_params must precede loss");
-  if (ctx->small_train_lds != 0) {
+  if (ctx->small_train) {
     run_small(ctx, ctx->gv, 2, 1, 0, true, 0, nullptr);
   } else {
     run_hidden_forward(ctx, ctx->gv);
@@ -1930,7 +1939,7 @@ int gco_get_grads(gco_ctx* ctx, float* gE, float* const* gW) {
     d_gW[l - 1] = tmp.get<float>(static_cast<size_t>(ctx->Pw) * w_elems(ctx, l));
     NEED(d_gW[l - 1], GCO_ENOMEM, "device scratch allocation failed");
   }
-  if (ctx->small_train_lds != 0) {
+  if (ctx->small_train) {
     run_small(ctx, ctx->gv, 4, 1, 0, true, 0, nullptr, d_gE, d_gW);
   } else {
     run_hidden_forward(ctx, ctx->gv);

@@ -392,7 +392,7 @@ void launch_adam_w(const Launch& ln, int Pw, const WeightTensor* tensors, int co
 
 // ---- whole epochs of small subgraphs in one launch (small_train.hip) ----
 // For two or three layers of width <= 64, weights per subgraph and no pre-reduced rows; a
-// subgraph's stream has to fit the LDS (small_train_lds_bytes <= a compute unit's).  Loss
+// subgraph's stream has to fit the LDS (small_train_lds).  Loss
 // partials as by launch_scalar_fused: one per subgraph and epoch.
 struct SmallTrain {
   void* H[3] = {};        // H[0]: the embeddings in storage type, H[l]: hidden layer l
@@ -415,9 +415,15 @@ struct SmallTrain {
   float *gE = nullptr, *gW[3] = {};  // passes = 4 (gE may be nullptr)
   int train_embed = 1;
 };
-size_t small_train_lds_bytes(int D, int L, int rows, int entries, bool mean);
+// Bytes of LDS for a subgraph, 0 where they exceed the limit: the stream and the width-1 vectors; with the
+// gathered rows; with the last layer's gradient rows as well.
+struct SmallLds {
+  size_t unstaged = 0, rows = 0, all_rows = 0;
+};
+SmallLds small_train_lds(int storage, int D, int L, int rows, int entries, bool mean, size_t limit);
+// lds: of the largest subgraph of the launch, unstaged != 0 or rows != 0.
 void launch_small_train(const Launch& ln, int storage, int D, int L, const GraphView& g, const SmallTrain& a,
-                        size_t lds);
+                        const SmallLds& lds);
 
 // fp32 -> bf16 copy (round to nearest even).
 // X[i, :] <- softmax((X[i, :] - log(-log(U[i, :]))) / tau), rows of width D (Sec. 3.2).

@@ -28,37 +28,37 @@ __device__ __forceinline__ f32x4 mfma(float a, float b, const f32x4& c) {
 }
 
 // This lane's four features of group q of row j.
-template <int D>
+template <int D, int PITCH = D>
 __device__ __forceinline__ f32x4 load4(const float* X, int j, int q, int h) {
   if (D == 8 && h >= 2) return f32x4{0.f, 0.f, 0.f, 0.f};
-  return *reinterpret_cast<const f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h);
+  return *reinterpret_cast<const f32x4*>(X + static_cast<size_t>(j) * PITCH + 16 * q + 4 * h);
 }
-template <int D>
+template <int D, int PITCH = D>
 __device__ __forceinline__ f32x4 load4(const bf16_t* X, int j, int q, int h) {
-  const uint2 u = *reinterpret_cast<const uint2*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h);
+  const uint2 u = *reinterpret_cast<const uint2*>(X + static_cast<size_t>(j) * PITCH + 16 * q + 4 * h);
   return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
                __uint_as_float(u.y & 0xffff0000u)};
 }
-template <int D>
+template <int D, int PITCH = D>
 __device__ __forceinline__ void store4(float* X, int j, int q, int h, const f32x4& v) {
   if (D == 8 && h >= 2) return;
-  *reinterpret_cast<f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h) = v;
+  *reinterpret_cast<f32x4*>(X + static_cast<size_t>(j) * PITCH + 16 * q + 4 * h) = v;
 }
-template <int D>
+template <int D, int PITCH = D>
 __device__ __forceinline__ void store4(bf16_t* X, int j, int q, int h, const f32x4& v) {
-  *reinterpret_cast<uint2*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * h) =
+  *reinterpret_cast<uint2*>(X + static_cast<size_t>(j) * PITCH + 16 * q + 4 * h) =
       make_uint2(f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]));
 }
 
 // The same of a gathered row.  Width 8: the lanes of the upper half, which such a row does not have, load
 // the lower one again instead of branching around the load; aggregate() drops what they sum.
-template <int D>
+template <int D, int PITCH = D>
 __device__ __forceinline__ f32x4 gather4(const float* X, int j, int q, int h) {
-  return *reinterpret_cast<const f32x4*>(X + static_cast<size_t>(j) * D + 16 * q + 4 * (D == 8 ? h % 2 : h));
+  return *reinterpret_cast<const f32x4*>(X + static_cast<size_t>(j) * PITCH + 16 * q + 4 * (D == 8 ? h % 2 : h));
 }
-template <int D>
+template <int D, int PITCH = D>
 __device__ __forceinline__ f32x4 gather4(const bf16_t* X, int j, int q, int h) {
-  return load4<D>(X, j, q, h);
+  return load4<D, PITCH>(X, j, q, h);
 }
 
 // One Adam step on a lane's four features.
@@ -78,7 +78,8 @@ __device__ __forceinline__ void loads_stay_here() { asm volatile("" ::: "memory"
 
 // ---- sources of gathered rows: request() starts the loads of a row (this lane's features of it:
 // 16 q + 4 h + j, h = lane % 4), add() uses them ----
-template <int D, typename T = float>
+// PITCH: elements from one row to the next.
+template <int D, typename T = float, int PITCH = D>
 struct PlainRows {
   struct Row {
     f32x4 x[TF<D>::NQ];
@@ -86,7 +87,7 @@ struct PlainRows {
   const T* X;
   __device__ __forceinline__ void request(Row& r, int j, int h) const {
 #pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = gather4<D>(X, j, q, h);
+    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = gather4<D, PITCH>(X, j, q, h);
   }
   __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
 #pragma unroll
@@ -121,6 +122,55 @@ struct LastRows {
       const f32x4 wq = D <= 64 ? w[D <= 64 ? q : 0] : *reinterpret_cast<const f32x4*>(w_lds + 16 * q + off);
 #pragma unroll
       for (int x = 0; x < 4; ++x) acc[q][x] = fmaf(val, r.x[q][x] > 0.f ? Store<T>::as_stored(r.gt * wq[x]) : 0.f, acc[q][x]);
+    }
+  }
+};
+
+// The ReLU decisions of a row of the last hidden layer, one bit per feature: bit f % 32 of word f / 32.
+template <int D>
+struct Mask {
+  static constexpr int NM = (D + 31) / 32;  // words of a row
+};
+
+// Rows of dL/dZ of the last hidden layer without the factor w[c]: g_t[j] where H[j, c] > 0.  The caller
+// multiplies the finished sum by w, so an entry costs its mask and one scalar instead of a row.
+template <int D>
+struct MaskRows {
+  static constexpr int NM = Mask<D>::NM;
+  struct Row {
+    uint32_t m[NM];
+    float gt;
+  };
+  const uint32_t* mask;
+  const float* g_t;
+  __device__ __forceinline__ void request(Row& r, int j, int) const {
+    r.gt = g_t[j];
+    if constexpr (NM == 1) {
+      r.m[0] = mask[j];
+    } else if constexpr (NM == 2) {
+      const uint2 u = *reinterpret_cast<const uint2*>(mask + 2 * static_cast<size_t>(j));
+      r.m[0] = u.x;
+      r.m[1] = u.y;
+    } else {
+      const uint4 u = *reinterpret_cast<const uint4*>(mask + 4 * static_cast<size_t>(j));
+      r.m[0] = u.x;
+      r.m[1] = u.y;
+      r.m[2] = u.z;
+      r.m[3] = u.w;
+    }
+  }
+  __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
+    const int c = __float_as_int(val * r.gt);
+#pragma unroll
+    for (int w = 0; w < NM; ++w) {
+      const uint32_t m = r.m[w] >> (4 * (threadIdx.x % 4));
+#pragma unroll
+      for (int q = 2 * w; q < 2 * w + 2 && q < TF<D>::NQ; ++q)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int b = 16 * (q % 2) + x;
+          acc[q][x] += __int_as_float(c & (static_cast<int>(m << (31 - b)) >> 31));  // all ones or zero
+        }
     }
   }
 };

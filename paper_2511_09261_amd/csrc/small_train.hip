@@ -4,15 +4,23 @@
 // Subgraphs are independent (Sec. 3.3), so with weights of their own nothing crosses a
 // workgroup: the phases of an epoch are separated by workgroup barriers (a fraction of a
 // microsecond) instead of launches (5 us and more each, four to eight per epoch).  The
-// subgraph's light stream, its row offsets, its weight matrices and every width-1 vector stay in
-// LDS for all epochs; features, gradients and the optimizer's state are read from and written to
-// memory, where they stay in the caches of the one compute unit that uses them.
+// subgraph's light stream, its row offsets, its weight matrices, the ReLU decisions of the last hidden
+// layer and every width-1 vector stay in LDS for all epochs.  Where they fit beside those (STAGED), so do
+// the rows that are gathered: the embeddings and, with three layers, H_1, whose place takes the rows of
+// G_Z1 later.  Otherwise these rows are gathered from memory, where they stay in the caches of the one
+// compute unit that uses them.  Adam's moments of E (and the fp32 E of bf16 storage) are in memory in
+// both forms, requested before the gather that precedes their use.
 //
 // The wide phases use the tile code of row_tiles.h (16 rows per wavefront at a time, tiles dealt
-// to the wavefronts in turn), the width-1 phases a segmented scan over the stream in LDS
-// (64 entries per step, whole rows per wavefront).  bf16 storage rounds where the launches of
-// its own do (stored features and gradients, the operands of the dense products) and multiplies
-// the rounded values on the fp32 matrix instructions, which is exact per product.
+// to the wavefronts in turn) with a gather of its own: one compute unit is bound by the instructions it
+// issues, so a row's entries lie in whole batches and are summed without a test per entry.  bf16 storage rounds where the launches of
+// its own do (stored features and gradients, the operands of the dense products); its products run on
+// the bf16 matrix instructions, those of fp32 storage on the fp32 ones.
+//
+// Last hidden layer, backward: dL/dZ = g_t w_out [H > 0], so the gather sums g_t over the mask bits, its
+// sum B is multiplied by w_out once, and with M = Hprev^T B
+//   dL/dW[a, c] = M[a, c] w_out[c]   and   dL/dw_out[c] = sum_a W[a, c] M[a, c]
+// (H = (A_hat Hprev) W where the mask is set): neither H nor its rows are needed.
 //
 // Best-by-loss snapshots are taken inside the epoch, between the loss and the update, so that tracking
 // them costs no second forward pass and no launch.
@@ -30,96 +38,581 @@
 namespace gco {
 namespace {
 
-// zero entries after the stream in LDS: a tile dealt row by row reads a longest row (below
-// kHeavyMin neighbours and the diagonal) and two batches past its last row's beginning
-constexpr int kSmallPad = kHeavyMin + 16;
+// A row's entries in LDS fill whole batches of kBatch; what is missing carries the value 0 and column R,
+// whose place in every vector and among the staged rows holds zeros.
+constexpr int kBatch = 4;
+// Rows up to this long are summed by the lanes of their own, what goes beyond by the whole wavefront.
+constexpr int kOwnEntries = 32;  // of feature rows, four lanes each
+constexpr int kOwnScalars = 64;  // of width-1 passes, four entries at a time
+constexpr int kSmallPad = 48;    // zero entries after the stream: read ahead, and instead of what a row does not have
 
-template <int D>
+// What of the gathered rows lies in LDS: nothing; the embeddings and H_1; also the rows of g_t [H > 0] of the
+// last layer (fp32, up to width 32).
+enum Staging : int { kUnstaged = 0, kRows = 1, kAllRows = 2 };
+
+template <typename T, int D>
 struct SK : TF<D> {
+  using TF<D>::DP;
+  using TF<D>::PT;
+  static constexpr bool BF = sizeof(T) == 2;
   static constexpr int NW = D <= 32 ? 16 : 8;  // wavefronts of the workgroup
   static constexpr int NT = 64 * NW;
-  static constexpr int WP = TF<D>::DP + 4;  // pitch of a weight matrix in LDS (floats)
-  static constexpr int kW = TF<D>::DP * WP;
+  static constexpr int NM = Mask<D>::NM;
+  // A weight matrix in LDS.  fp32: rows of pitch WP floats.  bf16: the operands of Z^T = W^T AGG^T, then
+  // those of G_H^T = W G_T^T, 16 bytes per lane (see operand_place).
+  static constexpr int WP = DP + 4;
+  static constexpr int kW = BF ? DP * DP : DP * WP;  // floats
+  // elements from one staged row to the next: gathered rows fall into different banks
+  static constexpr int PE = BF ? D + 8 : (D <= 16 ? D : D + 4);
+  static constexpr int PG = D + 8;                   // bf16: pitch of the tile of G_T
+  static constexpr int PER = (D * D + NT - 1) / NT;  // weights of a layer per thread
+  static constexpr bool W_IN_REGISTERS = PER == 1;   // with Adam's moments, for all epochs of a launch
+  static_assert(NT % D == 0, "a thread's weights are of one column");
+  // A wavefront's place for the sums of a tile, then for G_T; and the places for the wavefronts' weight
+  // gradients, which all of it becomes at the end of a layer: one each, or kSlots that they take in turn.
+  static constexpr int kSums = D == 64 ? 2 * kTile * PT : kTile * PT;  // floats
+  static constexpr int kTileGt = kTile * PG / 2;                       // bf16 with staged rows: G_T only
+  static constexpr int kSlots = DP * DP <= kSums ? NW : NW / 2;
+  static_assert(kSlots * DP * DP <= NW * kSums, "room for the sums");
+  static constexpr int kMatrixSlots = 3;  // bf16 with staged rows, whose place is short
 };
 
+// bf16 with staged rows: the gather runs on the matrix cores (aggregate_staged).
+template <typename T, int STAGED>
+constexpr bool kMatrixGather = sizeof(T) == 2 && STAGED != kUnstaged;
+
 // The workgroup's LDS, in floats from its start.
-template <int D>
+template <typename T, int D>
 struct Carve {
-  size_t w[2], wo, sums, gwo, c, t, p, rp, ent, valt, red, end;
-  __host__ __device__ Carve(int L, int rows, int entries, bool mean) {
-    const size_t r = (static_cast<size_t>(rows) + 7) / 4 * 4;
-    const size_t e = (static_cast<size_t>(entries) + kSmallPad + 3) / 4 * 4;
+  size_t w[2], wo, sums, slots, gwo, c, t, p, rp, mask, ent, valt, red, rows[3], col, split[3], pm, end;
+  // entries: of the stream before its rows are filled up
+  __host__ __device__ Carve(int L, int nrows, int entries, bool mean, int staged) {
+    using K = SK<T, D>;
+    const bool matrix = K::BF && staged != kUnstaged;
+    const size_t r = (static_cast<size_t>(nrows) + 7) / 4 * 4;
+    const size_t e = (static_cast<size_t>(entries) + static_cast<size_t>(matrix ? 0 : kBatch - 1) * nrows + kSmallPad + 7) / 8 * 8;
     size_t at = 0;
     auto take = [&](size_t floats) {
       const size_t x = at;
       at += (floats + 3) / 4 * 4;
       return x;
     };
-    w[0] = take(SK<D>::kW);
-    w[1] = L == 3 ? take(SK<D>::kW) : 0;
-    wo = take(SK<D>::DP);
-    sums = take(static_cast<size_t>(SK<D>::NW) * SK<D>::kWaveLds);
-    gwo = take(static_cast<size_t>(SK<D>::NW) * SK<D>::DP);
+    w[0] = take(K::kW);
+    w[1] = L == 3 ? take(K::kW) : 0;
+    wo = take(K::DP);
+    gwo = take(static_cast<size_t>(K::NW) * K::DP);
     c = take(r);
     t = take(r);
     p = take(r);
     rp = take(r);
-    ent = take(2 * e);
-    valt = mean ? take(e) : 0;
-    red = take(2 * SK<D>::NW + 4);  // the wavefronts' shares of the loss, the lowest loss, whether this one is lower
+    mask = ent = valt = col = pm = 0;
+    split[0] = split[1] = split[2] = 0;
+    red = take(2 * K::NW + 4);  // the wavefronts' shares of the loss, the lowest loss, whether this one is lower
+    if (matrix) {
+      col = take(e / 2);
+      split[0] = take(3 * e / 2);                    // the values in three bf16 parts
+      split[1] = mean ? take(3 * e / 2) : split[0];  // of the transposed matrix
+      split[2] = take(3 * e / 2);                    // value times g_t
+      pm = take(256 * 4);
+    } else {
+      mask = take(r * K::NM);
+      ent = take(2 * e);
+      valt = mean ? take(e) : 0;
+    }
+    // whole tiles and at least one row more than there are, which stay zero
+    const size_t rows_floats = static_cast<size_t>(padded_rows(nrows)) * K::PE * sizeof(T) / sizeof(float);
+    rows[0] = staged != kUnstaged ? take(rows_floats) : 0;
+    rows[1] = staged != kUnstaged && L == 3 ? take(rows_floats) : 0;
+    if (matrix) {  // rows of [H > 0] and the tiles of G_T; at the end of a layer the slots
+      slots = rows[2] = take(0);
+      sums = rows[2] + (rows_floats + 3) / 4 * 4;
+      const size_t both = (rows_floats + 3) / 4 * 4 + static_cast<size_t>(K::NW) * K::kTileGt;
+      const size_t sums_of_w = static_cast<size_t>(K::kMatrixSlots) * K::DP * K::DP;
+      take(both > sums_of_w ? both : sums_of_w);
+    } else {
+      rows[2] = staged == kAllRows ? take(rows_floats) : 0;
+      slots = sums = take(static_cast<size_t>(K::NW) * K::kSums);
+    }
     end = at;
   }
+  static __host__ __device__ int padded_rows(int nrows) { return (nrows + kTile) / kTile * kTile; }
 };
 
-// The light stream of the subgraph in LDS: rows and columns relative to its first row, 16 bits
-// each, and the entry's value (of A_hat, or of its transpose where that differs).
+// Sums over the lanes l, l ^ 16, l ^ 32, l ^ 48, without LDS (lane l ^ 32's half, then l ^ 16's row).
+__device__ __forceinline__ float add_over_h(float v) {
+  const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(y[0]) + __uint_as_float(y[1]);
+}
+__device__ __forceinline__ uint32_t or_over_h(uint32_t v) {
+  const auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  v = x[0] | x[1];
+  const auto y = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return y[0] | y[1];
+}
+template <int N>  // the lane N further round its row of 16
+__device__ __forceinline__ float rotated(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+}
+// Sum over the four lanes of a group (data-parallel-primitive permutations of a quad).
+__device__ __forceinline__ float quad_sum(float v) {
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));  // lanes 1 0 3 2
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4e, 0xf, 0xf, false));  // 2 3 0 1
+}
+// Sum over the wavefront in lane 63, by the moves of a scan.
+__device__ __forceinline__ double wave_total(double v) {
+#define GCO_STEP(C, M)                                                                       \
+  {                                                                                          \
+    const int hi = dpp_move<C, M>(0, __double2hiint(v)), lo = dpp_move<C, M>(0, __double2loint(v)); \
+    v += __hiloint2double(hi, lo);                                                           \
+  }
+  GCO_SCAN_STEPS(GCO_STEP)
+#undef GCO_STEP
+  return v;
+}
+
+// Between phases whose threads exchange data through LDS alone: unlike __syncthreads() it does not wait for
+// the stores to memory (Adam's moments, half a microsecond away) that only their own thread reads again.
+__device__ __forceinline__ void sync_lds() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// The light stream of the subgraph in LDS, row after row in whole batches: column (R where there is no
+// entry) in the lower half of x; in the upper half the row to gather in its place from memory, which has no
+// row R (the column, or the row itself); the value (of A_hat, or of its transpose where that differs) in y.
 struct StreamInLds {
   const uint2* ent;
   const float* valt;  // nullptr: the values of ent
-  const int* rp;
-  static constexpr bool kPreReduced = false;
-  static __device__ __forceinline__ bool by_row(int longest, int share) { return longest <= 3 * (share + 1); }
-  __device__ __forceinline__ int begin_of(int row) const { return rp[row]; }
-  __device__ __forceinline__ Entry at(int e) const {
+  const int* rp;      // [R+1] first entry of every row
+  int none;           // an entry past the last row's
+  __device__ __forceinline__ int column(int e) const { return ent[e].x & 0xffffu; }
+  // value of entry e times the scalar of its column
+  __device__ __forceinline__ float product(int e, const float* v) const {
     const uint2 x = ent[e];
-    return Entry{static_cast<int>(x.x & 0xffffu), static_cast<int>(x.x >> 16),
-                 valt != nullptr ? valt[e] : __uint_as_float(x.y)};
+    return (valt != nullptr ? valt[e] : __uint_as_float(x.y)) * v[x.x & 0xffffu];
   }
 };
+// bf16 with staged rows: rows not filled up; columns, and the values in three bf16 parts that add up to
+// them exactly (part q of entry e at split[q * stride + e]).
+struct SplitStream {
+  const uint16_t* col;
+  const bf16_t* split;
+  int stride;
+  const int* rp;
+  int none;
+  __device__ __forceinline__ int column(int e) const { return col[e]; }
+  __device__ __forceinline__ float product(int e, const float* v) const {
+    const float value = (bf16_to_f32(split[e]) + bf16_to_f32(split[stride + e])) + bf16_to_f32(split[2 * stride + e]);
+    return value * v[col[e]];
+  }
+};
+__device__ __forceinline__ void put_split(bf16_t* split, int stride, int e, float v) {
+  const bf16_t hi = f32_to_bf16(v);
+  const float r1 = v - bf16_to_f32(hi);
+  const bf16_t mid = f32_to_bf16(r1);
+  split[e] = hi;
+  split[stride + e] = mid;
+  split[2 * stride + e] = f32_to_bf16(r1 - bf16_to_f32(mid));
+}
 
-// finish(row, sum of the row's terms) for the rows whose entries fill [e0, e1) of the stream, by one
-// wavefront; term(entry) is an entry's contribution.
-template <class Term, class Finish>
-__device__ __forceinline__ void scan_rows(const StreamInLds& s, int e0, int e1, Term&& term, Finish&& finish) {
-  const int lane = threadIdx.x % 64;
-  int carry_row = -1;
-  float carry = 0.f;
-  for (int b = e0; b < e1; b += 64) {
-    const bool ok = b + lane < e1;
-    const Entry en = s.at(ok ? b + lane : e0);
-    const int row = ok ? en.row : -1;
-    float v = ok ? term(en) : 0.f;
-    const int after = b + 64 < e1 ? s.at(b + 64).row : -1;  // first row of the next step
-    v = scan_sum_by_key(v, row);
-    int next = __shfl_down(row, 1, 64);
-    if (lane == 63) next = after;
-    const float total = v + (row == carry_row ? carry : 0.f);
-    if (ok && next != row) finish(row, total);
-    const int row63 = __builtin_amdgcn_readlane(row, 63);
-    const float tot63 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(total), 63));
-    const bool runs_on = row63 >= 0 && after == row63;
-    carry_row = runs_on ? row63 : -1;
-    carry = runs_on ? tot63 : 0.f;
+// acc = (A_hat x)(row n of the tile at r0, this lane's features); zero for rows past R.  Four lanes
+// gather a row and sum its entries batch by batch, the next batch read ahead; a long row's entries from
+// kOwnEntries on are shared by the sixteen groups.  IN_LDS: where the rows lie.
+template <int D, bool IN_LDS, class Rows>
+__device__ __forceinline__ void aggregate_rows(const StreamInLds& st, const Rows& rows, int r0, int R, float* sums,
+                                               f32x4 (&acc)[TF<D>::NQ]) {
+  constexpr int NQ = TF<D>::NQ, PT = TF<D>::PT;
+  constexpr int UB = D <= 32 ? kBatch : 2;  // rows in flight
+  const int lane = threadIdx.x % 64, n = lane % 16, h = lane / 16;
+  const int group = lane / 4, gh = lane % 4;
+  struct Batch {
+    uint2 en[kBatch];
+    float val[kBatch];
+  };
+  auto read = [&](int e) {
+    Batch b;
+    const uint4 x = *reinterpret_cast<const uint4*>(st.ent + e), y = *reinterpret_cast<const uint4*>(st.ent + e + 2);
+    b.en[0] = make_uint2(x.x, x.y);
+    b.en[1] = make_uint2(x.z, x.w);
+    b.en[2] = make_uint2(y.x, y.y);
+    b.en[3] = make_uint2(y.z, y.w);
+    if (st.valt != nullptr) {
+      const float4 v = *reinterpret_cast<const float4*>(st.valt + e);
+      b.val[0] = v.x;
+      b.val[1] = v.y;
+      b.val[2] = v.z;
+      b.val[3] = v.w;
+    } else {
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) b.val[u] = __uint_as_float(b.en[u].y);
+    }
+    return b;
+  };
+  auto add = [&](const Batch& b, f32x4 (&sum)[NQ]) {
+#pragma unroll
+    for (int u0 = 0; u0 < kBatch; u0 += UB) {
+      typename Rows::Row x[UB];
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+        rows.request(x[u], IN_LDS ? b.en[u0 + u].x & 0xffffu : b.en[u0 + u].x >> 16, gh);
+#pragma unroll
+      for (int u = 0; u < UB; ++u) rows.add(x[u], b.val[u0 + u], sum);
+    }
+  };
+  const int row = r0 + group;
+  int e = st.rp[min(row, R)];
+  const int end = st.rp[min(row + 1, R)], own = min(end, e + kOwnEntries);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Batch b = read(e);
+  while (e < own) {
+    const Batch next = read(e + kBatch);
+    add(b, acc);
+    b = next;
+    e += kBatch;
+  }
+  unsigned long long todo = __ballot(gh == 0 && end > own);
+  while (todo != 0) {
+    const int l = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    const int last = __builtin_amdgcn_readlane(end, l);
+    f32x4 part[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) part[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int x = __builtin_amdgcn_readlane(own, l) + kBatch * group; x < last; x += kBatch * 16) add(read(x), part);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        float v = part[q][y];
+        v += rotated<8>(v);
+        v += rotated<4>(v);
+        v = add_over_h(v);
+        if (group == l / 4) acc[q][y] += v;
+      }
+  }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(sums + group * PT + 16 * q + 4 * gh) = acc[q];
+  wave_lds_handoff();
+  const bool valid = r0 + n < R;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(sums + n * PT + 16 * q + 4 * h);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) acc[q][y] = valid && (D > 8 || h < 2) ? v[y] : 0.f;
+  }
+  wave_lds_handoff();
+}
+
+// finish(row, sum of the row's terms, lane of the row) for every row, by its four lanes; term(entry, first
+// entry of the row) is an entry's contribution.  Four lanes sum a row, four batches in flight; a long row's entries from kOwnScalars
+// on are shared by the wavefront.
+template <int NW, class Stream, class Term, class Finish>
+__device__ __forceinline__ void sum_rows(const Stream& st, int R, int wave, Term&& term, Finish&& finish) {
+  const int lane = threadIdx.x % 64, group = lane / 4, gh = lane % 4;
+  for (int r0 = wave * kTile; r0 < R; r0 += NW * kTile) {
+    const int row = r0 + group;
+    const int begin = st.rp[min(row, R)], end = st.rp[min(row + 1, R)], own = min(end, begin + kOwnScalars);
+    float s = 0.f;
+    for (int e = begin; e < own; e += 4 * kBatch) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int x = e + u * kBatch + gh;
+        v[u] = term(x < own ? x : st.none, begin);
+      }
+      s += (v[0] + v[1]) + (v[2] + v[3]);
+    }
+    s = quad_sum(s);
+    unsigned long long todo = __ballot(gh == 0 && end > own);
+    while (todo != 0) {
+      const int l = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int last = __builtin_amdgcn_readlane(end, l);
+      float part = 0.f;
+      for (int e = __builtin_amdgcn_readlane(own, l); e < last; e += 64) {
+        part += term(e + lane < last ? e + lane : st.none, -1);
+      }
+      part = quad_sum(part);
+      part += rotated<8>(part);
+      part += rotated<4>(part);
+      part = add_over_h(part);
+      if (group == l / 4) s += part;
+    }
+    if (row < R) finish(row, s, gh);
   }
 }
 
+// ---- dense products of a 16-row tile.  Lane (n, h) holds features 16 q + 4 h + j of row n in x[q][j].
+// fp32: contraction step (q, j) of v_mfma_f32_16x16x4_f32.  bf16: step s of v_mfma_f32_16x16x32_bf16 holds,
+// at lane (n, h), the groups q = 2 s and 2 s + 1, i.e. contraction index 8 h + e stands for feature
+// 32 s + 16 (e / 4) + 4 h + e % 4.  Register r of the result at lane (n, h): row 4 h + r, column n. ----
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef short i16x4_t __attribute__((ext_vector_type(4)));
+
+template <int D>
+struct Packed {  // rounded operands of a bf16 tile
+  uint4 s[D / 32 > 0 ? D / 32 : 1];
+};
+template <int D>
+__device__ __forceinline__ Packed<D> pack_tile(const f32x4 (&x)[TF<D>::NQ]) {
+  Packed<D> p;
+#pragma unroll
+  for (int s = 0; s < D / 32; ++s)
+    p.s[s] = make_uint4(f32x2_to_bf16x2(x[2 * s][0], x[2 * s][1]), f32x2_to_bf16x2(x[2 * s][2], x[2 * s][3]),
+                        f32x2_to_bf16x2(x[2 * s + 1][0], x[2 * s + 1][1]),
+                        f32x2_to_bf16x2(x[2 * s + 1][2], x[2 * s + 1][3]));
+  return p;
+}
+__device__ __forceinline__ f32x4 mfma32(const uint4& a, const uint4& b, const f32x4& c) {
+  bf16x8_t av, bv;
+  __builtin_memcpy(&av, &a, 16);
+  __builtin_memcpy(&bv, &b, 16);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma16(const i16x4_t& a, const i16x4_t& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+}
+
+// Where W[f][o] (o: output feature) sits among the operands for a contraction over f with result rows o:
+// piece (o / 16, f / 32), lane (o % 16, h), element e, in bf16 values.
+template <int D>
+__device__ __forceinline__ int operand_place(int o, int f) {
+  return (((o / 16) * (D / 32) + f / 32) * 64 + (f / 4 % 4) * 16 + o % 16) * 8 + (f / 16 % 2) * 4 + f % 4;
+}
+
+// W[r][c] to its places in LDS.
+template <typename T, int D>
+__device__ __forceinline__ void put_weight(float* wl, int r, int c, float w) {
+  if constexpr (SK<T, D>::BF) {
+    bf16_t* fw = reinterpret_cast<bf16_t*>(wl);
+    const bf16_t x = f32_to_bf16(w);
+    fw[operand_place<D>(c, r)] = x;
+    fw[D * D + operand_place<D>(r, c)] = x;
+  } else {
+    wl[r * SK<T, D>::WP + c] = w;
+  }
+}
+
+// Group ta of x W (FORWARD) or of x W^T, this lane's row; p: x rounded (bf16).  on = the lane's n.
+template <typename T, int D, bool FORWARD>
+__device__ __forceinline__ f32x4 times_weights(const float* wl, const f32x4 (&x)[TF<D>::NQ], const Packed<D>& p, int ta,
+                                               int on, int h) {
+  using K = SK<T, D>;
+  f32x4 z = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (K::BF) {
+    const bf16_t* fw = reinterpret_cast<const bf16_t*>(wl) + (FORWARD ? 0 : D * D);
+#pragma unroll
+    for (int s = 0; s < D / 32; ++s)
+      z = mfma32(*reinterpret_cast<const uint4*>(fw + ((ta * (D / 32) + s) * 64 + h * 16 + on) * 8), p.s[s], z);
+  } else if constexpr (FORWARD) {
+#pragma unroll
+    for (int q = 0; q < K::NQ; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z = mfma(wl[(16 * q + 4 * h + j) * K::WP + 16 * ta + on], x[q][j], z);
+  } else {
+#pragma unroll
+    for (int q = 0; q < K::NQ; ++q) {
+      const f32x4 w = *reinterpret_cast<const f32x4*>(wl + (16 * ta + on) * K::WP + 16 * q + 4 * h);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) z = mfma(w[j], x[q][j], z);
+    }
+  }
+  return z;
+}
+
+// Transposing 8-byte LDS read: in every group of 16 lanes, lane i receives element i % 4 of the 8-byte
+// chunks addressed by lanes i / 4, i / 4 + 4, i / 4 + 8, i / 4 + 12 of the group.  With lane 4 j + r at row
+// j, columns 4 r .. 4 r + 3 of a 4 x 16 block, lane i has rows 0 .. 3 of column i.
+__device__ __forceinline__ i16x4_t lds_read_columns(const bf16_t* block, int pitch, int i) {
+  const bf16_t* chunk = block + (i / 4) * pitch + (i % 4) * 4;
+  const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)chunk));
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4_t*)(uintptr_t)at);
+}
+
+// acc = (A_hat x)(row n of the tile at r0, this lane's features) on the matrix cores:
+//   AGG^T[feature, row] = sum_slot X[slot, feature] S[slot, row], 32 entries ("slots") of the stream a step,
+// S[slot, row] = the entry's value if the slot belongs to the row, else 0.  Lane (n, h) of the operands
+// holds slots 8 h .. 8 h + 7 of the step: X comes from the gathered rows by transposing reads, whose lane 4 j + r
+// points at the row of slot 8 h + j (then 8 h + 4 + j); S is read from the split values and masked with the
+// row's range of slots.  The cost follows the tile's entries, however they are spread over its rows.
+template <int D, int PITCH>
+__device__ __forceinline__ void aggregate_staged(const SplitStream& st, const bf16_t* rows, const uint4* pair_mask, int r0,
+                                                 int R, f32x4 (&acc)[TF<D>::NQ]) {
+  constexpr int NQ = TF<D>::NQ;
+  const int lane = threadIdx.x % 64, n = lane % 16, h = lane / 16;
+  const int E0 = __builtin_amdgcn_readfirstlane(st.rp[r0]), E1 = __builtin_amdgcn_readfirstlane(st.rp[min(r0 + kTile, R)]);
+  const int ra = st.rp[min(r0 + n, R)], rb = st.rp[min(r0 + n + 1, R)];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int j = n / 4, r = n % 4;
+  int b = E0 / 8 * 8;
+  int c0 = st.col[b + 8 * h + j], c1 = st.col[b + 8 * h + 4 + j];
+  auto at = [](const bf16_t* p) {
+    const uint32_t x = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
+    return (__attribute__((address_space(3))) i16x4_t*)(uintptr_t)x;
+  };
+  for (; b < E1; b += 32) {
+    const bf16_t *x0 = rows + c0 * PITCH + 4 * r, *x1 = rows + c1 * PITCH + 4 * r;
+    i16x4_t lo4[NQ], hi4[NQ];
+#pragma unroll
+    for (int ta = 0; ta < NQ; ++ta) {
+      lo4[ta] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at(x0 + 16 * ta));
+      hi4[ta] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(at(x1 + 16 * ta));
+    }
+    const int slot = b + 8 * h;
+    uint4 s[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s[q] = *reinterpret_cast<const uint4*>(st.split + q * st.stride + slot);
+    c0 = st.col[slot + 32 + j];
+    c1 = st.col[slot + 36 + j];
+    const int from = min(max(ra - slot, 0), 8), to = min(max(rb - slot, 0), 8);
+    const uint4 pm = pair_mask[((1 << to) - 1) & ~((1 << from) - 1)];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      s[q].x &= pm.x;
+      s[q].y &= pm.y;
+      s[q].z &= pm.z;
+      s[q].w &= pm.w;
+    }
+#pragma unroll
+    for (int ta = 0; ta < NQ; ++ta) {
+      uint4 a;
+      const uint2 u = __builtin_bit_cast(uint2, lo4[ta]), v = __builtin_bit_cast(uint2, hi4[ta]);
+      a = make_uint4(u.x, u.y, v.x, v.y);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) acc[ta] = mfma32(a, s[q], acc[ta]);
+    }
+  }
+}
+
+// gw[ta][tb] += Hprev^T x over the 16 rows of the tile at r0: `tile` is this wavefront's LDS for x, PITCH
+// the pitch of Hprev's rows; STAGED: these are in LDS, and zero past row R.
+template <typename T, int D, int STAGED, int PITCH>
+__device__ __forceinline__ void weight_gradient(const T* Hprev, int r0, int R, const f32x4 (&x)[TF<D>::NQ],
+                                                const Packed<D>& p, float* tile, int n, int h,
+                                                f32x4 (&gw)[TF<D>::NQ][TF<D>::NQ]) {
+  using K = SK<T, D>;
+  constexpr int NQ = K::NQ, PT = K::PT;
+  if constexpr (K::BF) {
+    i16x4_t av[NQ], bv[NQ];
+    if constexpr (!STAGED) {
+#pragma unroll
+      for (int ta = 0; ta < NQ; ++ta)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = r0 + 4 * h + e;
+          av[ta][e] = r < R ? static_cast<short>(Hprev[static_cast<size_t>(r) * PITCH + 16 * ta + n]) : short{0};
+        }
+    }
+    bf16_t* tb16 = reinterpret_cast<bf16_t*>(tile);
+#pragma unroll
+    for (int s = 0; s < D / 32; ++s) {
+      *reinterpret_cast<uint2*>(tb16 + n * K::PG + 32 * s + 4 * h) = make_uint2(p.s[s].x, p.s[s].y);
+      *reinterpret_cast<uint2*>(tb16 + n * K::PG + 32 * s + 16 + 4 * h) = make_uint2(p.s[s].z, p.s[s].w);
+    }
+    wave_lds_handoff();
+    if constexpr (STAGED)
+#pragma unroll
+      for (int ta = 0; ta < NQ; ++ta) av[ta] = lds_read_columns(Hprev + (r0 + 4 * h) * PITCH + 16 * ta, PITCH, n);
+#pragma unroll
+    for (int tb = 0; tb < NQ; ++tb) bv[tb] = lds_read_columns(tb16 + 4 * h * K::PG + 16 * tb, K::PG, n);
+#pragma unroll
+    for (int ta = 0; ta < NQ; ++ta)
+#pragma unroll
+      for (int tb = 0; tb < NQ; ++tb) gw[ta][tb] = mfma16(av[ta], bv[tb], gw[ta][tb]);
+  } else {
+    float av[4][NQ];  // contraction index h of step s: row 4 s + h
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int ta = 0; ta < NQ; ++ta) {
+        const int r = r0 + 4 * s + h;
+        av[s][ta] = (STAGED || r < R) && (D >= 16 || n < D) ? Hprev[static_cast<size_t>(r) * PITCH + 16 * ta + n] : 0.f;
+      }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(tile + n * PT + 16 * q + 4 * h) = x[q];
+    wave_lds_handoff();
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      float bv[NQ];
+#pragma unroll
+      for (int tb = 0; tb < NQ; ++tb) bv[tb] = tile[(4 * s + h) * PT + 16 * tb + n];
+#pragma unroll
+      for (int ta = 0; ta < NQ; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < NQ; ++tb) gw[ta][tb] = mfma(av[s][ta], bv[tb], gw[ta][tb]);
+    }
+  }
+  wave_lds_handoff();
+}
+
+// What a launch is for; each is compiled by itself.  Training does not carry the gradients' stores, and
+// forward and loss not the registers of the backward pass (which spill, so that a launch of its own started
+// later: 512 subgraphs of 60 rows of width 16, forward 17.6 -> 11.2 us).
+enum class Purpose { kForward, kTrain, kGradients };  // passes 1 and 2; 3; 4
+
+// A weight with Adam's moments: of hidden layers 1 .. L - 1, this thread's elements tid + i NT, then of
+// w_out, element tid.  In registers for all epochs of a launch where that is one element per layer.
+template <typename T, int D, int L>
+struct Weights {
+  using K = SK<T, D>;
+  float w[L - 1], m[L - 1], v[L - 1];  // W_IN_REGISTERS
+  float wo, mo, vo;
+  __device__ __forceinline__ void load(const SmallTrain& a, int k, int tid) {
+    if (K::W_IN_REGISTERS) {
+#pragma unroll
+      for (int l = 0; l < L - 1; ++l) {
+        const size_t at = static_cast<size_t>(k) * D * D + min(tid, D * D - 1);
+        w[l] = a.W[l][at];
+        m[l] = a.mW[l][at];
+        v[l] = a.vW[l][at];
+      }
+    }
+    const size_t at = static_cast<size_t>(k) * D + min(tid, D - 1);
+    wo = a.W[L - 1][at];
+    mo = a.mW[L - 1][at];
+    vo = a.vW[L - 1][at];
+  }
+  __device__ __forceinline__ void store(const SmallTrain& a, int k, int tid) const {
+    if (K::W_IN_REGISTERS && tid < D * D) {
+#pragma unroll
+      for (int l = 0; l < L - 1; ++l) {
+        const size_t at = static_cast<size_t>(k) * D * D + tid;
+        a.W[l][at] = w[l];
+        a.mW[l][at] = m[l];
+        a.vW[l][at] = v[l];
+      }
+    }
+    if (tid < D) {
+      const size_t at = static_cast<size_t>(k) * D + tid;
+      a.W[L - 1][at] = wo;
+      a.mW[L - 1][at] = mo;
+      a.vW[L - 1][at] = vo;
+    }
+  }
+  // to the snapshot
+  __device__ __forceinline__ void keep(const SmallTrain& a, int k, int tid) const {
+#pragma unroll
+    for (int l = 0; l < L - 1; ++l) {
+      const size_t at = static_cast<size_t>(k) * D * D;
+      if (K::W_IN_REGISTERS) {
+        if (tid < D * D) a.W_best[l][at + tid] = w[l];
+      } else {
+        for (int i = tid; i < D * D; i += K::NT) a.W_best[l][at + i] = a.W[l][at + i];
+      }
+    }
+    if (tid < D) a.W_best[L - 1][static_cast<size_t>(k) * D + tid] = wo;
+  }
+};
+
 // The thread's number.  HIDE: unknown to the compiler at the places where it is asked for, so that
 // addresses made from it are worked out again in every phase of an epoch.  Known, they are all made
-// ahead of the loop over the epochs, and held in registers across it they and others spill (three
-// layers of width 32: 75 registers, 33 with this), each reload waiting for every load in flight:
-// 256 subgraphs of 200 rows of width 32, three layers, 47.6 -> 43.9 us per epoch, of 128 rows of width
-// 64 65.2 -> 60.9.  Two layers of width 8 or 16 spill twelve at most, and working the addresses out costs
-// more (200 rows: 14.3 us against 15.0).
+// ahead of the loop over the epochs, and held in registers across it they and others spill, each reload
+// waiting for every load in flight.  Two layers of width 8 or 16 have registers to spare.
 template <bool HIDE>
 __device__ __forceinline__ int thread_number() {
   int tid = threadIdx.x;
@@ -128,130 +621,126 @@ __device__ __forceinline__ int thread_number() {
 }
 
 // Backward of hidden layer l (see BwdArgs), then Adam on W_l (and on w_out by the last layer).
-template <typename T, int D, int L, bool GRADS, bool LAST, bool TO_EMBED>
-__device__ __forceinline__ void backward_layer(const SmallTrain& a, const StreamInLds& st, const GraphView& g, float* smem,
-                               const Carve<D>& cv, const int k, const int R, const size_t first, const AdamStep& adE,
-                               const AdamStep& adW) {
-  using K = SK<D>;
-  constexpr int NQ = K::NQ, DP = K::DP, PT = K::PT, NW = K::NW, WP = K::WP;
+template <typename T, int D, int L, Purpose FOR, int STAGED, bool LAST, bool TO_EMBED, class Stream>
+__device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream& st, float* smem, const Carve<T, D>& cv, const int k, const int R, const size_t first, const AdamStep& adE,
+                               const AdamStep& adW, const bool last_epoch, Weights<T, D, L>& wts) {
+  using K = SK<T, D>;
+  constexpr int NQ = K::NQ, DP = K::DP, NW = K::NW;
   constexpr int l = LAST ? L - 1 : 1;
+  constexpr bool GRADS = FOR == Purpose::kGradients;
+  constexpr int PITCH = STAGED ? K::PE : D;
   static_assert(TO_EMBED == (l == 1), "the layer's number");
-  using Rows = std::conditional_t<LAST, LastRows<D, T>, PlainRows<D, T>>;
+  constexpr bool kMatrix = kMatrixGather<T, STAGED>, kFormed = LAST && STAGED == kAllRows;
+  using Rows = std::conditional_t<LAST && !kFormed, MaskRows<D>, PlainRows<D, T, PITCH>>;
   const int tid = thread_number<(L == 3 || D >= 32)>(), lane = tid % 64, n = lane % 16, h = lane / 16;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  float* gt = smem + cv.sums + wave * K::kWaveLds;
+  float* gt = smem + cv.sums + wave * (kMatrix ? K::kTileGt : K::kSums);
   float* wl = smem + cv.w[l - 1];
-  const T* Hprev = static_cast<const T*>(a.H[l - 1]) + first * D;
+  // rows of Hprev, and of G_Z between two hidden layers (staged: in H_1's place, whose last use is here)
+  T* Hprev = STAGED ? reinterpret_cast<T*>(smem + cv.rows[l - 1]) : static_cast<T*>(a.H[l - 1]) + first * D;
+  T* GZ = STAGED ? reinterpret_cast<T*>(smem + cv.rows[1]) : static_cast<T*>(a.GZ) + first * D;
   Rows rows;
+  f32x4 wo[LAST ? NQ : 1];  // w_out, this lane's features
+  const bf16_t* gathered = reinterpret_cast<const bf16_t*>(smem + (LAST ? cv.rows[2] : cv.rows[1]));  // kMatrix
+  const uint4* pair_mask = reinterpret_cast<const uint4*>(smem + cv.pm);
   if constexpr (LAST) {
-    rows.H = static_cast<const T*>(a.H[l]) + first * D;
-    rows.g_t = smem + cv.p;  // g_t has taken the place of p
+    if constexpr (kFormed) {
+      rows.X = reinterpret_cast<const T*>(smem + cv.rows[2]);
+    } else {
+      rows.mask = reinterpret_cast<const uint32_t*>(smem + cv.mask);
+      rows.g_t = smem + cv.p;  // g_t has taken the place of p
+    }
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) rows.w[q] = *reinterpret_cast<const f32x4*>(smem + cv.wo + 16 * q + 4 * (lane % 4));
+    for (int q = 0; q < NQ; ++q) wo[q] = *reinterpret_cast<const f32x4*>(smem + cv.wo + 16 * q + 4 * h);
   } else {
-    rows.X = static_cast<const T*>(a.GZ) + first * D;
+    rows.X = GZ;
   }
-  f32x4 gw[NQ][NQ], gwo[LAST ? NQ : 1];
+  f32x4 gw[NQ][NQ];
 #pragma unroll
   for (int ta = 0; ta < NQ; ++ta)
 #pragma unroll
     for (int tb = 0; tb < NQ; ++tb) gw[ta][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int q = 0; q < (LAST ? NQ : 1); ++q) gwo[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool update_e = TO_EMBED && !GRADS && a.train_embed;
+  const bool need_gh = !TO_EMBED || (GRADS ? a.gE != nullptr : a.train_embed);
+  constexpr bool kEInLds = STAGED && !K::BF;  // the staged rows are the embeddings themselves
 
-  for (int r0 = wave * kTile; r0 < R; r0 += NW * kTile) {
+  for (int r0 = wave * kTile; r0 < R; r0 += K::NW * kTile) {
     const int row = r0 + n, safe = min(row, R - 1);
-    // rows of Hprev as the A operand of the weight gradient
-    float av[4][NQ];
+    f32x4 e[TO_EMBED ? NQ : 1], m[TO_EMBED ? NQ : 1], v[TO_EMBED ? NQ : 1];
+    auto request_state = [&]() {
+      if (!update_e) return;
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int ta = 0; ta < NQ; ++ta) {
-        const int hr = r0 + 4 * s + h;
-        av[s][ta] = hr < R && (D >= 16 || n < D) ? Store<T>::get(Hprev + static_cast<size_t>(hr) * D + 16 * ta + n) : 0.f;
+      for (int ta = 0; ta < (TO_EMBED ? NQ : 0); ++ta) {
+        if (!kEInLds) e[ta] = load4<D>(a.E + first * D, safe, ta, h);
+        m[ta] = load4<D>(a.mE + first * D, safe, ta, h);
+        v[ta] = load4<D>(a.vE + first * D, safe, ta, h);
       }
-    TileFacts<D> f;
-    f.request(st, r0, R);
-    f.request_entries(st);
+      loads_stay_here();
+    };
+    // width 32: sixteen wavefronts leave 128 registers, too few to hold the state during the gather
+    if (D != 32) request_state();
     f32x4 acc[NQ];
-    aggregate<D>(g, st, rows, f, r0, R, nullptr, gt, acc, [&](const typename Rows::Row& own) {
-      if constexpr (LAST) {
+    if constexpr (kMatrix) aggregate_staged<D, K::PE>(st, gathered, pair_mask, r0, R, acc);
+    else aggregate_rows<D, (LAST || STAGED != kUnstaged)>(st, rows, r0, R, gt, acc);
+    Packed<D> pk;
+    if constexpr (K::BF) pk = pack_tile<D>(acc);
+    weight_gradient<T, D, STAGED, PITCH>(Hprev, r0, R, acc, pk, gt, n, h, gw);
+    if (!need_gh) continue;
+    if (D == 32) request_state();
+    if constexpr (LAST) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-          for (int y = 0; y < 4; ++y) gwo[q][y] = fmaf(own.x[q][y], own.gt, gwo[q][y]);
-      }
-    });
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-#pragma unroll
-      for (int y = 0; y < 4; ++y) acc[q][y] = Store<T>::as_stored(acc[q][y]);
-      *reinterpret_cast<f32x4*>(gt + n * PT + 16 * q + 4 * h) = acc[q];
+      for (int q = 0; q < NQ; ++q) acc[q] *= wo[q];
+      if constexpr (K::BF) pk = pack_tile<D>(acc);
     }
-    wave_lds_handoff();
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      float bv[NQ];
-#pragma unroll
-      for (int tb = 0; tb < NQ; ++tb) bv[tb] = gt[(4 * s + h) * PT + 16 * tb + n];
-#pragma unroll
-      for (int ta = 0; ta < NQ; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < NQ; ++tb) gw[ta][tb] = mfma(av[s][ta], bv[tb], gw[ta][tb]);
-    }
-    wave_lds_handoff();
-    if (TO_EMBED && (GRADS ? a.gE == nullptr : !a.train_embed)) continue;
     const int on = operand_lane<D>(n);
 #pragma unroll
     for (int ta = 0; ta < NQ; ++ta) {
-      f32x4 e, m, v;
-      if (TO_EMBED) {
-        e = load4<D>(a.E + first * D, safe, ta, h);
-        m = load4<D>(a.mE + first * D, safe, ta, h);
-        v = load4<D>(a.vE + first * D, safe, ta, h);
-      } else {
-        e = load4<D>(Hprev, safe, ta, h);
-      }
-      f32x4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const f32x4 w = *reinterpret_cast<const f32x4*>(wl + (16 * ta + on) * WP + 16 * q + 4 * h);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) z = mfma(w[j], acc[q][j], z);
-      }
+      f32x4 z = times_weights<T, D, false>(wl, acc, pk, ta, on, h);
       if (row < R) {
         if constexpr (TO_EMBED && GRADS) {
           store4<D>(a.gE + first * D, row, ta, h, z);
         } else if constexpr (TO_EMBED) {
-          adam_rows(adE, z, e, m, v);
-          store4<D>(a.mE + first * D, row, ta, h, m);
-          store4<D>(a.vE + first * D, row, ta, h, v);
-          store4<D>(a.E + first * D, row, ta, h, e);
-          if constexpr (sizeof(T) == 2) store4<D>(static_cast<T*>(a.Eb) + first * D, row, ta, h, e);
+          f32x4 ee, mm = m[ta], vv = v[ta];
+          if constexpr (kEInLds) ee = load4<D, PITCH>(Hprev, row, ta, h);
+          else ee = e[ta];
+          adam_rows(adE, z, ee, mm, vv);
+          store4<D>(a.mE + first * D, row, ta, h, mm);
+          store4<D>(a.vE + first * D, row, ta, h, vv);
+          if (!kEInLds || last_epoch) store4<D>(a.E + first * D, row, ta, h, ee);
+          if constexpr (STAGED) store4<D, PITCH>(Hprev, row, ta, h, ee);
+          if (K::BF && (!STAGED || last_epoch)) store4<D>(static_cast<T*>(a.Eb) + first * D, row, ta, h, ee);
         } else {
+          const f32x4 hp = load4<D, PITCH>(Hprev, row, ta, h);
 #pragma unroll
-          for (int x = 0; x < 4; ++x) z[x] = e[x] > 0.f ? z[x] : 0.f;
-          store4<D>(static_cast<T*>(a.GZ) + first * D, row, ta, h, z);
+          for (int x = 0; x < 4; ++x) z[x] = hp[x] > 0.f ? z[x] : 0.f;
+          store4<D, PITCH>(GZ, row, ta, h, z);
         }
       }
     }
   }
 
   // the wavefronts' sums of the weight gradient, in order, and Adam on W_l
-  if constexpr (LAST) {
+  const float* Wg = a.W[l - 1] + static_cast<size_t>(k) * D * D;
+  float w[K::PER], mw[K::PER], vw[K::PER];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) {
-        const float s = groups_sum(gwo[q][y]);
-        if (lane < 4) smem[cv.gwo + wave * DP + 16 * q + 4 * lane + y] = s;
+  for (int i = 0; i < K::PER; ++i) {
+    const int idx = min(tid + i * K::NT, D * D - 1);
+    if (!GRADS && K::W_IN_REGISTERS) {
+      w[i] = wts.w[l - 1];
+      mw[i] = wts.m[l - 1];
+      vw[i] = wts.v[l - 1];
+    } else {
+      w[i] = Wg[idx];
+      if (!GRADS) {
+        mw[i] = a.mW[l - 1][static_cast<size_t>(k) * D * D + idx];
+        vw[i] = a.vW[l - 1][static_cast<size_t>(k) * D * D + idx];
       }
+    }
   }
-  __syncthreads();  // the row sums have served
-  constexpr bool kHalves = DP * DP > K::kWaveLds;  // the place holds half the wavefronts' sums
-  constexpr int kSlots = kHalves ? NW / 2 : NW;
-  static_assert(kSlots * DP * DP <= NW * K::kWaveLds, "room for the sums");
-  float* slots = smem + cv.sums;
+  loads_stay_here();
+  sync_lds();  // the row sums have served
+  constexpr int kSlots = kMatrix ? K::kMatrixSlots : K::kSlots;
+  float* slots = smem + cv.slots;
   auto each = [&](auto&& fn) {
     float* mine = slots + (wave % kSlots) * DP * DP;
 #pragma unroll
@@ -261,80 +750,79 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
 #pragma unroll
         for (int r = 0; r < 4; ++r) fn(mine[(16 * ta + 4 * h + r) * DP + 16 * tb + n], gw[ta][tb][r]);
   };
-  if (wave >= NW - kSlots) each([](float& place, float x) { place = x; });
-  __syncthreads();
-  if (kHalves) {
-    if (wave < kSlots) each([](float& place, float x) { place = x + place; });
-    __syncthreads();
+#pragma unroll
+  for (int turn = 0; turn * kSlots < NW; ++turn) {
+    if (wave / kSlots == turn) {
+      if (turn == 0) each([](float& place, float x) { place = x; });
+      else each([](float& place, float x) { place += x; });
+    }
+    sync_lds();
   }
-  if constexpr (GRADS) {
-    for (int idx = tid; idx < D * D; idx += K::NT) {
+  float column = 0.f;  // this thread's share of the gradient of w_out
+#pragma unroll
+  for (int i = 0; i < K::PER; ++i) {
+    const int idx = tid + i * K::NT;
+    if (idx < D * D) {
+      const int r = idx / D, c = idx % D;
       float s = 0.f;
 #pragma unroll
-      for (int q = 0; q < kSlots; ++q) s += slots[q * DP * DP + idx / D * DP + idx % D];
-      a.gW[l - 1][static_cast<size_t>(k) * D * D + idx] = s;
+      for (int q = 0; q < kSlots; ++q) s += slots[q * DP * DP + r * DP + c];
+      if (LAST) {
+        column = fmaf(Store<T>::as_stored(w[i]), s, column);
+        s *= smem[cv.wo + c];
+      }
+      const size_t at = static_cast<size_t>(k) * D * D + idx;
+      if constexpr (GRADS) {
+        a.gW[l - 1][at] = s;
+      } else {
+        adam_value(adW, s, w[i], mw[i], vw[i]);
+        if (K::W_IN_REGISTERS) {
+          wts.w[l - 1] = w[i];
+          wts.m[l - 1] = mw[i];
+          wts.v[l - 1] = vw[i];
+        } else {
+          a.W[l - 1][at] = w[i];
+          a.mW[l - 1][at] = mw[i];
+          a.vW[l - 1][at] = vw[i];
+        }
+        put_weight<T, D>(wl, r, c, w[i]);
+      }
     }
-    if (LAST && tid < D) {
+  }
+  if constexpr (LAST) {
+    if (D <= 8) column += rotated<8>(column);
+    if (D <= 16) column = add_over_h(column);
+    else if (D == 32) column += __shfl_xor(column, 32, 64);
+    if (lane < D) smem[cv.gwo + wave * DP + lane] = column;
+    sync_lds();
+    if (tid < D) {
       float s = 0.f;
 #pragma unroll
       for (int q = 0; q < NW; ++q) s += smem[cv.gwo + q * DP + tid];
-      a.gW[L - 1][static_cast<size_t>(k) * D + tid] = s;
+      if constexpr (GRADS) {
+        a.gW[L - 1][static_cast<size_t>(k) * D + tid] = s;
+      } else {
+        adam_value(adW, s, wts.wo, wts.mo, wts.vo);
+        smem[cv.wo + tid] = wts.wo;
+      }
     }
-    __syncthreads();
-    return;
   }
-  float* W = a.W[l - 1] + static_cast<size_t>(k) * D * D;
-  float* mW = a.mW[l - 1] + static_cast<size_t>(k) * D * D;
-  float* vW = a.vW[l - 1] + static_cast<size_t>(k) * D * D;
-  for (int idx = tid; idx < D * D; idx += K::NT) {
-    const int r = idx / D, c = idx % D;
-    float w = W[idx], m = mW[idx], v = vW[idx], s = 0.f;
-#pragma unroll
-    for (int q = 0; q < kSlots; ++q) s += slots[q * DP * DP + r * DP + c];
-    adam_value(adW, s, w, m, v);
-    W[idx] = w;
-    mW[idx] = m;
-    vW[idx] = v;
-    wl[r * WP + c] = Store<T>::as_stored(w);
-  }
-  if (LAST && tid < D) {
-    const size_t idx = static_cast<size_t>(k) * D + tid;
-    float w = a.W[L - 1][idx], m = a.mW[L - 1][idx], v = a.vW[L - 1][idx], s = 0.f;
-#pragma unroll
-    for (int q = 0; q < NW; ++q) s += smem[cv.gwo + q * DP + tid];
-    adam_value(adW, s, w, m, v);
-    a.W[L - 1][idx] = w;
-    a.mW[L - 1][idx] = m;
-    a.vW[L - 1][idx] = v;
-    smem[cv.wo + tid] = w;
-  }
-  __syncthreads();
+  // rows of E or G_Z in memory are gathered next
+  if (STAGED) sync_lds();
+  else __syncthreads();
 }
 
-// Copies the weight sets of subgraph k to the snapshot.
-template <int D, int L>
-__device__ __forceinline__ void keep_weights(const SmallTrain& a, int k) {
-#pragma unroll
-  for (int l = 0; l < L; ++l) {
-    const int elems = l < L - 1 ? D * D : D;
-    for (int i = threadIdx.x; i < elems; i += SK<D>::NT)
-      a.W_best[l][static_cast<size_t>(k) * elems + i] = a.W[l][static_cast<size_t>(k) * elems + i];
-  }
-}
-
-// What a launch is for; each is compiled by itself.  Training does not carry the gradients' stores, and
-// forward and loss not the registers of the backward pass (which spill, so that a launch of its own started
-// later: 512 subgraphs of 60 rows of width 16, forward 17.6 -> 11.2 us).
-enum class Purpose { kForward, kTrain, kGradients };  // passes 1 and 2; 3; 4
-
-template <typename T, int D, int L, Purpose FOR>
-__global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, SmallTrain a) {
-  using K = SK<D>;
-  constexpr int NQ = K::NQ, DP = K::DP, NW = K::NW, NT = K::NT, WP = K::WP;
+template <typename T, int D, int L, Purpose FOR, int STAGED>
+__global__ __launch_bounds__((SK<T, D>::NT)) void small_train_kernel(GraphView g, SmallTrain a) {
+  using K = SK<T, D>;
+  constexpr int NQ = K::NQ, DP = K::DP, NW = K::NW, NT = K::NT;
+  constexpr int PITCH = STAGED ? K::PE : D;
   extern __shared__ __align__(16) float smem[];
   const int k = blockIdx.x;
   if (g.loss_ptr[k + 1] == g.loss_ptr[k]) return;  // the subgraph sits out
   const int rbeg = g.part_rows[k], R = g.part_rows[k + 1] - rbeg;
+  Weights<T, D, L> wts;
+  if (FOR == Purpose::kTrain) wts.load(a, k, threadIdx.x);
   if (R == 0) {  // no rows: a loss of nothing
     if (a.passes == 1) return;
     if constexpr (FOR == Purpose::kGradients) {
@@ -346,9 +834,9 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
       return;
     }
     for (int ep = threadIdx.x; ep < a.epochs; ep += NT) a.loss_partial[static_cast<size_t>(ep) * g.num_loss_slots + k] = 0.0;
-    if (a.best_loss != nullptr && a.best_loss[k] > 0.0) {  // its one model, whose loss is 0 from the first epoch on
+    if (FOR == Purpose::kTrain && a.best_loss != nullptr && a.best_loss[k] > 0.0) {  // its one model, whose loss is 0 from the first epoch on
       __syncthreads();
-      keep_weights<D, L>(a, k);
+      wts.keep(a, k, threadIdx.x);
       if (threadIdx.x == 0) {
         a.best_loss[k] = 0.0;
         a.has_best[k] = 1;
@@ -359,7 +847,8 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   const size_t first = rbeg;
   const bool mean = g.wval != g.wval_t;
   const int es = g.wrowptr[rbeg], En = g.wrowptr[rbeg + R] - es;
-  const Carve<D> cv(L, R, En, mean);
+  const Carve<T, D> cv(L, R, En, mean, STAGED);
+  constexpr bool kMatrix = kMatrixGather<T, STAGED>;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   int* rp = reinterpret_cast<int*>(smem + cv.rp);
@@ -368,45 +857,108 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
   double* lowest = dred + NW;
   int* lower = reinterpret_cast<int*>(lowest + 1);
 
-  for (int i = tid; i <= R; i += NT) rp[i] = g.wrowptr[rbeg + i] - es;
-  for (int i = tid; i < R; i += NT) smem[cv.c + i] = a.c[rbeg + i];
-  for (int e = tid; e < En + kSmallPad; e += NT) {
-    uint2 x = make_uint2(0u, 0u);
-    if (e < En) {
-      x.x = static_cast<uint32_t>(g.went[es + e].x - rbeg) | static_cast<uint32_t>(g.wrowid[es + e] - rbeg) << 16;
-      x.y = __float_as_uint(g.wval[es + e]);
+  // first entries of the rows, each row filled up to whole batches: a scan over the rows by the first wavefront
+  if (wave == 0) {
+    int at = 0;
+    for (int r = 0; r < R; r += 64) {
+      const int i = r + tid;
+      int len = i < R ? g.wrowptr[rbeg + i + 1] - g.wrowptr[rbeg + i] : 0;
+      if (!kMatrix) len = (len + kBatch - 1) / kBatch * kBatch;
+      int before = len;
+#define GCO_STEP(C, M) before += dpp_move<C, M>(0, before);
+      GCO_SCAN_STEPS(GCO_STEP)
+#undef GCO_STEP
+      if (i < R) rp[i] = at + before - len;
+      at += __builtin_amdgcn_readlane(before, 63);
     }
-    ent[e] = x;
-    if (mean) smem[cv.valt + e] = e < En ? g.wval_t[es + e] : 0.f;
+    if (tid == 0) rp[R] = at;
+  }
+  for (int i = tid; i < R; i += NT) smem[cv.c + i] = a.c[rbeg + i];
+  if (tid == 0) {  // column R of the vectors, and of the mask
+    smem[cv.t + R] = smem[cv.p + R] = 0.f;
+    if (!kMatrix)
+#pragma unroll
+      for (int x = 0; x < K::NM; ++x) reinterpret_cast<uint32_t*>(smem + cv.mask)[R * K::NM + x] = 0u;
+  }
+  __syncthreads();
+  const int none = rp[R];
+  uint16_t* col = reinterpret_cast<uint16_t*>(smem + cv.col);
+  bf16_t* split[3];
+  for (int q = 0; q < 3; ++q) split[q] = reinterpret_cast<bf16_t*>(smem + cv.split[q]);
+  const int stride = (none + kSmallPad + 7) / 8 * 8;  // of a part of the split values
+  if constexpr (kMatrix) {
+    const int es = g.wrowptr[rbeg];
+    for (int e = tid; e < stride; e += NT) {
+      const bool in = e < En;
+      col[e] = static_cast<uint16_t>(in ? g.went[es + e].x - rbeg : R);
+      put_split(split[0], stride, e, in ? g.wval[es + e] : 0.f);
+      put_split(split[2], stride, e, 0.f);
+      if (mean) put_split(split[1], stride, e, in ? g.wval_t[es + e] : 0.f);
+    }
+    uint4* pair_mask = reinterpret_cast<uint4*>(smem + cv.pm);  // halves all ones where the bit of the pattern is set
+    for (int x = tid; x < 256; x += NT) {
+      uint32_t d[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        d[q] = ((x >> (2 * q)) & 1 ? 0xffffu : 0u) | ((x >> (2 * q + 1)) & 1 ? 0xffff0000u : 0u);
+      pair_mask[x] = make_uint4(d[0], d[1], d[2], d[3]);
+    }
+  } else {
+    for (int i = tid; i < R * kBatch; i += NT) {  // four threads a row
+      const int r = i / kBatch, from = g.wrowptr[rbeg + r], len = g.wrowptr[rbeg + r + 1] - from, to = rp[r];
+      for (int e = i % kBatch; e < rp[r + 1] - to; e += kBatch) {
+        const int c = e < len ? g.went[from + e].x - rbeg : R;
+        ent[to + e] = make_uint2(static_cast<uint32_t>(c) | static_cast<uint32_t>(e < len ? c : r) << 16,
+                                 e < len ? __float_as_uint(g.wval[from + e]) : 0u);
+        if (mean) smem[cv.valt + to + e] = e < len ? g.wval_t[from + e] : 0.f;
+      }
+    }
+    for (int e = tid; e < kSmallPad; e += NT) {
+      ent[none + e] = make_uint2(static_cast<uint32_t>(R), 0u);
+      if (mean) smem[cv.valt + none + e] = 0.f;
+    }
   }
 #pragma unroll
   for (int l = 1; l < L; ++l)
     for (int idx = tid; idx < DP * DP; idx += NT) {
       const int r = idx / DP, c = idx % DP;
-      smem[cv.w[l - 1] + r * WP + c] =
-          r < D && c < D ? Store<T>::as_stored(a.W[l - 1][static_cast<size_t>(k) * D * D + r * D + c]) : 0.f;
+      put_weight<T, D>(smem + cv.w[l - 1], r, c,
+                       r < D && c < D ? a.W[l - 1][static_cast<size_t>(k) * D * D + r * D + c] : 0.f);
     }
   if (tid < DP) smem[cv.wo + tid] = tid < D ? a.W[L - 1][static_cast<size_t>(k) * D + tid] : 0.f;
   if (tid == 0) *lowest = a.best_loss != nullptr ? a.best_loss[k] : 0.0;
-  __syncthreads();
-  const StreamInLds fwd{ent, nullptr, rp};
-  const StreamInLds bwd{ent, mean ? smem + cv.valt : nullptr, rp};
-
-  // width-1 phases: whole rows of this wavefront, cut at equal shares of the entries
-  auto first_row_from = [&](int e) {
-    int lo = 0, hi = R;  // the first row whose entries begin at e or later
-    while (lo < hi) {
-      const int mid = (lo + hi) / 2;
-      if (rp[mid] >= e) hi = mid; else lo = mid + 1;
+  if constexpr (STAGED) {
+    T* place = reinterpret_cast<T*>(smem + cv.rows[0]);
+    const T* from = static_cast<const T*>(a.H[0]) + first * D;
+    const int whole = Carve<T, D>::padded_rows(R);
+    constexpr int kVec = 16 / sizeof(T), kPieces = D / kVec;  // 16 bytes at a time
+    for (int i = tid; i < whole * kPieces; i += NT) {
+      const int r = i / kPieces, x = (i % kPieces) * kVec;
+      uint4 u = make_uint4(0u, 0u, 0u, 0u);
+      if (r < R) u = *reinterpret_cast<const uint4*>(from + static_cast<size_t>(r) * D + x);
+      *reinterpret_cast<uint4*>(place + r * K::PE + x) = u;
+      if (L == 3 && r >= R)
+        *reinterpret_cast<uint4*>(reinterpret_cast<T*>(smem + cv.rows[1]) + r * K::PE + x) = u;
+      if (STAGED == kAllRows && r >= R)
+        *reinterpret_cast<uint4*>(reinterpret_cast<T*>(smem + cv.rows[2]) + r * K::PE + x) = u;
     }
-    return lo;
-  };
-  const int e0 = rp[first_row_from(static_cast<int>(static_cast<int64_t>(En) * wave / NW))];
-  const int e1 = rp[first_row_from(static_cast<int>(static_cast<int64_t>(En) * (wave + 1) / NW))];
+  }
+  __syncthreads();
+  // of A_hat and of its transpose
+  const auto fwd = [&] {
+    if constexpr (kMatrix) return SplitStream{col, split[0], stride, rp, none};
+    else return StreamInLds{ent, nullptr, rp, none};
+  }();
+  const auto bwd = [&] {
+    if constexpr (kMatrix) return SplitStream{col, split[1], stride, rp, none};
+    else return StreamInLds{ent, mean ? smem + cv.valt : nullptr, rp, none};
+  }();
   float *tv = smem + cv.t, *pv = smem + cv.p;
+  uint32_t* mask = reinterpret_cast<uint32_t*>(smem + cv.mask);
 
   for (int ep = 0; ep < a.epochs; ++ep) {
     const int tid = thread_number<(L == 3 || D == 64)>(), lane = tid % 64, n = lane % 16, h = lane / 16;
+    const bool last_epoch = ep == a.epochs - 1;
     AdamStep adE = a.adam, adW = a.adam;
     if (a.adam.per_part != nullptr) {
       const float2* bc = a.adam.per_part + static_cast<size_t>(ep) * (2 * g.P);  // [P] embeddings, [P] weights
@@ -421,67 +973,94 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
     // hidden layers of Eq. 3; the last one also leaves t = H w_out
 #pragma unroll
     for (int l = 1; l < L; ++l) {
-      const PlainRows<D, T> rows{static_cast<const T*>(a.H[l - 1]) + first * D};
+      const bool last = l == L - 1;
+      using Rows = PlainRows<D, T, PITCH>;
+      const Rows rows{STAGED ? reinterpret_cast<const T*>(smem + cv.rows[l - 1])
+                             : static_cast<const T*>(a.H[l - 1]) + first * D};
       T* Y = static_cast<T*>(a.H[l]) + first * D;
+      // H is read again only where it is the next layer's input, and through gco_get_hidden
+      const bool to_memory = FOR != Purpose::kTrain || last_epoch || (!STAGED && !last);
       const float* wl = smem + cv.w[l - 1];
-      float* sums = smem + cv.sums + wave * K::kWaveLds;
+      float* sums = smem + cv.sums + wave * K::kSums;
+      if (kMatrix && last && wave == NW - 1 && lane < K::PE / 8)  // [H > 0] of row R, where the slots were
+        reinterpret_cast<uint4*>(smem + cv.rows[2])[R * (K::PE / 8) + lane] = make_uint4(0u, 0u, 0u, 0u);
       for (int r0 = wave * kTile; r0 < R; r0 += NW * kTile) {
         const int row = r0 + n;
-        TileFacts<D> f;
-        f.request(fwd, r0, R);
-        f.request_entries(fwd);
         f32x4 acc[NQ];
-        aggregate<D>(g, fwd, rows, f, r0, R, nullptr, sums, acc, [](const typename PlainRows<D, T>::Row&) {});
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-          for (int y = 0; y < 4; ++y) acc[q][y] = Store<T>::as_stored(acc[q][y]);
+        if constexpr (kMatrix)
+          aggregate_staged<D, K::PE>(fwd, rows.X, reinterpret_cast<const uint4*>(smem + cv.pm), r0, R, acc);
+        else
+          aggregate_rows<D, (STAGED != kUnstaged)>(fwd, rows, r0, R, sums, acc);
+        Packed<D> pk;
+        if constexpr (K::BF) pk = pack_tile<D>(acc);
         float part = 0.f;
+        uint32_t bits[NQ];
         const int on = operand_lane<D>(n);
 #pragma unroll
         for (int ta = 0; ta < NQ; ++ta) {
-          f32x4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) z = mfma(wl[(16 * q + 4 * h + j) * WP + 16 * ta + on], acc[q][j], z);
+          f32x4 z = times_weights<T, D, true>(wl, acc, pk, ta, on, h);
+          bits[ta] = 0u;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             z[j] = Store<T>::as_stored(fmaxf(z[j], 0.f));
-            if (l == L - 1) part = fmaf(z[j], smem[cv.wo + 16 * ta + 4 * h + j], part);
+            if (last) {
+              part = fmaf(z[j], smem[cv.wo + 16 * ta + 4 * h + j], part);
+              bits[ta] |= z[j] > 0.f ? 1u << j : 0u;
+            }
           }
-          if (row < R) store4<D>(Y, row, ta, h, z);
+          if (row < R) {
+            if (kMatrix && last && FOR != Purpose::kForward) {
+              constexpr uint32_t one = 0x3f80u;
+              reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(smem + cv.rows[2]) + row * K::PE + 16 * ta + 4 * h)[0] =
+                  make_uint2((z[0] > 0.f ? one : 0u) | (z[1] > 0.f ? one << 16 : 0u),
+                             (z[2] > 0.f ? one : 0u) | (z[3] > 0.f ? one << 16 : 0u));
+            }
+            if (to_memory) store4<D>(Y, row, ta, h, z);
+            if (STAGED && !last) store4<D, PITCH>(reinterpret_cast<T*>(smem + cv.rows[1]), row, ta, h, z);
+          }
         }
-        if (l == L - 1) {
-          part += __shfl_xor(part, 16, 64);
-          part += __shfl_xor(part, 32, 64);
-          if (h == 0 && row < R) tv[row] = part;
+        if (last) {
+          part = add_over_h(part);
+          uint32_t m[K::NM];
+          if (FOR != Purpose::kForward && !kMatrix)
+#pragma unroll
+            for (int x = 0; x < K::NM; ++x)
+              m[x] = or_over_h((bits[2 * x] | (2 * x + 1 < NQ ? bits[2 * x + 1 < NQ ? 2 * x + 1 : 0] << 16 : 0u)) << (4 * h));
+          if (h == 0 && row < R) {
+            tv[row] = part;
+            if (FOR != Purpose::kForward && !kMatrix)
+#pragma unroll
+              for (int x = 0; x < K::NM; ++x) mask[row * K::NM + x] = m[x];
+          }
         }
       }
-      __syncthreads();
+      if (STAGED || last) sync_lds();
+      else __syncthreads();  // H_l is gathered next
     }
     // Eq. 4, the loss of Eq. 5 with its derivative, and the first backward aggregation
-    const bool keep_p = ep == a.epochs - 1;
-    scan_rows(fwd, e0, e1, [&](const Entry& en) { return en.val * tv[en.col]; },
-              [&](int row, float s) {
-                const float p = 1.f / (1.f + expf(-s));
-                pv[row] = p;
-                if (keep_p) a.p[rbeg + row] = p;
-              });
+    sum_rows<NW>(fwd, R, wave, [&](int e, int) { return fwd.product(e, tv); },
+                 [&](int row, float s, int part) {
+                   const float p = 1.f / (1.f + expf(-s));
+                   if (part == 0) pv[row] = p;
+                   if (part == 1 && last_epoch) a.p[rbeg + row] = p;
+                 });
     if (FOR == Purpose::kForward && a.passes == 1) return;
-    __syncthreads();
+    sync_lds();
     double lsum = 0.0;
-    scan_rows(fwd, e0, e1, [&](const Entry& en) { return en.col == en.row ? 0.f : pv[en.col]; },
-              [&](int row, float s) {
-                const float p = pv[row], c = smem[cv.c + row];
-                tv[row] = (c + a.q * s) * p * (1.f - p);
-                lsum += static_cast<double>(p) *
-                        (static_cast<double>(c) + 0.5 * static_cast<double>(a.q) * static_cast<double>(s));
-              });
-    lsum = wave_sum(lsum);
-    if (lane == 0) dred[wave] = lsum;
-    __syncthreads();
-    if (tid == 0) {
+    // a row's first entry is the diagonal one, which counts nothing
+    sum_rows<NW>(fwd, R, wave, [&](int e, int begin) { return e == begin ? 0.f : pv[fwd.column(e)]; },
+                 [&](int row, float s, int part) {
+                   const float p = pv[row], c = smem[cv.c + row];
+                   if (part == 0) tv[row] = (c + a.q * s) * p * (1.f - p);
+                   if (part == 0)
+                     lsum += static_cast<double>(p) *
+                             (static_cast<double>(c) + 0.5 * static_cast<double>(a.q) * static_cast<double>(s));
+                 });
+    lsum = wave_total(lsum);
+    if (lane == 63) dred[wave] = lsum;
+    sync_lds();
+    // by the last wavefront, which has the fewest tiles
+    if (tid == NT - 64) {
       double total = 0.0;
 #pragma unroll
       for (int w = 0; w < NW; ++w) total += dred[w];
@@ -496,61 +1075,109 @@ __global__ __launch_bounds__(SK<D>::NT) void small_train_kernel(GraphView g, Sma
     if constexpr (FOR == Purpose::kForward) {
       return;
     } else {
-    scan_rows(bwd, e0, e1, [&](const Entry& en) { return en.val * tv[en.col]; },
-              [&](int row, float s) { pv[row] = s; });
-    __syncthreads();
-    if (*lower) {  // the parameters this loss belongs to, before they change
-      const float4* from = reinterpret_cast<const float4*>(a.E + first * D);
-      float4* to = reinterpret_cast<float4*>(a.E_best + first * D);
-      for (int i = tid; i < R * (D / 4); i += NT) to[i] = from[i];
-      keep_weights<D, L>(a, k);
-      __syncthreads();
-    }
-    constexpr bool kGrads = FOR == Purpose::kGradients;
-    if constexpr (L == 2) {
-      backward_layer<T, D, L, kGrads, true, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
-    } else {
-      backward_layer<T, D, L, kGrads, true, false>(a, bwd, g, smem, cv, k, R, first, adE, adW);
-      backward_layer<T, D, L, kGrads, false, true>(a, bwd, g, smem, cv, k, R, first, adE, adW);
-    }
+      uint32_t* mask = reinterpret_cast<uint32_t*>(smem + cv.mask);
+      sum_rows<NW>(bwd, R, wave, [&](int e, int) { return bwd.product(e, tv); },
+                   [&](int row, float s, int part) {
+                     if constexpr (STAGED == kAllRows) {  // the rows of g_t [H > 0]
+#pragma unroll
+                       for (int q = 0; q < NQ; ++q) {
+                         const uint32_t m = mask[row * K::NM + q / 2] >> (16 * (q % 2) + 4 * part);
+                         f32x4 x;
+#pragma unroll
+                         for (int j = 0; j < 4; ++j) x[j] = (m >> j) & 1u ? s : 0.f;
+                         store4<D, PITCH>(reinterpret_cast<T*>(smem + cv.rows[2]), row, q, part, x);
+                       }
+                     } else if (part == 0) {
+                       pv[row] = s;
+                     }
+                   });
+      sync_lds();
+      if constexpr (kMatrix) {
+        for (int e = tid; e < none; e += NT) put_split(split[2], stride, e, bwd.product(e, pv));
+        sync_lds();
+      }
+      if (FOR == Purpose::kTrain && *lower) {  // the parameters this loss belongs to, before they change
+        __syncthreads();  // E in memory is that of every wavefront
+        for (int i = tid; i < R * (D / 4); i += NT) {
+          const int r = i / (D / 4), x = i % (D / 4);
+          const float* from = STAGED && !K::BF ? smem + cv.rows[0] + r * K::PE : a.E + (first + r) * D;
+          reinterpret_cast<float4*>(a.E_best + (first + r) * D)[x] = reinterpret_cast<const float4*>(from)[x];
+        }
+        wts.keep(a, k, tid);
+        __syncthreads();
+      }
+      // what the entries of the last layer's gather count for
+      auto last_stream = bwd;
+      if constexpr (kMatrix) last_stream.split = split[2];
+      if constexpr (L == 2) {
+        backward_layer<T, D, L, FOR, STAGED, true, true>(a, last_stream, smem, cv, k, R, first, adE, adW, last_epoch, wts);
+      } else {
+        backward_layer<T, D, L, FOR, STAGED, true, false>(a, last_stream, smem, cv, k, R, first, adE, adW, last_epoch, wts);
+        backward_layer<T, D, L, FOR, STAGED, false, true>(a, bwd, smem, cv, k, R, first, adE, adW, last_epoch, wts);
+      }
     }
   }
+  if (FOR == Purpose::kTrain) wts.store(a, k, threadIdx.x);
 }
 
 template <typename T, int D, int L>
-void launch_t(const Launch& ln, const GraphView& g, const SmallTrain& a, size_t lds) {
-  auto run = [&](auto kernel) {
+void launch_t(const Launch& ln, const GraphView& g, const SmallTrain& a, const SmallLds& lds) {
+  constexpr int kThreads = SK<T, D>::NT;
+  auto run = [&](auto kernel, size_t bytes) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              static_cast<int>(lds));
-    kernel<<<g.P, SK<D>::NT, lds, ln.st>>>(g, a);
+                              static_cast<int>(bytes));
+    kernel<<<g.P, kThreads, bytes, ln.st>>>(g, a);
   };
-  if (a.passes <= 2) run(small_train_kernel<T, D, L, Purpose::kForward>);
-  else if (a.passes == 3) run(small_train_kernel<T, D, L, Purpose::kTrain>);
-  else run(small_train_kernel<T, D, L, Purpose::kGradients>);
+  // the forward pass takes its sums in one order whatever the launch is for
+  constexpr int kOther = sizeof(T) == 2 ? kRows : kUnstaged;
+  const bool other = kOther == kRows && lds.rows != 0;
+  const size_t bytes = other ? lds.rows : lds.unstaged;
+  if (a.passes <= 2) {
+    if (other) run(small_train_kernel<T, D, L, Purpose::kForward, kOther>, bytes);
+    else run(small_train_kernel<T, D, L, Purpose::kForward, kUnstaged>, bytes);
+  } else if (a.passes == 4) {
+    if (other) run(small_train_kernel<T, D, L, Purpose::kGradients, kOther>, bytes);
+    else run(small_train_kernel<T, D, L, Purpose::kGradients, kUnstaged>, bytes);
+  } else {
+    if constexpr (sizeof(T) == 4 && D <= 32)
+      if (lds.all_rows != 0) return run(small_train_kernel<T, D, L, Purpose::kTrain, kAllRows>, lds.all_rows);
+    if (lds.rows != 0) run(small_train_kernel<T, D, L, Purpose::kTrain, kRows>, lds.rows);
+    else run(small_train_kernel<T, D, L, Purpose::kTrain, kUnstaged>, lds.unstaged);
+  }
 }
 
 template <typename T, int D>
-void launch_l(const Launch& ln, int L, const GraphView& g, const SmallTrain& a, size_t lds) {
+void launch_l(const Launch& ln, int L, const GraphView& g, const SmallTrain& a, const SmallLds& lds) {
   if (L == 2) launch_t<T, D, 2>(ln, g, a, lds);
   else if (L == 3) launch_t<T, D, 3>(ln, g, a, lds);
 }
 
 }  // namespace
 
-size_t small_train_lds_bytes(int D, int L, int rows, int entries, bool mean) {
-  size_t floats = 0;
-  switch (D) {
-    case 8: floats = Carve<8>(L, rows, entries, mean).end; break;
-    case 16: floats = Carve<16>(L, rows, entries, mean).end; break;
-    case 32: floats = Carve<32>(L, rows, entries, mean).end; break;
-    case 64: floats = Carve<64>(L, rows, entries, mean).end; break;
-    default: return static_cast<size_t>(-1);
+SmallLds small_train_lds(int storage, int D, int L, int rows, int entries, bool mean, size_t limit) {
+  auto of = [&](auto carve) {
+    auto fits = [&](int staged) {
+      const size_t bytes = carve(staged) * sizeof(float);
+      return bytes <= limit ? bytes : 0;
+    };
+    return SmallLds{fits(kUnstaged), fits(kRows), fits(kAllRows)};
+  };
+  if (rows >= 0xffff) return SmallLds{};  // columns and rows are numbered in 16 bits
+  if (storage == GCO_STORAGE_BF16) {
+    if (D != 64) return SmallLds{};
+    return of([&](int s) { return Carve<bf16_t, 64>(L, rows, entries, mean, s).end; });
   }
-  return floats * sizeof(float);
+  switch (D) {
+    case 8: return of([&](int s) { return Carve<float, 8>(L, rows, entries, mean, s).end; });
+    case 16: return of([&](int s) { return Carve<float, 16>(L, rows, entries, mean, s).end; });
+    case 32: return of([&](int s) { return Carve<float, 32>(L, rows, entries, mean, s).end; });
+    case 64: return of([&](int s) { return Carve<float, 64>(L, rows, entries, mean, s).end; });
+    default: return SmallLds{};
+  }
 }
 
 void launch_small_train(const Launch& ln, int storage, int D, int L, const GraphView& g, const SmallTrain& a,
-                        size_t lds) {
+                        const SmallLds& lds) {
   ln.begin(KK_SMALL_TRAIN);
   if (storage == GCO_STORAGE_BF16) {
     if (D == 64) launch_l<bf16_t, 64>(ln, L, g, a, lds);

@@ -184,3 +184,48 @@ def test_gradients_come_from_the_kernel_that_trains(gco, D, L, norm, problem):
     E1, W1 = ctx.get_params()                  # nothing was updated
     assert np.array_equal(E1, E) and all(np.array_equal(a, b.astype(np.float32)) for a, b in zip(W1, Ws))
     ctx.destroy()
+
+
+@pytest.mark.parametrize("D,L,norm,storage,rows", [
+    # the gathered rows in LDS (all; all but the gradient's; none), the gather on the matrix cores (bf16, up to about
+    # 270 rows of two layers) and beside it
+    (8, 3, "sym", "fp32", 250), (16, 2, "mean", "fp32", 255), (16, 3, "sym", "fp32", 600), (32, 2, "sym", "fp32", 250),
+    (32, 2, "mean", "fp32", 600), (32, 3, "mean", "fp32", 250), (64, 2, "sym", "fp32", 120), (64, 3, "sym", "fp32", 120),
+    (64, 2, "sym", "bf16", 240), (64, 2, "mean", "bf16", 200), (64, 3, "mean", "bf16", 100), (64, 2, "sym", "bf16", 400),
+    (64, 3, "sym", "bf16", 130)])
+def test_rows_of_every_length(gco, D, L, norm, storage, rows):
+    """Rows of 1, 3 and up to about 250 neighbours in one tile: entries in batches, longer rows shared by the wavefront
+    (from 32 entries of feature rows and 64 of scalars on), rows cut over the steps of the matrix gather."""
+    P = 256
+    lengths = [31, 32, 63, 64, 65, 100, min(rows - 1, 240)]
+    u, v = [], []
+    for q, hub in enumerate(lengths):
+        hub = min(hub, rows - 1)
+        u.append(np.full(hub, 3 * q))
+        v.append((3 * q + 1 + np.arange(hub)) % rows)
+    u.append(np.arange(rows // 2))
+    v.append(np.arange(rows // 2) + 1)
+    u, v = np.concatenate(u), np.concatenate(v)
+    base = np.arange(P) * rows
+    g = inputs.from_edges(P * rows, (base[:, None] + u).ravel(), (base[:, None] + v).ravel())
+    part = np.repeat(np.arange(P), rows).astype(np.int32)
+    E, Ws = inputs.init_params(g.n, part, P, L, D, 5)
+    E = (E * 3).astype(np.float32)
+    ctx = gco.Context(num_layers=L, dim=D, norm=norm, storage=storage, lr=1e-2)
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    spec = gcn.Spec(num_layers=L, norm=norm, lr=1e-2, storage="bf16" if storage == "bf16" else "exact")
+    lg = gcn.local_graph(g.n, g.rowptr, g.col, part, P, norm)
+    ctx.set_profiling(1)
+    total, _ = ctx.loss()
+    got = ctx.train(6)
+    assert used(ctx) == 2 and got[0] == total
+    st = gcn.init_state(E, Ws)
+    want, _ = gcn.train(lg, st, spec, 6)
+    tol, bound = (1e-4, 1e-2) if storage == "fp32" else (2e-2, 0.13)   # as above
+    assert np.abs(got - want).max() <= tol * np.abs(want).max()
+    dE, dW = ctx.get_params()
+    assert rel_l2(dE, st.E) <= bound
+    for l in range(L):
+        assert rel_l2(dW[l], st.Ws[l]) <= bound
+    ctx.destroy()
