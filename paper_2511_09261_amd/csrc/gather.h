@@ -26,26 +26,20 @@ struct PlainSrc {
   }
 };
 
-// Gradient of the last hidden layer's pre-activation, formed on the fly:
-// v = sb[j] * g_t[j] * w_out[c] * [H[j, c] > 0]
-template <typename T, int D>
-struct LastSrc {
-  static constexpr int VEC = Store<T>::VEC;
-  const T* H;
+// Gradient of the last hidden layer's pre-activation without the factor w_out:
+// v = sb[j] * g_t[j] where bit c of row j's mask (bit c % 32 of word c / 32) is set
+template <int D>
+struct MaskSrc {
+  static constexpr int VEC = 4;
+  const uint32_t* mask;
   const float* sb;
   const float* g_t;
-  const float* w_out;  // [Pw, D]
-  int wout_stride;
-  float w[VEC];
-  __device__ __forceinline__ void set_part(int k, int c0) {
-#pragma unroll
-    for (int x = 0; x < VEC; ++x) w[x] = w_out[static_cast<size_t>(k) * wout_stride + c0 + x];
-  }
+  __device__ __forceinline__ void set_part(int, int) {}
   __device__ __forceinline__ void load(int j, int c0, float (&v)[VEC]) const {
-    Store<T>::load(H + static_cast<size_t>(j) * D + c0, v);
+    const uint32_t m = mask[static_cast<size_t>(j) * ((D + 31) / 32) + c0 / 32] >> (c0 % 32);
     const float s = sb[j] * g_t[j];
 #pragma unroll
-    for (int x = 0; x < VEC; ++x) v[x] = v[x] > 0.f ? s * w[x] : 0.f;
+    for (int x = 0; x < VEC; ++x) v[x] = (m >> x) & 1u ? s : 0.f;
   }
 };
 

@@ -191,6 +191,7 @@ struct gco_ctx {
   float* gW_partial[3] = {};  // [l-1] for hidden layers; the scalar layer uses gwout_partial
   float* gwout_partial = nullptr;
   void* H[3] = {};            // H[0] aliases the embedding in storage type
+  uint32_t* mask = nullptr;   // bits H > 0 of the last hidden layer (fp32 storage)
   void* GZ[3] = {};
   void* GT = nullptr;         // rows of A_hat^T G_Z of the layer in hand (split_grad_w())
   float *t = nullptr, *z = nullptr, *p = nullptr, *g_z = nullptr, *g_t = nullptr;
@@ -1311,6 +1312,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     GALLOC(ctx->gW_partial[l - 1],
            static_cast<size_t>(std::max({g.num_wblocks[WM_BWD], g.num_wblocks[WM_EMBED], g.num_wblocks[WM_GRADW]})) * D * D);
   }
+  if (L >= 2 && !ctx->wave_path()) GALLOC(ctx->mask, static_cast<size_t>(n) * ((D + 31) / 32));
   // G_Z between two hidden layers; the wave-per-tile kernels also store that of the last one
   for (int l = 1; l <= (ctx->wave_path() ? L - 1 : L - 2); ++l) {
     uint8_t* q = nullptr;
@@ -1506,8 +1508,9 @@ int gco_set_linear_penalty(gco_ctx* ctx, const float* extra) {
 
 // ---- one epoch ------------------------------------------------------------------
 
-// Hidden layers of Eq. 3 and the transform of the scalar layer: leaves t.
-static void run_hidden_forward(gco_ctx* ctx, const GraphView& gv) {
+// Hidden layers of Eq. 3 and the transform of the scalar layer: leaves t.  keep_last: also the activations of
+// the last hidden layer, which only gco_get_hidden reads.
+static void run_hidden_forward(gco_ctx* ctx, const GraphView& gv, bool keep_last) {
   const Launch ln = ctx->launch();
   const gco_config& c = ctx->cfg;
   const int D = c.dim, L = c.num_layers;
@@ -1518,8 +1521,9 @@ static void run_hidden_forward(gco_ctx* ctx, const GraphView& gv) {
     for (int l = 1; l <= L - 1; ++l) {
       const bool last = l == L - 1;
       const bool ready = l == 1 && ctx->heavy_E_valid && ctx->d_heavy_partial_E != nullptr;
-      launch_fwd_hidden(ln, c.storage, D, gv, ctx->H[l - 1], ctx->W[l - 1], ws, ctx->H[l],
-                        last ? ctx->W[L - 1] : nullptr, wos, ctx->t,
+      void* H = last && !keep_last && !ctx->wave_path() ? nullptr : ctx->H[l];
+      launch_fwd_hidden(ln, c.storage, D, gv, ctx->H[l - 1], ctx->W[l - 1], ws, H,
+                        last ? ctx->W[L - 1] : nullptr, wos, ctx->t, ctx->mask,
                         ready ? ctx->d_heavy_partial_E : ctx->d_heavy_partial, ready);
     }
   }
@@ -1614,7 +1618,7 @@ static void run_small(gco_ctx* ctx, const GraphView& gv, int passes, int epochs,
 
 static void run_forward(gco_ctx* ctx) {
   if (ctx->small_train) return run_small(ctx, ctx->gv, 1, 1, 0, true, 0, nullptr);
-  run_hidden_forward(ctx, ctx->gv);
+  run_hidden_forward(ctx, ctx->gv, true);
   run_scalar_layer(ctx, ctx->gv, 1, 0);
 }
 
@@ -1652,6 +1656,7 @@ static void run_backward(gco_ctx* ctx, const GraphView& gv, const gco_ctx::Activ
       const bool last = l == L - 1, to_embed = l == 1;
       a.GZ_in = last ? nullptr : ctx->GZ[l];
       a.Hcur = last ? ctx->H[l] : nullptr;
+      a.mask = ctx->mask;
       a.Hprev = ctx->H[l - 1];
       a.W = ctx->W[l - 1];
       a.w_stride = ws;
@@ -1771,7 +1776,7 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
         adE.per_part = ctx->d_bc + static_cast<size_t>(e) * (P + Pw);
         adW.per_part = adE.per_part + P;
       }
-      run_hidden_forward(ctx, gv);
+      run_hidden_forward(ctx, gv, e0 + e == epochs - 1);
       run_scalar_layer(ctx, gv, 3, e);
       if (ctx->best_on) {
         // the parameters still are the ones this loss belongs to
@@ -1916,7 +1921,7 @@ int gco_loss(gco_ctx* ctx, double* total, double* per_part) {
   if (ctx->small_train) {
     run_small(ctx, ctx->gv, 2, 1, 0, true, 0, nullptr);
   } else {
-    run_hidden_forward(ctx, ctx->gv);
+    run_hidden_forward(ctx, ctx->gv, true);
     run_scalar_layer(ctx, ctx->gv, 2, 0);
   }
   launch_loss_reduce(ctx->launch(), ctx->gv, ctx->loss_partial, 1, 0, ctx->loss_part, ctx->loss_one);
@@ -1942,7 +1947,7 @@ int gco_get_grads(gco_ctx* ctx, float* gE, float* const* gW) {
   if (ctx->small_train) {
     run_small(ctx, ctx->gv, 4, 1, 0, true, 0, nullptr, d_gE, d_gW);
   } else {
-    run_hidden_forward(ctx, ctx->gv);
+    run_hidden_forward(ctx, ctx->gv, true);
     run_scalar_layer(ctx, ctx->gv, 3, 0);
     run_backward(ctx, ctx->gv, ctx->full, false, AdamStep{}, AdamStep{}, d_gE, d_gW);
   }

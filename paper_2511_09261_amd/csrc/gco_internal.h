@@ -219,12 +219,13 @@ enum EmbedMode : int { EMBED_ADAM = 0, EMBED_WRITE_GRAD = 1, EMBED_SKIP = 2 };
 // ---- launchers implemented in train_kernels.hip (storage: 0 fp32, 1 bf16) ----
 
 // Hidden layer forward: Y = relu((A_hat X) W^k); with w_out != nullptr also
-// t = Y w_out^k (the scalar layer's transform fused into the last hidden layer).
+// t = Y w_out^k (the scalar layer's transform fused into the last hidden layer), and, in fp32 storage,
+// the bits Y > 0 to `mask` ([n, (D + 31) / 32] words), with Y itself only if Y != nullptr.
 // partial_ready: the chunk partials of the pre-reduced rows for X are in heavy_partial
 // already (bf16 storage only; otherwise a launch of its own computes them first).
 void launch_fwd_hidden(const Launch& ln, int storage, int D, const GraphView& g, const void* X,
                        const float* W, int w_stride, void* Y, const float* w_out,
-                       int wout_stride, float* t, float* heavy_partial, bool partial_ready = false);
+                       int wout_stride, float* t, uint32_t* mask, float* heavy_partial, bool partial_ready = false);
 
 // t = X w^k (used only when L = 1).
 void launch_fwd_gemv(const Launch& ln, int storage, int D, const GraphView& g, const void* X,
@@ -299,8 +300,8 @@ void launch_bwd_readout(const Launch& ln, const GraphView& g, const float* g_z, 
                         const ScalarStaging* sg);
 
 // Backward of hidden layer l (and of the scalar layer when `last`):
-//   last:  G_Z[j,:] = g_t[j] * w_out^k * [Hcur[j,:] > 0] is formed while gathering,
-//          and gw_out partials = sum_i Hcur[i,:] g_t[i] are produced;
+//   last:  G_Z[j,:] = g_t[j] * w_out^k * [Hcur[j,:] > 0] is formed while gathering (fp32: from the bits of
+//          `mask`), and gw_out partials = sum_i Hcur[i,:] g_t[i] are produced;
 //   else:  G_Z is read from GZ_in.
 //   G_T = A_hat^T G_Z;  gW partial += Hprev^T G_T;  G_Hprev = G_T W^T.
 //   to_embed: Hprev is the embedding: apply `mode` (Adam / write gE / nothing);
@@ -308,7 +309,8 @@ void launch_bwd_readout(const Launch& ln, const GraphView& g, const float* g_z, 
 struct BwdArgs {
   const void* GZ_in = nullptr;   // [n, D] storage type (not last)
   void* GZ_last = nullptr;       // [n, D] bf16: where the wave-per-tile path forms G_Z of the last hidden layer
-  const void* Hcur = nullptr;    // [n, D] storage type (last)
+  const void* Hcur = nullptr;    // [n, D] bf16 (last)
+  const uint32_t* mask = nullptr;  // [n, (D + 31) / 32] bits Hcur > 0 (last, fp32 storage)
   const float* g_t = nullptr;    // [n] (last)
   const float* w_out = nullptr;  // [Pw, D] (last)
   int wout_stride = 0;
@@ -336,7 +338,7 @@ void launch_bwd_hidden(const Launch& ln, int storage, int D, bool last, bool to_
 // decomposition WM_EMBED (first layer) or WM_BWD, those of w_out by the last hidden layer's
 void launch_fwd_hidden_f32(const Launch& ln, int D, const GraphView& g, const void* X, const float* W,
                            int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
-                           float* heavy_partial);
+                           uint32_t* mask, float* heavy_partial);
 void launch_bwd_hidden_f32(const Launch& ln, int D, bool last, bool to_embed, const GraphView& gt,
                            const BwdArgs& a);
 

@@ -97,35 +97,6 @@ struct PlainRows {
   }
 };
 
-// Rows of dL/dZ of the last hidden layer, formed from H and the scalar layer's gradient:
-// g_t[j] w[c] where H[j, c] > 0, rounded as stored.
-template <int D, typename T = float>
-struct LastRows {
-  struct Row {
-    f32x4 x[TF<D>::NQ];
-    float gt;
-  };
-  const T* H;
-  const float* g_t;
-  f32x4 w[D <= 64 ? TF<D>::NQ : 1];
-  const float* w_lds;  // width 128: w is read from LDS when used (32 registers less)
-  __device__ __forceinline__ void request(Row& r, int j, int h) const {
-    r.gt = g_t[j];
-#pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) r.x[q] = gather4<D>(H, j, q, h);
-  }
-  __device__ __forceinline__ void add(const Row& r, float val, f32x4 (&acc)[TF<D>::NQ]) const {
-    int off = 4 * (threadIdx.x % 4);
-    if (D > 64) asm volatile("" : "+v"(off));  // not read ahead of the loop over the entries
-#pragma unroll
-    for (int q = 0; q < TF<D>::NQ; ++q) {
-      const f32x4 wq = D <= 64 ? w[D <= 64 ? q : 0] : *reinterpret_cast<const f32x4*>(w_lds + 16 * q + off);
-#pragma unroll
-      for (int x = 0; x < 4; ++x) acc[q][x] = fmaf(val, r.x[q][x] > 0.f ? Store<T>::as_stored(r.gt * wq[x]) : 0.f, acc[q][x]);
-    }
-  }
-};
-
 // The ReLU decisions of a row of the last hidden layer, one bit per feature: bit f % 32 of word f / 32.
 template <int D>
 struct Mask {
@@ -194,15 +165,40 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
-// Sum over the lanes of equal number modulo 4 (a gathered row's sixteen groups); every lane ends with
-// the total, in a fixed order.
-__device__ __forceinline__ float groups_sum(float v) {
-#define GCO_ROR(N) \
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
-  GCO_ROR(8) GCO_ROR(4)
-#undef GCO_ROR
-  v += __shfl_xor(v, 16, 64);
-  return v + __shfl_xor(v, 32, 64);
+// Sum (or) over the lanes l, l ^ 16, l ^ 32, l ^ 48 without LDS: first the other half, then the other row.
+__device__ __forceinline__ float add_over_h(float v) {
+  const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(y[0]) + __uint_as_float(y[1]);
+}
+__device__ __forceinline__ uint32_t or_over_h(uint32_t v) {
+  const auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  v = x[0] | x[1];
+  const auto y = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return y[0] | y[1];
+}
+template <int N>  // the lane N further round its row of 16
+__device__ __forceinline__ float rotated(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+}
+// Sum over the lanes of equal number modulo D (8, 16, 32 or 64).
+template <int D>
+__device__ __forceinline__ float column_sum(float v) {
+  if (D <= 8) v += rotated<8>(v);
+  if (D <= 16) v = add_over_h(v);
+  else if (D == 32) v += __shfl_xor(v, 32, 64);
+  return v;
+}
+
+// The words of a row from the four lanes (n, h) that hold its features 16 q + 4 h + j, whose decisions are
+// bits j of bits[q].  Every lane of the row ends with all words.
+template <int D>
+__device__ __forceinline__ void row_mask(int h, const uint32_t (&bits)[TF<D>::NQ], uint32_t (&m)[Mask<D>::NM]) {
+#pragma unroll
+  for (int w = 0; w < Mask<D>::NM; ++w)
+    m[w] = or_over_h((bits[2 * w] | (2 * w + 1 < TF<D>::NQ ? bits[2 * w + 1 < TF<D>::NQ ? 2 * w + 1 : 0] << 16 : 0u))
+                     << (4 * h));
 }
 
 // What the aggregation of a tile starts from, requested a tile ahead: the tile's range of the
@@ -282,19 +278,18 @@ struct TileFacts {
 };
 
 // acc = (A_hat x)(row n of the tile at r0, this lane's features); zero for rows past r1.
-// `sums` is kWaveLds floats of this wavefront's LDS.  on_own(x) is called by one lane group
-// for every row of the tile with the gathered row itself.
+// `sums` is kWaveLds floats of this wavefront's LDS.
 //
 // The lanes of a group that gathers a row are neighbours (lane 4 group + h holds features
 // 16 q + 4 h + j), because the cache looks at four neighbouring lanes at once: a row or a stream
 // entry is one look-up per group.  With the groups in the layout of the products (lane n + 16 h) every lane
 // was one of its own, and these bounded the kernels where rows are not short: 19 000 rows of width 16
 // with 30 neighbours, 6.5 million look-ups a launch.  The sums change layout on their way through LDS.
-template <int D, class Stream, class Rows, class OnOwn>
+template <int D, class Stream, class Rows>
 __device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stream, const Rows& rows,
                                           const TileFacts<D>& f, int r0, int r1,
                                           const float* __restrict__ heavy_partial, float* sums,
-                                          f32x4 (&acc)[TF<D>::NQ], OnOwn&& on_own) {
+                                          f32x4 (&acc)[TF<D>::NQ]) {
   constexpr int NQ = TF<D>::NQ, U = TF<D>::U, PT = TF<D>::PT;
   const int lane = threadIdx.x % 64, n = lane % 16, h = lane / 16;
   const int group = lane / 4, gh = lane % 4;
@@ -324,10 +319,8 @@ __device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stre
 #pragma unroll
     for (int q = 0; q < NQ; ++q) *reinterpret_cast<f32x4*>(place + 16 * q + 4 * gh) = acc[q];
   };
-  if (f.by_row && cur < r1) {  // a row begins with its diagonal entry
-    on_own(x[0]);
-    if (Stream::kPreReduced) pre_reduced = en[0].row < 0;
-  }
+  // a row begins with its diagonal entry
+  if (Stream::kPreReduced && f.by_row && cur < r1) pre_reduced = en[0].row < 0;
   for (int b = 0; b < share; b += U, e += U) {
     Entry nx[U];
     TileFacts<D>::request_entries_at(stream, e + U, nx);
@@ -344,10 +337,7 @@ __device__ __forceinline__ void aggregate(const GraphView& g, const Stream& stre
           cur = row;
           if (Stream::kPreReduced) pre_reduced |= en[u].row < 0;
           place = carries + group * PT;
-          if (en[u].col == row) {  // the row's diagonal entry
-            place = sums + (row - r0) * PT;
-            on_own(x[u]);
-          }
+          if (en[u].col == row) place = sums + (row - r0) * PT;  // the row's diagonal entry
         }
         rows.add(x[u], en[u].val, acc);
       }

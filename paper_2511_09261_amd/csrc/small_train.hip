@@ -138,23 +138,6 @@ struct Carve {
   static __host__ __device__ int padded_rows(int nrows) { return (nrows + kTile) / kTile * kTile; }
 };
 
-// Sums over the lanes l, l ^ 16, l ^ 32, l ^ 48, without LDS (lane l ^ 32's half, then l ^ 16's row).
-__device__ __forceinline__ float add_over_h(float v) {
-  const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
-  const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(y[0]) + __uint_as_float(y[1]);
-}
-__device__ __forceinline__ uint32_t or_over_h(uint32_t v) {
-  const auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  v = x[0] | x[1];
-  const auto y = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  return y[0] | y[1];
-}
-template <int N>  // the lane N further round its row of 16
-__device__ __forceinline__ float rotated(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
-}
 // Sum over the four lanes of a group (data-parallel-primitive permutations of a quad).
 __device__ __forceinline__ float quad_sum(float v) {
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xb1, 0xf, 0xf, false));  // lanes 1 0 3 2
@@ -790,9 +773,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     }
   }
   if constexpr (LAST) {
-    if (D <= 8) column += rotated<8>(column);
-    if (D <= 16) column = add_over_h(column);
-    else if (D == 32) column += __shfl_xor(column, 32, 64);
+    column = column_sum<D>(column);
     if (lane < D) smem[cv.gwo + wave * DP + lane] = column;
     sync_lds();
     if (tid < D) {
@@ -1022,10 +1003,7 @@ __global__ __launch_bounds__((SK<T, D>::NT)) void small_train_kernel(GraphView g
         if (last) {
           part = add_over_h(part);
           uint32_t m[K::NM];
-          if (FOR != Purpose::kForward && !kMatrix)
-#pragma unroll
-            for (int x = 0; x < K::NM; ++x)
-              m[x] = or_over_h((bits[2 * x] | (2 * x + 1 < NQ ? bits[2 * x + 1 < NQ ? 2 * x + 1 : 0] << 16 : 0u)) << (4 * h));
+          if (FOR != Purpose::kForward && !kMatrix) row_mask<D>(h, bits, m);
           if (h == 0 && row < R) {
             tv[row] = part;
             if (FOR != Purpose::kForward && !kMatrix)

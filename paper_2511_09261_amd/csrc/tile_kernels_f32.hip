@@ -12,6 +12,12 @@
 // layout on their way through LDS.  The weight gradient contracts over the rows of the tile: its A operand (rows of
 // Hprev) is read from memory in operand layout, G_T goes through wave-private LDS.
 //
+// Last hidden layer: its forward pass stores one bit per feature, H > 0, instead of H (unless asked for H).  Since
+// dL/dZ = g_t w_out [H > 0], the backward gather sums B = A_hat^T (g_t [H > 0]) over those bits, G_T = B w_out, and with
+// M = Hprev^T B:  dL/dW[a, c] = M[a, c] w_out[c],  dL/dw_out[c] = sum_a W[a, c] M[a, c]  (H = (A_hat Hprev) W where
+// the bit is set).  A neighbour costs 4 to 16 bytes of bits and its g_t instead of its row: backward of the last hidden
+// layer, 150 k rows of width 64, 95.5 -> 69.6 us, 700 k of width 16 with Adam 74.7 -> 62.2, forward there 33.9 -> 32.3.
+//
 // The aggregation walks the light stream (per row its diagonal entry, then its neighbours;
 // rows with >= kHeavyMin neighbours hold only the diagonal entry and come pre-reduced): the
 // tile's entries are dealt to the 16 lane groups in equal contiguous shares, whatever the
@@ -21,9 +27,8 @@
 // in order.  One fixed order of additions.
 //
 // What bounds it: at widths 8 .. 64 memory (Adam's E, m, v; the gather), in bytes that pass the L2s: 700 k rows of
-// width 16, embedding backward 417 MB in 74 us, forward 144 MB in 35 (5.6 and 4.1 TB/s); 150 k of width
-// 64, 406 MB in 67 us, hidden backward 544 in 93, embedding backward 687 in 116 (5.8 to 6.1).  So registers are
-// kept low enough for many wavefronts per SIMD and there is no workgroup barrier; at width
+// width 16 with H stored and gathered, embedding backward 417 MB in 74 us, forward 144 MB in 35 (5.6 and 4.1 TB/s); 150 k
+// of width 64, forward 406 MB in 67 us, embedding backward 687 in 116 (5.9 to 6.1).  So registers are kept low enough for many wavefronts per SIMD and there is no workgroup barrier; at width
 // 128 the matrix cores (3 x 2 x 16 x 128 x 128 operations per tile at 64 per cycle and SIMD).
 #include "device_utils.h"
 #include "gather.h"
@@ -88,9 +93,9 @@ constexpr size_t fwd_tile_lds() {
 template <int D>
 __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 : 2))) void fwd_tile_kernel(
     GraphView g, const float* __restrict__ X, const float* __restrict__ W, int w_stride, float* __restrict__ Y,
-    const float* __restrict__ w_out, int wout_stride, float* __restrict__ t,
+    const float* __restrict__ w_out, int wout_stride, float* __restrict__ t, uint32_t* __restrict__ mask,
     const float* __restrict__ heavy_partial) {
-  constexpr int NQ = TK<D>::NQ;
+  constexpr int NQ = TK<D>::NQ, NM = Mask<D>::NM;
   constexpr int kTaUnroll = D <= 64 ? NQ : 1;
   extern __shared__ __align__(16) unsigned char smem[];
   f32x4* wl = reinterpret_cast<f32x4*>(smem);
@@ -128,9 +133,10 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
     const int row = r0 + n;
     nf.request(stream, r0 + kTile, r1);
     f32x4 acc[NQ];
-    aggregate<D>(g, stream, rows, f, r0, r1, heavy_partial, sums, acc, [](const typename PlainRows<D>::Row&) {});
+    aggregate<D>(g, stream, rows, f, r0, r1, heavy_partial, sums, acc);
     nf.request_entries(stream);
     float part = 0.f;
+    uint32_t bits[NQ];
     const int wlane = operand_lane<D>(lane);
 #pragma unroll kTaUnroll
     for (int ta = 0; ta < NQ; ++ta) {
@@ -148,12 +154,22 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
 #pragma unroll
         for (int j = 0; j < 4; ++j) part = fmaf(z[j], w[j], part);
       }
-      if (row < r1) store4<D>(Y, row, ta, h, z);
+      bits[ta] = 0u;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bits[ta] |= z[j] > 0.f ? 1u << j : 0u;
+      if (row < r1 && Y != nullptr) store4<D>(Y, row, ta, h, z);
     }
     if (last) {
-      part += __shfl_xor(part, 16, 64);
-      part += __shfl_xor(part, 32, 64);
-      if (h == 0 && row < r1) t[row] = part;
+      part = add_over_h(part);
+      uint32_t m[NM];
+      row_mask<D>(h, bits, m);
+      if (h == 0 && row < r1) {
+        t[row] = part;
+        uint32_t* to = mask + static_cast<size_t>(row) * NM;
+        if constexpr (NM == 1) *to = m[0];
+        else if constexpr (NM == 2) *reinterpret_cast<uint2*>(to) = make_uint2(m[0], m[1]);
+        else *reinterpret_cast<uint4*>(to) = make_uint4(m[0], m[1], m[2], m[3]);
+      }
     }
     f = nf;
   }
@@ -175,7 +191,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   using T = TK<D>;
   constexpr int NQ = T::NQ, DP = T::DP, PT = T::PT, TB = T::TB;
   constexpr int WM = TO_EMBED ? WM_EMBED : WM_BWD;
-  using Rows = std::conditional_t<LAST, LastRows<D>, PlainRows<D>>;
+  using Rows = std::conditional_t<LAST, MaskRows<D>, PlainRows<D>>;
   constexpr int kTaUnroll = D <= 64 ? NQ : 1;
   // when the epilogue's rows are requested: as early as the registers allow
   // (ROLLING: each 16 features' worth during the products of the 16 before)
@@ -224,16 +240,16 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   const bool alone = !T::SHARED_GW && runs[0].tile1 == runs[kWavesPerBlock - 1].tile1;
   if (alone && wave > 0) return;
   Rows rows;
+  const float* wk = LAST ? a.w_out + static_cast<size_t>(k) * a.wout_stride : nullptr;
+  f32x4 wo[LAST && D <= 64 ? NQ : 1];  // w_out, this lane's features
   if constexpr (LAST) {
-    rows.H = static_cast<const float*>(a.Hcur);
+    rows.mask = a.mask;
     rows.g_t = a.g_t;
-    const float* wk = a.w_out + static_cast<size_t>(k) * a.wout_stride;
     if (D <= 64) {
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) rows.w[D <= 64 ? q : 0] = load4<D>(wk, 0, q, lane % 4);
-    } else {
-      if (tid < D) last[tid] = wk[tid];  // that place receives the gradient of w_out at the end
-      rows.w_lds = last;
+      for (int q = 0; q < NQ; ++q) wo[D <= 64 ? q : 0] = load4<D>(wk, 0, q, h);
+    } else {  // 32 registers less: read from LDS when used; the place receives the gradient of w_out at the end
+      if (tid < D) last[tid] = wk[tid];
       __syncthreads();
     }
   } else {
@@ -244,10 +260,6 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   for (int ta = 0; ta < NQ; ++ta)
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) gw[ta][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 gwo[LAST ? NQ : 1];  // this lane's share of the gradient of w_out
-#pragma unroll
-  for (int q = 0; q < (LAST ? NQ : 1); ++q) gwo[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-
   // what the epilogue needs of the row: Adam's E, m, v, or the row of Hprev for its mask
   const bool adam = TO_EMBED && a.mode == EMBED_ADAM;
   f32x4 s_e[NS], s_m[TO_EMBED ? NS : 1], s_v[TO_EMBED ? NS : 1];
@@ -283,14 +295,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
     }
     if (kState == BEFORE_GATHER) request_state(row, 0);
     f32x4 acc[NQ];
-    aggregate<D>(g, stream, rows, f, r0, r1, a.heavy_partial, gt, acc, [&](const typename Rows::Row& own) {
-      if constexpr (LAST) {  // gradient of w_out
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-          for (int y = 0; y < 4; ++y) gwo[q][y] = fmaf(own.x[q][y], own.gt, gwo[q][y]);
-      }
-    });
+    aggregate<D>(g, stream, rows, f, r0, r1, a.heavy_partial, gt, acc);
     nf.request_entries(stream);
     if (kState != BEFORE_GATHER) request_state(row, 0);
     // gW[a, c] += sum over the tile's rows of Hprev[row, a] G_T[row, c]
@@ -333,6 +338,11 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
     // G_Hprev^T = W G_T^T and the epilogue
     if (!(TO_EMBED && a.mode == EMBED_SKIP)) {
       const int wlane = operand_lane<D>(lane);
+      if constexpr (LAST) {  // until here the sums were without w_out
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          acc[q] *= D <= 64 ? wo[D <= 64 ? q : 0] : *reinterpret_cast<const f32x4*>(last + 16 * q + 4 * h);
+      }
 #pragma unroll kTaUnroll
       for (int ta = 0; ta < NQ; ++ta) {
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
@@ -367,38 +377,60 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
     f = nf;
   }
 
-  // one partial per workgroup
+  // one partial per workgroup; LAST: M first, from which both gradients follow
   float* out = a.gW_partial + static_cast<size_t>(blockIdx.x) * D * D;
-  if (D > 64) __syncthreads();  // w_out has served
-  if constexpr (LAST) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const float s = groups_sum(gwo[q][x]);
-        if (lane < 4) last[wave * DP + 16 * q + 4 * lane + x] = s;
-      }
-  }
   if constexpr (T::SHARED_GW) {
 #pragma unroll
-    for (int ta = 0; ta < NQ; ++ta)
+    for (int tb = 0; tb < TB; ++tb) {
+      const int c = 16 * (wave * TB + tb) + n;
+      const float scale = LAST ? wk[c] : 1.f;
+      float column = 0.f;
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb)
+      for (int ta = 0; ta < NQ; ++ta)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          out[(16 * ta + 4 * h + r) * D + 16 * (wave * TB + tb) + n] = gw[ta][tb][r];
-    __syncthreads();
+        for (int r = 0; r < 4; ++r) {
+          const int at = (16 * ta + 4 * h + r) * D + c;
+          if (LAST) column = fmaf(Wk[at], gw[ta][tb][r], column);
+          out[at] = LAST ? gw[ta][tb][r] * scale : gw[ta][tb][r];
+        }
+      if (LAST) {
+        column = add_over_h(column);
+        if (h == 0) a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + c] = column;
+      }
+    }
   } else if (alone) {
 #pragma unroll
-    for (int ta = 0; ta < NQ; ++ta)
+    for (int tb = 0; tb < TB; ++tb) {
+      const int c = 16 * tb + n;
+      const bool in = D >= 16 || n < D;
+      const float scale = LAST && in ? wk[c] : 1.f;
+      float column = 0.f;
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb)
+      for (int ta = 0; ta < NQ; ++ta)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (D >= 16 || (4 * h + r < D && n < D)) out[(16 * ta + 4 * h + r) * D + 16 * tb + n] = gw[ta][tb][r];
+          if (D >= 16 || (4 * h + r < D && in)) {
+            const int at = (16 * ta + 4 * h + r) * D + c;
+            if (LAST) column = fmaf(Wk[at], gw[ta][tb][r], column);
+            out[at] = LAST ? gw[ta][tb][r] * scale : gw[ta][tb][r];
+          }
+      if (LAST) {
+        column = add_over_h(column);
+        if (h == 0 && in) a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + c] = column;
+      }
+    }
   } else {
     // (wave 0 + wave 2) + (wave 1 + wave 3)
     float* buf = gt_all;
+    constexpr int kPer = (D * D + kBlock - 1) / kBlock;
+    static_assert(kBlock % D == 0 || D > kBlock, "a thread's weights are of one column");
+    float w[LAST ? kPer : 1], scale = 1.f;
+    if constexpr (LAST) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) w[i] = Wk[min(tid + i * kBlock, D * D - 1)];
+      scale = wk[tid % D];
+      loads_stay_here();
+    }
     __syncthreads();
     for (int pass = 0; pass < 2; ++pass) {
       if (wave / 2 == pass) {
@@ -415,18 +447,28 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
       }
       __syncthreads();
     }
-    for (int idx = tid; idx < D * D; idx += kBlock) {
-      const int p = (idx / D) * DP + idx % D;
-      out[idx] = buf[p] + buf[DP * DP + p];
-    }
-  }
-  if (LAST && alone) wave_lds_handoff();
-  if (LAST && tid < D) {
-    float s = 0.f;
+    float column = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w)
-      if (w == 0 || !alone) s += last[w * DP + tid];
-    a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + tid] = s;
+    for (int i = 0; i < kPer; ++i) {
+      const int idx = tid + i * kBlock;
+      if (idx < D * D) {
+        const int p = (idx / D) * DP + idx % D;
+        const float m = buf[p] + buf[DP * DP + p];
+        if (LAST) column = fmaf(w[LAST ? i : 0], m, column);
+        out[idx] = LAST ? m * scale : m;
+      }
+    }
+    if constexpr (LAST) {
+      column = column_sum<D>(column);
+      if (lane < D) last[wave * DP + lane] = column;
+      __syncthreads();
+      if (tid < D) {
+        float s = 0.f;
+#pragma unroll
+        for (int v = 0; v < kWavesPerBlock; ++v) s += last[v * DP + tid];
+        a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + tid] = s;
+      }
+    }
   }
 }
 
@@ -439,7 +481,7 @@ void allow_lds(K kernel, size_t bytes) {
 
 template <int D>
 void fwd_t(const Launch& ln, const GraphView& g, const float* X, const float* W, int w_stride, float* Y,
-           const float* w_out, int wout_stride, float* t, float* heavy_partial) {
+           const float* w_out, int wout_stride, float* t, uint32_t* mask, float* heavy_partial) {
   if (g.num_chunks > 0) {
     ln.begin(KK_HEAVY);
     heavy_wide_kernel<D, PlainSrc<float, D>>
@@ -449,7 +491,7 @@ void fwd_t(const Launch& ln, const GraphView& g, const float* X, const float* W,
   allow_lds(fwd_tile_kernel<D>, fwd_tile_lds<D>());
   ln.begin(KK_FWD_HIDDEN);
   fwd_tile_kernel<D><<<g.num_wblocks[WM_FWD], kBlock, fwd_tile_lds<D>(), ln.st>>>(
-      g, X, W, w_stride, Y, w_out, wout_stride, t, heavy_partial);
+      g, X, W, w_stride, Y, w_out, wout_stride, t, mask, heavy_partial);
   ln.end(KK_FWD_HIDDEN);
 }
 
@@ -465,8 +507,8 @@ void bwd_t(const Launch& ln, bool last, bool to_embed, const GraphView& gt, cons
   if (gt.num_chunks > 0) {
     ln.begin(KK_HEAVY);
     if (last) {
-      LastSrc<float, D> src{static_cast<const float*>(a.Hcur), gt.sb, a.g_t, a.w_out, a.wout_stride, {}};
-      heavy_wide_kernel<D, LastSrc<float, D>><<<gt.num_chunks, kBlock, 0, ln.st>>>(gt, src, a.heavy_partial);
+      MaskSrc<D> src{a.mask, gt.sb, a.g_t};
+      heavy_wide_kernel<D, MaskSrc<D>><<<gt.num_chunks, kBlock, 0, ln.st>>>(gt, src, a.heavy_partial);
     } else {
       PlainSrc<float, D> src{static_cast<const float*>(a.GZ_in), gt.sb};
       heavy_wide_kernel<D, PlainSrc<float, D>><<<gt.num_chunks, kBlock, 0, ln.st>>>(gt, src, a.heavy_partial);
@@ -496,9 +538,9 @@ void bwd_t(const Launch& ln, bool last, bool to_embed, const GraphView& gt, cons
 
 void launch_fwd_hidden_f32(const Launch& ln, int D, const GraphView& g, const void* X, const float* W,
                            int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
-                           float* heavy_partial) {
+                           uint32_t* mask, float* heavy_partial) {
   GCO_BY_WIDTH(D, (fwd_t<DD>(ln, g, static_cast<const float*>(X), W, w_stride, static_cast<float*>(Y), w_out,
-                             wout_stride, t, heavy_partial)))
+                             wout_stride, t, mask, heavy_partial)))
 }
 
 void launch_bwd_hidden_f32(const Launch& ln, int D, bool last, bool to_embed, const GraphView& gt,

@@ -396,11 +396,11 @@ void allow_lds(K kernel, size_t bytes) {
 
 void launch_fwd_hidden(const Launch& ln, int storage, int D, const GraphView& g, const void* X,
                        const float* W, int w_stride, void* Y, const float* w_out, int wout_stride,
-                       float* t, float* heavy_partial, bool partial_ready) {
+                       float* t, uint32_t* mask, float* heavy_partial, bool partial_ready) {
   if (storage == GCO_STORAGE_BF16) {
     launch_fwd_hidden_bf16(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, heavy_partial, partial_ready);
   } else {
-    launch_fwd_hidden_f32(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, heavy_partial);
+    launch_fwd_hidden_f32(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, mask, heavy_partial);
   }
 }
 

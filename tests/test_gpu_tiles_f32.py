@@ -172,3 +172,23 @@ def test_partial_sums_take_the_memory_of_the_workgroups_there_are(gco):
     rows = (3 + (L - 1) + (L - 2)) * n * D * 4       # E, m, v, the hidden layers, the gradient between two
     assert total <= rows + (L - 1) * 512 * D * D * 4 + 200 * n
     ctx.destroy()
+
+
+@pytest.mark.parametrize("D,L", [(8, 2), (16, 3), (64, 2), (128, 3)])
+def test_hidden_activations_are_those_of_the_last_epoch(gco, D, L):
+    """Training keeps the last hidden layer's activations only in its last epoch: they are the ones a forward pass
+    at the parameters before that epoch leaves, bit for bit."""
+    g, part, P = ragged_subgraphs(7)
+    E, Ws = inputs.init_params(g.n, part, P, L, D, 3)
+    ctx = gco.Context(num_layers=L, dim=D)
+    ctx.set_scalar_layer_form("streams")
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    ctx.train(2)
+    ctx.forward()
+    want = ctx.get_hidden(L - 1)
+    assert (want > 0).any()
+    ctx.set_params(E, Ws)
+    ctx.train(3)
+    assert np.array_equal(ctx.get_hidden(L - 1), want)
+    ctx.destroy()
