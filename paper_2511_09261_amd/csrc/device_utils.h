@@ -114,11 +114,15 @@ __device__ __forceinline__ float quotient_in_range(float n, float d) {
   return fmaf(fmaf(-d, q, n), r, q);
 }
 
-// One Adam step on N embedding values or weights (constants of AdamStep), with the correctly
+// One Adam step on N embedding values, or on one weight (constants of AdamStep), with the correctly
 // rounded square root and division: every launch that may update a parameter in fp32 takes the
 // same step, and a subgraph does not train differently because other kernels were chosen for it.
 // With a usual eps, v is taken as at least 2^-100 for its square root, 2^-50, which eps swallows: the same
 // sum.  Beyond the ranges (uniform over the wavefront) the general functions serve.
+template <class Step>
+__device__ __forceinline__ bool adam_in_range(const Step& ad, float largest_v) {
+  return ad.eps >= 1e-9f && ad.eps <= 1.f && ad.inv_sqrt_bc2 <= 64.f && !__any(largest_v > 0x1p100f);
+}
 template <int N, class Step>
 __device__ __forceinline__ void adam_values(const Step& ad, const float (&g)[N], float (&e)[N], float (&m)[N],
                                             float (&v)[N]) {
@@ -129,7 +133,7 @@ __device__ __forceinline__ void adam_values(const Step& ad, const float (&g)[N],
     v[x] = ad.b2 * v[x] + (1.f - ad.b2) * g[x] * g[x];
     top = fmaxf(top, v[x]);
   }
-  if (ad.eps >= 1e-9f && ad.eps <= 1.f && ad.inv_sqrt_bc2 <= 64.f && !__any(top > 0x1p100f)) {
+  if (adam_in_range(ad, top)) {
 #pragma unroll
     for (int x = 0; x < N; ++x) {
       const float root = sqrt_in_range(fmaxf(v[x], 0x1p-100f));
@@ -147,6 +151,15 @@ __device__ __forceinline__ void adam_value(const Step& ad, float g, float& e, fl
   e = e1[0];
   m = m1[0];
   v = v1[0];
+}
+template <class Step>
+__device__ __forceinline__ void adam_weight(const Step& ad, float g, float& w, float& m, float& v) {
+  m = ad.b1 * m + (1.f - ad.b1) * g;
+  v = ad.b2 * v + (1.f - ad.b2) * g * g;
+  if (adam_in_range(ad, v))
+    w -= quotient_in_range(ad.lr * (m * ad.inv_bc1), sqrt_in_range(fmaxf(v, 0x1p-100f)) * ad.inv_sqrt_bc2 + ad.eps);
+  else
+    w -= ad.lr * (m * ad.inv_bc1) / (sqrtf(v) * ad.inv_sqrt_bc2 + ad.eps);
 }
 
 // Sum over the 64 lanes of a wavefront in a fixed butterfly order; every lane

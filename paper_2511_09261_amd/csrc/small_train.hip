@@ -20,7 +20,9 @@
 // Last hidden layer, backward: dL/dZ = g_t w_out [H > 0], so the gather sums g_t over the mask bits, its
 // sum B is multiplied by w_out once, and with M = Hprev^T B
 //   dL/dW[a, c] = M[a, c] w_out[c]   and   dL/dw_out[c] = sum_a W[a, c] M[a, c]
-// (H = (A_hat Hprev) W where the mask is set): neither H nor its rows are needed.
+// (H = (A_hat Hprev) W where the mask is set): neither H nor its rows are needed.  bf16: B enters M in two bf16
+// parts, because the gradient of w_out would otherwise carry its rounding on top of W's (16 x 252 rows of width 64
+// against 64 bits, in one part 8.1e-4, in two 6.7e-4, from H g_t 7.3e-4).
 //
 // Best-by-loss snapshots are taken inside the epoch, between the loss and the update, so that tracking
 // them costs no second forward pass and no launch.
@@ -360,6 +362,22 @@ __device__ __forceinline__ f32x4 mfma16(const i16x4_t& a, const i16x4_t& b, cons
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
+// What rounding x to p left off, rounded.
+template <int D>
+__device__ __forceinline__ Packed<D> pack_rest(const f32x4 (&x)[TF<D>::NQ], const Packed<D>& p) {
+  f32x4 rest[TF<D>::NQ];
+#pragma unroll
+  for (int s = 0; s < D / 32; ++s) {
+    const uint32_t w[4] = {p.s[s].x, p.s[s].y, p.s[s].z, p.s[s].w};
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      rest[2 * s + d / 2][2 * (d % 2)] = x[2 * s + d / 2][2 * (d % 2)] - __uint_as_float(w[d] << 16);
+      rest[2 * s + d / 2][2 * (d % 2) + 1] = x[2 * s + d / 2][2 * (d % 2) + 1] - __uint_as_float(w[d] & 0xffff0000u);
+    }
+  }
+  return pack_tile<D>(rest);
+}
+
 // Where W[f][o] (o: output feature) sits among the operands for a contraction over f with result rows o:
 // piece (o / 16, f / 32), lane (o % 16, h), element e, in bf16 values.
 template <int D>
@@ -473,8 +491,9 @@ __device__ __forceinline__ void aggregate_staged(const SplitStream& st, const bf
 }
 
 // gw[ta][tb] += Hprev^T x over the 16 rows of the tile at r0: `tile` is this wavefront's LDS for x, PITCH
-// the pitch of Hprev's rows; STAGED: these are in LDS, and zero past row R.
-template <typename T, int D, int STAGED, int PITCH>
+// the pitch of Hprev's rows; STAGED: these are in LDS, and zero past row R.  bf16: x rounded, WHOLE: and what the
+// rounding left off.
+template <typename T, int D, int STAGED, int PITCH, bool WHOLE>
 __device__ __forceinline__ void weight_gradient(const T* Hprev, int r0, int R, const f32x4 (&x)[TF<D>::NQ],
                                                 const Packed<D>& p, float* tile, int n, int h,
                                                 f32x4 (&gw)[TF<D>::NQ][TF<D>::NQ]) {
@@ -492,21 +511,26 @@ __device__ __forceinline__ void weight_gradient(const T* Hprev, int r0, int R, c
         }
     }
     bf16_t* tb16 = reinterpret_cast<bf16_t*>(tile);
-#pragma unroll
-    for (int s = 0; s < D / 32; ++s) {
-      *reinterpret_cast<uint2*>(tb16 + n * K::PG + 32 * s + 4 * h) = make_uint2(p.s[s].x, p.s[s].y);
-      *reinterpret_cast<uint2*>(tb16 + n * K::PG + 32 * s + 16 + 4 * h) = make_uint2(p.s[s].z, p.s[s].w);
-    }
-    wave_lds_handoff();
     if constexpr (STAGED)
 #pragma unroll
       for (int ta = 0; ta < NQ; ++ta) av[ta] = lds_read_columns(Hprev + (r0 + 4 * h) * PITCH + 16 * ta, PITCH, n);
 #pragma unroll
-    for (int tb = 0; tb < NQ; ++tb) bv[tb] = lds_read_columns(tb16 + 4 * h * K::PG + 16 * tb, K::PG, n);
+    for (int part = 0; part < (WHOLE ? 2 : 1); ++part) {
+      const Packed<D> px = part == 0 ? p : pack_rest<D>(x, p);
 #pragma unroll
-    for (int ta = 0; ta < NQ; ++ta)
+      for (int s = 0; s < D / 32; ++s) {
+        *reinterpret_cast<uint2*>(tb16 + n * K::PG + 32 * s + 4 * h) = make_uint2(px.s[s].x, px.s[s].y);
+        *reinterpret_cast<uint2*>(tb16 + n * K::PG + 32 * s + 16 + 4 * h) = make_uint2(px.s[s].z, px.s[s].w);
+      }
+      wave_lds_handoff();
 #pragma unroll
-      for (int tb = 0; tb < NQ; ++tb) gw[ta][tb] = mfma16(av[ta], bv[tb], gw[ta][tb]);
+      for (int tb = 0; tb < NQ; ++tb) bv[tb] = lds_read_columns(tb16 + 4 * h * K::PG + 16 * tb, K::PG, n);
+#pragma unroll
+      for (int ta = 0; ta < NQ; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < NQ; ++tb) gw[ta][tb] = mfma16(av[ta], bv[tb], gw[ta][tb]);
+      if (WHOLE && part == 0) wave_lds_handoff();
+    }
   } else {
     float av[4][NQ];  // contraction index h of step s: row 4 s + h
 #pragma unroll
@@ -667,7 +691,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
     else aggregate_rows<D, (LAST || STAGED != kUnstaged)>(st, rows, r0, R, gt, acc);
     Packed<D> pk;
     if constexpr (K::BF) pk = pack_tile<D>(acc);
-    weight_gradient<T, D, STAGED, PITCH>(Hprev, r0, R, acc, pk, gt, n, h, gw);
+    weight_gradient<T, D, STAGED, PITCH, LAST>(Hprev, r0, R, acc, pk, gt, n, h, gw);
     if (!need_gh) continue;
     if (D == 32) request_state();
     if constexpr (LAST) {
@@ -758,7 +782,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
       if constexpr (GRADS) {
         a.gW[l - 1][at] = s;
       } else {
-        adam_value(adW, s, w[i], mw[i], vw[i]);
+        adam_weight(adW, s, w[i], mw[i], vw[i]);
         if (K::W_IN_REGISTERS) {
           wts.w[l - 1] = w[i];
           wts.m[l - 1] = mw[i];
@@ -783,7 +807,7 @@ __device__ __forceinline__ void backward_layer(const SmallTrain& a, const Stream
       if constexpr (GRADS) {
         a.gW[L - 1][static_cast<size_t>(k) * D + tid] = s;
       } else {
-        adam_value(adW, s, wts.wo, wts.mo, wts.vo);
+        adam_weight(adW, s, wts.wo, wts.mo, wts.vo);
         smem[cv.wo + tid] = wts.wo;
       }
     }

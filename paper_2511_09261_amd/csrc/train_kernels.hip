@@ -260,7 +260,7 @@ __device__ inline void adam_on_weight(const WeightTensor& wt, int64_t gid, float
   if (wt.grad_out != nullptr) wt.grad_out[gid] = gsum;
   if (update) {
     float w = wt.W[gid], m = wt.m[gid], v = wt.v[gid];
-    adam_value(adk, gsum, w, m, v);
+    adam_weight(adk, gsum, w, m, v);
     wt.m[gid] = m;
     wt.v[gid] = v;
     wt.W[gid] = w;
