@@ -137,7 +137,7 @@ struct gco_ctx {
     int32_t* block = nullptr;  // one allocation and one copy hold all of the following
     size_t capacity = 0;       // in ints
     const WaveRun* wave_runs[kWaveMaps] = {};
-    int num_wblocks[kWaveMaps] = {};
+    int num_wblocks[kWaveMaps] = {}, eighth[kWaveMaps] = {};
     const int32_t *blk_k = nullptr, *nblk_k = nullptr, *wblk_k[kWaveMaps] = {}, *chunk_part = nullptr,
                   *heavy_rows = nullptr;
     // workgroups that hold partials, per weight set: wide kernels, wave kernels, narrow tiles
@@ -515,6 +515,18 @@ Grouping grouping_of(int storage, int dim, int n, int v) {
   return f32 && dim <= 32 && gathers_rows && bytes > 32.0 * 1024 * 1024 ? Grouping::kIfEven : Grouping::kNone;
 }
 
+// Whether launch ids go round the XCDs in contiguous eighths of the workgroups (GraphView::eighth): where the
+// rows of the runs exceed one L2 (4 MB), in launches that gather rows and whose workgroups are not grouped already.
+// fp32, us per epoch without / with: width 16, 150 k rows 132 / 123, 400 k 138 / 128; width 64, 40 k rows 149 / 135, 80 k
+// 135 / 123, 150 k in 24 uneven subgraphs forward 65.8 / 47.5, embedding backward 114 / 99; width 128, 20 k rows 313 / 277.
+// bf16: width 64, 300 k rows 492 / 452; width 128, 400 k 1294 / 1235; not its embedding backward, which is bound by
+// Adam's state and takes longer (1.1 M rows of width 64 421 / 433, 0.5 M of width 128 394 / 405).  One subgraph: no difference.
+bool eighths_of(int storage, int dim, int64_t rows, int v, Grouping grouping) {
+  const bool f32 = storage == GCO_STORAGE_FP32;
+  const bool gathers_rows = v == WM_FWD || v == WM_BWD || (v == WM_EMBED && f32);
+  return grouping == Grouping::kNone && gathers_rows && static_cast<double>(rows) * dim * (f32 ? 4 : 2) > 4.0 * 1024 * 1024;
+}
+
 void wave_map_of(int storage, int dim, int v, int P, const std::vector<int>& part_rows, const std::vector<int>& wrow,
                  const uint8_t* active, std::vector<int>& wblk_k, std::vector<WaveRun>& wave_runs) {
   const bool f32 = storage == GCO_STORAGE_FP32;
@@ -615,11 +627,17 @@ int upload_active_maps(gco_ctx* ctx, gco_ctx::ActiveMaps& m, const uint8_t* acti
   put_lists(&m.pbl_ptr, &m.pbl_list, blk_k, Pw);
   put_lists(&m.nwbl_ptr, &m.nwbl_list, nblk_k, Pw);
   std::vector<int> narrow;
+  int64_t rows = 0;  // of the subgraphs that take part
+  for (int k = 0; k < P; ++k)
+    if (active == nullptr || active[k]) rows += h.part_rows[k + 1] - h.part_rows[k];
   for (int v = 0; v < kWaveMaps; ++v) {
     std::vector<int> wk;
     std::vector<WaveRun> runs;
     wave_map_of(ctx->cfg.storage, ctx->cfg.dim, v, P, h.part_rows, h.wrow, active, wk, runs);
     m.num_wblocks[v] = static_cast<int>(wk.size());
+    // grouped by subgraph, its workgroups are not in the order of the subgraphs
+    const Grouping grouping = std::is_sorted(wk.begin(), wk.end()) ? Grouping::kNone : Grouping::kAlways;
+    m.eighth[v] = eighths_of(ctx->cfg.storage, ctx->cfg.dim, rows, v, grouping) ? (m.num_wblocks[v] + 7) / 8 : 0;
     put(&m.wblk_k[v], wk.data(), wk.size());
     static_assert(sizeof(WaveRun) % 16 == 0 && alignof(WaveRun) == 16, "runs lie at 16-byte boundaries of the block");
     std::vector<int32_t> words(runs.size() * (sizeof(WaveRun) / sizeof(int32_t)));
@@ -668,6 +686,7 @@ GraphView view_with(const gco_ctx* ctx, const gco_ctx::ActiveMaps& m) {
     g.wblk_k[v] = m.wblk_k[v];
     g.wave_runs[v] = m.wave_runs[v];
     g.num_wblocks[v] = m.num_wblocks[v];
+    g.eighth[v] = m.eighth[v];
   }
   g.chunk_part = m.chunk_part;
   g.heavy_rows = m.heavy_rows;
@@ -1252,6 +1271,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     g.wave_runs[v] = ctx->full.wave_runs[v];
     g.wblk_k[v] = ctx->full.wblk_k[v];
     g.num_wblocks[v] = ctx->full.num_wblocks[v];
+    g.eighth[v] = ctx->full.eighth[v];
   }
   g.wrowptr = ctx->d_wrowptr;
   g.wtile_hptr = ctx->d_wtile_hptr;

@@ -114,6 +114,10 @@ struct GraphView {
   const int* wblk_k[kWaveMaps] = {};
   const WaveRun* wave_runs[kWaveMaps] = {};
   int num_wblocks[kWaveMaps] = {};
+  // Launches that gather rows: workgroup ids are dealt to the 8 XCDs round-robin, so that neighbouring workgroups, which
+  // gather from the same subgraph, would each fetch its rows into an L2 of their own.  eighth[m] != 0: launch id b stands
+  // for workgroup (b % 8) eighth + b / 8 (none past the last one), and an XCD works through a contiguous eighth.
+  int eighth[kWaveMaps] = {};
   // light stream: per row its diagonal entry {i, A_hat_ii}, then its packed entries unless
   // the row is pre-reduced; row i owns went[wrowptr[i] .. wrowptr[i+1]).  went_t holds the
   // entries of A_hat^T.  kEntPad zero entries follow the last row.
@@ -162,6 +166,15 @@ struct GraphView {
   float* hpart_partial = nullptr;
   int* hpart_count = nullptr;
 };
+
+inline int launch_ids(const GraphView& g, WaveMap m) { return g.eighth[m] != 0 ? 8 * g.eighth[m] : g.num_wblocks[m]; }
+#if defined(__HIPCC__)
+// The workgroup that this launch id stands for; num_wblocks[m] or more: none.
+__device__ __forceinline__ int workgroup_number(const GraphView& g, WaveMap m) {
+  const int b = blockIdx.x;
+  return g.eighth[m] != 0 ? b % 8 * g.eighth[m] + b / 8 : b;
+}
+#endif
 
 // The view of the transposed matrix: scale vectors and entry arrays exchanged.
 inline GraphView transposed(const GraphView& g) {

@@ -101,8 +101,10 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 6 : (D == 32 ? 4 : (D == 64 ? 3 :
   f32x4* wl = reinterpret_cast<f32x4*>(smem);
   const int tid = threadIdx.x, lane = tid % 64, n = lane % 16, h = lane / 16;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-  const int k = g.wblk_k[WM_FWD][blockIdx.x];
-  const WaveRun run = g.wave_runs[WM_FWD][blockIdx.x * kWavesPerBlock + wave];
+  const int wg = workgroup_number(g, WM_FWD);
+  if (wg >= g.num_wblocks[WM_FWD]) return;
+  const int k = g.wblk_k[WM_FWD][wg];
+  const WaveRun run = g.wave_runs[WM_FWD][wg * kWavesPerBlock + wave];
   if (k < 0) return;
   // A operands of Z^T = W^T AGG^T: wl[(ta NQ + q) 64 + lane][j] = W[16 q + 4 h + j][16 ta + n]
   const float* Wk = W + static_cast<size_t>(k) * w_stride;
@@ -190,7 +192,7 @@ template <int D, bool LAST, bool TO_EMBED>
 __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_tile_kernel(GraphView g, BwdArgs a) {
   using T = TK<D>;
   constexpr int NQ = T::NQ, DP = T::DP, PT = T::PT, TB = T::TB;
-  constexpr int WM = TO_EMBED ? WM_EMBED : WM_BWD;
+  constexpr WaveMap WM = TO_EMBED ? WM_EMBED : WM_BWD;
   using Rows = std::conditional_t<LAST, MaskRows<D>, PlainRows<D>>;
   constexpr int kTaUnroll = D <= 64 ? NQ : 1;
   // when the epilogue's rows are requested: as early as the registers allow
@@ -204,7 +206,9 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   f32x4* wl = reinterpret_cast<f32x4*>(smem);
   float* gt_all = reinterpret_cast<float*>(smem) + (T::W_IN_LDS ? DP * DP : 0);
   float* last = reinterpret_cast<float*>(smem + bwd_tile_lds<D>()) - kWavesPerBlock * DP;
-  const int k = g.wblk_k[WM][blockIdx.x];
+  const int wg = workgroup_number(g, WM);
+  if (wg >= g.num_wblocks[WM]) return;
+  const int k = g.wblk_k[WM][wg];
   if (k < 0) return;
   const AdamStep ad = a.adam.for_part(k);
   const int tid = threadIdx.x, lane = tid % 64, n = lane % 16, h = lane / 16;
@@ -214,7 +218,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   const float* __restrict__ Wk = a.W + static_cast<size_t>(k) * a.w_stride;
   // Rows of this wavefront, kStep apart; with shared accumulators the workgroup's wavefronts
   // take turns and all of them go through the same number of tiles.
-  const WaveRun* runs = g.wave_runs[WM] + blockIdx.x * kWavesPerBlock;
+  const WaveRun* runs = g.wave_runs[WM] + wg * kWavesPerBlock;
   int r0, r1;
   constexpr int kStep = T::SHARED_GW ? kWavesPerBlock * kTile : kTile;
   if (T::SHARED_GW) {
@@ -378,7 +382,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   }
 
   // one partial per workgroup; LAST: M first, from which both gradients follow
-  float* out = a.gW_partial + static_cast<size_t>(blockIdx.x) * D * D;
+  float* out = a.gW_partial + static_cast<size_t>(wg) * D * D;
   if constexpr (T::SHARED_GW) {
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
@@ -395,7 +399,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
         }
       if (LAST) {
         column = add_over_h(column);
-        if (h == 0) a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + c] = column;
+        if (h == 0) a.gwout_partial[static_cast<size_t>(wg) * D + c] = column;
       }
     }
   } else if (alone) {
@@ -416,7 +420,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
           }
       if (LAST) {
         column = add_over_h(column);
-        if (h == 0 && in) a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + c] = column;
+        if (h == 0 && in) a.gwout_partial[static_cast<size_t>(wg) * D + c] = column;
       }
     }
   } else {
@@ -466,7 +470,7 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
         float s = 0.f;
 #pragma unroll
         for (int v = 0; v < kWavesPerBlock; ++v) s += last[v * DP + tid];
-        a.gwout_partial[static_cast<size_t>(blockIdx.x) * D + tid] = s;
+        a.gwout_partial[static_cast<size_t>(wg) * D + tid] = s;
       }
     }
   }
@@ -490,7 +494,7 @@ void fwd_t(const Launch& ln, const GraphView& g, const float* X, const float* W,
   }
   allow_lds(fwd_tile_kernel<D>, fwd_tile_lds<D>());
   ln.begin(KK_FWD_HIDDEN);
-  fwd_tile_kernel<D><<<g.num_wblocks[WM_FWD], kBlock, fwd_tile_lds<D>(), ln.st>>>(
+  fwd_tile_kernel<D><<<launch_ids(g, WM_FWD), kBlock, fwd_tile_lds<D>(), ln.st>>>(
       g, X, W, w_stride, Y, w_out, wout_stride, t, mask, heavy_partial);
   ln.end(KK_FWD_HIDDEN);
 }
@@ -499,7 +503,7 @@ template <int D, bool LAST, bool TO_EMBED>
 void bwd_launch(const Launch& ln, const GraphView& gt, const BwdArgs& a) {
   allow_lds(bwd_tile_kernel<D, LAST, TO_EMBED>, bwd_tile_lds<D>());
   bwd_tile_kernel<D, LAST, TO_EMBED>
-      <<<gt.num_wblocks[TO_EMBED ? WM_EMBED : WM_BWD], kBlock, bwd_tile_lds<D>(), ln.st>>>(gt, a);
+      <<<launch_ids(gt, TO_EMBED ? WM_EMBED : WM_BWD), kBlock, bwd_tile_lds<D>(), ln.st>>>(gt, a);
 }
 
 template <int D>

@@ -491,7 +491,9 @@ __global__ __launch_bounds__(kBlock, D == 64 && !EARLY ? 3 : 2) void fwd_wave_ke
   uint4* pair_mask = reinterpret_cast<uint4*>(smem + G_::w_bytes + D * sizeof(float));
   unsigned char* wave_mem = reinterpret_cast<unsigned char*>(pair_mask + 256);
 
-  const int k = g.wblk_k[WM_FWD][blockIdx.x];
+  const int wg = workgroup_number(g, WM_FWD);
+  if (wg >= g.num_wblocks[WM_FWD]) return;
+  const int k = g.wblk_k[WM_FWD][wg];
   if (k < 0) return;
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
@@ -502,7 +504,7 @@ __global__ __launch_bounds__(kBlock, D == 64 && !EARLY ? 3 : 2) void fwd_wave_ke
   if (tid < D) wo[tid] = w_out != nullptr ? w_out[static_cast<size_t>(k) * wout_stride + tid] : 0.f;
   __syncthreads();  // the only workgroup barrier: W^k and w_out are in LDS
 
-  const WaveRun run = g.wave_runs[WM_FWD][blockIdx.x * (kBlock / 64) + wave];
+  const WaveRun run = g.wave_runs[WM_FWD][wg * (kBlock / 64) + wave];
   if (run.tile0 >= run.tile1) return;
   unsigned char* my_lds = wave_mem + wave * G_::wave_bytes;
   bf16_t* ot = reinterpret_cast<bf16_t*>(my_lds);  // overlays the row buffer
@@ -681,8 +683,10 @@ __global__ __launch_bounds__(kBlock, 2) void bwd_wave_kernel(GraphView g, BwdArg
   unsigned char* wave_mem = reinterpret_cast<unsigned char*>(pair_mask + 256);
   static_assert(!GWI || 4 * G_::bwd_wave_bytes >= 2 * D * D * sizeof(float), "room for the gradient reduction");
 
-  constexpr int WM = TO_EMBED ? WM_EMBED : WM_BWD;
-  const int k = g.wblk_k[WM][blockIdx.x];
+  constexpr WaveMap WM = TO_EMBED ? WM_EMBED : WM_BWD;
+  const int wg = workgroup_number(g, WM);
+  if (wg >= g.num_wblocks[WM]) return;
+  const int k = g.wblk_k[WM][wg];
   if (k < 0) return;
   const AdamStep ad = a.adam.for_part(k);
   const int tid = threadIdx.x, lane = tid % 64;
@@ -695,7 +699,7 @@ __global__ __launch_bounds__(kBlock, 2) void bwd_wave_kernel(GraphView g, BwdArg
 
   const bf16_t* GZ = static_cast<const bf16_t*>(a.GZ_in);
   const bf16_t* Hprev = static_cast<const bf16_t*>(a.Hprev);
-  const WaveRun run = g.wave_runs[WM][blockIdx.x * (kBlock / 64) + wave];
+  const WaveRun run = g.wave_runs[WM][wg * (kBlock / 64) + wave];
   unsigned char* R = wave_mem + wave * G_::bwd_wave_bytes;
   const bool need_gh = !(TO_EMBED && a.mode == EMBED_SKIP);
   constexpr int NTW = GWI ? G_::NT : 1;
@@ -947,7 +951,7 @@ __global__ __launch_bounds__(kBlock, 2) void bwd_wave_kernel(GraphView g, BwdArg
       }
       __syncthreads();
     }
-    float* out = a.gW_partial + static_cast<size_t>(blockIdx.x) * D * D;
+    float* out = a.gW_partial + static_cast<size_t>(wg) * D * D;
     for (int idx = tid; idx < D * D; idx += kBlock) out[idx] = buf[idx] + buf[D * D + idx];
   }
 }
@@ -1143,10 +1147,10 @@ static void bwd_wave_t(const Launch& ln, bool to_embed, const GraphView& gt, con
   ln.begin(kind);
   if (to_embed) {
     allow_lds(bwd_wave_kernel<D, true>, bwd_wave_lds<D>());
-    bwd_wave_kernel<D, true><<<gt.num_wblocks[WM_EMBED], kBlock, bwd_wave_lds<D>(), ln.st>>>(gt, a);
+    bwd_wave_kernel<D, true><<<launch_ids(gt, WM_EMBED), kBlock, bwd_wave_lds<D>(), ln.st>>>(gt, a);
   } else {
     allow_lds(bwd_wave_kernel<D, false>, bwd_wave_lds<D>());
-    bwd_wave_kernel<D, false><<<gt.num_wblocks[WM_BWD], kBlock, bwd_wave_lds<D>(), ln.st>>>(gt, a);
+    bwd_wave_kernel<D, false><<<launch_ids(gt, WM_BWD), kBlock, bwd_wave_lds<D>(), ln.st>>>(gt, a);
   }
   ln.end(kind);
 }
@@ -1170,7 +1174,7 @@ void launch_fwd_hidden_wave(const Launch& ln, int D, const GraphView& g, const v
                             float* heavy_partial) {
   auto run = [&](auto kernel, size_t lds) {
     allow_lds(kernel, lds);
-    kernel<<<g.num_wblocks[WM_FWD], kBlock, lds, ln.st>>>(g, static_cast<const bf16_t*>(X), W, w_stride,
+    kernel<<<launch_ids(g, WM_FWD), kBlock, lds, ln.st>>>(g, static_cast<const bf16_t*>(X), W, w_stride,
                                                           static_cast<bf16_t*>(Y), w_out, wout_stride, t, heavy_partial);
   };
   // Width 64: up to two workgroups per CU the registers of EARLY_ROWS are there for nothing else
