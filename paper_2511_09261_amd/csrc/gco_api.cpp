@@ -163,6 +163,15 @@ struct gco_ctx {
   bool small_train = false;
   SmallLds small_lds;
   int2* d_fused_cuts = nullptr;
+  // one-layer model with fixed embeddings: its workgroups (0: not used), the ones that hold partials of each weight
+  // set, X = A_hat E of the training call under way, the second set of weights and moments
+  struct Fixed {
+    ScalarStaging sg;
+    int workgroups = 0, most_partials = 0;
+    const int32_t *set_ptr = nullptr, *list = nullptr;
+    float *X = nullptr, *gw_partial = nullptr;
+    ScalarWeights other;
+  } fixed;
   int32_t* d_heavy_ptr = nullptr;
   int2 *d_went = nullptr, *d_went_t = nullptr;
   float *d_wval = nullptr, *d_wval_t = nullptr;
@@ -248,6 +257,7 @@ struct gco_ctx {
     has_graph = has_params = probs_valid = false;
     heavy_E_valid = false;
     num_hparts = 0;
+    fixed = Fixed{};
     best_on = best_alloc = false;
     loss_hist_cap = 0;
     loss_hist = nullptr;
@@ -573,6 +583,81 @@ bool small_train_pays(const gco_config& c, int P, int n, int64_t entries, int ma
                          hidden * (k.more + 1e-3 * (k.per_row * n + k.per_entry * static_cast<double>(entries)) +
                                    k.adam * 1e-6 * P * c.dim * c.dim + k.longest_there * longest);
   return one < (P <= 256 ? 0.95 : 0.85) * several;
+}
+
+// Tables of the width-1 launches (ScalarStaging): per_part[k] workgroups of `waves` wavefronts for subgraph k.
+struct ScalarTables {
+  std::vector<int> wg_ptr, wg_k, launch_of;
+  std::vector<int2> cuts;
+};
+ScalarTables scalar_tables(const std::vector<int>& part_rows, const std::vector<int>& wrow, const std::vector<int>& per_part,
+                           int waves, bool launch_order) {
+  const int P = static_cast<int>(per_part.size());
+  ScalarTables t;
+  t.wg_ptr.assign(static_cast<size_t>(P) + 1, 0);
+  for (int kk = 0; kk < P; ++kk) {
+    t.wg_ptr[kk + 1] = t.wg_ptr[kk] + per_part[kk];
+    t.wg_k.insert(t.wg_k.end(), static_cast<size_t>(per_part[kk]), kk);
+  }
+  // Launch order: workgroup ids go round the 8 XCDs, so the workgroups of a subgraph get ids
+  // that are equal mod 8: they share one L2, and the vector they all copy is fetched into it
+  // once.  Subgraphs are dealt to the XCD with the least work so far; launch_of[b] = workgroup
+  // that launch id b stands for (-1: none).
+  if (launch_order) {
+    std::vector<std::vector<int>> on_xcd(8);
+    for (int kk = 0; kk < P; ++kk) {
+      size_t best = 0;
+      for (size_t x = 1; x < 8; ++x)
+        if (on_xcd[x].size() < on_xcd[best].size()) best = x;
+      for (int w = t.wg_ptr[kk]; w < t.wg_ptr[kk + 1]; ++w) on_xcd[best].push_back(w);
+    }
+    size_t depth = 0;
+    for (const auto& v : on_xcd) depth = std::max(depth, v.size());
+    t.launch_of.assign(depth * 8, -1);
+    for (size_t x = 0; x < 8; ++x)
+      for (size_t q = 0; q < on_xcd[x].size(); ++q) t.launch_of[q * 8 + x] = on_xcd[x][q];
+  }
+  // rows of every subgraph cut into contiguous runs of about equal cost (entries of the light
+  // stream plus one per row), one per wavefront of its workgroups; a run is handed over as its
+  // range of the stream
+  t.cuts.resize(static_cast<size_t>(t.wg_ptr[P]) * waves);
+  for (int kk = 0; kk < P; ++kk) {
+    const int rb = part_rows[kk], re = part_rows[kk + 1];
+    const int V = per_part[kk] * waves;
+    // cost of the subgraph's rows before row r
+    auto before = [&](int r) { return static_cast<double>(wrow[r] - wrow[rb]) + (r - rb); };
+    int r = rb;
+    for (int v = 0; v < V; ++v) {
+      const int start = r;
+      if (v == V - 1) {
+        r = re;
+      } else {  // rows as long as their end is within the wavefront's share of the cost
+        const double want = before(re) * (v + 1) / V;
+        int lo = r, hi = re;
+        while (lo < hi) {
+          const int mid = (lo + hi) / 2;
+          if (before(mid + 1) <= want) lo = mid + 1; else hi = mid;
+        }
+        r = lo;
+      }
+      t.cuts[static_cast<size_t>(t.wg_ptr[kk]) * waves + v] = make_int2(wrow[start], wrow[r]);
+    }
+  }
+  return t;
+}
+int upload_scalar_tables(gco_ctx* ctx, const ScalarTables& t, int2** cuts, int32_t** wg_k, int32_t** wg_ptr,
+                         int32_t** launch_of) {
+  GALLOC(*cuts, t.cuts.size());
+  GALLOC(*wg_k, t.wg_k.size());
+  GALLOC(*wg_ptr, t.wg_ptr.size());
+  HIPCHK(h2d(ctx, *cuts, t.cuts.data(), t.cuts.size()));
+  HIPCHK(h2d(ctx, *wg_k, t.wg_k.data(), t.wg_k.size()));
+  HIPCHK(h2d(ctx, *wg_ptr, t.wg_ptr.data(), t.wg_ptr.size()));
+  if (!t.launch_of.empty()) {
+    GALLOC(*launch_of, t.launch_of.size());
+    HIPCHK(h2d(ctx, *launch_of, t.launch_of.data(), t.launch_of.size()));
+  }
+  return GCO_OK;
 }
 
 // Workgroup ids grouped by the subgraph they work on (ascending within a group);
@@ -1122,7 +1207,6 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
       // workgroups per subgraph: one, or (staged) a share of about two per compute unit in
       // proportion to the subgraph's entries, such that a wavefront keeps a few steps of work
       const int NW = ctx->fused_scalar ? fused_nw : scalar_staged_waves();
-      std::vector<int> wg_ptr(static_cast<size_t>(P) + 1, 0);
       const int64_t target = std::max<int64_t>(P, std::min<int64_t>(512, total_light / (static_cast<int64_t>(NW) * 256)));
       std::vector<int> per_part(static_cast<size_t>(P), 1);
       if (ctx->staged_scalar && total_light > 0) {
@@ -1130,74 +1214,59 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
         per_part = apportion(work, target, std::vector<int>(static_cast<size_t>(P), 1),
                              std::vector<int>(static_cast<size_t>(P), static_cast<int>(target)));
       }
-      for (int kk = 0; kk < P; ++kk) {
-        const int per = per_part[kk];
-        wg_ptr[kk + 1] = wg_ptr[kk] + per;
-        for (int q = 0; q < per; ++q) ctx->hm.staged_k.push_back(kk);
-      }
-      const int num_wgs = wg_ptr[P];
-      ctx->num_loss_slots = num_wgs;
-      // Launch order of the staged form: workgroup ids go round the 8 XCDs, so the
-      // workgroups of a subgraph get ids that are equal mod 8: they share one L2, and the
-      // vector they all copy is fetched into it once.  Subgraphs are dealt to the XCD with
-      // the least work so far; launch_of[b] = workgroup that launch id b stands for (-1: none).
-      std::vector<int> launch_of;
-      if (ctx->staged_scalar) {
-        std::vector<std::vector<int>> on_xcd(8);
-        for (int kk = 0; kk < P; ++kk) {
-          size_t best = 0;
-          for (size_t x = 1; x < 8; ++x)
-            if (on_xcd[x].size() < on_xcd[best].size()) best = x;
-          for (int w = wg_ptr[kk]; w < wg_ptr[kk + 1]; ++w) on_xcd[best].push_back(w);
-        }
-        size_t depth = 0;
-        for (const auto& v : on_xcd) depth = std::max(depth, v.size());
-        launch_of.assign(depth * 8, -1);
-        for (size_t x = 0; x < 8; ++x)
-          for (size_t q = 0; q < on_xcd[x].size(); ++q) launch_of[q * 8 + x] = on_xcd[x][q];
-      }
-      ctx->staged_wgs = static_cast<int>(launch_of.size());
-      // rows of every subgraph cut into contiguous runs of about equal cost (entries of the
-      // light stream plus one per row), one per wavefront of its workgroups; a run is handed
-      // over as its range of the stream
-      std::vector<int2> cuts(static_cast<size_t>(num_wgs) * NW);
-      for (int kk = 0; kk < P; ++kk) {
-        const int rb = part_rows[kk], re = part_rows[kk + 1];
-        const int V = (wg_ptr[kk + 1] - wg_ptr[kk]) * NW;
-        // cost of the subgraph's rows before row r
-        auto before = [&](int r) { return static_cast<double>(wrow[r] - wrow[rb]) + (r - rb); };
-        int r = rb;
-        for (int v = 0; v < V; ++v) {
-          const int start = r;
-          if (v == V - 1) {
-            r = re;
-          } else {  // rows as long as their end is within the wavefront's share of the cost
-            const double want = before(re) * (v + 1) / V;
-            int lo = r, hi = re;
-            while (lo < hi) {
-              const int mid = (lo + hi) / 2;
-              if (before(mid + 1) <= want) lo = mid + 1; else hi = mid;
-            }
-            r = lo;
-          }
-          cuts[static_cast<size_t>(wg_ptr[kk]) * NW + v] = make_int2(wrow[start], wrow[r]);
-        }
-      }
+      const ScalarTables tables = scalar_tables(part_rows, wrow, per_part, NW, ctx->staged_scalar);
+      ctx->hm.staged_k = tables.wg_k;
+      ctx->num_loss_slots = tables.wg_ptr[P];
+      ctx->staged_wgs = static_cast<int>(tables.launch_of.size());
       std::vector<int> heavy_ptr(static_cast<size_t>(P) + 1, 0);
       for (int kk : ctx->hm.heavy_part) heavy_ptr[kk + 1]++;
       for (int kk = 0; kk < P; ++kk) heavy_ptr[kk + 1] += heavy_ptr[kk];
-      GALLOC(ctx->d_fused_cuts, cuts.size());
       GALLOC(ctx->d_heavy_ptr, heavy_ptr.size());
-      GALLOC(ctx->d_staged_k, ctx->hm.staged_k.size());
-      GALLOC(ctx->d_staged_ptr, wg_ptr.size());
-      if (!launch_of.empty()) {
-        GALLOC(ctx->d_staged_launch, launch_of.size());
-        HIPCHK(h2d(ctx, ctx->d_staged_launch, launch_of.data(), launch_of.size()));
-      }
-      HIPCHK(h2d(ctx, ctx->d_fused_cuts, cuts.data(), cuts.size()));
       HIPCHK(h2d(ctx, ctx->d_heavy_ptr, heavy_ptr.data(), heavy_ptr.size()));
-      HIPCHK(h2d(ctx, ctx->d_staged_k, ctx->hm.staged_k.data(), ctx->hm.staged_k.size()));
-      HIPCHK(h2d(ctx, ctx->d_staged_ptr, wg_ptr.data(), wg_ptr.size()));
+      const int rc = upload_scalar_tables(ctx, tables, &ctx->d_fused_cuts, &ctx->d_staged_k, &ctx->d_staged_ptr, &ctx->d_staged_launch);
+      if (rc != GCO_OK) return rc;
+    }
+    // One-layer model with fixed embeddings: workgroups for the two launches of its epochs (launch_fixed_probs)
+    ctx->fixed.workgroups = 0;
+    if (L == 1 && !ctx->cfg.train_embed && form == GCO_SCALAR_AUTO && staged_cap <= scalar_staged_max_cap() && total_light > 0) {
+      const int64_t target = std::max<int64_t>(P, std::min<int64_t>(512, total_light / 1024));
+      const std::vector<double> work(light_of.begin(), light_of.end());
+      std::vector<int> lo(static_cast<size_t>(P), 0), hi(static_cast<size_t>(P), 0);  // none where there are no rows
+      for (int kk = 0; kk < P; ++kk)
+        if (part_rows[kk + 1] > part_rows[kk]) {
+          lo[kk] = 1;
+          hi[kk] = static_cast<int>(target);
+        }
+      const std::vector<int> per_part = apportion(work, target, lo, hi);
+      const ScalarTables tables = scalar_tables(part_rows, wrow, per_part, scalar_staged_waves(), true);
+      int2* cuts = nullptr;
+      int32_t *wg_k = nullptr, *wg_ptr = nullptr, *launch_of = nullptr;
+      const int rc = upload_scalar_tables(ctx, tables, &cuts, &wg_k, &wg_ptr, &launch_of);
+      if (rc != GCO_OK) return rc;
+      ScalarStaging& sg = ctx->fixed.sg;
+      sg.num_launch = static_cast<int>(tables.launch_of.size());
+      sg.cap = staged_cap;
+      sg.cuts = cuts;
+      sg.wg_k = wg_k;
+      sg.wg_ptr = wg_ptr;
+      sg.launch_of = launch_of;
+      std::vector<int> heavy_ptr(static_cast<size_t>(P) + 1, 0), list(static_cast<size_t>(tables.wg_ptr[P])),
+          all{0, tables.wg_ptr[P]};
+      for (int kk : ctx->hm.heavy_part) heavy_ptr[kk + 1]++;
+      for (int kk = 0; kk < P; ++kk) heavy_ptr[kk + 1] += heavy_ptr[kk];
+      for (size_t q = 0; q < list.size(); ++q) list[q] = static_cast<int>(q);
+      int32_t *d_heavy_ptr = nullptr, *d_list = nullptr, *d_all = nullptr;
+      GALLOC(d_heavy_ptr, heavy_ptr.size());
+      GALLOC(d_list, list.size());
+      GALLOC(d_all, all.size());
+      HIPCHK(h2d(ctx, d_heavy_ptr, heavy_ptr.data(), heavy_ptr.size()));
+      HIPCHK(h2d(ctx, d_list, list.data(), list.size()));
+      HIPCHK(h2d(ctx, d_all, all.data(), all.size()));
+      sg.heavy_ptr = d_heavy_ptr;
+      ctx->fixed.list = d_list;
+      ctx->fixed.set_ptr = ctx->Pw == 1 ? d_all : wg_ptr;
+      ctx->fixed.workgroups = tables.wg_ptr[P];
+      ctx->fixed.most_partials = ctx->Pw == 1 ? tables.wg_ptr[P] : *std::max_element(per_part.begin(), per_part.end());
     }
   }
   ctx->full = gco_ctx::ActiveMaps{};  // their blocks went with the graph before
@@ -1352,7 +1421,14 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   GALLOC(ctx->p, static_cast<size_t>(n));
   GALLOC(ctx->g_z, static_cast<size_t>(n));
   GALLOC(ctx->g_t, static_cast<size_t>(n));
-  GALLOC(ctx->loss_partial, static_cast<size_t>(g.num_loss_slots) * kLossSets);
+  if (ctx->fixed.workgroups != 0) {
+    const size_t weights = static_cast<size_t>(ctx->Pw) * D;
+    GALLOC(ctx->fixed.gw_partial, static_cast<size_t>(ctx->fixed.workgroups) * D);
+    GALLOC(ctx->fixed.other.W, weights);
+    GALLOC(ctx->fixed.other.m, weights);
+    GALLOC(ctx->fixed.other.v, weights);
+  }
+  GALLOC(ctx->loss_partial, static_cast<size_t>(std::max(g.num_loss_slots, ctx->fixed.workgroups)) * kLossSets);
   GALLOC(ctx->loss_part, static_cast<size_t>(P));
   GALLOC(ctx->loss_one, 1);
   HIPCHK(hipStreamSynchronize(st));
@@ -1738,6 +1814,22 @@ static void copy_params(gco_ctx* ctx, const GraphView& gv, const int32_t* flag, 
                       ctx->W, elems, L);
 }
 
+// One-layer model, embeddings fixed, all subgraphs.  X = A_hat E takes one aggregation, an epoch on it saves three passes
+// over the entries and four launches (18.8 k rows of width 64 in 4 subgraphs: X 27 us, an epoch 45 -> 18), so a call of few
+// epochs (under four) keeps the general launches; so do bf16 rows so many that X in fp32 no longer stays in the caches, where reading it
+// costs more than the passes that it saves.
+static bool fixed_path(gco_ctx* ctx, int epochs, bool all) {
+  if (ctx->fixed.workgroups == 0 || !all || ctx->best_on || epochs < 4) return false;
+  const size_t nd = static_cast<size_t>(ctx->n) * ctx->cfg.dim;
+  if (ctx->cfg.storage == GCO_STORAGE_BF16 && nd * sizeof(float) > (size_t{64} << 20)) return false;
+  if (ctx->fixed.X == nullptr) {  // kept for the calls to come; without room for it the general launches serve
+    float* X = nullptr;
+    if (!ctx->galloc(&X, nd)) return false;
+    ctx->fixed.X = X;
+  }
+  return true;
+}
+
 // `epochs` training epochs of the subgraphs with active[k] != 0 (nullptr: all of them); the
 // others keep their parameters, optimizer state, step counts and probabilities.
 static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, double* loss_per_epoch) {
@@ -1769,6 +1861,31 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
   for (int64_t t : ctx->stepW) uniform = uniform && t == ctx->stepE[0];
   const gco_config& c = ctx->cfg;
   std::vector<float2> bc;
+  const bool fixed = fixed_path(ctx, epochs, active == nullptr);
+  const ScalarWeights own{ctx->W[0], ctx->mW[0], ctx->vW[0]};
+  ScalarWeights from = own;      // where the weights are
+  AdamStep pending{};            // of the gradients not yet applied
+  GraphView gx = gv;             // with the loss partials of the fixed path
+  // up to this many partials every workgroup sums them itself before it uses the weights; beyond, a launch does
+  const bool own_adam = ctx->fixed.most_partials <= 192;
+  if (fixed) {
+    gx.loss_ptr = ctx->fixed.sg.wg_ptr;
+    gx.loss_list = ctx->fixed.list;
+    gx.num_loss_slots = ctx->fixed.workgroups;
+    launch_propagate(ctx->launch(), c.storage, c.dim, gv, ctx->H[0], ctx->fixed.X, ctx->d_heavy_partial);
+  }
+  // Adam on the weights from the partials of the fixed path
+  auto fixed_adam = [&](const AdamStep& ad) {
+    WeightTensor wt;
+    wt.W = own.W;
+    wt.m = own.m;
+    wt.v = own.v;
+    wt.partial = ctx->fixed.gw_partial;
+    wt.blk_ptr = ctx->fixed.set_ptr;
+    wt.blk_list = ctx->fixed.list;
+    wt.elems = c.dim;
+    launch_adam_w(ctx->launch(), Pw, &wt, 1, ad, true, ctx->fixed.most_partials >= 512);
+  };
   // the loss partials of up to kLossSets epochs are reduced by one launch; so are the
   // per-subgraph bias corrections of those epochs uploaded at once
   for (int e0 = 0; e0 < epochs; e0 += kLossSets) {
@@ -1783,6 +1900,12 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
           const AdamStep ad = adam_constants(c, t0 + e0 + e + 1);
           bc[static_cast<size_t>(e) * (P + Pw) + q] = make_float2(ad.inv_bc1, ad.inv_sqrt_bc2);
         }
+      // the step of an epoch's gradients is taken by the next epoch's launch, which may follow this copy
+      if (fixed && e0 > 0 && own_adam) {
+        launch_fixed_probs(ctx->launch(), c.dim, gv, ctx->fixed.sg, ctx->fixed.workgroups, ctx->fixed.X, Pw == 1, from,
+                           from.W == own.W ? ctx->fixed.other : own, pending, ctx->fixed.gw_partial, ctx->p);
+        from = from.W == own.W ? ctx->fixed.other : own;
+      }
       HIPCHK(h2d(ctx, ctx->d_bc, bc.data(), bc.size()));
     }
     if (ctx->small_train) {
@@ -1796,6 +1919,24 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
         adE.per_part = ctx->d_bc + static_cast<size_t>(e) * (P + Pw);
         adW.per_part = adE.per_part + P;
       }
+      if (fixed) {
+        const int at = e0 + e;
+        const bool step = own_adam && at > 0 && !(e == 0 && !uniform);  // the one before has not been taken yet
+        // in the end the weights have to be in their own place: steps alternate, a first copy makes them even
+        const bool move = step || (own_adam && at == 0 && epochs % 2 == 0);
+        const ScalarWeights to = !move ? from : (from.W == own.W ? ctx->fixed.other : own);
+        launch_fixed_probs(ctx->launch(), c.dim, gv, ctx->fixed.sg, ctx->fixed.workgroups, ctx->fixed.X, Pw == 1, from, to,
+                           pending, step ? ctx->fixed.gw_partial : nullptr, ctx->p);
+        from = to;
+        launch_fixed_loss(ctx->launch(), c.dim, gv, ctx->fixed.sg, ctx->p, ctx->d_c,
+                          c.problem == GCO_PROBLEM_MAXCUT ? 2.f : c.alpha, ctx->g_z,
+                          ctx->loss_partial + static_cast<size_t>(e) * gx.num_loss_slots, ctx->fixed.X,
+                          ctx->fixed.gw_partial);
+        pending = adW;
+        if (!own_adam || at == epochs - 1) fixed_adam(adW);
+        ctx->probs_valid = true;
+        continue;
+      }
       run_hidden_forward(ctx, gv, e0 + e == epochs - 1);
       run_scalar_layer(ctx, gv, 3, e);
       if (ctx->best_on) {
@@ -1806,7 +1947,7 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
       }
       run_backward(ctx, gv, maps, true, adE, adW, nullptr, nullptr);
     }
-    launch_loss_reduce(ctx->launch(), gv, ctx->loss_partial, ne, gv.num_loss_slots, nullptr, ctx->loss_hist + e0);
+    launch_loss_reduce(ctx->launch(), gx, ctx->loss_partial, ne, gx.num_loss_slots, nullptr, ctx->loss_hist + e0);
   }
   for (int k = 0; k < P; ++k)
     if (actE[k]) ctx->stepE[k] += epochs;

@@ -378,6 +378,26 @@ void launch_fwd_hidden_wave(const Launch& ln, int D, const GraphView& g, const v
 // L = 1 backward: gw partial = sum_i X[i,:] g_t[i]; gE[i,:] = g_t[i] w^k.
 void launch_bwd_single(const Launch& ln, int storage, int D, const GraphView& g, const BwdArgs& a);
 
+// ---- one-layer model whose embeddings are not trained: with X = A_hat E, formed once for a training call, an epoch is
+//   p = sigmoid(X w);  s = A_loc p, loss, g_z = dL/dz;  dL/dw = X^T g_z
+// instead of six dependent launches (E w, A_hat, A_loc, A_hat^T, E^T, Adam), four of them over the entries ----
+// X = A_hat E (fp32 rows) from E in storage type.
+void launch_propagate(const Launch& ln, int storage, int D, const GraphView& g, const void* E, float* X,
+                      float* heavy_partial);
+// The weights of the scalar layer with Adam's moments, [Pw, D] each.
+struct ScalarWeights {
+  float *W = nullptr, *m = nullptr, *v = nullptr;
+};
+// p = sigmoid(X w).  Workgroups and their row ranges as for launch_fixed_loss.  gw_partial != nullptr: w is first taken
+// from `from` by an Adam step on the sum of the partials [workgroups, D] of its subgraph (of all, if shared), in every
+// workgroup alike, and goes to `to`, which is not `from`; else from == to, or `to` receives a copy.
+void launch_fixed_probs(const Launch& ln, int D, const GraphView& g, const ScalarStaging& sg, int workgroups,
+                        const float* X, bool shared, const ScalarWeights& from, const ScalarWeights& to,
+                        const AdamStep& adam, const float* gw_partial, float* p);
+// g_z and the loss partials as launch_loss in its staged form, and the partials of X^T g_z per workgroup.
+void launch_fixed_loss(const Launch& ln, int D, const GraphView& g, const ScalarStaging& sg, const float* p, const float* c,
+                       float q, float* g_z, double* loss_partial, const float* X, float* gw_partial);
+
 // Sum the per-workgroup partials of each weight tensor in a fixed order, then
 // apply Adam (or only write the gradient when grad_out != nullptr).  Up to three
 // tensors (one per layer) are served by one launch.

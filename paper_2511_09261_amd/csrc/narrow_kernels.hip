@@ -497,6 +497,195 @@ __global__ __launch_bounds__(64 * NW) void narrow_staged_kernel(GraphView g, Op 
 
 constexpr int kStagedWaves = 8;
 
+// ---------------------------------------------------------------------------
+// One-layer model on X = A_hat E (see launch_propagate): the two launches of an epoch.  A workgroup's rows are those
+// whose entries its wavefronts sum.  X is read in 16-byte pieces, D / 4 lanes a row; both kernels request X before
+// what they have to wait for (the weights; the entries and the gathered p).
+// 18.8 k rows of width 64 in 4 subgraphs: 5.2 us
+// and 12.6, where the six launches of the general epoch took 4.1 + 8.6 + 8.5 + 7.9 + 6.2 + 9.1.  Bound by their chains of
+// dependent loads: tables, p into LDS, entries, g_z, the sum over the lane groups.
+// ---------------------------------------------------------------------------
+constexpr int kFixedThreads = 64 * kStagedWaves;
+constexpr int kFixedAhead = 4;  // rows per lane group requested ahead
+
+// Rows [x, y) of a workgroup: its range of the light stream begins and ends with diagonal entries.
+__device__ __forceinline__ int2 rows_of(const GraphView& g, const ScalarStaging& sg, int wg, int rend) {
+  const int e0 = sg.cuts[static_cast<size_t>(wg) * kStagedWaves].x;
+  const int e1 = sg.cuts[static_cast<size_t>(wg) * kStagedWaves + kStagedWaves - 1].y;
+  if (e0 >= e1) return make_int2(rend, rend);
+  return make_int2(g.went[e0].x, e1 < g.wrowptr[rend] ? g.went[e1].x : rend);
+}
+
+// Lane group's rows first, first + kGroups, ... of [first, end): request kFixedAhead of them.
+template <int D>
+struct FixedRows {
+  static constexpr int LPR = D / 4, kGroups = kFixedThreads / LPR;
+  float4 x[kFixedAhead];
+  __device__ __forceinline__ void request(const float* __restrict__ X, int row, int end) {
+#pragma unroll
+    for (int u = 0; u < kFixedAhead; ++u) {
+      const int r = row + u * kGroups;
+      x[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (r < end) x[u] = *reinterpret_cast<const float4*>(X + static_cast<size_t>(r) * D + threadIdx.x % LPR * 4);
+    }
+  }
+};
+
+// sums[c] (c < D) of `part` over the lane groups' values, in order, in every thread with tid < D.
+template <int D>
+__device__ __forceinline__ float sum_over_groups(float (*red)[D], const float4& part) {
+  constexpr int LPR = D / 4, kGroups = kFixedThreads / LPR;
+  const int tid = threadIdx.x;
+  *reinterpret_cast<float4*>(&red[tid / LPR][tid % LPR * 4]) = part;
+  __syncthreads();
+  float s = 0.f;
+  if (tid < D)
+    for (int q = 0; q < kGroups; ++q) s += red[q][tid];
+  return s;
+}
+
+template <int D>
+__global__ __launch_bounds__(kFixedThreads) void fixed_probs_kernel(GraphView g, ScalarStaging sg, int workgroups,
+                                                                    const float* __restrict__ X, int shared,
+                                                                    ScalarWeights from, ScalarWeights to, AdamStep adam,
+                                                                    const float* __restrict__ gw_partial,
+                                                                    float* __restrict__ p) {
+  using F = FixedRows<D>;
+  __shared__ __align__(16) float red[F::kGroups][D];
+  __shared__ __align__(16) float w_s[D];
+  const int wg = sg.launch_of[blockIdx.x];
+  if (wg < 0) return;
+  const int k = sg.wg_k[wg], kw = shared ? 0 : k, tid = threadIdx.x;
+  const int2 rows = rows_of(g, sg, wg, g.part_rows[k + 1]);
+  F ahead;
+  int row = rows.x + tid / F::LPR;
+  ahead.request(X, row, rows.y);
+  const size_t at = static_cast<size_t>(kw) * D + min(tid, D - 1);
+  float w = from.W[at], m = from.m[at], v = from.v[at];
+  if (gw_partial != nullptr) {
+    const int q0 = shared ? 0 : sg.wg_ptr[k], q1 = shared ? workgroups : sg.wg_ptr[k + 1];
+    float4 part = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int q = q0 + tid / F::LPR; q < q1; q += F::kGroups) {
+      const float4 x = *reinterpret_cast<const float4*>(gw_partial + static_cast<size_t>(q) * D + tid % F::LPR * 4);
+      part.x += x.x;
+      part.y += x.y;
+      part.z += x.z;
+      part.w += x.w;
+    }
+    const float grad = sum_over_groups<D>(red, part);
+    if (tid < D) adam_weight(adam.for_part(kw), grad, w, m, v);
+  }
+  if (tid < D) {
+    w_s[tid] = w;
+    if (to.W != from.W && wg == (shared ? 0 : sg.wg_ptr[k])) {
+      to.W[at] = w;
+      to.m[at] = m;
+      to.v[at] = v;
+    }
+  }
+  __syncthreads();
+  const float4 wv = *reinterpret_cast<const float4*>(w_s + tid % F::LPR * 4);
+  // all lanes of the workgroup go through the same number of rounds
+  for (int base = rows.x; base < rows.y; base += kFixedAhead * F::kGroups, row += kFixedAhead * F::kGroups) {
+    F next;
+    next.request(X, row + kFixedAhead * F::kGroups, rows.y);
+#pragma unroll
+    for (int u = 0; u < kFixedAhead; ++u) {
+      const float4 x = ahead.x[u];
+      float z = fmaf(x.w, wv.w, fmaf(x.z, wv.z, fmaf(x.y, wv.y, x.x * wv.x)));
+#pragma unroll
+      for (int o = 1; o < F::LPR; o *= 2) z += __shfl_xor(z, o, 64);
+      const int r = row + u * F::kGroups;
+      if (tid % F::LPR == 0 && r < rows.y) p[r] = 1.f / (1.f + expf(-z));
+    }
+    ahead = next;
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(kFixedThreads) void fixed_loss_kernel(GraphView g, LossOp op, ScalarStaging sg,
+                                                                   const float* g_z,  // what op writes
+                                                                   double* __restrict__ loss_partial,
+                                                                   const float* __restrict__ X,
+                                                                   float* __restrict__ gw_partial) {
+  using F = FixedRows<D>;
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ __align__(16) float sums[F::kGroups][D];
+  float* buf = reinterpret_cast<float*>(smem);
+  float* red = buf + sg.cap;
+  double* dred = reinterpret_cast<double*>(red + kStagedWaves);
+  const int wg = sg.launch_of[blockIdx.x];
+  if (wg < 0) return;
+  const int k = sg.wg_k[wg], s = wg - sg.wg_ptr[k], per = sg.wg_ptr[k + 1] - sg.wg_ptr[k];
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int rbeg = g.part_rows[k], rend = g.part_rows[k + 1];
+  const int2 mine = sg.cuts[static_cast<size_t>(wg) * kStagedWaves + wave];
+  const int2 rows = rows_of(g, sg, wg, rend);
+  F ahead;
+  int row = rows.x + tid / F::LPR;
+  ahead.request(X, row, rows.y);
+  for (int base = rbeg; base < rend; base += kStagedLoads * kFixedThreads) {
+    float v[kStagedLoads];
+#pragma unroll
+    for (int u = 0; u < kStagedLoads; ++u) {
+      const int i = base + u * kFixedThreads + tid;
+      v[u] = i < rend ? op.p[i] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kStagedLoads; ++u) {
+      const int i = base + u * kFixedThreads + tid;
+      if (i < rend) buf[i - rbeg] = v[u];
+    }
+  }
+  __syncthreads();
+  const StagedOp<LossOp> sop{op, buf, rbeg};
+  double lsum = 0.0;
+  stream_rows<StagedOp<LossOp>, 4>(g.went, g.wval, g.wrowid, sop, mine.x, mine.y, lsum);
+  const int h1 = sg.heavy_ptr[k + 1];
+  for (int hh = sg.heavy_ptr[k] + s; hh < h1; hh += per) {
+    const int i = g.heavy_rows[hh];
+    const float total = heavy_row_sum<StagedOp<LossOp>, kFixedThreads>(g, g.ent, sop, i, red);
+    if (tid == 0) sop.finish(i, total, lsum, sop.row_inputs(i));
+  }
+  lsum = wave_sum(lsum);
+  if (lane == 0) dred[wave] = lsum;
+  __syncthreads();  // also: g_z of the workgroup's rows is there
+  if (tid == 0) {
+    double total = 0.0;
+    for (int w = 0; w < kStagedWaves; ++w) total += dred[w];
+    loss_partial[wg] = total;
+  }
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&](const float4& x, float gz) {
+    acc.x = fmaf(x.x, gz, acc.x);
+    acc.y = fmaf(x.y, gz, acc.y);
+    acc.z = fmaf(x.z, gz, acc.z);
+    acc.w = fmaf(x.w, gz, acc.w);
+  };
+  // a row with very many neighbours is its summing workgroup's, wherever it lies
+  auto light = [&](int r) { return g.num_heavy == 0 || g.heavy_of_row[r] < 0; };
+  for (; row < rows.y; row += kFixedAhead * F::kGroups) {
+    F next;
+    next.request(X, row + kFixedAhead * F::kGroups, rows.y);
+    float gz[kFixedAhead];
+#pragma unroll
+    for (int u = 0; u < kFixedAhead; ++u) {
+      const int r = row + u * F::kGroups;
+      gz[u] = r < rows.y && light(r) ? g_z[r] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kFixedAhead; ++u) add(ahead.x[u], gz[u]);
+    ahead = next;
+  }
+  if (tid < F::LPR)
+    for (int hh = sg.heavy_ptr[k] + s; hh < h1; hh += per) {
+      const int i = g.heavy_rows[hh];
+      add(*reinterpret_cast<const float4*>(X + static_cast<size_t>(i) * D + tid * 4), g_z[i]);
+    }
+  const float grad = sum_over_groups<D>(sums, acc);
+  if (tid < D) gw_partial[static_cast<size_t>(wg) * D + tid] = grad;
+}
+
 template <class Op>
 void launch_staged(const Launch& ln, int kind, const GraphView& g, const Op& op, const ScalarStaging& sg,
                    double* loss_partial) {
@@ -564,6 +753,38 @@ void launch_bwd_readout(const Launch& ln, const GraphView& g, const float* g_z, 
                         const ScalarStaging* sg) {
   if (sg != nullptr) launch_staged(ln, KK_BWD_READOUT, transposed(g), BackOp{g_z, g_t}, *sg, nullptr);
   else launch_narrow(ln, KK_BWD_READOUT, transposed(g), BackOp{g_z, g_t}, nullptr);
+}
+
+#define GCO_BY_WIDTH(D, ...)                                  \
+  switch (D) {                                                \
+    case 8: { constexpr int DD = 8; __VA_ARGS__; } break;     \
+    case 16: { constexpr int DD = 16; __VA_ARGS__; } break;   \
+    case 32: { constexpr int DD = 32; __VA_ARGS__; } break;   \
+    case 64: { constexpr int DD = 64; __VA_ARGS__; } break;   \
+    case 128: { constexpr int DD = 128; __VA_ARGS__; } break; \
+    default: break;                                           \
+  }
+
+void launch_fixed_probs(const Launch& ln, int D, const GraphView& g, const ScalarStaging& sg, int workgroups,
+                        const float* X, bool shared, const ScalarWeights& from, const ScalarWeights& to,
+                        const AdamStep& adam, const float* gw_partial, float* p) {
+  ln.begin(KK_FWD_READOUT);
+  GCO_BY_WIDTH(D, (fixed_probs_kernel<DD><<<sg.num_launch, kFixedThreads, 0, ln.st>>>(
+                      g, sg, workgroups, X, shared ? 1 : 0, from, to, adam, gw_partial, p)))
+  ln.end(KK_FWD_READOUT);
+}
+
+void launch_fixed_loss(const Launch& ln, int D, const GraphView& g, const ScalarStaging& sg, const float* p, const float* c,
+                       float q, float* g_z, double* loss_partial, const float* X, float* gw_partial) {
+  const size_t lds = scalar_staged_lds_bytes(sg.cap);
+  ln.begin(KK_LOSS);
+  GCO_BY_WIDTH(D, {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fixed_loss_kernel<DD>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    (fixed_loss_kernel<DD><<<sg.num_launch, kFixedThreads, lds, ln.st>>>(g, LossOp{p, c, q, g_z}, sg, g_z, loss_partial, X,
+                                                                         gw_partial));
+  })
+  ln.end(KK_LOSS);
 }
 
 }  // namespace gco

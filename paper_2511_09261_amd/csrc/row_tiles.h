@@ -220,6 +220,11 @@ struct StreamInMemory {
     return Entry{c.x, wrowid[e], __int_as_float(c.y)};
   }
 };
+// The same with the fp32 values beside it (bf16 storage packs the entries' values otherwise).
+struct StreamWithValues : StreamInMemory {
+  const float* wval;
+  __device__ __forceinline__ Entry at(int e) const { return Entry{went[e].x, wrowid[e], wval[e]}; }
+};
 template <int D>
 struct TileFacts {
   int a, b;  // row n's range; rows past the end have the empty range at the end of the tile's

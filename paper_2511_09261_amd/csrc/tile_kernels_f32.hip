@@ -476,6 +476,54 @@ __global__ __launch_bounds__(kBlock, D <= 16 ? 4 : (D == 32 ? 3 : 2)) void bwd_t
   }
 }
 
+// ---------------------------------------------------------------------------
+// X = A_hat E, rows in fp32 (see launch_propagate).  The runs of the forward launch, in tiles of RT rows.
+// ---------------------------------------------------------------------------
+template <typename T, int D, int RT>
+__global__ __launch_bounds__(kBlock) void propagate_kernel(GraphView g, const T* __restrict__ E, float* __restrict__ X,
+                                                           const float* __restrict__ heavy_partial) {
+  __shared__ __align__(16) float all[kWavesPerBlock * TK<D>::kWaveLds];
+  const int wg = workgroup_number(g, WM_FWD);
+  if (wg >= g.num_wblocks[WM_FWD] || g.wblk_k[WM_FWD][wg] < 0) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), n = threadIdx.x % 16, h = threadIdx.x % 64 / 16;
+  const WaveRun run = g.wave_runs[WM_FWD][wg * kWavesPerBlock + wave];
+  int r0 = __builtin_amdgcn_readfirstlane(run.rbeg + run.tile0 * RT);
+  const int r1 = __builtin_amdgcn_readfirstlane(min(run.rend, run.rbeg + run.tile1 * RT));
+  if (r0 >= r1) return;
+  StreamWithValues stream;
+  stream.went = g.went;
+  stream.wrowid = g.wrowid;
+  stream.wrowptr = g.wrowptr;
+  stream.wval = g.wval;
+  const PlainRows<D, T> rows{E};
+  TileFacts<D> f, nf;
+  f.request(stream, r0, r1);
+  f.request_entries(stream);
+  for (; r0 < r1; r0 += kTile) {
+    nf.request(stream, r0 + kTile, r1);
+    f32x4 acc[TK<D>::NQ];
+    aggregate<D>(g, stream, rows, f, r0, r1, heavy_partial, all + wave * TK<D>::kWaveLds, acc);
+    nf.request_entries(stream);
+#pragma unroll
+    for (int q = 0; q < TK<D>::NQ; ++q)
+      if (r0 + n < r1) store4<D>(X, r0 + n, q, h, acc[q]);
+    f = nf;
+  }
+}
+
+template <typename T, int D, int RT>
+void propagate_t(const Launch& ln, const GraphView& g, const void* E, float* X, float* heavy_partial) {
+  const T* rows = static_cast<const T*>(E);
+  if (g.num_chunks > 0) {
+    ln.begin(KK_HEAVY);
+    heavy_wide_kernel<D, PlainSrc<T, D>><<<g.num_chunks, kBlock, 0, ln.st>>>(g, PlainSrc<T, D>{rows, g.sb}, heavy_partial);
+    ln.end(KK_HEAVY);
+  }
+  ln.begin(KK_FWD_HIDDEN);
+  propagate_kernel<T, D, RT><<<launch_ids(g, WM_FWD), kBlock, 0, ln.st>>>(g, rows, X, heavy_partial);
+  ln.end(KK_FWD_HIDDEN);
+}
+
 template <typename K>
 void allow_lds(K kernel, size_t bytes) {
   if (bytes > 48 * 1024)
@@ -550,6 +598,16 @@ void launch_fwd_hidden_f32(const Launch& ln, int D, const GraphView& g, const vo
 void launch_bwd_hidden_f32(const Launch& ln, int D, bool last, bool to_embed, const GraphView& gt,
                            const BwdArgs& a) {
   GCO_BY_WIDTH(D, (bwd_t<DD>(ln, last, to_embed, gt, a)))
+}
+
+void launch_propagate(const Launch& ln, int storage, int D, const GraphView& g, const void* E, float* X,
+                      float* heavy_partial) {
+  if (storage == GCO_STORAGE_BF16) {
+    if (D == 64) propagate_t<bf16_t, 64, kWaveRows>(ln, g, E, X, heavy_partial);
+    else if (D == 128) propagate_t<bf16_t, 128, kWaveRows>(ln, g, E, X, heavy_partial);
+  } else {
+    GCO_BY_WIDTH(D, (propagate_t<float, DD, kTileRowsF32>(ln, g, E, X, heavy_partial)))
+  }
 }
 
 }  // namespace gco

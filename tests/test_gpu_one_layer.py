@@ -1,0 +1,70 @@
+"""GPU parity of the one-layer model whose embeddings are not trained: a training call of four epochs or more runs on
+X = A_hat E, two launches an epoch.  Loss trajectories and weights against the fp64 oracle (1e-4 over a dozen epochs, as
+in test_gpu_parity; bf16 2e-2), and against the general launches, which shorter calls take."""
+import numpy as np
+import pytest
+
+from oracle import gcn
+from paper_2511_09261_amd import inputs
+from tests.parity import rel_l2
+from tests.test_gpu_tiles_f32 import ragged_subgraphs
+
+pytestmark = pytest.mark.gpu
+
+
+def graph(many):
+    g, part, P = ragged_subgraphs(3)            # 1 .. 700 rows, rows of up to 257 neighbours
+    if many:                                    # one subgraph whose partials are more than a workgroup sums itself
+        rs = np.random.RandomState(5)
+        n = 30_000
+        g = inputs.from_edges(n, rs.randint(0, n, 250_000), np.minimum((n * rs.rand(250_000) ** 4).astype(np.int64), n - 1))
+        return g, (np.arange(n) % 2).astype(np.int32) * 2, 4   # subgraphs 1 and 3 have no node
+    return g, part, P
+
+
+@pytest.mark.parametrize("D,norm,storage,problem,share,many", [
+    (8, "sym", "fp32", "mis", False, False), (16, "mean", "fp32", "maxcut", False, False), (32, "sym", "fp32", "mis", True, False),
+    (64, "mean", "fp32", "mis", False, True), (128, "sym", "fp32", "mis", False, False), (64, "sym", "bf16", "mis", False, False),
+    (128, "mean", "bf16", "mis", True, False), (16, "sym", "fp32", "mis", False, True), (32, "mean", "fp32", "mis", True, True)])
+def test_training_on_propagated_embeddings(gco, D, norm, storage, problem, share, many):
+    g, part, P = graph(many)
+    E, Ws = inputs.init_params(g.n, part, 1 if share else P, 1, D, 5)
+    E = (E * 3).astype(np.float32)
+    ctx = gco.Context(problem=problem, num_layers=1, dim=D, norm=norm, storage=storage, weight_sharing=share,
+                      train_embed=False, lr=1e-2)
+    ctx.upload_graph(g.n, g.rowptr, g.col, part, P)
+    spec = gcn.Spec(problem=problem, num_layers=1, norm=norm, weight_sharing=share, train_embed=False, lr=1e-2,
+                    storage="bf16" if storage == "bf16" else "exact")
+    lg = gcn.local_graph(g.n, g.rowptr, g.col, part, P, norm)
+    tol = 1e-4 if storage == "fp32" else 2e-2
+    for epochs in (12, 5):                      # the weights end in their own place after an even and an odd number of steps
+        ctx.set_params(E, Ws)
+        ctx.set_profiling(1)
+        ctx.reset_timing()
+        got = ctx.train(epochs)
+        t = ctx.get_timing()
+        ctx.set_profiling(0)
+        assert t["bwd_readout"]["launches"] == 0 and t["loss"]["launches"] == epochs
+        st = gcn.init_state(E, Ws)
+        want, _ = gcn.train(lg, st, spec, epochs)
+        assert np.abs(got - want).max() <= tol * np.abs(want).max()
+        E1, W1 = ctx.get_params()
+        assert np.array_equal(E1, E) and rel_l2(W1[0], st.Ws[0]) <= 100 * tol
+    # the general launches (calls of three epochs), then step counts that differ (a subset first) over more than 64 epochs
+    p = ctx.get_probs()
+    ctx.set_params(E, Ws)
+    pieces = np.concatenate([ctx.train(3), ctx.train(2)])
+    assert np.abs(got - pieces).max() <= 1e-5 * np.abs(pieces).max()
+    assert rel_l2(ctx.get_probs(), p) <= 1e-4 and rel_l2(ctx.get_params()[1][0], W1[0]) <= 1e-4
+    ctx.train_subset(2, np.array([0], dtype=np.int32))
+    W0, (mE, vE, mW, vW, _), steps = ctx.get_params()[1], ctx.get_opt_state(), ctx.get_steps()
+    long = ctx.train(70)
+    W70 = ctx.get_params()[1][0]
+    assert (np.diff(ctx.get_steps()[0]) != 0).any() or P == 1
+    ctx.set_params(E, W0)
+    ctx.set_opt_state(mE, vE, mW, vW, 0)
+    ctx.set_steps(*steps)
+    short = np.concatenate([ctx.train(2) for _ in range(35)])
+    assert np.abs(long - short).max() <= 1e-3 * np.abs(short).max()
+    assert rel_l2(W70, ctx.get_params()[1][0]) <= 1e-2
+    ctx.destroy()
