@@ -17,6 +17,7 @@
 #include "gco.h"
 #include "gco_internal.h"
 #include "graph_kernels.h"
+#include "host_copy.h"
 
 using namespace gco;
 
@@ -101,6 +102,7 @@ struct gco_ctx {
   hipStream_t st = nullptr;
   std::string err;
   ProfilerImpl prof;
+  HostCopies copies;
 
   // ---- graph ----
   bool has_graph = false;
@@ -310,16 +312,21 @@ struct Scratch {
   }
 };
 
+// Copies to and from the caller's memory, through the context's pinned ring.  Host to device returns with the host
+// buffer the caller's again, the device side in stream order; device to host when the host buffer is filled.
 template <typename T>
 hipError_t h2d(gco_ctx* ctx, T* dst, const T* src, size_t count) {
   if (count == 0) return hipSuccess;
+  if (ctx->copies.allocate()) return ctx->copies.in(dst, src, count * sizeof(T), ctx->st);
   hipError_t e = hipMemcpyAsync(dst, src, count * sizeof(T), hipMemcpyHostToDevice, ctx->st);
   if (e != hipSuccess) return e;
-  return hipStreamSynchronize(ctx->st);  // the host buffer belongs to the caller again on return
+  return hipStreamSynchronize(ctx->st);
 }
+// ring = false: for a caller that must not allocate.
 template <typename T>
-hipError_t d2h(gco_ctx* ctx, T* dst, const T* src, size_t count) {
+hipError_t d2h(gco_ctx* ctx, T* dst, const T* src, size_t count, bool ring = true) {
   if (count == 0) return hipStreamSynchronize(ctx->st);
+  if (ring && ctx->copies.allocate()) return ctx->copies.out(dst, src, count * sizeof(T), ctx->st);
   hipError_t e = hipMemcpyAsync(dst, src, count * sizeof(T), hipMemcpyDeviceToHost, ctx->st);
   if (e != hipSuccess) return e;
   return hipStreamSynchronize(ctx->st);
@@ -895,6 +902,7 @@ int gco_create(const gco_config* cfg, gco_ctx** out) {
 int gco_destroy(gco_ctx* ctx) {
   if (!ctx) return GCO_EINVAL;
   ctx->free_graph();
+  ctx->copies.release();
   delete ctx;
   return GCO_OK;
 }
@@ -2169,7 +2177,7 @@ static RepairBuffers repair_buffers(unsigned char* q, size_t n) {
   return b;
 }
 
-static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, const RepairBuffers& b, uint8_t* x,
+static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, const RepairBuffers& b, bool ring, uint8_t* x,
                              int64_t* objective, int64_t* conflicts_before, int64_t* conflicts_after) {
   const int n = ctx->n;
   hipStream_t st = ctx->st;
@@ -2195,7 +2203,7 @@ static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, cons
         else launch_repair_round_all(st, n, ctx->nnz_full, ctx->d_rowptr, ctx->d_col, p_orig, state, last);
       }
       int left = 0;
-      HIPCHK(d2h(ctx, &left, undecided, 1));
+      HIPCHK(d2h(ctx, &left, undecided, 1, ring));
       if (left == 0) break;
     }
     if (local) {
@@ -2207,8 +2215,8 @@ static int round_repair_impl(gco_ctx* ctx, float thr, int32_t repair_scope, cons
   }
   launch_edge_counts(st, n, ctx->nnz_full, ctx->d_rowptr, ctx->d_col, x_orig, counts + 4);
   unsigned long long h[8];
-  HIPCHK(d2h(ctx, h, counts, 8));
-  HIPCHK(d2h(ctx, x, x_orig, static_cast<size_t>(n)));
+  HIPCHK(d2h(ctx, h, counts, 8, ring));
+  HIPCHK(d2h(ctx, x, x_orig, static_cast<size_t>(n), ring));
   if (conflicts_before) *conflicts_before = static_cast<int64_t>(h[1]);
   if (conflicts_after) *conflicts_after = static_cast<int64_t>(h[5]);
   if (objective)
@@ -2226,7 +2234,7 @@ int gco_round_repair(gco_ctx* ctx, float thr, int32_t repair_scope, uint8_t* x, 
   Scratch tmp(ctx);
   unsigned char* base = tmp.get<unsigned char>(repair_bytes(static_cast<size_t>(ctx->n)));
   NEED(base, GCO_ENOMEM, "device scratch allocation failed");
-  return round_repair_impl(ctx, thr, repair_scope, repair_buffers(base, static_cast<size_t>(ctx->n)), x, objective,
+  return round_repair_impl(ctx, thr, repair_scope, repair_buffers(base, static_cast<size_t>(ctx->n)), true, x, objective,
                            conflicts_before, conflicts_after);
 }
 
@@ -2245,7 +2253,7 @@ int gco_round_repair_static(gco_ctx* ctx, float thr, int32_t repair_scope, uint8
   NEED(repair_bytes(static_cast<size_t>(ctx->n)) <= kStaticScratchBytes, GCO_ERANGE,
        "static work area too small for n = %d", ctx->n);
   return round_repair_impl(ctx, thr, repair_scope,
-                           repair_buffers(static_cast<unsigned char*>(base), static_cast<size_t>(ctx->n)), x,
+                           repair_buffers(static_cast<unsigned char*>(base), static_cast<size_t>(ctx->n)), false, x,
                            objective, conflicts_before, conflicts_after);
 }
 

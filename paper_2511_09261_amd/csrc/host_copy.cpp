@@ -1,0 +1,191 @@
+// The runtime's own path for pageable memory pins or stages the caller's pages on every call, and copy engine and processor
+// wait for each other.  Here the engine fills (or drains) 2 MB slots of a pinned ring while the processor copies the slot
+// before; small copies share a slot, and only a slot that is left has an event.
+// Calls by the runtime's path / here: gco_get_probs (4.5 MB) 275 / 226 us, gco_cut_edges (two lists of 8.8 MB) 1110 / 860,
+// gco_set_params (72 MB) 2620 / 2000; a read-out of 1.1 M nodes 2.56 -> 2.06 ms.
+// From 6 MB on four threads share the processor's part, the longer one: it includes the caller's page faults (8.8 MB into
+// fresh pages 540 us by one thread, 234 by four; 77 MB to the device 2.3 ms and 1.1, on the bus 1.4).  Starting them takes
+// 50 us, so below they cost more than they save (read-out with the line at 16 MB 2.20 ms).
+#include "host_copy.h"
+
+#include <algorithm>
+#include <atomic>
+#include <cstring>
+#include <new>
+#include <system_error>
+#include <thread>
+#include <vector>
+
+namespace gco {
+namespace {
+
+constexpr size_t kThreadedBytes = size_t{6} << 20;
+constexpr size_t kLine = 64;  // copies in a slot begin at multiples of it
+
+// memcpy by the calling thread and, if asked for and to be had, three more that live as long as the object.
+class Copier {
+ public:
+  explicit Copier(bool threaded) {
+    if (!threaded) return;
+    try {
+      helpers_.reserve(3);
+      for (int t = 1; t <= 3; ++t) helpers_.emplace_back([this, t] { serve(t); });
+    } catch (const std::system_error&) {  // fewer will do
+    } catch (const std::bad_alloc&) {
+    }
+    crew_.store(static_cast<int>(helpers_.size()) + 1, std::memory_order_release);
+  }
+  ~Copier() {
+    job_.store(-1, std::memory_order_release);
+    for (std::thread& t : helpers_) t.join();
+  }
+  Copier(const Copier&) = delete;
+  Copier& operator=(const Copier&) = delete;
+  void operator()(void* dst, const void* src, size_t bytes) {
+    dst_ = static_cast<char*>(dst);
+    src_ = static_cast<const char*>(src);
+    bytes_ = bytes;
+    finished_.store(0, std::memory_order_relaxed);
+    job_.store(++jobs_, std::memory_order_release);
+    share(0);
+    while (finished_.load(std::memory_order_acquire) < static_cast<int>(helpers_.size())) std::this_thread::yield();
+  }
+
+ private:
+  void share(int t) {
+    const size_t parts = helpers_.empty() ? 1 : static_cast<size_t>(crew_.load(std::memory_order_relaxed));
+    const size_t each = (bytes_ / parts + kLine - 1) / kLine * kLine, from = std::min(bytes_, each * static_cast<size_t>(t));
+    const size_t to = static_cast<size_t>(t) + 1 == parts ? bytes_ : std::min(bytes_, from + each);
+    if (to > from) std::memcpy(dst_ + from, src_ + from, to - from);
+  }
+  void serve(int t) {
+    while (crew_.load(std::memory_order_acquire) == 0) std::this_thread::yield();
+    for (int seen = 0;;) {
+      const int job = job_.load(std::memory_order_acquire);
+      if (job < 0) return;
+      if (job == seen) {
+        std::this_thread::yield();
+        continue;
+      }
+      seen = job;
+      share(t);
+      finished_.fetch_add(1, std::memory_order_release);
+    }
+  }
+  std::atomic<int> crew_{0}, job_{0}, finished_{0};
+  int jobs_ = 0;
+  char* dst_ = nullptr;
+  const char* src_ = nullptr;
+  size_t bytes_ = 0;
+  std::vector<std::thread> helpers_;
+};
+
+}  // namespace
+
+bool HostCopies::allocate() {
+  if (base_ != nullptr) return true;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, kSlots * kSlot, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  for (int s = 0; s < kSlots; ++s)
+    if (hipEventCreateWithFlags(&done_[s], hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      while (s-- > 0) (void)hipEventDestroy(done_[s]);
+      (void)hipHostFree(p);
+      return false;
+    }
+  base_ = static_cast<char*>(p);
+  slot_ = 0;
+  used_ = 0;
+  return true;
+}
+
+// The stream has to be idle, or the copies into the ring's last slot done.
+void HostCopies::release() {
+  if (base_ == nullptr) return;
+  for (int s = 0; s < kSlots; ++s) {
+    (void)wait(s);
+    (void)hipEventDestroy(done_[s]);
+  }
+  (void)hipHostFree(base_);
+  base_ = nullptr;
+}
+
+hipError_t HostCopies::wait(int slot) {
+  if (!busy_[slot]) return hipSuccess;
+  busy_[slot] = false;
+  return hipEventSynchronize(done_[slot]);
+}
+
+hipError_t HostCopies::leave(hipStream_t st) {
+  if (used_ > 0) {
+    const hipError_t e = hipEventRecord(done_[slot_], st);
+    if (e != hipSuccess) return e;
+    busy_[slot_] = true;
+  }
+  slot_ = (slot_ + 1) % kSlots;
+  used_ = 0;
+  return wait(slot_);
+}
+
+hipError_t HostCopies::in(void* dev, const void* src, size_t bytes, hipStream_t st) {
+  Copier copy(bytes >= kThreadedBytes);
+  for (size_t at = 0; at < bytes;) {
+    if (used_ + kLine > kSlot || (bytes <= kSlot && used_ + bytes > kSlot)) {  // no room, or not for one piece
+      const hipError_t e = leave(st);
+      if (e != hipSuccess) return e;
+    }
+    const size_t n = std::min(bytes - at, kSlot - used_);
+    char* place = base_ + static_cast<size_t>(slot_) * kSlot + used_;
+    copy(place, static_cast<const char*>(src) + at, n);
+    const hipError_t e = hipMemcpyAsync(static_cast<char*>(dev) + at, place, n, hipMemcpyHostToDevice, st);
+    if (e != hipSuccess) return e;
+    used_ = std::min(kSlot, (used_ + n + kLine - 1) / kLine * kLine);
+    at += n;
+  }
+  return hipSuccess;
+}
+
+hipError_t HostCopies::out(void* dst, const void* dev, size_t bytes, hipStream_t st) {
+  if (bytes <= kSlot) {
+    if (used_ + bytes > kSlot) {
+      const hipError_t e = leave(st);
+      if (e != hipSuccess) return e;
+    }
+    char* place = base_ + static_cast<size_t>(slot_) * kSlot + used_;
+    hipError_t e = hipMemcpyAsync(place, dev, bytes, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    std::fill(busy_, busy_ + kSlots, false);  // every copy before is done as well
+    used_ = 0;
+    std::memcpy(dst, place, bytes);
+    return hipSuccess;
+  }
+  hipError_t e = leave(st);
+  if (e != hipSuccess) return e;
+  Copier copy(bytes >= kThreadedBytes);
+  const size_t pieces = (bytes + kSlot - 1) / kSlot;
+  const int first = slot_;
+  auto slot = [&](size_t i) { return static_cast<int>((static_cast<size_t>(first) + i) % kSlots); };
+  auto size = [&](size_t i) { return std::min(kSlot, bytes - i * kSlot); };
+  // a copy to the device that still reads the slot comes first on the stream
+  auto request = [&](size_t i) {
+    hipError_t err = hipMemcpyAsync(base_ + static_cast<size_t>(slot(i)) * kSlot, static_cast<const char*>(dev) + i * kSlot,
+                                    size(i), hipMemcpyDeviceToHost, st);
+    if (err == hipSuccess) err = hipEventRecord(done_[slot(i)], st);
+    busy_[slot(i)] = err == hipSuccess;
+    return err;
+  };
+  for (size_t i = 0; e == hipSuccess && i < std::min<size_t>(pieces, kSlots); ++i) e = request(i);
+  for (size_t i = 0; e == hipSuccess && i < pieces; ++i) {
+    e = wait(slot(i));
+    if (e != hipSuccess) break;
+    copy(static_cast<char*>(dst) + i * kSlot, base_ + static_cast<size_t>(slot(i)) * kSlot, size(i));
+    if (i + kSlots < pieces) e = request(i + kSlots);
+  }
+  return e;
+}
+
+}  // namespace gco

@@ -1,0 +1,30 @@
+"""Copies between the caller's memory and the device, byte for byte, where the pieces of the pinned ring (2 MB, four of
+them) and the shares of its threads (from 6 MB on) begin and end."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SLOT = 2 << 20
+
+
+@pytest.mark.parametrize("nbytes", [32, SLOT - 32, SLOT, SLOT + 32, 3 * SLOT - 32, 3 * SLOT, 4 * SLOT + 32, 8 * SLOT, 9 * SLOT + 4064])
+def test_parameters_come_back_as_they_went(gco, nbytes):
+    D = 8
+    n = nbytes // (4 * D)
+    rs = np.random.RandomState(n)
+    E, W = rs.random_sample((n, D)).astype(np.float32), [rs.random_sample((1, D, D)).astype(np.float32),
+                                                         rs.random_sample((1, D, 1)).astype(np.float32)]
+    ctx = gco.Context(dim=D)
+    ctx.upload_graph(n, np.zeros(n + 1, dtype=np.int64), np.zeros(0, dtype=np.int32), None, 1)
+    for shift in range(2):                    # the second time from another place of the ring
+        ctx.set_params(E + shift, W)
+        got, gotW = ctx.get_params()
+        assert np.array_equal(got, E + shift) and all(np.array_equal(a, b) for a, b in zip(gotW, W))
+        m = [E + 2.0] + [w + 1 for w in W]
+        ctx.set_opt_state(m[0], m[0] * 2, m[1:], [w * 3 for w in m[1:]], 4)
+        mE, vE, mW, vW, step = ctx.get_opt_state()
+        assert step == 4 and np.array_equal(mE, m[0]) and np.array_equal(vE, m[0] * 2)
+        assert all(np.array_equal(a, b) for a, b in zip(mW, m[1:]))
+        assert all(np.array_equal(a, b * 3) for a, b in zip(vW, m[1:]))
+    ctx.destroy()
