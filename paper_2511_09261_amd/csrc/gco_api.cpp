@@ -178,6 +178,7 @@ struct gco_ctx {
   int2 *d_went = nullptr, *d_went_t = nullptr;
   float *d_wval = nullptr, *d_wval_t = nullptr;
   int32_t* d_wrowid = nullptr;
+  uint32_t* d_wpair = nullptr;
   int32_t* d_wtile_hptr = nullptr;
   int2 *d_ent = nullptr, *d_ent_t = nullptr;
   float* d_diag = nullptr;
@@ -1079,8 +1080,16 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
     launch_fill_u32(st, ctx->d_wval + nnz_light, kEntPad, 0u);
     GALLOC(ctx->d_wrowid, static_cast<size_t>(nnz_light) + kEntPad);
     launch_fill_u32(st, ctx->d_wrowid + nnz_light, kEntPad, 0xffffffffu);
+    ctx->d_wpair = nullptr;
+    int most = 0;
+    for (int k = 0; k < P; ++k) most = std::max(most, part_rows[k + 1] - part_rows[k]);
+    if (most < 0xffff) {
+      GALLOC(ctx->d_wpair, static_cast<size_t>(nnz_light) + kEntPad);
+      launch_fill_u32(st, ctx->d_wpair + nnz_light, kEntPad, 0u);
+    }
     launch_light_fill(st, n, ctx->d_lrowptr, ctx->d_ent, ctx->d_diag, d_wptr64, ctx->d_wrowptr, ctx->d_went,
-                      ctx->d_wval, ctx->d_wrowid, ctx->wave_path());
+                      ctx->d_wval, ctx->d_wrowid, ctx->d_part, ctx->d_perm, ctx->d_part_rows, ctx->d_wpair,
+                      ctx->wave_path());
     if (ctx->d_ent_t == ctx->d_ent) {
       ctx->d_went_t = ctx->d_went;
       ctx->d_wval_t = ctx->d_wval;
@@ -1090,7 +1099,8 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
       GALLOC(ctx->d_went_t, static_cast<size_t>(nnz_light) + kEntPad);
       launch_fill_u32(st, ctx->d_went_t + nnz_light, 2 * kEntPad, 0u);
       launch_light_fill(st, n, ctx->d_lrowptr, ctx->d_ent_t, ctx->d_diag, d_wptr64, ctx->d_wrowptr,
-                        ctx->d_went_t, ctx->d_wval_t, nullptr, ctx->wave_path());
+                        ctx->d_went_t, ctx->d_wval_t, nullptr, nullptr, nullptr, nullptr, nullptr,
+                        ctx->wave_path());
     }
   }
 
@@ -1357,6 +1367,7 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
   g.wval = ctx->d_wval;
   g.wval_t = ctx->d_wval_t;
   g.wrowid = ctx->d_wrowid;
+  g.wpair = ctx->d_wpair;
   g.nblk_k = ctx->full.nblk_k;
   g.nblk_s = ctx->d_nblk_s;
   g.nblk_S = ctx->d_nblk_S;

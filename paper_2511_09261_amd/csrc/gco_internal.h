@@ -134,6 +134,9 @@ struct GraphView {
   const float* wval = nullptr;
   const float* wval_t = nullptr;
   const int* wrowid = nullptr;
+  // column (lower half) and row (upper half; 0xffff where wrowid is -2) of every entry, counted from the subgraph's
+  // first row; nullptr where a subgraph has 65535 rows or more
+  const uint32_t* wpair = nullptr;
   // narrow kernels: same scheme with kNarrowRows-row tiles
   const int* nblk_k = nullptr;
   const int* nblk_s = nullptr;

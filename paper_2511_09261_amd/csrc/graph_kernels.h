@@ -34,8 +34,10 @@ void launch_pack_entries(hipStream_t st, int n, const int32_t* rowptr, const int
 // row is pre-reduced): per-row entry counts, then the fill at scanned offsets; went holds
 // {column, value} with the value as a bf16 pair (split) or in fp32, wval the value in fp32.
 void launch_light_count(hipStream_t st, int n, const int32_t* rowptr, int64_t* count);
+// wpair (may be nullptr): column and row of every entry, see GraphView::wpair; part and perm in their usual orders.
 void launch_light_fill(hipStream_t st, int n, const int32_t* rowptr, const int2* ent, const float* diag,
-                       const int64_t* wptr64, int32_t* wrowptr, int2* went, float* wval, int32_t* wrowid, bool split);
+                       const int64_t* wptr64, int32_t* wrowptr, int2* went, float* wval, int32_t* wrowid,
+                       const int32_t* part, const int32_t* perm, const int32_t* part_rows, uint32_t* wpair, bool split);
 void launch_linear_coeff(hipStream_t st, int n, const float* c_base, const float* extra_orig,
                          const int32_t* perm, float* c);
 

@@ -253,7 +253,11 @@ __global__ __launch_bounds__(kBlock) void light_fill_kernel(int n, const int32_t
                                                             int32_t* __restrict__ wrowptr,
                                                             int2* __restrict__ went,
                                                             float* __restrict__ wval,
-                                                            int32_t* __restrict__ wrowid, int split) {
+                                                            int32_t* __restrict__ wrowid,
+                                                            const int32_t* __restrict__ part,
+                                                            const int32_t* __restrict__ perm,
+                                                            const int32_t* __restrict__ part_rows,
+                                                            uint32_t* __restrict__ wpair, int split) {
   const int i = blockIdx.x * (kBlock / 64) + threadIdx.x / 64;
   if (i > n) return;
   const int lane = threadIdx.x % 64;
@@ -261,7 +265,10 @@ __global__ __launch_bounds__(kBlock) void light_fill_kernel(int n, const int32_t
   if (i == n) return;
   const int64_t out = wptr64[i];
   const int deg = rowptr[i + 1] - rowptr[i];
+  const int first = wpair != nullptr ? part_rows[part[perm[i]]] : 0;  // row of the subgraph
   if (lane == 0) {
+    if (wpair != nullptr)
+      wpair[out] = static_cast<uint32_t>(i - first) | (deg >= kHeavyMin ? 0xffffu : static_cast<uint32_t>(i - first)) << 16;
     went[out] = make_int2(i, split ? split_bf16(diag[i]) : __float_as_int(diag[i]));
     wval[out] = diag[i];
     if (wrowid != nullptr) wrowid[out] = deg >= kHeavyMin ? -2 : i;
@@ -272,6 +279,7 @@ __global__ __launch_bounds__(kBlock) void light_fill_kernel(int n, const int32_t
     went[out + 1 + q] = make_int2(en.x, split ? split_bf16(__int_as_float(en.y)) : en.y);
     wval[out + 1 + q] = __int_as_float(en.y);
     if (wrowid != nullptr) wrowid[out + 1 + q] = i;
+    if (wpair != nullptr) wpair[out + 1 + q] = static_cast<uint32_t>(en.x - first) | static_cast<uint32_t>(i - first) << 16;
   }
 }
 
@@ -690,9 +698,10 @@ void launch_light_count(hipStream_t st, int n, const int32_t* rowptr, int64_t* c
 }
 
 void launch_light_fill(hipStream_t st, int n, const int32_t* rowptr, const int2* ent, const float* diag,
-                       const int64_t* wptr64, int32_t* wrowptr, int2* went, float* wval, int32_t* wrowid, bool split) {
+                       const int64_t* wptr64, int32_t* wrowptr, int2* went, float* wval, int32_t* wrowid,
+                       const int32_t* part, const int32_t* perm, const int32_t* part_rows, uint32_t* wpair, bool split) {
   light_fill_kernel<<<blocks_for(static_cast<int64_t>(n) + 1, kBlock / 64), kBlock, 0, st>>>(
-      n, rowptr, ent, diag, wptr64, wrowptr, went, wval, wrowid, split ? 1 : 0);
+      n, rowptr, ent, diag, wptr64, wrowptr, went, wval, wrowid, part, perm, part_rows, wpair, split ? 1 : 0);
 }
 
 void launch_linear_coeff(hipStream_t st, int n, const float* c_base, const float* extra_orig,
