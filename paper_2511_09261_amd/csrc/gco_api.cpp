@@ -206,7 +206,7 @@ struct gco_ctx {
   uint32_t* mask = nullptr;   // bits H > 0 of the last hidden layer (fp32 storage)
   void* GZ[3] = {};
   void* GT = nullptr;         // rows of A_hat^T G_Z of the layer in hand (split_grad_w())
-  float *t = nullptr, *z = nullptr, *p = nullptr, *g_z = nullptr, *g_t = nullptr;
+  float *t = nullptr, *p = nullptr, *g_z = nullptr, *g_t = nullptr;
   double *loss_partial = nullptr, *loss_part = nullptr, *loss_hist = nullptr, *loss_one = nullptr;
   int64_t loss_hist_cap = 0;
 
@@ -805,7 +805,7 @@ void traffic_model(gco_ctx* ctx) {
     kb[KK_FWD_HIDDEN] = base + (n * 4 + Pw * D * 4) / (L - 1);
   }
   kb[KK_FWD_GEMV] = n * D * s + Pw * D * 4 + n * 4;
-  kb[KK_FWD_READOUT] = idx + scales + 3 * n * 4;
+  kb[KK_FWD_READOUT] = idx + scales + 2 * n * 4;
   kb[KK_LOSS] = idx + 3 * n * 4;
   kb[KK_BWD_READOUT] = idx + scales + 2 * n * 4;
   // the three passes in one launch: t and c in, p and g_t out; z and dL/dz never travel
@@ -1436,7 +1436,6 @@ int gco_upload_graph(gco_ctx* ctx, int64_t n64, const int64_t* rowptr, const int
                                                           g.num_wblocks[WM_EMBED]})) * D);
   GALLOC(ctx->d_bc, static_cast<size_t>(kLossSets) * (P + ctx->Pw));
   GALLOC(ctx->t, static_cast<size_t>(n));
-  GALLOC(ctx->z, static_cast<size_t>(n));
   GALLOC(ctx->p, static_cast<size_t>(n));
   GALLOC(ctx->g_z, static_cast<size_t>(n));
   GALLOC(ctx->g_t, static_cast<size_t>(n));
@@ -1664,7 +1663,7 @@ static void run_scalar_layer(gco_ctx* ctx, const GraphView& gv, int passes, int 
     staging.wg_ptr = ctx->d_staged_ptr;
     staging.launch_of = ctx->d_staged_launch;
     const ScalarStaging* sg = ctx->staged_scalar ? &staging : nullptr;
-    launch_fwd_readout(ln, gv, ctx->t, ctx->z, ctx->p, sg);
+    launch_fwd_readout(ln, gv, ctx->t, ctx->p, sg);
     if (passes >= 2) launch_loss(ln, gv, ctx->p, ctx->d_c, q, ctx->g_z, partial, sg);
     if (passes >= 3) launch_bwd_readout(ln, gv, ctx->g_z, ctx->g_t, sg);
   }

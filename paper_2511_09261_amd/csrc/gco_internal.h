@@ -271,8 +271,8 @@ int scalar_staged_waves();
 int scalar_staged_max_cap();  // largest cap the kernel's one-round copy covers
 size_t scalar_staged_lds_bytes(int cap);
 
-// z = A_hat t, p = sigmoid(z).
-void launch_fwd_readout(const Launch& ln, const GraphView& g, const float* t, float* z, float* p,
+// p = sigmoid(A_hat t).
+void launch_fwd_readout(const Launch& ln, const GraphView& g, const float* t, float* p,
                         const ScalarStaging* sg);
 
 // s = A_loc p; g_z = (c + q s) p (1 - p); loss partial per workgroup (g.num_loss_slots of them).

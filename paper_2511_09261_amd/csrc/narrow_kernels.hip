@@ -53,14 +53,12 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
 struct ReadoutOp {  // z = A_hat t, p = sigmoid(z)
   static constexpr bool kWeighted = true;
   const float* __restrict__ t;
-  float* __restrict__ z;
   float* __restrict__ p;
   __device__ __forceinline__ const float* source() const { return t; }
   __device__ __forceinline__ float gather(int j) const { return t[j]; }
   static constexpr bool kRowInputs = false;
   __device__ __forceinline__ float2 row_inputs(int) const { return make_float2(0.f, 0.f); }
   __device__ __forceinline__ void finish(int i, float s, double&, float2) const {
-    z[i] = s;
     p[i] = 1.f / (1.f + expf(-s));
   }
 };
@@ -777,10 +775,10 @@ size_t scalar_staged_lds_bytes(int cap) {
   return static_cast<size_t>(cap) * sizeof(float) + static_cast<size_t>(kStagedWaves) * (sizeof(float) + sizeof(double));
 }
 
-void launch_fwd_readout(const Launch& ln, const GraphView& g, const float* t, float* z, float* p,
+void launch_fwd_readout(const Launch& ln, const GraphView& g, const float* t, float* p,
                         const ScalarStaging* sg) {
-  if (sg != nullptr) launch_staged(ln, KK_FWD_READOUT, g, ReadoutOp{t, z, p}, *sg, nullptr);
-  else launch_narrow(ln, KK_FWD_READOUT, g, ReadoutOp{t, z, p}, nullptr);
+  if (sg != nullptr) launch_staged(ln, KK_FWD_READOUT, g, ReadoutOp{t, p}, *sg, nullptr);
+  else launch_narrow(ln, KK_FWD_READOUT, g, ReadoutOp{t, p}, nullptr);
 }
 
 void launch_loss(const Launch& ln, const GraphView& g, const float* p, const float* c, float q, float* g_z,
