@@ -17,7 +17,6 @@ struct PlainSrc {
   static constexpr int VEC = Store<T>::VEC;
   const T* X;
   const float* sb;
-  __device__ __forceinline__ void set_part(int, int) {}
   __device__ __forceinline__ void load(int j, int c0, float (&v)[VEC]) const {
     Store<T>::load(X + static_cast<size_t>(j) * D + c0, v);
     const float s = sb[j];
@@ -34,7 +33,6 @@ struct MaskSrc {
   const uint32_t* mask;
   const float* sb;
   const float* g_t;
-  __device__ __forceinline__ void set_part(int, int) {}
   __device__ __forceinline__ void load(int j, int c0, float (&v)[VEC]) const {
     const uint32_t m = mask[static_cast<size_t>(j) * ((D + 31) / 32) + c0 / 32] >> (c0 % 32);
     const float s = sb[j] * g_t[j];
@@ -68,19 +66,17 @@ __device__ __forceinline__ void gather_range(const Src& src, const int* __restri
   }
 }
 
-// Chunked pre-reduction of very long rows: partial[c, :] = sum_{e in chunk c} src(col[e]).
+// Chunked pre-reduction of very long rows: partial[c, :] = sum_{e in chunk c} src(col[e]), by one workgroup; red is
+// kBlock * VEC floats of its LDS.
 template <int D, class Src>
-__global__ __launch_bounds__(kBlock) void heavy_wide_kernel(GraphView g, Src src, float* partial) {
+__device__ __forceinline__ void reduce_chunk_of(const GraphView& g, Src src, float* __restrict__ partial, int ch, float* red) {
   constexpr int VEC = Src::VEC;
   constexpr int LPR = D / VEC;
   constexpr int G = kBlock / LPR;
-  __shared__ float red[kBlock * VEC];
-  const int ch = blockIdx.x;
   const int tid = threadIdx.x;
   const int grp = tid / LPR;
   const int c0 = (tid % LPR) * VEC;
   if (g.chunk_part[ch] < 0) return;  // the row's subgraph sits out
-  src.set_part(g.chunk_part[ch], c0);
   float acc[VEC];
 #pragma unroll
   for (int x = 0; x < VEC; ++x) acc[x] = 0.f;
@@ -93,6 +89,12 @@ __global__ __launch_bounds__(kBlock) void heavy_wide_kernel(GraphView g, Src src
     for (int gq = 0; gq < G; ++gq) s += red[gq * D + tid];
     partial[static_cast<size_t>(ch) * D + tid] = s;
   }
+}
+
+template <int D, class Src>
+__global__ __launch_bounds__(kBlock) void heavy_wide_kernel(GraphView g, Src src, float* partial) {
+  __shared__ float red[kBlock * Src::VEC];
+  reduce_chunk_of<D>(g, src, partial, blockIdx.x, red);
 }
 
 }  // namespace gco

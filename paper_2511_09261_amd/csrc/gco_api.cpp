@@ -1804,10 +1804,11 @@ static void run_backward(gco_ctx* ctx, const GraphView& gv, const gco_ctx::Activ
   const bool many_partials = writers / ctx->Pw >= 512;
   // the last launch of an epoch also pre-reduces the long rows of the new embeddings
   ChunkTail tail;
-  const bool fold = update && c.train_embed && ctx->wave_path() && L >= 2 && gv.num_chunks > 0 && !many_partials;
+  const bool fold = update && c.train_embed && L >= 2 && gv.num_chunks > 0 && !many_partials;
   if (fold) {
     tail.g = gv;
-    tail.X = ctx->Eb;
+    tail.storage = c.storage;
+    tail.X = ctx->H[0];
     tail.partial = ctx->d_heavy_partial_E;
     tail.D = D;
   }

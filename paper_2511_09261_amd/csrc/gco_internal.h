@@ -235,10 +235,10 @@ enum EmbedMode : int { EMBED_ADAM = 0, EMBED_WRITE_GRAD = 1, EMBED_SKIP = 2 };
 // ---- launchers implemented in train_kernels.hip (storage: 0 fp32, 1 bf16) ----
 
 // Hidden layer forward: Y = relu((A_hat X) W^k); with w_out != nullptr also
-// t = Y w_out^k (the scalar layer's transform fused into the last hidden layer), and, in fp32 storage,
-// the bits Y > 0 to `mask` ([n, (D + 31) / 32] words), with Y itself only if Y != nullptr.
+// t = Y w_out^k (the scalar layer's transform fused into the last hidden layer), in fp32 storage
+// the bits Y > 0 to `mask` ([n, (D + 31) / 32] words), and Y itself only if Y != nullptr.
 // partial_ready: the chunk partials of the pre-reduced rows for X are in heavy_partial
-// already (bf16 storage only; otherwise a launch of its own computes them first).
+// already (otherwise a launch of its own computes them first).
 void launch_fwd_hidden(const Launch& ln, int storage, int D, const GraphView& g, const void* X,
                        const float* W, int w_stride, void* Y, const float* w_out,
                        int wout_stride, float* t, uint32_t* mask, float* heavy_partial, bool partial_ready = false);
@@ -354,7 +354,7 @@ void launch_bwd_hidden(const Launch& ln, int storage, int D, bool last, bool to_
 // decomposition WM_EMBED (first layer) or WM_BWD, those of w_out by the last hidden layer's
 void launch_fwd_hidden_f32(const Launch& ln, int D, const GraphView& g, const void* X, const float* W,
                            int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
-                           uint32_t* mask, float* heavy_partial);
+                           uint32_t* mask, float* heavy_partial, bool partial_ready);
 void launch_bwd_hidden_f32(const Launch& ln, int D, bool last, bool to_embed, const GraphView& gt,
                            const BwdArgs& a);
 
@@ -416,11 +416,12 @@ struct WeightTensor {
 };
 // many_partials: few weight sets with hundreds of partials each; the sum over a set's
 // partials is then shared by 16 wavefronts per 64 weights.
-// tail (bf16 storage, not with many_partials): the same launch also pre-reduces the chunks
-// of the rows with very many neighbours of view g from the bf16 rows X into `partial`,
+// tail (not with many_partials): the same launch also pre-reduces the chunks
+// of the rows with very many neighbours of view g from the rows X (storage type) into `partial`,
 // ready for the next forward pass.
 struct ChunkTail {
   GraphView g;
+  int storage = 0;
   const void* X = nullptr;
   float* partial = nullptr;
   int D = 0;

@@ -533,8 +533,8 @@ void allow_lds(K kernel, size_t bytes) {
 
 template <int D>
 void fwd_t(const Launch& ln, const GraphView& g, const float* X, const float* W, int w_stride, float* Y,
-           const float* w_out, int wout_stride, float* t, uint32_t* mask, float* heavy_partial) {
-  if (g.num_chunks > 0) {
+           const float* w_out, int wout_stride, float* t, uint32_t* mask, float* heavy_partial, bool partial_ready) {
+  if (g.num_chunks > 0 && !partial_ready) {
     ln.begin(KK_HEAVY);
     heavy_wide_kernel<D, PlainSrc<float, D>>
         <<<g.num_chunks, kBlock, 0, ln.st>>>(g, PlainSrc<float, D>{X, g.sb}, heavy_partial);
@@ -590,9 +590,9 @@ void bwd_t(const Launch& ln, bool last, bool to_embed, const GraphView& gt, cons
 
 void launch_fwd_hidden_f32(const Launch& ln, int D, const GraphView& g, const void* X, const float* W,
                            int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
-                           uint32_t* mask, float* heavy_partial) {
+                           uint32_t* mask, float* heavy_partial, bool partial_ready) {
   GCO_BY_WIDTH(D, (fwd_t<DD>(ln, g, static_cast<const float*>(X), W, w_stride, static_cast<float*>(Y), w_out,
-                             wout_stride, t, mask, heavy_partial)))
+                             wout_stride, t, mask, heavy_partial, partial_ready)))
 }
 
 void launch_bwd_hidden_f32(const Launch& ln, int D, bool last, bool to_embed, const GraphView& gt,

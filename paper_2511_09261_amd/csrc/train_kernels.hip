@@ -8,6 +8,7 @@
 // Every sum is taken in an order fixed by the launch shape, so results are
 // bit-identical from run to run.
 #include "device_utils.h"
+#include "gather.h"
 #include "gco_internal.h"
 #include "heavy_chunk.h"
 
@@ -271,18 +272,21 @@ __device__ inline void adam_on_weight(const WeightTensor& wt, int64_t gid, float
 // (pairwise inside a group, groups in list order) so that 16 loads are in flight.
 // DC > 0 (the feature width): the workgroups from weight_blocks on pre-reduce, for the next
 // forward pass, the chunks of the rows with very many neighbours from the bf16 working copy
-// of the embeddings, which the launch before this one has finished writing.
-template <int DC>
+// of the embeddings (fp32 storage: from these), which the launch before this one has finished writing.  A launch of its
+// own for this is a few microseconds of latency with 30 to 100 workgroups: width 16 in fp32, 700 000 rows in 48
+// subgraphs, 7.2 us and the gap before it, beside 12.6 us of Adam alone; together 15.3 us.
+template <int DC, typename T = bf16_t>
 __global__ __launch_bounds__(kBlock) void adam_w_kernel(int Pw, WeightTensors wts, AdamStep ad, int update,
                                                         int weight_blocks, GraphView g,
-                                                        const bf16_t* __restrict__ Eb,
+                                                        const T* __restrict__ Eb,
                                                         float* __restrict__ chunk_partial) {
   if constexpr (DC > 0) {
     __shared__ float red[kBlock * 8];
     if (static_cast<int>(blockIdx.x) >= weight_blocks) {
       const int ch = blockIdx.x - weight_blocks;
       if (g.chunk_part[ch] < 0) return;  // the row's subgraph sits out
-      reduce_chunk<DC>(g, ChunkPlainRows<DC>{Eb}, chunk_partial, ch, red);
+      if constexpr (sizeof(T) == 2) reduce_chunk<DC>(g, ChunkPlainRows<DC>{Eb}, chunk_partial, ch, red);
+      else reduce_chunk_of<DC>(g, PlainSrc<T, DC>{Eb, g.sb}, chunk_partial, ch, red);
       return;
     }
   }
@@ -400,7 +404,7 @@ void launch_fwd_hidden(const Launch& ln, int storage, int D, const GraphView& g,
   if (storage == GCO_STORAGE_BF16) {
     launch_fwd_hidden_bf16(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, heavy_partial, partial_ready);
   } else {
-    launch_fwd_hidden_f32(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, mask, heavy_partial);
+    launch_fwd_hidden_f32(ln, D, g, X, W, w_stride, Y, w_out, wout_stride, t, mask, heavy_partial, partial_ready);
   }
 }
 
@@ -486,16 +490,21 @@ void launch_adam_w(const Launch& ln, int Pw, const WeightTensor* tensors, int co
     adam_w_split_kernel<<<blocks, 64 * kAdamSplit, 0, ln.st>>>(Pw, wts, adam, update ? 1 : 0);
   } else {
     const int blocks = static_cast<int>((total + kBlock - 1) / kBlock);
-    const bf16_t* Eb = tail ? static_cast<const bf16_t*>(tail->X) : nullptr;
-    if (tail != nullptr && tail->D == 64)
-      adam_w_kernel<64><<<blocks + tail->g.num_chunks, kBlock, 0, ln.st>>>(Pw, wts, adam, update ? 1 : 0, blocks,
-                                                                          tail->g, Eb, tail->partial);
-    else if (tail != nullptr && tail->D == 128)
-      adam_w_kernel<128><<<blocks + tail->g.num_chunks, kBlock, 0, ln.st>>>(Pw, wts, adam, update ? 1 : 0, blocks,
-                                                                           tail->g, Eb, tail->partial);
-    else
-      adam_w_kernel<0><<<blocks, kBlock, 0, ln.st>>>(Pw, wts, adam, update ? 1 : 0, blocks, GraphView{}, nullptr,
-                                                     nullptr);
+    auto with_tail = [&](auto kernel, auto* rows) {
+      kernel<<<blocks + tail->g.num_chunks, kBlock, 0, ln.st>>>(Pw, wts, adam, update ? 1 : 0, blocks, tail->g, rows,
+                                                               tail->partial);
+    };
+    if (tail != nullptr && tail->storage == GCO_STORAGE_BF16) {
+      const bf16_t* rows = static_cast<const bf16_t*>(tail->X);
+      if (tail->D == 64) with_tail(adam_w_kernel<64, bf16_t>, rows);
+      else with_tail(adam_w_kernel<128, bf16_t>, rows);
+    } else if (tail != nullptr) {
+      const float* rows = static_cast<const float*>(tail->X);
+      GCO_DISPATCH_D(float, tail->D, (with_tail(adam_w_kernel<DD, float>, rows)))
+    } else {
+      adam_w_kernel<0, bf16_t><<<blocks, kBlock, 0, ln.st>>>(Pw, wts, adam, update ? 1 : 0, blocks, GraphView{},
+                                                             nullptr, nullptr);
+    }
   }
   ln.end(KK_ADAM_W);
 }

@@ -62,6 +62,28 @@ def test_tile_and_row_length_edges(gco, D, L, norm, share):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("D", [8, 16, 32, 64, 128])
+def test_long_rows_reduced_ahead_are_those_of_the_new_embeddings(gco, D):
+    """The last launch of a training epoch pre-reduces the long rows for the forward pass after it: bit for bit what that
+    pass forms itself from the same parameters, also after a subset trained."""
+    g, part, P = ragged_subgraphs(D)
+    L = 2 + (D >= 32)
+    E, Ws = inputs.init_params(g.n, part, P, L, D, 3)
+    ctx, fresh = (gco.Context(num_layers=L, dim=D) for _ in range(2))
+    for c in (ctx, fresh):
+        c.set_scalar_layer_form("streams")
+        c.upload_graph(g.n, g.rowptr, g.col, part, P)
+    ctx.set_params(E, Ws)
+    for run in (lambda: ctx.train(2), lambda: ctx.train_subset(2, np.array([10], dtype=np.int32))):
+        run()
+        ctx.forward()
+        fresh.set_params(*ctx.get_params())
+        fresh.forward()
+        assert np.array_equal(ctx.get_probs(), fresh.get_probs())
+    ctx.destroy()
+    fresh.destroy()
+
+
 def test_workgroups_grouped_by_xcd(gco):
     """Rows of more than 32 MB in more than eight subgraphs: the launches whose workgroups are
     grouped by XCD, with idle workgroups among them, against the oracle."""
