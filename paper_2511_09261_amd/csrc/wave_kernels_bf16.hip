@@ -103,22 +103,29 @@ __host__ __device__ constexpr int acc_feature(int tn, int h, int r) { return 32 
 // wfr[((tj * KS2 + ks2) * 64 + lane) * 8 + e] = W[feature_of(ks2, h, e)][32 tj + n].
 template <int D>
 __device__ __forceinline__ void load_weight_fragments(const float* __restrict__ Wk, bf16_t* wfr) {
-  constexpr int kPer = D * D / 4 / kBlock;  // float4 loads per thread
-  static_assert(D * D % (4 * kBlock) == 0, "whole float4 loads");
-  float4 v[kPer];
+  constexpr int JB = D / 4;                   // blocks of 4 x 4 weights along a row of W
+  constexpr int kPer = D * D / 16 / kBlock;   // blocks per thread
+  static_assert(D * D % (16 * kBlock) == 0, "whole blocks");
+  float4 v[kPer][4];
 #pragma unroll
-  for (int q = 0; q < kPer; ++q) v[q] = reinterpret_cast<const float4*>(Wk)[threadIdx.x + q * kBlock];
+  for (int q = 0; q < kPer; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int b = threadIdx.x + q * kBlock;
+      v[q][i] = reinterpret_cast<const float4*>(Wk)[(4 * (b / JB) + i) * JB + b % JB];
+    }
+  // a block's four features are one run e%4 = 0..3 of feature_of: 8 bytes per column
 #pragma unroll
   for (int q = 0; q < kPer; ++q) {
-    const int idx = (threadIdx.x + q * kBlock) * 4;
-    const int f = idx / D, j0 = idx % D;  // W[f][j0 .. j0+3]
+    const int b = threadIdx.x + q * kBlock;
+    const int f = 4 * (b / JB), j0 = 4 * (b % JB);
     // inverse of feature_of: f = 32 tn + 16 p + 8 (e/4) + 4 h + e%4
-    const int ks2 = f / 16, h = (f / 4) % 2, e = ((f / 8) % 2) * 4 + f % 4;
-    const float w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+    const int ks2 = f / 16, h = (f / 4) % 2, e0 = ((f / 8) % 2) * 4;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int j = j0 + x;
-      wfr[(((j / 32) * WG<D>::KS2 + ks2) * 64 + h * 32 + j % 32) * 8 + e] = f32_to_bf16(w[x]);
+      *reinterpret_cast<uint2*>(wfr + (((j / 32) * WG<D>::KS2 + ks2) * 64 + h * 32 + j % 32) * 8 + e0) =
+          make_uint2(f32x2_to_bf16x2((&v[q][0].x)[x], (&v[q][1].x)[x]), f32x2_to_bf16x2((&v[q][2].x)[x], (&v[q][3].x)[x]));
     }
   }
 }
@@ -196,7 +203,12 @@ __device__ __forceinline__ auto& select_array(A& a, B& b) {
 // A_hat X in fp32 (zero for rows past nrows).  `went` is the light stream of the matrix
 // that is applied (A_hat or its transpose); xf (xf_bytes) and wts (wts_bytes) are this
 // wavefront's LDS; pair_mask is the workgroup's table from fill_pair_masks.  on_tile may
-// overwrite xf.
+// overwrite xf.  prepare() runs once, while the run's first entries travel: the workgroup's weights and
+// tables go to LDS there (with a barrier, so every wavefront of the workgroup gets here, also one without tiles).
+// A workgroup is short (8 tiles per wavefront at width 128 and half a million rows), so what it waits for before its
+// first product counts: with the run's record, the entries and the weights fetched one after another, and W stored
+// 2 bytes at a time, the forward pass of 500 000 rows of width 128 took 115 us, now 104; of 104 000 rows of width 64,
+// 14.6 and 12.3.  The backward passes, which have more to do per tile, change by less than 2 %.
 // EARLY_ROWS: the source rows of a step are requested during the step before it, as soon as
 // that step's rows are parked in LDS (their registers are free again), together with the
 // entries of the step after; the products and tile epilogues of a step then run beside the
@@ -208,12 +220,12 @@ __device__ __forceinline__ auto& select_array(A& a, B& b) {
 // through the whole step, and are read from there when the step ends.  The copy is issued
 // before the step's row requests, so it has landed when the rows have (vector memory
 // operations complete in order); the kernels at the register limit use it.
-template <int D, bool EARLY_ROWS, bool LDS_ENTRIES, typename OnTile>
+template <int D, bool EARLY_ROWS, bool LDS_ENTRIES, typename Prepare, typename OnTile>
 __device__ __forceinline__ void stream_tiles(const GraphView& g, const int2* __restrict__ went,
                                              const bf16_t* __restrict__ X, const WaveRun& run,
                                              unsigned char* xf, uint32_t* wts, const uint4* pair_mask,
                                              const float* __restrict__ heavy_partial, unsigned char* ent_lds,
-                                             OnTile&& on_tile) {
+                                             Prepare&& prepare, OnTile&& on_tile) {
   using G_ = WG<D>;
   static_assert(!(EARLY_ROWS && LDS_ENTRIES), "one way of prefetching entries at a time");
   const int lane = threadIdx.x % 64;
@@ -234,6 +246,11 @@ __device__ __forceinline__ void stream_tiles(const GraphView& g, const int2* __r
     return *p;
   };
   int factsA = tile_facts(tile0), factsB = tile_facts(tile0 + 1), factsC = tile_facts(tile0 + 2);
+  int2 cur[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) cur[j] = went[E0 + grp * 8 + j];  // of an empty run: the stream's first entries
+  prepare();
+  if (tile0 >= tile1) return;
   int tau = tile0;
   int row0 = rbeg + tau * RW, nrows = min(RW, rend - row0);
   int te0 = __builtin_amdgcn_readlane(factsA, 0), te1 = __builtin_amdgcn_readlane(factsA, nrows);
@@ -244,9 +261,6 @@ __device__ __forceinline__ void stream_tiles(const GraphView& g, const int2* __r
 #pragma unroll
     for (int r = 0; r < 16; ++r) agg[tn][r] = 0.f;
 
-  int2 cur[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) cur[j] = went[E0 + grp * 8 + j];
   // The first entries are taken here, before the loop.  Inside the loop the entries of a
   // step arrive together with the rows of the step before; if the compiler had to allow
   // for these first loads still being on their way at the top of the loop, it would put a
@@ -493,24 +507,23 @@ __global__ __launch_bounds__(kBlock, D == 64 && !EARLY ? 3 : 2) void fwd_wave_ke
 
   const int wg = workgroup_number(g, WM_FWD);
   if (wg >= g.num_wblocks[WM_FWD]) return;
-  const int k = g.wblk_k[WM_FWD][wg];
-  if (k < 0) return;
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int k = g.wblk_k[WM_FWD][wg];
+  const WaveRun run = g.wave_runs[WM_FWD][wg * (kBlock / 64) + wave];
+  if (k < 0) return;
   const int n = lane % 32, h = lane / 32;
   const int grp = lane / G_::LPR, c0 = (lane % G_::LPR) * 8;
-  load_weight_fragments<D>(W + static_cast<size_t>(k) * w_stride, wfr);
-  fill_pair_masks(pair_mask);
-  if (tid < D) wo[tid] = w_out != nullptr ? w_out[static_cast<size_t>(k) * wout_stride + tid] : 0.f;
-  __syncthreads();  // the only workgroup barrier: W^k and w_out are in LDS
-
-  const WaveRun run = g.wave_runs[WM_FWD][wg * (kBlock / 64) + wave];
-  if (run.tile0 >= run.tile1) return;
   unsigned char* my_lds = wave_mem + wave * G_::wave_bytes;
   bf16_t* ot = reinterpret_cast<bf16_t*>(my_lds);  // overlays the row buffer
   stream_tiles<D, EARLY, false>(g, g.went, X, run, my_lds,
                   reinterpret_cast<uint32_t*>(my_lds + G_::xf_bytes), pair_mask, heavy_partial, nullptr,
-                  [&](int row0, int nrows, const floatx16 (&agg)[G_::NT]) {
+                  [&]() {
+    load_weight_fragments<D>(W + static_cast<size_t>(k) * w_stride, wfr);
+    fill_pair_masks(pair_mask);
+    if (tid < D) wo[tid] = w_out != nullptr ? w_out[static_cast<size_t>(k) * wout_stride + tid] : 0.f;
+    __syncthreads();  // the only workgroup barrier: W^k and w_out are in LDS
+  }, [&](int row0, int nrows, const floatx16 (&agg)[G_::NT]) {
     // Z^T = W^T AGG^T: the rounded aggregate is the B operand as it stands
     floatx16 z[G_::NT];
 #pragma unroll
@@ -686,20 +699,17 @@ __global__ __launch_bounds__(kBlock, 2) void bwd_wave_kernel(GraphView g, BwdArg
   constexpr WaveMap WM = TO_EMBED ? WM_EMBED : WM_BWD;
   const int wg = workgroup_number(g, WM);
   if (wg >= g.num_wblocks[WM]) return;
-  const int k = g.wblk_k[WM][wg];
-  if (k < 0) return;
-  const AdamStep ad = a.adam.for_part(k);
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int k = g.wblk_k[WM][wg];
+  const WaveRun run = g.wave_runs[WM][wg * (kBlock / 64) + wave];
+  if (k < 0) return;
+  const AdamStep ad = a.adam.for_part(k);
   const int n = lane % 32, h = lane / 32;
   const int grp = lane / G_::LPR, sub = lane % G_::LPR;
-  load_weight_fragments_t<D>(a.W + static_cast<size_t>(k) * a.w_stride, wfr);
-  fill_pair_masks(pair_mask);
-  __syncthreads();
 
   const bf16_t* GZ = static_cast<const bf16_t*>(a.GZ_in);
   const bf16_t* Hprev = static_cast<const bf16_t*>(a.Hprev);
-  const WaveRun run = g.wave_runs[WM][wg * (kBlock / 64) + wave];
   unsigned char* R = wave_mem + wave * G_::bwd_wave_bytes;
   const bool need_gh = !(TO_EMBED && a.mode == EMBED_SKIP);
   constexpr int NTW = GWI ? G_::NT : 1;
@@ -711,9 +721,9 @@ __global__ __launch_bounds__(kBlock, 2) void bwd_wave_kernel(GraphView g, BwdArg
 #pragma unroll
       for (int r = 0; r < 16; ++r) gw[ta][tb][r] = 0.f;
 
-  if (run.tile0 < run.tile1) {
+  {
     const int rbeg = run.rbeg;
-    const int row_end = min(run.rend, rbeg + run.tile1 * RW);
+    const int row_end = run.tile0 < run.tile1 ? min(run.rend, rbeg + run.tile1 * RW) : 0;  // 0: no rows
     // rows RPL grp + u (u < RPL) of a tile, features 8 sub .. + 7: what this lane loads of
     // Hprev and what it stores of the result
     constexpr int RPL = RW / G_::NG;
@@ -732,7 +742,11 @@ __global__ __launch_bounds__(kBlock, 2) void bwd_wave_kernel(GraphView g, BwdArg
 
     stream_tiles<D, false, G_::BWD_LDS_ENTRIES>(g, g.went, GZ, run, R, reinterpret_cast<uint32_t*>(R + G_::region_bytes),
                     pair_mask, a.heavy_partial, R + G_::region_bytes + G_::wts_bytes,
-                    [&](int row0, int nrows, const floatx16 (&agg)[G_::NT]) {
+                    [&]() {
+      load_weight_fragments_t<D>(a.W + static_cast<size_t>(k) * a.w_stride, wfr);
+      fill_pair_masks(pair_mask);
+      __syncthreads();
+    }, [&](int row0, int nrows, const floatx16 (&agg)[G_::NT]) {
       // G_T^T rounded to bf16: B operands of the second product
       uint4 bq[G_::KS2];
 #pragma unroll
