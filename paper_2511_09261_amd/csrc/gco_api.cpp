@@ -1736,6 +1736,22 @@ static void run_forward(gco_ctx* ctx) {
   run_scalar_layer(ctx, ctx->gv, 1, 0);
 }
 
+// Weight sets with hundreds of partials each (launch_adam_w), in the run over all subgraphs: a subset with a few
+// hundred partials per weight set is no case for one thread per weight either (400 partials: 18 us, split 7.5; 103:
+// 10.8, 8.4).
+static bool many_partials(const gco_ctx* ctx) {
+  const GraphView& all = ctx->gv;
+  const int writers = ctx->cfg.num_layers == 1 ? all.num_blocks
+                                               : std::max({all.num_wblocks[WM_BWD], all.num_wblocks[WM_EMBED],
+                                                           ctx->wave_path() ? all.num_nblocks : 0});
+  return writers / ctx->Pw >= 512;
+}
+
+// Whether the last launch of a training epoch also pre-reduces the long rows of the new embeddings.
+static bool chunks_follow(const gco_ctx* ctx) {
+  return ctx->cfg.train_embed && ctx->cfg.num_layers >= 2 && ctx->gv.num_chunks > 0 && !many_partials(ctx);
+}
+
 // Backward pass from g_t on (run_scalar_layer with passes = 3 has run).
 // update = true: an Adam step with the constants adE (embedding rows) and adW (weights);
 // update = false: gradients are written to gE / gW.  gv and maps name the subgraphs that
@@ -1795,16 +1811,10 @@ static void run_backward(gco_ctx* ctx, const GraphView& gv, const gco_ctx::Activ
     wt[l - 1].blk_ptr = L == 1 ? maps.pbl_ptr : (narrow ? maps.nwbl_ptr : maps.wpbl_ptr[wm]);
     wt[l - 1].blk_list = L == 1 ? maps.pbl_list : (narrow ? maps.nwbl_list : maps.wpbl_list[wm]);
   }
-  // of the run over all subgraphs: a subset with a few hundred partials per weight set is no
-  // case for one thread per weight either (400 partials: 18 us, split 7.5; 103: 10.8, 8.4)
-  const GraphView& all = ctx->gv;
-  const int writers = L == 1 ? all.num_blocks
-                             : std::max({all.num_wblocks[WM_BWD], all.num_wblocks[WM_EMBED],
-                                         ctx->wave_path() ? all.num_nblocks : 0});
-  const bool many_partials = writers / ctx->Pw >= 512;
+  const bool many = many_partials(ctx);
   // the last launch of an epoch also pre-reduces the long rows of the new embeddings
   ChunkTail tail;
-  const bool fold = update && c.train_embed && L >= 2 && gv.num_chunks > 0 && !many_partials;
+  const bool fold = update && chunks_follow(ctx);
   if (fold) {
     tail.g = gv;
     tail.storage = c.storage;
@@ -1813,7 +1823,7 @@ static void run_backward(gco_ctx* ctx, const GraphView& gv, const gco_ctx::Activ
     tail.D = D;
   }
   if (update && c.train_embed && !fold) ctx->heavy_E_valid = false;  // the embeddings change, the partials do not follow
-  launch_adam_w(ln, ctx->Pw, wt, L, adW, update, many_partials, fold ? &tail : nullptr);
+  launch_adam_w(ln, ctx->Pw, wt, L, adW, update, many, fold ? &tail : nullptr);
   // a run over a subset refreshes only its own subgraphs' chunks: valid only on top of valid
   if (fold) ctx->heavy_E_valid = ctx->heavy_E_valid || &maps == &ctx->full;
   if (update) ctx->probs_valid = true;  // p is that of the parameters before the step
@@ -1905,6 +1915,12 @@ static int train_impl(gco_ctx* ctx, int32_t epochs, const uint8_t* active, doubl
     wt.elems = c.dim;
     launch_adam_w(ctx->launch(), Pw, &wt, 1, ad, true, ctx->fixed.most_partials >= 512);
   };
+  // A subset's epochs refresh their own subgraphs' chunk sums only, so all are formed here once; else every epoch would
+  // form its own again (6 of 64 subgraphs, 104 000 rows of width 64: 6.7 us of 168).
+  if (active != nullptr && !ctx->small_train && !ctx->heavy_E_valid && chunks_follow(ctx)) {
+    launch_pre_reduce(ctx->launch(), c.storage, c.dim, ctx->gv, ctx->H[0], ctx->d_heavy_partial_E);
+    ctx->heavy_E_valid = true;
+  }
   // the loss partials of up to kLossSets epochs are reduced by one launch; so are the
   // per-subgraph bias corrections of those epochs uploaded at once
   for (int e0 = 0; e0 < epochs; e0 += kLossSets) {

@@ -419,6 +419,8 @@ struct WeightTensor {
 // tail (not with many_partials): the same launch also pre-reduces the chunks
 // of the rows with very many neighbours of view g from the rows X (storage type) into `partial`,
 // ready for the next forward pass.
+//
+// launch_pre_reduce: the chunk sums of the rows X, of all subgraphs of view g, in a launch of their own.
 struct ChunkTail {
   GraphView g;
   int storage = 0;
@@ -426,6 +428,9 @@ struct ChunkTail {
   float* partial = nullptr;
   int D = 0;
 };
+void launch_pre_reduce(const Launch& ln, int storage, int D, const GraphView& g, const void* X, float* partial);
+void launch_pre_reduce_bf16(const Launch& ln, int D, const GraphView& g, const void* X, float* partial);
+void launch_pre_reduce_f32(const Launch& ln, int D, const GraphView& g, const void* X, float* partial);
 void launch_adam_w(const Launch& ln, int Pw, const WeightTensor* tensors, int count, const AdamStep& adam,
                    bool update, bool many_partials, const ChunkTail* tail = nullptr);  // adam.per_part, if set, is indexed by weight set; sets without partials are left alone
 

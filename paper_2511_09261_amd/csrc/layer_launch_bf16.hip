@@ -50,6 +50,11 @@ void bwd_t(const Launch& ln, bool last, bool to_embed, const GraphView& gt, cons
 
 }  // namespace
 
+void launch_pre_reduce_bf16(const Launch& ln, int D, const GraphView& g, const void* X, float* partial) {
+  if (D == 64) pre_reduce<64>(ln, g, X, partial);
+  else if (D == 128) pre_reduce<128>(ln, g, X, partial);
+}
+
 void launch_fwd_hidden_bf16(const Launch& ln, int D, const GraphView& g, const void* X, const float* W,
                             int w_stride, void* Y, const float* w_out, int wout_stride, float* t,
                             float* heavy_partial, bool partial_ready) {

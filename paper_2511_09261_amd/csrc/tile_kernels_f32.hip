@@ -532,14 +532,18 @@ void allow_lds(K kernel, size_t bytes) {
 }
 
 template <int D>
+void pre_reduce_t(const Launch& ln, const GraphView& g, const float* X, float* heavy_partial) {
+  if (g.num_chunks == 0) return;
+  ln.begin(KK_HEAVY);
+  heavy_wide_kernel<D, PlainSrc<float, D>>
+      <<<g.num_chunks, kBlock, 0, ln.st>>>(g, PlainSrc<float, D>{X, g.sb}, heavy_partial);
+  ln.end(KK_HEAVY);
+}
+
+template <int D>
 void fwd_t(const Launch& ln, const GraphView& g, const float* X, const float* W, int w_stride, float* Y,
            const float* w_out, int wout_stride, float* t, uint32_t* mask, float* heavy_partial, bool partial_ready) {
-  if (g.num_chunks > 0 && !partial_ready) {
-    ln.begin(KK_HEAVY);
-    heavy_wide_kernel<D, PlainSrc<float, D>>
-        <<<g.num_chunks, kBlock, 0, ln.st>>>(g, PlainSrc<float, D>{X, g.sb}, heavy_partial);
-    ln.end(KK_HEAVY);
-  }
+  if (!partial_ready) pre_reduce_t<D>(ln, g, X, heavy_partial);
   allow_lds(fwd_tile_kernel<D>, fwd_tile_lds<D>());
   ln.begin(KK_FWD_HIDDEN);
   fwd_tile_kernel<D><<<launch_ids(g, WM_FWD), kBlock, fwd_tile_lds<D>(), ln.st>>>(
@@ -598,6 +602,10 @@ void launch_fwd_hidden_f32(const Launch& ln, int D, const GraphView& g, const vo
 void launch_bwd_hidden_f32(const Launch& ln, int D, bool last, bool to_embed, const GraphView& gt,
                            const BwdArgs& a) {
   GCO_BY_WIDTH(D, (bwd_t<DD>(ln, last, to_embed, gt, a)))
+}
+
+void launch_pre_reduce_f32(const Launch& ln, int D, const GraphView& g, const void* X, float* partial) {
+  GCO_BY_WIDTH(D, (pre_reduce_t<DD>(ln, g, static_cast<const float*>(X), partial)))
 }
 
 void launch_propagate(const Launch& ln, int storage, int D, const GraphView& g, const void* E, float* X,

@@ -475,6 +475,11 @@ void launch_bwd_single(const Launch& ln, int storage, int D, const GraphView& g,
   ln.end(KK_BWD_EMBED);
 }
 
+void launch_pre_reduce(const Launch& ln, int storage, int D, const GraphView& g, const void* X, float* partial) {
+  if (storage == GCO_STORAGE_BF16) launch_pre_reduce_bf16(ln, D, g, X, partial);
+  else launch_pre_reduce_f32(ln, D, g, X, partial);
+}
+
 void launch_adam_w(const Launch& ln, int Pw, const WeightTensor* tensors, int count, const AdamStep& adam,
                    bool update, bool many_partials, const ChunkTail* tail) {
   WeightTensors wts;

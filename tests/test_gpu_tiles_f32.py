@@ -62,19 +62,21 @@ def test_tile_and_row_length_edges(gco, D, L, norm, share):
     ctx.destroy()
 
 
-@pytest.mark.parametrize("D", [8, 16, 32, 64, 128])
-def test_long_rows_reduced_ahead_are_those_of_the_new_embeddings(gco, D):
+@pytest.mark.parametrize("D,storage", [(8, "fp32"), (16, "fp32"), (32, "fp32"), (64, "fp32"), (128, "fp32"), (64, "bf16"),
+                                       (128, "bf16")])
+def test_long_rows_reduced_ahead_are_those_of_the_new_embeddings(gco, D, storage):
     """The last launch of a training epoch pre-reduces the long rows for the forward pass after it: bit for bit what that
-    pass forms itself from the same parameters, also after a subset trained."""
+    pass forms itself from the same parameters, also where a subset trained, first of all or after the others."""
     g, part, P = ragged_subgraphs(D)
     L = 2 + (D >= 32)
     E, Ws = inputs.init_params(g.n, part, P, L, D, 3)
-    ctx, fresh = (gco.Context(num_layers=L, dim=D) for _ in range(2))
+    ctx, fresh = (gco.Context(num_layers=L, dim=D, storage=storage) for _ in range(2))
     for c in (ctx, fresh):
         c.set_scalar_layer_form("streams")
         c.upload_graph(g.n, g.rowptr, g.col, part, P)
     ctx.set_params(E, Ws)
-    for run in (lambda: ctx.train(2), lambda: ctx.train_subset(2, np.array([10], dtype=np.int32))):
+    subset = lambda *parts: ctx.train_subset(2, np.array(parts, dtype=np.int32))
+    for run in (lambda: subset(11), lambda: ctx.train(2), lambda: subset(10)):
         run()
         ctx.forward()
         fresh.set_params(*ctx.get_params())
