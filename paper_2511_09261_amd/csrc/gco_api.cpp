@@ -548,7 +548,7 @@ bool eighths_of(int storage, int dim, int64_t rows, int v, Grouping grouping) {
 void wave_map_of(int storage, int dim, int v, int P, const std::vector<int>& part_rows, const std::vector<int>& wrow,
                  const uint8_t* active, std::vector<int>& wblk_k, std::vector<WaveRun>& wave_runs) {
   const bool f32 = storage == GCO_STORAGE_FP32;
-  const int target = f32 ? wave_blocks_f32(dim, v) : (dim == 128 ? kWaveBlocksFor128 : kWaveBlocksFor)[v];
+  const int target = f32 ? wave_blocks_f32(dim, v) : wave_blocks_bf16(dim, v, part_rows[P]);
   build_wave_map(P, part_rows, wrow, f32 && v != WM_NARROW ? kTileRowsF32 : kWaveRows, target,
                  (f32 ? kWaveRowCostF32 : kWaveRowCost)[v], grouping_of(storage, dim, part_rows[P], v), wblk_k,
                  wave_runs, active);

@@ -27,9 +27,20 @@ enum WaveMap : int { WM_FWD = 0, WM_BWD = 1, WM_EMBED = 2, WM_NARROW = 3, WM_GRA
 constexpr double kWaveRowCost[kWaveMaps] = {1.25, 1.5, 100.0, 1.0, 100.0};
 // workgroups aimed at (measured best); WM_GRADW: one per compute unit, which is all that fit at its size
 constexpr int kWaveBlocksFor[kWaveMaps] = {768, 512, 3072, 2048, 256};
-// width 128 (two workgroups of the layer kernels per compute unit): forward two rounds of 512,
-// embedding backward twelve
+// width 128 (two workgroups of the layer kernels per compute unit): embedding backward twelve rounds of 512, forward and
+// hidden backward one up to ten tiles per wavefront of a round, from there two, which even out the last tiles.
+// Forward / hidden backward in us, three layers, bf16 (the figure taken first):
+//   100 k rows in 16 subgraphs of spread 0.4:  45.7 / 54.8, two rounds 59.4 / 71.3
+//   250 k rows in 32:                          70.3 / 90.8, two rounds 77.3 / 99.5
+//   500 k rows in 64:                         100.0 / 153, two rounds 105.8 / 153
+//   900 k rows in 64 of spread 0.3:           224.9 / 339, one round 234.5 / 344
+//   1.6 M rows in 96:                         315.5 / 501, one round 328.3 / 524
 constexpr int kWaveBlocksFor128[kWaveMaps] = {1024, 1024, 6144, 2048, 256};
+inline int wave_blocks_bf16(int dim, int map, int64_t rows) {
+  if (dim != 128) return kWaveBlocksFor[map];
+  const bool one_round = (map == WM_FWD || map == WM_BWD) && rows <= int64_t{512} * 4 * 10 * kWaveRows;
+  return one_round ? 512 : kWaveBlocksFor128[map];
+}
 // fp32 storage: rows of a tile; workgroups aimed at, in rounds of those resident at once.  Up to
 // width 32 two rounds, from width 64 on, where W and the first tile cost more per workgroup, one.
 // Forward / hidden / embedding backward in us, three layers (the figure taken first):
