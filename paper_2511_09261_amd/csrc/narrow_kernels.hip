@@ -134,6 +134,38 @@ struct LocalOp {
   __device__ __forceinline__ void finish(int i, float s, double& ls, float2 y) const { op.finish(i + rbeg, s, ls, y); }
 };
 
+// Sum and epilogue of the rows in K steps of 64 entries from g0 on; nrow0 = this lane's row in the step after them.
+// carry_row and carry_sum: the row that runs on from the previous step, and its sum so far.
+template <class Op, int K>
+__device__ __forceinline__ void reduce_steps(const Op& op, int g0, int E1, const int (&col)[K], const int (&rows)[K],
+                                             const float (&w)[K], const float (&x)[K], const float2 (&y)[K], int nrow0,
+                                             int& carry_row, float& carry_sum, double& lsum) {
+  const int lane = threadIdx.x % 64;
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    const int e0 = g0 + 64 * u;
+    if (e0 < E1) {
+      const int nrow = u + 1 < K ? rows[(u + 1) % K] : nrow0;
+      const int next_first = __builtin_amdgcn_readfirstlane(nrow);  // -1 past the range
+      const int row = rows[u];
+      const bool valid = row >= 0;  // inside the range and not the entry of a pre-reduced row
+      float v = 0.f;
+      // the diagonal entry is the one whose column is the row itself (no self loops)
+      if (valid) v = Op::kWeighted ? w[u] * x[u] : (col[u] == row ? 0.f : x[u]);
+      v = scan_sum_by_key(v, row);
+      int next_row = __shfl_down(row, 1, 64);
+      if (lane == 63) next_row = next_first;
+      const float total = v + (row == carry_row ? carry_sum : 0.f);
+      if (valid && next_row != row) op.finish(row, total, lsum, y[u]);
+      const int row63 = __builtin_amdgcn_readlane(row, 63);
+      const float tot63 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(total), 63));
+      const bool runs_on = row63 >= 0 && next_first == row63;
+      carry_row = runs_on ? row63 : -1;
+      carry_sum = runs_on ? tot63 : 0.f;
+    }
+  }
+}
+
 template <class Op, int K, class Entries, class Between = NothingBetween>
 __device__ __forceinline__ void stream_rows(const Entries& entries, const float* __restrict__ wval, const Op& op, int E0,
                                             int E1, double& lsum, Between&& between = NothingBetween{}) {
@@ -169,33 +201,11 @@ __device__ __forceinline__ void stream_rows(const Entries& entries, const float*
       }
     }
   };
-  int carry_row = -1;     // the row that runs on from the previous step, and its sum so far
+  int carry_row = -1;
   float carry_sum = 0.f;
   // the K steps of one group; nrow0 = this lane's row in the first step of the group after it
   auto reduce_group = [&](int g0, const Group& s, int nrow0) {
-#pragma unroll
-    for (int u = 0; u < K; ++u) {
-      const int e0 = g0 + 64 * u;
-      if (e0 < E1) {
-        const int nrow = u + 1 < K ? s.row[(u + 1) % K] : nrow0;
-        const int next_first = __builtin_amdgcn_readfirstlane(nrow);  // -1 past the range
-        const int row = s.row[u];
-        const bool valid = row >= 0;  // inside the range and not the entry of a pre-reduced row
-        float v = 0.f;
-        // the diagonal entry is the one whose column is the row itself (no self loops)
-        if (valid) v = Op::kWeighted ? s.w[u] * s.x[u] : (s.col[u] == row ? 0.f : s.x[u]);
-        v = scan_sum_by_key(v, row);
-        int next_row = __shfl_down(row, 1, 64);
-        if (lane == 63) next_row = next_first;
-        const float total = v + (row == carry_row ? carry_sum : 0.f);
-        if (valid && next_row != row) op.finish(row, total, lsum, s.y[u]);
-        const int row63 = __builtin_amdgcn_readlane(row, 63);
-        const float tot63 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(total), 63));
-        const bool runs_on = row63 >= 0 && next_first == row63;
-        carry_row = runs_on ? row63 : -1;
-        carry_sum = runs_on ? tot63 : 0.f;
-      }
-    }
+    reduce_steps<Op, K>(op, g0, E1, s.col, s.row, s.w, s.x, s.y, nrow0, carry_row, carry_sum, lsum);
   };
   // Three groups of registers take turns: while one is reduced, the scalars of the next are
   // being gathered (its entries arrived a group ago) and the entries of the one after are
@@ -380,6 +390,47 @@ struct FusedBackOp {
   __device__ __forceinline__ void finish(int i, float s, double&, float2) const { g_t[i] = s; }
 };
 
+// A wavefront's whole range of the light stream (at most 64 K entries) in registers: entries and the values of A_hat and
+// of its transpose.
+template <int K>
+struct HeldEntries {
+  PairEntries::Raw raw[K];
+  float w[K], wt[K];
+  __device__ __forceinline__ void request(const GraphView& g, int E0, int E1) {
+    const PairEntries entries{g.wpair};
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+      const int idx = E0 + 64 * u + static_cast<int>(threadIdx.x % 64);
+      raw[u] = PairEntries::none();
+      w[u] = wt[u] = 0.f;
+      if (idx < E1) {
+        raw[u] = entries.load(idx);
+        w[u] = g.wval[idx];
+        wt[u] = g.wval_t[idx];
+      }
+    }
+  }
+};
+// stream_rows over a held range, with the values w of its matrix.
+template <class Op, int K>
+__device__ __forceinline__ void held_rows(const HeldEntries<K>& held, const float (&w)[K], const Op& op, int E0, int E1,
+                                          double& lsum) {
+  int col[K], row[K];
+  float x[K];
+  float2 y[K];
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    col[u] = PairEntries::column(held.raw[u]);
+    row[u] = PairEntries::row(held.raw[u]);
+    x[u] = 0.f;
+    y[u] = make_float2(0.f, 0.f);
+    if (row[u] != -1) x[u] = op.gather(col[u]);
+  }
+  int carry_row = -1;
+  float carry_sum = 0.f;
+  reduce_steps<Op, K>(op, E0, E1, col, row, w, x, y, -1, carry_row, carry_sum, lsum);
+}
+
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void scalar_layer_fused_kernel(
     GraphView g, const int2* __restrict__ cuts, const int* __restrict__ heavy_ptr, int cap,
@@ -399,11 +450,26 @@ __global__ __launch_bounds__(64 * NW) void scalar_layer_fused_kernel(
   const int h0 = heavy_ptr[k], h1 = heavy_ptr[k + 1];
   double lsum = 0.0;
 
+  // A range that fits is read once for the three passes, beside t and the coefficients: between the passes nothing then
+  // comes from memory.  8 subgraphs of 1250 rows, 240 entries a wavefront: 14.2 us with the entries read in every pass
+  // and the coefficients between them, 12.8 so; what is left are three chains of segmented sums and five barriers.
+  constexpr int kHeld = 8, kAhead = 2;
+  const bool held = mine.y - mine.x <= 64 * kHeld;
+  HeldEntries<kHeld> mine_held;
+  if (held) mine_held.request(g, mine.x, mine.y);
+  float c_ahead[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    const int r = rbeg + tid + u * 64 * NW;
+    c_ahead[u] = passes >= 2 && r < rend ? cl[r] : 0.f;
+  }
   for (int r = rbeg + tid; r < rend; r += 64 * NW) bufA[r - rbeg] = t[r];
   __syncthreads();
   {
     const FusedReadoutOp op{bufA, bufB, p, rbeg};
-    stream_rows<LocalOp<FusedReadoutOp>, 8>(PairEntries{g.wpair}, g.wval, {op, rbeg}, mine.x, mine.y, lsum);
+    const LocalOp<FusedReadoutOp> local{op, rbeg};
+    if (held) held_rows(mine_held, mine_held.w, local, mine.x, mine.y, lsum);
+    else stream_rows<LocalOp<FusedReadoutOp>, 8>(PairEntries{g.wpair}, g.wval, local, mine.x, mine.y, lsum);
     for (int hh = h0; hh < h1; ++hh) {
       const int i = g.heavy_rows[hh];
       const float total = heavy_row_sum<FusedReadoutOp, 64 * NW>(g, g.ent, op, i, red);
@@ -414,11 +480,18 @@ __global__ __launch_bounds__(64 * NW) void scalar_layer_fused_kernel(
   __syncthreads();
   // t has served; its place takes the linear coefficients, which the loss pass replaces row
   // by row with dL/dz (no dependent global load inside the pass)
-  for (int r = rbeg + tid; r < rend; r += 64 * NW) bufA[r - rbeg] = cl[r];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    const int r = rbeg + tid + u * 64 * NW;
+    if (r < rend) bufA[r - rbeg] = c_ahead[u];
+  }
+  for (int r = rbeg + tid + kAhead * 64 * NW; r < rend; r += 64 * NW) bufA[r - rbeg] = cl[r];
   __syncthreads();
   {
     const FusedLossOp op{bufB, bufA, q, rbeg};
-    stream_rows<LocalOp<FusedLossOp>, 8>(PairEntries{g.wpair}, g.wval, {op, rbeg}, mine.x, mine.y, lsum);
+    const LocalOp<FusedLossOp> local{op, rbeg};
+    if (held) held_rows(mine_held, mine_held.w, local, mine.x, mine.y, lsum);
+    else stream_rows<LocalOp<FusedLossOp>, 8>(PairEntries{g.wpair}, g.wval, local, mine.x, mine.y, lsum);
     for (int hh = h0; hh < h1; ++hh) {
       const int i = g.heavy_rows[hh];
       const float total = heavy_row_sum<FusedLossOp, 64 * NW>(g, g.ent, op, i, red);
@@ -436,7 +509,9 @@ __global__ __launch_bounds__(64 * NW) void scalar_layer_fused_kernel(
   if (passes < 3) return;
   {
     const FusedBackOp op{bufA, g_t, rbeg};
-    stream_rows<LocalOp<FusedBackOp>, 8>(PairEntries{g.wpair}, g.wval_t, {op, rbeg}, mine.x, mine.y, lsum);
+    const LocalOp<FusedBackOp> local{op, rbeg};
+    if (held) held_rows(mine_held, mine_held.wt, local, mine.x, mine.y, lsum);
+    else stream_rows<LocalOp<FusedBackOp>, 8>(PairEntries{g.wpair}, g.wval_t, local, mine.x, mine.y, lsum);
     for (int hh = h0; hh < h1; ++hh) {
       const int i = g.heavy_rows[hh];
       const float total = heavy_row_sum<FusedBackOp, 64 * NW>(g, g.ent_t, op, i, red);
