@@ -234,6 +234,7 @@ int gco_apportion(const double* work, int32_t n, int64_t target, const int32_t* 
  * each workgroup of a hidden layer's launch serves (-1: none), for storage and dim as in
  * gco_config and subgraphs of rows[k] nodes with entries[k] local CSR entries spread evenly
  * over them.  kind 0: forward, 1: backward of a layer that is not the first, 2: backward of the first.
+ * In list order, which the fixed orders of additions follow; a launch may start them in another.
  * Two-call pattern: with part = NULL only *count is written; otherwise *count is the
  * capacity of part on entry.  Host memory. */
 int gco_workgroup_parts(int32_t storage, int32_t dim, int32_t kind, const int32_t* rows, const int32_t* entries,

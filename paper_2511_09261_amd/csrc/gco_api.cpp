@@ -799,10 +799,12 @@ void traffic_model(gco_ctx* ctx) {
   const double idx = nnz * 4 + (n + 1) * 4, scales = 2 * n * 4;
   double* kb = ctx->kind_bytes;
   for (int k = 0; k < KK_COUNT; ++k) kb[k] = 0;
+  // fp32: the last hidden layer leaves its ReLU decisions, a bit each, and its backward gathers those instead of rows
+  const double kept_off = s == 4 && L >= 2 ? n * D * s - n * std::ceil(D / 32) * 4 : 0;
   // hidden forward: X read + Y write + W (+ t and w_out on the last hidden layer; averaged)
   if (L >= 2) {
     const double base = idx + scales + 2 * n * D * s + Pw * D * D * 4;
-    kb[KK_FWD_HIDDEN] = base + (n * 4 + Pw * D * 4) / (L - 1);
+    kb[KK_FWD_HIDDEN] = base + (n * 4 + Pw * D * 4 - kept_off) / (L - 1);
   }
   kb[KK_FWD_GEMV] = n * D * s + Pw * D * 4 + n * 4;
   kb[KK_FWD_READOUT] = idx + scales + 2 * n * 4;
@@ -817,7 +819,7 @@ void traffic_model(gco_ctx* ctx) {
   const double last_extra = wave ? 0 : n * 4;  // g_t read
   if (wave) kb[KK_FORM_GZ] = 2 * n * D * s + n * 4 + Pw * D * 4;
   // gathered gradient source + Hprev read + GZ write + W (the weight gradient itself: Pw D^2)
-  kb[KK_BWD_HIDDEN] = idx + scales + 3 * n * D * s + 2 * Pw * D * D * 4 + (L == 3 ? last_extra : 0);
+  kb[KK_BWD_HIDDEN] = idx + scales + 3 * n * D * s + 2 * Pw * D * D * 4 + (L == 3 ? last_extra - kept_off : 0);
   if (split) {
     // the weight gradient moves to grad_w, which reads Hprev and the stored rows of G_T
     kb[KK_BWD_HIDDEN] += n * D * s - Pw * D * D * 4;
@@ -830,7 +832,7 @@ void traffic_model(gco_ctx* ctx) {
     kb[KK_BWD_EMBED] = idx + scales + 2 * n * D * s + Pw * D * D * 4 + adam_e;
   else if (L >= 2)
     kb[KK_BWD_EMBED] = idx + scales + n * D * s + hprev_read + 2 * Pw * D * D * 4 + adam_e +
-                       (L == 2 ? last_extra : 0);
+                       (L == 2 ? last_extra - kept_off : 0);
   else
     kb[KK_BWD_EMBED] = n * 4 + hprev_read + adam_e + Pw * D * 4;
   // one launch serves all weight tensors: the gradient in, W, m, v in and out

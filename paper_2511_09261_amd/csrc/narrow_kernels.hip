@@ -346,7 +346,8 @@ __global__ __launch_bounds__(kBlock) void narrow_stream_kernel(GraphView g, Op o
 // bufB: p) and separates the passes by workgroup barriers.  Each wavefront sums a
 // contiguous range of the subgraph's rows (cut on the host into equal shares of entries)
 // with the stream routine above (cuts[k * NW + w] = its range of the light stream); rows
-// with very many neighbours are summed by the whole workgroup after each pass.  `passes` = 1 stops after the probabilities, 2 after the loss.
+// with very many neighbours are summed by the whole workgroup after each pass.  `passes` = 1 stops after the
+// probabilities, 2 after the loss.
 // ---------------------------------------------------------------------------
 struct FusedReadoutOp {
   static constexpr bool kWeighted = true;

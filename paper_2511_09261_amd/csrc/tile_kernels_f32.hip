@@ -26,10 +26,12 @@
 // carry place if the row began in an earlier group; the row's own lanes then add its carries
 // in order.  One fixed order of additions.
 //
-// What bounds it: at widths 8 .. 64 memory (Adam's E, m, v; the gather), in bytes that pass the L2s: 700 k rows of
-// width 16 with H stored and gathered, embedding backward 417 MB in 74 us, forward 144 MB in 35 (5.6 and 4.1 TB/s); 150 k
-// of width 64, forward 406 MB in 67 us, embedding backward 687 in 116 (5.9 to 6.1).  So registers are kept low enough for many wavefronts per SIMD and there is no workgroup barrier; at width
-// 128 the matrix cores (3 x 2 x 16 x 128 x 128 operations per tile at 64 per cycle and SIMD).
+// What bounds it: at widths 8 .. 64 memory (Adam's E, m, v; the gather), so registers are kept low enough for many
+// wavefronts per SIMD and there is no workgroup barrier; at width 128 the matrix cores (3 x 2 x 16 x 128 x 128
+// operations per tile at 64 per cycle and SIMD).  In bytes that pass the L2s, with H stored and gathered and launch ids
+// dealt round the XCDs one by one: 700 k rows of width 16, embedding backward 417 MB in 74 us, forward 144 MB in 35 (5.6
+// and 4.1 TB/s); 150 k of width 64, forward 406 MB in 67 us, embedding backward 687 in 116 (5.9 to 6.1).  With contiguous
+// eighths (GraphView::eighth) the latter two take 48 and 101 us.
 #include "device_utils.h"
 #include "gather.h"
 #include "gco_internal.h"
